@@ -382,7 +382,8 @@ int g_force_mb = 0;
 // One tile form: wave tile (32*MB) tokens x (32*H) weight rows, WN waves along N and WK along K.
 struct TileForm { int mb, h, wk, wn; };
 
-// Forced value (bl_set_tuning "gemm_mb"): 100*(WK-1) + 10*MB + H; four waves per workgroup, WN = 4 / WK.
+// Forced value (bl_set_tuning "gemm_mb"): 100*(WK-1) + 10*MB + H; four waves per workgroup, WN = 4 / WK.  (From 1000 on: the
+// forms of bl_gemm_narrow.hip.)
 TileForm form_of_code(int code) {
     TileForm f;
     const int waves = 4;
@@ -411,6 +412,33 @@ TileForm choose_tile(int64_t M, int64_t rows) {
     return f;
 }
 
+// The kernel of bl_gemm_narrow.hip (waves along K, no barriers) where its estimated time is below this file's: its code, or 0.
+// The estimates are straight lines through measured times (us) with the workgroups per compute unit x; this file's forms,
+// weights cold: 32 x 256 tiles (and, below 128 tokens, the K split) 3.4 + 0.20 KC up to x = 1 (1536^2: 8.2 us, 4096^2: 14.2,
+// 11008 -> 4096: 37.7), 19.1 for KC = 64 at x = 1.34; 64 x 256 tiles 26 us for KC = 64 and 69 for KC = 172 up to x = 2;
+// 64 x 512 tiles 0.40 x per tile of K (KC = 64, x = 3: 80 us).
+int choose_narrow(const GemmProblem* ps, int count, int64_t M) {
+    if (g_force_mb) return g_force_mb >= 1000 && gemm_narrow_takes(ps, count, M) ? g_force_mb : 0;
+    if (!gemm_narrow_takes(ps, count, M)) return 0;
+    const int found = compute_unit_count(), cus = found > 0 ? found : 256;
+    int64_t rows = 0;
+    int KC = 0;
+    for (int i = 0; i < count; ++i) {
+        rows += (int64_t)ps[i].row_blocks * kTileN;
+        KC = ps[i].KC > KC ? ps[i].KC : KC;
+    }
+    const TileForm f = choose_tile(M, rows);
+    const int64_t gx = (rows + f.wn * f.h * 32 - 1) / (f.wn * f.h * 32), gy = (M + 32 * f.mb - 1) / (32 * f.mb);
+    const float x = (float)(gx * gy) / (float)cus;
+    float per_tile;
+    if (f.h == 4) per_tile = 0.40f * x;
+    else if (f.mb == 1 || f.wk > 1) per_tile = x <= 1.0f ? 0.20f : 0.20f + 0.13f * (x - 1.0f);
+    else per_tile = x <= 2.0f ? 0.36f : 0.18f * x;
+    float narrow_us = 0.0f;
+    const int code = gemm_narrow_best(ps, count, M, cus, narrow_us);
+    return narrow_us < 3.4f + (float)KC * per_tile ? code : 0;
+}
+
 // One LdsCeiling per kernel: the larger forms need more than the 64 KiB a kernel gets without asking.
 template <typename Kernel, typename Arg>
 hipError_t launch_form(Kernel kernel, size_t lds_bytes, int threads, unsigned grid, const Arg& arg, int M, int gx, hipStream_t s) {
@@ -432,6 +460,7 @@ hipError_t launch_form(Kernel kernel, size_t lds_bytes, int threads, unsigned gr
 void set_gemm_mb(int mb) { g_force_mb = mb; }
 
 bool gemm_form_exists(int code) {
+    if (code >= 1000) return gemm_narrow_form_exists(code);
     const TileForm f = form_of_code(code);
 #define X(MB, H, WK, WN) if (f.mb == MB && f.h == H && f.wk == WK && f.wn == WN) return true;
     BL_GEMM_FORMS(X)
@@ -440,6 +469,7 @@ bool gemm_form_exists(int code) {
 }
 
 hipError_t launch_gemm(const GemmProblem& p, int64_t M, hipStream_t s) {
+    if (const int narrow = choose_narrow(&p, 1, M)) return launch_gemm_narrow(&p, 1, M, narrow, s);
     const int64_t rows = (int64_t)p.row_blocks * kTileN;
     const TileForm f = choose_tile(M, rows);
     const int64_t gx = (rows + f.wn * f.h * 32 - 1) / (f.wn * f.h * 32);
@@ -459,6 +489,7 @@ hipError_t launch_gemm(const GemmProblem& p, int64_t M, hipStream_t s) {
 hipError_t launch_gemm_batch(const GemmProblem* ps, int count, int64_t M, hipStream_t s) {
     if (count == 1) return launch_gemm(ps[0], M, s);
     if (count < 1 || count > kMaxGemmBatch) return hipErrorInvalidValue;
+    if (const int narrow = choose_narrow(ps, count, M)) return launch_gemm_narrow(ps, count, M, narrow, s);
     int64_t rows = 0;
     for (int i = 0; i < count; ++i) rows += (int64_t)ps[i].row_blocks * kTileN;
     const TileForm f = choose_tile(M, rows);

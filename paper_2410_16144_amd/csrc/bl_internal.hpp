@@ -166,6 +166,11 @@ hipError_t launch_decode_split(const DecodeBatch& b, int tiles_per_wave, bool fu
 hipError_t launch_gemm(const GemmProblem& p, int64_t M, hipStream_t s);
 constexpr int kMaxGemmBatch = BL_MAX_GEMM_BATCH;
 hipError_t launch_gemm_batch(const GemmProblem* ps, int count, int64_t M, hipStream_t s);   // 1 <= count <= kMaxGemmBatch
+// bl_gemm for few tokens (bl_gemm_narrow.hip); a form's code is 1000 * (32-row strips) + tokens of a workgroup
+bool gemm_narrow_form_exists(int code);
+bool gemm_narrow_takes(const GemmProblem* ps, int count, int64_t M);
+int gemm_narrow_best(const GemmProblem* ps, int count, int64_t M, int cus, float& us);   // the form with the smallest estimate
+hipError_t launch_gemm_narrow(const GemmProblem* ps, int count, int64_t M, int code, hipStream_t s);
 hipError_t launch_tl2_pack(const int8_t* w, int64_t N, int64_t K, int64_t Np, int64_t Kp, uint32_t* packed,
                            int32_t* bad_count, hipStream_t s);
 hipError_t launch_tl2_unpack(const uint32_t* packed, int64_t N, int64_t K, int64_t Np, int64_t Kp, int8_t* w,
@@ -199,7 +204,7 @@ inline void note_kernel(const char* fmt, int grid, int a = 0, int b = 0, int c =
 // Launch-shape overrides for experiments (0 = choose automatically).
 void set_gemv_waves(int waves);
 void set_attn_groups(int groups);   // bl_attn_decode's workgroups per head; 0 automatic
-void set_gemm_mb(int mb);         // 0 automatic, else 1000*W + 100*(WK-1) + 10*MB + H (see bl_gemm.hip)
+void set_gemm_mb(int mb);         // 0 automatic, else a form's code (see bl_gemm.hip and bl_gemm_narrow.hip)
 bool gemm_form_exists(int code);  // whether that code names a tile form the library has
 void set_decode_stage(int v);     // 1: the matrix-core decode kernel never stages activations in LDS
 void set_decode_split(int v);     // -1 never split row blocks over workgroups, 0 automatic, n: n workgroups per compute unit

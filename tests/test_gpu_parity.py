@@ -674,6 +674,30 @@ def test_gemm_parity_every_wave_tile(dev, ops, tile):
         binding.bl_set_tuning("gemm_mb", 0)
 
 
+@pytest.mark.parametrize("form", [1016, 1032, 2016, 2032, 4032, 4064])
+def test_gemm_parity_every_few_token_form(dev, ops, form):
+    """The waves-along-K kernel at the edges of its tiles: one tile of K (most waves have no step), an odd tile count (the
+    last pair is half a pair), fewer and more pairs than waves and than steps in flight, tokens and rows on either side of
+    a workgroup's; and several products of different N in one launch."""
+    from paper_2410_16144_amd import binding
+    binding.bl_set_tuning("gemm_mb", form)
+    try:
+        for M, N, K in ((1, 1, 64), (15, 33, 100), (16, 64, 64 * 3), (17, 65, 64 * 16), (33, 130, 64 * 17), (64, 96, 64 * 33),
+                        (65, 200, 64 * 50), (129, 300, 1000)):
+            w, s, x = _problem(M * 11 + N + K + form, M, K, N, p_zero=0.4, outl=0.01)
+            _assert_product(ops, dev, "gemm", w, s, x)
+            assert "gemm_narrow_kernel<%d, %d," % (form % 100, form // 1000) in binding.bl_last_kernel()
+        M, K, ns = 50, 64 * 21, (70, 33, 256, 200)
+        x = _problem(5300 + form, M, K, 64)[2]
+        qa = ops.quant_act(_to_dev_bf16(x, dev) if x.dtype == np.uint16 else torch.from_numpy(x).to(dev))
+        pws = [ops.pack_ternary(torch.from_numpy(_problem(5400 + n, 1, K, n)[0]).to(dev), 0.01 * (i + 1)) for i, n in enumerate(ns)]
+        together = ops.gemm_batch(pws, qa)
+        binding.bl_set_tuning("gemm_mb", 22)
+        assert all(torch.equal(o, ops.gemm(pw, qa)) for o, pw in zip(together, pws))
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)
+
+
 def test_gemm_long_k(dev, ops):
     M, N, K = 70, 130, 65536 + 64     # 1025 K steps (odd: the K-split form pads one group), ragged M and N
     w, s, x = _problem(3200, M, K, N, p_zero=0.4, outl=0.01)
