@@ -695,7 +695,8 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const AttnArgs p) {
     }
 }
 
-// A prompt's attention on the matrix cores: one workgroup per (head, block of 64 consecutive prompt tokens), 16 queries
+// A prompt's attention on the matrix cores for head sizes that are 4 more than a multiple of 8 (the others, up to 128, take
+// the kernel of bl_attn_prompt.hip, whose 16-byte requests they do not fit): one workgroup per (head, block of 64 consecutive prompt tokens), 16 queries
 // per wave.  The block walks the cache's 64-row chunks up to its last token's; per chunk a wave forms its 16 x 64
 // scores S = Q K^T and then O += P V with 16x16x32 bf16 products, keeping the running maximum, sum and output of
 // every query in registers (the usual rescaling by 2^(old maximum - new maximum); the scores carry log2(e), so the
@@ -1036,7 +1037,9 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     kv_append_kernel<<<dim3((unsigned)a.M), dim3(256), 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // head sizes up to 128 take the matrix-core kernel (a block of 64 tokens per workgroup); larger ones go token by token
+    // head sizes up to 128 take a matrix-core kernel (a block of 64 tokens per workgroup): the one of bl_attn_prompt.hip where
+    // a cache row's head is whole 16-byte pieces, else the one of this file; larger ones go token by token
+    if (attn_prompt_takes(a.n_heads, a.head_dim)) return launch_attn_prompt(a, s);
     static_assert(BL_ATTN_BLOCK_MAX_HEAD_DIM == 128, "the dispatch below covers head sizes up to 8 sixteens");
     switch ((a.head_dim + 15) / 16) {
         case 1: return launch_attn_block<1>(p, a.M, s);

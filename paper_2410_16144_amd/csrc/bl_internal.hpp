@@ -183,6 +183,8 @@ hipError_t launch_rope_table(float* table, int head_dim, int max_pos, double the
 int attn_chunks(int max_pos);
 hipError_t launch_attn_decode(const ::bl_attn_args& a, hipStream_t s);
 hipError_t launch_pos_advance(int32_t* pos, hipStream_t s);
+bool attn_prompt_takes(int n_heads, int head_dim);
+hipError_t launch_attn_prompt(const ::bl_attn_prefill_args& a, hipStream_t s);   // keys and values in the cache already
 hipError_t launch_attn_prefill(const ::bl_attn_prefill_args& a, hipStream_t s);
 
 // The calling thread's most recent product launch: kernel template instance and grid, for tools that label what they

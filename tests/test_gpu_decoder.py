@@ -825,6 +825,15 @@ def test_attn_prefill_parity(dev, mods, n_heads, head_dim, max_pos, pos0, M):
     assert np.all(np.abs(kc64[pos0 + M - 1] - want_k) <= np.maximum(np.abs(want_k), 1e-30) * 2.0 ** -7)
 
 
+@pytest.mark.parametrize("n_heads,head_dim,pos0,M", [(2, 8, 31, 33), (2, 24, 0, 32), (2, 32, 127, 65), (3, 72, 128, 1), (2, 80, 96, 64),
+                                                     (2, 88, 33, 31), (2, 96, 0, 129), (1, 104, 255, 66), (2, 112, 160, 40), (9, 128, 129, 95)])
+def test_attn_prefill_every_head_size_class(dev, mods, n_heads, head_dim, pos0, M):
+    """Each instance of the transposed-score kernel that the cases above leave out (head sizes in sixteens, whole and half),
+    at the edges of its 32-row chunks, of the four sets that share them out (a set without a chunk, a step with fewer
+    chunks than sets) and of its 64-token blocks.  Tolerance: the same derivation as above."""
+    test_attn_prefill_parity(dev, mods, n_heads, head_dim, pos0 + M + 3, pos0, M)
+
+
 def test_prompt_then_tokens(dev, mods):
     """A prompt in two pieces through DecoderStack.prefill (products as bl_gemm over all rows, attention on the matrix
     cores), then single tokens: the caches and hidden states follow those of the same tokens taken one at a time through
