@@ -26,7 +26,6 @@ namespace {
 // RMSNorm + quantizer
 
 constexpr int kNormThreads = 1024;
-constexpr int kNormWaves = kNormThreads / kWave;
 
 struct NormArgs {
     const float* a;
@@ -68,9 +67,10 @@ __device__ __forceinline__ void store4(float* row, int k, int K, const float (&v
     }
 }
 
-// Thread t holds elements 4 (t + 1024 i) .. + 3, i = 0 .. NV-1.
-template <int MODE, int NV, bool VEC>
-__global__ __launch_bounds__(kNormThreads) void norm_quant_kernel(const NormArgs p) {
+// Thread t holds elements 4 (t + THREADS i) .. + 3, i = 0 .. NV-1.
+template <int MODE, int NV, bool VEC, int THREADS>
+__global__ __launch_bounds__(THREADS) void norm_quant_kernel(const NormArgs p) {
+    constexpr int kNormWaves = THREADS / kWave;
     __shared__ float s_ss[kNormWaves];
     __shared__ float s_max[kNormWaves];
     __shared__ int s_sum[kNormWaves];
@@ -80,12 +80,23 @@ __global__ __launch_bounds__(kNormThreads) void norm_quant_kernel(const NormArgs
     float x[NV][4];
     // short rows: the norm weights are requested with the row, before the first barrier (one memory round trip
     // instead of two); long rows have no registers to spare for that
-    constexpr bool kGammaEarly = NV <= 4;
+    constexpr int kEarlyVectors = THREADS <= 512 ? 6 : 4;   // (512 threads have twice the registers)
+    constexpr bool kGammaEarly = NV <= kEarlyVectors;
     float gam[kGammaEarly ? NV : 1][4];
     float ss = 0.0f;
+    // the gated form's inputs, all requested together (its arithmetic has branches that loads do not cross)
+    constexpr bool kGatedEarly = MODE == BL_NORM_GATED && NV <= kEarlyVectors;
+    float gate[kGatedEarly ? NV : 1][4], up[kGatedEarly ? NV : 1][4];
+    if constexpr (kGatedEarly) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            load4<VEC>(p.a + row, (tid + i * THREADS) * 4, K, gate[i]);
+            load4<VEC>(p.b + row, (tid + i * THREADS) * 4, K, up[i]);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int k = (tid + i * kNormThreads) * 4;
+        const int k = (tid + i * THREADS) * 4;
         if constexpr (kGammaEarly) load4<VEC>(p.gamma, k, K, gam[i]);
         if constexpr (MODE == BL_NORM_PLAIN) {
             load4<VEC>(p.a + row, k, K, x[i]);
@@ -100,10 +111,21 @@ __global__ __launch_bounds__(kNormThreads) void norm_quant_kernel(const NormArgs
             }
         } else {
             float g[4], u[4];
-            load4<VEC>(p.a + row, k, K, g);
-            load4<VEC>(p.b + row, k, K, u);
+            if constexpr (kGatedEarly) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[i][j] = silu(g[j]) * u[j];
+                for (int j = 0; j < 4; ++j) { g[j] = gate[i][j]; u[j] = up[i][j]; }
+            } else {
+                load4<VEC>(p.a + row, k, K, g);
+                load4<VEC>(p.b + row, k, K, u);
+            }
+            if constexpr (NV <= 8) {
+                silu4(g, x[i]);
+            } else {   // no registers to spare for two ways of computing it
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[i][j] = silu(g[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[i][j] *= u[j];
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) ss += x[i][j] * x[i][j];
@@ -119,7 +141,7 @@ __global__ __launch_bounds__(kNormThreads) void norm_quant_kernel(const NormArgs
     float amax = 0.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int k = (tid + i * kNormThreads) * 4;
+        const int k = (tid + i * THREADS) * 4;
         float g[4];
         if constexpr (kGammaEarly) {
 #pragma unroll
@@ -148,17 +170,11 @@ __global__ __launch_bounds__(kNormThreads) void norm_quant_kernel(const NormArgs
     int sum = 0;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int k = (tid + i * kNormThreads) * 4;
-        uint32_t word = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int v = quant_one(x[i][j], inv);   // elements from K on are zero and quantize to zero
-            sum += v;
-            word |= (uint32_t)(v & 0xff) << (8 * j);
-        }
+        const int k = (tid + i * THREADS) * 4;
+        const uint32_t word = quantize4(x[i][0], x[i][1], x[i][2], x[i][3], inv, sum);   // elements from K on are zero and quantize to zero
         if (k < K) *reinterpret_cast<uint32_t*>(qrow + k) = word;
     }
-    for (int k = (K + 3) / 4 * 4 + tid * 4; k < p.Kp; k += kNormThreads * 4) *reinterpret_cast<uint32_t*>(qrow + k) = 0;
+    for (int k = (K + 3) / 4 * 4 + tid * 4; k < p.Kp; k += THREADS * 4) *reinterpret_cast<uint32_t*>(qrow + k) = 0;
     sum = wave_sum(sum);
     if (lane == 0) s_sum[wave] = sum;
     __syncthreads();
@@ -171,22 +187,45 @@ __global__ __launch_bounds__(kNormThreads) void norm_quant_kernel(const NormArgs
     }
 }
 
-template <int MODE, int NV>
+template <int MODE, int THREADS, int NV>
 hipError_t launch_norm_nv(const NormArgs& p, int M, bool vec, hipStream_t s) {
-    if (vec) norm_quant_kernel<MODE, NV, true><<<dim3((unsigned)M), dim3(kNormThreads), 0, s>>>(p);
-    else norm_quant_kernel<MODE, NV, false><<<dim3((unsigned)M), dim3(kNormThreads), 0, s>>>(p);
+    if (vec) norm_quant_kernel<MODE, NV, true, THREADS><<<dim3((unsigned)M), dim3(THREADS), 0, s>>>(p);
+    else norm_quant_kernel<MODE, NV, false, THREADS><<<dim3((unsigned)M), dim3(THREADS), 0, s>>>(p);
     return hipGetLastError();
 }
 
+// The smallest instance up to MAX_NV vectors per thread that holds the row.
+template <int MODE, int THREADS, int MAX_NV>
+hipError_t launch_norm_threads(const NormArgs& p, int M, bool vec, hipStream_t s) {
+    const int per_thread = (p.K + THREADS * 4 - 1) / (THREADS * 4);
+    if (per_thread <= 1) return launch_norm_nv<MODE, THREADS, 1>(p, M, vec, s);
+    if (per_thread <= 2) return launch_norm_nv<MODE, THREADS, 2>(p, M, vec, s);
+    if constexpr (MAX_NV >= 4) {
+        if (per_thread <= 3) return launch_norm_nv<MODE, THREADS, 3>(p, M, vec, s);
+        if (per_thread <= 4) return launch_norm_nv<MODE, THREADS, 4>(p, M, vec, s);
+    }
+    if constexpr (MAX_NV >= 6)
+        if (per_thread <= 6) return launch_norm_nv<MODE, THREADS, 6>(p, M, vec, s);
+    if constexpr (MAX_NV >= 12) {
+        if (per_thread <= 8) return launch_norm_nv<MODE, THREADS, 8>(p, M, vec, s);
+        if (per_thread <= 12) return launch_norm_nv<MODE, THREADS, 12>(p, M, vec, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// Threads per row: as few as leave a thread two (rows up to 2048) or four (up to 8192) vectors -- a row's three reductions and
+// barriers cost by the wave -- and 1024 for longer rows, where one row's loads and arithmetic have to be spread out.  Measured
+// with 1024 / 512 / 256 threads (us): 2048 rows of 768, plain 9.9 / 5.7 / 4.0; 1 row of 4096 3.0 / 2.6 / 2.8; 512 rows of 4096,
+// gated 5.5 / 4.8 / 4.8; 2048 of 4096, plain 12.8 / 8.8 / 7.4, residual 19.1 / 17.8 / 17.7, gated 16.2 / 13.8 / 14.7; 512 of 8192, residual
+// 8.3 / 8.0 / 9.3; 256 of 12032, residual 7.1 / 7.5 / 9.3; 512 of 12032, residual 13.5 / 14.7 / 15.6.  The gated form, with twice
+// the arithmetic per byte, gains from 512 threads also there once every compute unit has two rows: 15.7 / 13.7 / 14.0.
 template <int MODE>
 hipError_t launch_norm_mode(const NormArgs& p, int M, bool vec, hipStream_t s) {
-    const int per_thread = (p.K + kNormThreads * 4 - 1) / (kNormThreads * 4);
-    if (per_thread <= 1) return launch_norm_nv<MODE, 1>(p, M, vec, s);
-    if (per_thread <= 2) return launch_norm_nv<MODE, 2>(p, M, vec, s);
-    if (per_thread <= 4) return launch_norm_nv<MODE, 4>(p, M, vec, s);
-    if (per_thread <= 8) return launch_norm_nv<MODE, 8>(p, M, vec, s);
-    if (per_thread <= 12) return launch_norm_nv<MODE, 12>(p, M, vec, s);
-    return hipErrorInvalidValue;
+    if (p.K <= 2048) return launch_norm_threads<MODE, 256, 2>(p, M, vec, s);
+    if (p.K <= 8192) return launch_norm_threads<MODE, 512, 4>(p, M, vec, s);
+    if constexpr (MODE == BL_NORM_GATED)
+        if (p.K <= 12288 && M >= 512) return launch_norm_threads<MODE, 512, 6>(p, M, vec, s);
+    return launch_norm_threads<MODE, kNormThreads, 12>(p, M, vec, s);
 }
 static_assert(BL_NORM_MAX_K == 12 * kNormThreads * 4, "the longest row fills 12 vectors per thread");
 
@@ -220,8 +259,9 @@ __device__ __forceinline__ void wide_inputs(const NormArgs& p, int64_t row, int 
         float g[4], u[4];
         load4<VEC>(p.a + row, k, K, g);
         load4<VEC>(p.b + row, k, K, u);
+        silu4(g, x);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[j] = silu(g[j]) * u[j];
+        for (int j = 0; j < 4; ++j) x[j] *= u[j];
     }
 }
 
@@ -297,14 +337,9 @@ __global__ __launch_bounds__(kWideThreads) void norm_wide_quant_kernel(const Nor
         float x[4], g[4] = {1.0f, 1.0f, 1.0f, 1.0f};
         if constexpr (MODE != BL_NORM_PREMULTIPLIED) load4<VEC>(p.gamma, k, K, g);
         wide_inputs<MODE, VEC>(p, row, k, K, true, x);
-        uint32_t word = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            x[j] = MODE == BL_NORM_PREMULTIPLIED ? x[j] * r : (x[j] * g[j]) * r;
-            const int v = quant_one(x[j], inv);
-            sum += v;
-            word |= (uint32_t)(v & 0xff) << (8 * j);
-        }
+        for (int j = 0; j < 4; ++j) x[j] = MODE == BL_NORM_PREMULTIPLIED ? x[j] * r : (x[j] * g[j]) * r;
+        const uint32_t word = quantize4(x[0], x[1], x[2], x[3], inv, sum);
         if (p.y) store4<VEC>(p.y + row, k, K, x);
         if (qrow && k < K) *reinterpret_cast<uint32_t*>(qrow + k) = word;
     }

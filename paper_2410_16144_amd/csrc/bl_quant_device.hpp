@@ -46,6 +46,28 @@ __device__ __forceinline__ float wave_sum_f(float v) {   // a fixed tree: the sa
 
 __device__ __forceinline__ float silu(float t) { return t / (1.0f + expf(-t)); }
 
+// silu of four values.  Where all of the wave's are below 80 in size nothing overflows or leaves the normal range, and the
+// exponential and the quotient need no special cases: exp(-t) = 2^n 2^((h - n) + l) with h + l = -t log2(e) to twice the
+// precision and n = h rounded, the quotient by the reciprocal and one correction step (errors against 64 bits as with expf and
+// the IEEE division, 14 instructions instead of about 26).  Any other wave takes silu().
+__device__ __forceinline__ void silu4(const float (&t)[4], float (&y)[4]) {
+    const float size = fmaxf(fmaxf(fabsf(t[0]), fabsf(t[1])), fmaxf(fabsf(t[2]), fabsf(t[3])));
+    if (__any(!(size < 80.0f))) {   // uniform
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = silu(t[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            constexpr float kLog2e = 0x1.715476p+0f, kLog2eRest = 0x1.4ae0cp-26f;
+            const float h = -t[j] * kLog2e;
+            const float l = __builtin_fmaf(-t[j], kLog2eRest, __builtin_fmaf(-t[j], kLog2e, -h)), n = rintf(h);
+            const float d = 1.0f + __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((h - n) + l), (int)n);
+            const float r = __builtin_amdgcn_rcpf(d), q = t[j] * r;
+            y[j] = __builtin_fmaf(__builtin_fmaf(-d, q, t[j]), r, q);
+        }
+    }
+}
+
 // q = clip(round_half_even(v * inv), -128, 127)
 __device__ __forceinline__ int quant_one(float v, float inv) {
     float r = rintf(v * inv);
@@ -124,32 +146,32 @@ __device__ __forceinline__ float absmax8(const float (&v)[8]) {
     return m;
 }
 
-// Quantize 8 values and store them as 8 bytes at q8; returns their sum.
-__device__ __forceinline__ int quantize8(const float (&v)[8], float inv, int8_t* q8) {
-    uint32_t lo = 0, hi = 0;
+// Four codes as the bytes of a word, quant_one(v[0]) lowest; their sum is added to `sum`.  The same codes as quant_one: the
+// product is clipped before it is rounded (the limits are whole numbers, so the order does not matter), and adding 1.5 * 2^23
+// rounds to nearest, ties to even, leaving the integer in the low bits.  4 vector instructions per code instead of 9 -- the
+// quantizer's second pass is bound by the vector ALU.
+__device__ __forceinline__ uint32_t quantize4(float v0, float v1, float v2, float v3, float inv, int& sum) {
+    const auto code = [&](float v) { return __float_as_uint(__builtin_amdgcn_fmed3f(v * inv, -128.0f, 127.0f) + 12582912.0f); };
+    const uint32_t low = __builtin_amdgcn_perm(code(v1), code(v0), 0x0c0c0400u);    // bytes 0 and 1
+    const uint32_t high = __builtin_amdgcn_perm(code(v3), code(v2), 0x04000c0cu);   // bytes 2 and 3
+    const uint32_t word = low | high;
+    sum = __builtin_amdgcn_sdot4((int)word, 0x01010101, sum, false);
+    return word;
+}
+
+// Quantize 8 values to 8 bytes; returns their sum.
+__device__ __forceinline__ int quantize8_packed(const float (&v)[8], float inv, uint32_t& lo, uint32_t& hi) {
     int sum = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int a = quant_one(v[i], inv), b = quant_one(v[4 + i], inv);
-        sum += a + b;
-        lo |= (uint32_t)(a & 0xff) << (8 * i);
-        hi |= (uint32_t)(b & 0xff) << (8 * i);
-    }
-    *reinterpret_cast<uint2*>(q8) = make_uint2(lo, hi);
+    lo = quantize4(v[0], v[1], v[2], v[3], inv, sum);
+    hi = quantize4(v[4], v[5], v[6], v[7], inv, sum);
     return sum;
 }
 
-// The same, the 8 bytes returned instead of stored.
-__device__ __forceinline__ int quantize8_packed(const float (&v)[8], float inv, uint32_t& lo, uint32_t& hi) {
-    lo = hi = 0;
-    int sum = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int a = quant_one(v[i], inv), b = quant_one(v[4 + i], inv);
-        sum += a + b;
-        lo |= (uint32_t)(a & 0xff) << (8 * i);
-        hi |= (uint32_t)(b & 0xff) << (8 * i);
-    }
+// The same, stored at q8.
+__device__ __forceinline__ int quantize8(const float (&v)[8], float inv, int8_t* q8) {
+    uint32_t lo, hi;
+    const int sum = quantize8_packed(v, inv, lo, hi);
+    *reinterpret_cast<uint2*>(q8) = make_uint2(lo, hi);
     return sum;
 }
 
@@ -185,15 +207,7 @@ __device__ __forceinline__ int thread_quantize(const void* row, int K, int Kp, f
         for (int k = tid * 8; k < K; k += nthreads * 8) {
             float v[8];
             load8<BF16>(row, k, v);
-            uint32_t lo = 0, hi = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int a = quant_one(v[i], inv), b = quant_one(v[4 + i], inv);
-                sum += a + b;
-                lo |= (uint32_t)(a & 0xff) << (8 * i);
-                hi |= (uint32_t)(b & 0xff) << (8 * i);
-            }
-            *reinterpret_cast<uint2*>(qrow + k) = make_uint2(lo, hi);
+            sum += quantize8(v, inv, qrow + k);
         }
     } else {
         for (int k = tid; k < K; k += nthreads) {

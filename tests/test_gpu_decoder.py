@@ -93,6 +93,38 @@ def test_norm_quant_parity(dev, mods, mode, M, K, wide):
     np.testing.assert_array_equal(qa.q_sum.cpu().numpy(), q_sum)
 
 
+@pytest.mark.parametrize("mode,M,K", [("plain", 1, 2048), ("residual", 2, 2052), ("gated", 1, 8192), ("plain", 2, 8196),
+                                      ("gated", 511, 8200), ("gated", 512, 8200), ("gated", 512, 12288), ("gated", 512, 12292)])
+def test_norm_quant_at_the_edges_of_the_thread_counts(dev, mods, mode, M, K):
+    """256, 512 and 1024 threads per row: the longest row of each and the first beyond, and the gated form's change at 512
+    rows.  Tolerance: the same derivation as above."""
+    test_norm_quant_parity(dev, mods, mode, M, K, False)
+
+
+@pytest.mark.parametrize("K", [512, 45056])
+def test_norm_quant_gate_of_any_size(dev, mods, K):
+    """The gate's two ways of computing silu meet at a size of 80: waves below it, waves with one element at or above it, and
+    waves far beyond, where exp overflows.  The row's largest value sets the scale of the comparison (3e-6, as above), so
+    each size gets a row of its own."""
+    B, dec, ops = mods
+    r = _rng(77)
+    sizes = [1e-30, 1e-3, 1.0, 20.0, 79.99, 80.0, 87.5, 100.0, 1e4]
+    a = r.uniform(-1.0, 1.0, (len(sizes), K)).astype(np.float32)
+    for i, v in enumerate(sizes):
+        a[i] *= np.float32(v)
+        a[i, 0], a[i, K - 1] = v, -v
+    b = r.uniform(0.5, 1.0, a.shape).astype(np.float32)
+    gamma = r.uniform(0.5, 1.5, K).astype(np.float32)
+    y = torch.empty(a.shape, device=dev)
+    scratch = torch.empty(len(sizes) * B.BL_NORM_SCRATCH_BYTES, dtype=torch.uint8, device=dev)
+    for use_scratch in (False, True):
+        dec.norm_quant(B.BL_NORM_GATED, _t(gamma, dev), 1e-5, a=_t(a, dev), b=_t(b, dev), y=y, scratch=scratch if use_scratch else None)
+        with np.errstate(over="ignore"):
+            want = D.rmsnorm(D.gated_ffn_input(a, b), gamma, 1e-5)
+        tol = 3e-6 * np.abs(want).max(axis=1, keepdims=True) + 1e-30
+        assert np.all(np.abs(y.cpu().numpy() - want) <= tol)
+
+
 def test_norm_quant_zero_row_and_no_quantizer(dev, mods):
     B, dec, ops = mods
     K = 512
