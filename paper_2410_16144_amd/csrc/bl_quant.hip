@@ -16,24 +16,36 @@ constexpr int kQuantThreads = 256;
 
 constexpr int kRegVectors = 6;   // 8-element vectors a thread keeps in registers: rows up to 256 * 8 * 6 = 12288 elements
 
-// One token row by one workgroup.  Rows of up to 12288 vector-loadable elements are read ONCE: all of a thread's
-// loads are issued together and the raw values stay in registers between the absmax pass and the rounding pass.
-// Longer or unaligned rows are read twice (the second read hits L2).
-template <bool BF16, bool VEC>
+// One token row by one workgroup.  Rows of up to 12288 elements are read ONCE: all of a thread's loads are issued together and
+// the raw values stay in registers between the absmax pass and the rounding pass.  Longer rows are read twice (the second
+// read hits L2).  VEC: the row is 16-byte aligned and a multiple of 8 long; otherwise the same vectors are loaded at any address
+// and one thread picks up the last few elements (512 rows of 12036 fp32 read element by element: 27 us).
+// NV: vectors a thread keeps (a short row asked to load six per thread, five of them nothing but its first elements again,
+// took 8.7 us instead of 5.4 for 2048 unaligned bf16 rows of 771).
+template <bool BF16, bool VEC, int NV>
 __device__ __forceinline__ void quant_row(const void* row, int K, int Kp, int8_t* qrow, float* a_scale, int32_t* q_sum,
                                           float* s_max, int* s_sum) {
     const int tid = threadIdx.x;
-    const bool in_regs = VEC && K <= kQuantThreads * 8 * kRegVectors;   // uniform
-    Raw8<BF16> raw[kRegVectors];
+    const bool in_regs = K >= 8 && K <= kQuantThreads * 8 * NV;   // uniform
+    Raw8<BF16> raw[NV];
     float amax = 0.0f;
-    if (VEC && in_regs) {
+    if (in_regs) {
 #pragma unroll
-        for (int i = 0; i < kRegVectors; ++i) {
-            const int k = (tid + i * kQuantThreads) * 8;
-            raw[i] = load_raw8<BF16>(row, k < K ? k : 0);
+        for (int i = 0; i < NV; ++i) {
+            const int k = (tid + i * kQuantThreads) * 8, at = k + 8 <= K ? k : 0;
+            raw[i] = VEC ? load_raw8<BF16>(row, at) : load_raw8_any<BF16>(row, at);
+        }
+        if constexpr (!VEC) {
+            const int k = K & ~7;   // the last few elements, if any: one thread's, in one of its vectors
+            if (k < K && tid == (k / 8) % kQuantThreads) {
+                const Raw8<BF16> tail = load_raw8_tail<BF16>(row, k, K);
+#pragma unroll
+                for (int i = 0; i < NV; ++i)
+                    if (i == (k / 8) / kQuantThreads) raw[i] = tail;
+            }
         }
 #pragma unroll
-        for (int i = 0; i < kRegVectors; ++i) {
+        for (int i = 0; i < NV; ++i) {
             float v[8];
             unpack_raw8<BF16>(raw[i], v);
             if ((tid + i * kQuantThreads) * 8 < K) amax = fmaxf(amax, absmax8(v));
@@ -52,15 +64,15 @@ __device__ __forceinline__ void quant_row(const void* row, int K, int Kp, int8_t
     quant_scales(amax, inv, scale);
 
     int sum = 0;
-    if (VEC && in_regs) {
+    if (in_regs) {
 #pragma unroll
-        for (int i = 0; i < kRegVectors; ++i) {
+        for (int i = 0; i < NV; ++i) {
             const int k = (tid + i * kQuantThreads) * 8;
             float v[8];
             unpack_raw8<BF16>(raw[i], v);
             if (k < K) sum += quantize8(v, inv, qrow + k);
         }
-        for (int k = K + tid; k < Kp; k += kQuantThreads) qrow[k] = 0;   // layout padding
+        for (int k = (K + 7) / 8 * 8 + tid * 8; k < Kp; k += kQuantThreads * 8) *reinterpret_cast<uint2*>(qrow + k) = make_uint2(0, 0);   // layout padding
     } else {
         sum = thread_quantize<BF16, VEC>(row, K, Kp, inv, qrow, tid, kQuantThreads);
     }
@@ -74,6 +86,15 @@ __device__ __forceinline__ void quant_row(const void* row, int K, int Kp, int8_t
         *a_scale = scale;
         if (q_sum) *q_sum = total;
     }
+}
+
+// The instance by the row's length.
+template <bool BF16, bool VEC>
+__device__ __forceinline__ void quant_row(const void* row, int K, int Kp, int8_t* qrow, float* a_scale, int32_t* q_sum,
+                                          float* s_max, int* s_sum) {
+    if (K <= kQuantThreads * 8) quant_row<BF16, VEC, 1>(row, K, Kp, qrow, a_scale, q_sum, s_max, s_sum);             // uniform
+    else if (K <= 2 * kQuantThreads * 8) quant_row<BF16, VEC, 2>(row, K, Kp, qrow, a_scale, q_sum, s_max, s_sum);
+    else quant_row<BF16, VEC, kRegVectors>(row, K, Kp, qrow, a_scale, q_sum, s_max, s_sum);
 }
 
 // Up to BL_MAX_BATCH activation matrices in one launch: workgroup = one token row of one of them.

@@ -123,6 +123,48 @@ __device__ __forceinline__ Raw8<BF16> load_raw8(const void* row, int k) {
     return r;
 }
 
+// The same from any element's address (the memory system takes vectors at any alignment; only their lines may be two).
+template <bool BF16>
+__device__ __forceinline__ Raw8<BF16> load_raw8_any(const void* row, int k) {
+    typedef uint32_t u32x4_2 __attribute__((ext_vector_type(4), aligned(2)));
+    typedef uint32_t u32x4_4 __attribute__((ext_vector_type(4), aligned(4)));
+    Raw8<BF16> r;
+    if constexpr (BF16) {
+        const u32x4_2 t = *reinterpret_cast<const u32x4_2*>(static_cast<const uint16_t*>(row) + k);
+        r.a = make_uint4(t[0], t[1], t[2], t[3]);
+        r.b = r.a;
+    } else {
+        const u32x4_4* p = reinterpret_cast<const u32x4_4*>(static_cast<const float*>(row) + k);
+        const u32x4_4 t = p[0], u = p[1];
+        r.a = make_uint4(t[0], t[1], t[2], t[3]);
+        r.b = make_uint4(u[0], u[1], u[2], u[3]);
+    }
+    return r;
+}
+
+// The last K - k < 8 elements of a row, zeros behind them.
+template <bool BF16>
+__device__ __forceinline__ Raw8<BF16> load_raw8_tail(const void* row, int k, int K) {
+    uint32_t e[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {   // no branches: the loads go out together
+        const int at = min(k + j, K - 1);
+        if constexpr (BF16) e[j] = static_cast<const uint16_t*>(row)[at];
+        else e[j] = static_cast<const uint32_t*>(row)[at];
+    }
+    uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t v = k + j < K ? e[j] : 0;
+        if constexpr (BF16) w[j / 2] |= v << (16 * (j & 1));
+        else w[j] = v;
+    }
+    Raw8<BF16> r;
+    r.a = make_uint4(w[0], w[1], w[2], w[3]);
+    r.b = BF16 ? r.a : make_uint4(w[4], w[5], w[6], w[7]);
+    return r;
+}
+
 template <bool BF16>
 __device__ __forceinline__ void unpack_raw8(const Raw8<BF16>& r, float (&v)[8]) {
     if constexpr (BF16) {
@@ -175,48 +217,39 @@ __device__ __forceinline__ int quantize8(const float (&v)[8], float inv, int8_t*
     return sum;
 }
 
-template <bool BF16>
-__device__ __forceinline__ float load1(const void* row, int k) {
-    if constexpr (BF16) return bf16_to_f32(static_cast<const uint16_t*>(row)[k]);
-    else return static_cast<const float*>(row)[k];
+// VEC: the row is 16-byte aligned and a multiple of 8 long; otherwise vectors at any address and a tail of up to 7 elements,
+// which falls to the thread whose turn it is.
+template <bool BF16, bool VEC, typename Fn>
+__device__ __forceinline__ void for_thread_vectors(const void* row, int K, int tid, int nthreads, Fn fn) {
+    const int full = VEC ? K : K & ~7;
+    for (int k = tid * 8; k < full; k += nthreads * 8) {
+        float v[8];
+        unpack_raw8<BF16>(VEC ? load_raw8<BF16>(row, k) : load_raw8_any<BF16>(row, k), v);
+        fn(k, v);
+    }
+    if (!VEC && full < K && tid == (full / 8) % nthreads) {
+        float v[8];
+        unpack_raw8<BF16>(load_raw8_tail<BF16>(row, full, K), v);
+        fn(full, v);
+    }
 }
 
 // max |x| over this thread's share of a row (threads stride the row).  K <= BL_MAX_K: 32-bit indices.
 template <bool BF16, bool VEC>
 __device__ __forceinline__ float thread_absmax(const void* row, int K, int tid, int nthreads) {
     float amax = 0.0f;
-    if constexpr (VEC) {
-        for (int k = tid * 8; k < K; k += nthreads * 8) {
-            float v[8];
-            load8<BF16>(row, k, v);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[i]));
-        }
-    } else {
-        for (int k = tid; k < K; k += nthreads) amax = fmaxf(amax, fabsf(load1<BF16>(row, k)));
-    }
+    for_thread_vectors<BF16, VEC>(row, K, tid, nthreads, [&](int, const float (&v)[8]) { amax = fmaxf(amax, absmax8(v)); });
     return amax;
 }
 
-// Quantize this thread's share of a row into qrow (global or LDS); returns the thread's sum(q).
+// Quantize this thread's share of a row into qrow (global or LDS, 8-byte aligned, Kp a multiple of 64); returns the
+// thread's sum(q).
 template <bool BF16, bool VEC>
 __device__ __forceinline__ int thread_quantize(const void* row, int K, int Kp, float inv, int8_t* qrow,
                                                int tid, int nthreads) {
     int sum = 0;
-    if constexpr (VEC) {
-        for (int k = tid * 8; k < K; k += nthreads * 8) {
-            float v[8];
-            load8<BF16>(row, k, v);
-            sum += quantize8(v, inv, qrow + k);
-        }
-    } else {
-        for (int k = tid; k < K; k += nthreads) {
-            int a = quant_one(load1<BF16>(row, k), inv);
-            sum += a;
-            qrow[k] = (int8_t)a;
-        }
-    }
-    for (int k = K + tid; k < Kp; k += nthreads) qrow[k] = 0;  // layout padding
+    for_thread_vectors<BF16, VEC>(row, K, tid, nthreads, [&](int k, const float (&v)[8]) { sum += quantize8(v, inv, qrow + k); });
+    for (int k = (K + 7) / 8 * 8 + tid * 8; k < Kp; k += nthreads * 8) *reinterpret_cast<uint2*>(qrow + k) = make_uint2(0, 0);  // layout padding
     return sum;
 }
 

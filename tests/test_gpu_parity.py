@@ -653,6 +653,33 @@ def test_decode_streaming_and_ordinary_weight_loads_agree(dev, ops, stream):
         binding.bl_set_tuning("decode_stream", 0)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("K", [1, 7, 8, 9, 15, 63, 65, 2047, 2052, 4084, 12283, 12289, 16390])
+def test_quant_rows_at_any_address(dev, ops, K, bf16):
+    """Rows that are not 16-byte aligned or not whole vectors long: an odd stride and an odd first element, the row's last
+    0 to 7 elements, shorter than one vector, on either side of what stays in registers.  Bit for bit the oracle's."""
+    from paper_2410_16144_amd import binding
+    M, ldx, first = 3, K + 3, 1
+    x = synth.activations(synth.rng_for(6100 + K), M, K, outlier_frac=0.01)
+    x[1] = 0.0
+    x[2, K - 1] = 50.0       # the largest value is the row's last element
+    bits = synth.to_bf16_bits(x)
+    flat = np.full(first + M * ldx, 3e4, np.float32)      # what lies around the rows must not be seen
+    view = flat[first:].reshape(M, ldx)
+    view[:, :K] = synth.bf16_bits_to_f32(bits) if bf16 else x
+    t = torch.from_numpy(flat).to(dev)
+    if bf16:
+        t = t.to(torch.bfloat16)
+    qa = ops.alloc_quant(M, K, dev)
+    qa.q.fill_(77)
+    binding.bl_quant_act(t.data_ptr() + first * t.element_size(), binding.BL_BF16 if bf16 else binding.BL_F32, M, K, ldx,
+                         qa.q.data_ptr(), qa.a_scale.data_ptr(), qa.q_sum.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    q, a_scale, q_sum = oracle.quant_act(bits if bf16 else x)
+    assert np.array_equal(qa.q.cpu().numpy()[:, :K], q) and not qa.q[:, K:].any()
+    assert np.array_equal(qa.a_scale.cpu().numpy(), a_scale) and np.array_equal(qa.q_sum.cpu().numpy(), q_sum)
+
+
 # ------------------------------------------------------------------ prefill product
 
 @pytest.mark.parametrize("M,N,K", [(1, 64, 64), (7, 70, 100), (33, 200, 1000), (128, 256, 512), (130, 320, 1536),
