@@ -422,7 +422,7 @@ struct AttnArgs {
     uint16_t*      k_cache;
     uint16_t*      v_cache;
     float*         out;
-    float*         scratch;     // per query [n_heads][chunks][head_dim + 2] (weighted values, maximum, sum), then n_heads counters
+    float*         scratch;     // per query [n_heads][chunks][head_dim + 2] (weighted values, maximum, sum), then n_heads counters, kAttnCounterStride words apart
     int32_t        n_heads, head_dim, max_pos, chunks;
     // several consecutive tokens (a prompt): pos is null, query z has position pos0 + z, its own row of q_lin and out
     // and its own part of scratch; keys and values are in the cache already (kv_append_kernel)
@@ -458,6 +458,49 @@ __device__ __forceinline__ float read_published(float* at) {
     return __uint_as_float(__hip_atomic_load(reinterpret_cast<unsigned int*>(at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// Up to kMergeTogether workgroups' figures (all that bl_attn_decode launches by itself): every value is requested at once -- a
+// read of this kind is a round trip to memory (32 heads of 128, 32 workgroups per head, four values at a time: 17.6 us, this: 16.0).  The threads of a workgroup are kAttnThreads / MAXD teams of
+// MAXD, each taking every so-manieth deposit.  s_f: kMergeTogether floats, s_red: kAttnWaves, s_o: [teams][MAXD].
+constexpr int kMergeTogether = 64;   // one wave reads all maxima and sums
+static_assert(kMergeTogether <= kWave, "one lane per deposit");
+template <int MAXD, int N>   // N: deposits it can take
+__device__ __forceinline__ void attn_merge_together(const AttnArgs& p, float* scratch, float* out, int head, int used, float* s_f,
+                                                    float* s_red, float* s_o) {
+    constexpr int kTeams = kAttnThreads / MAXD, kMine = N / kTeams;
+    const int tid = threadIdx.x, d = p.head_dim;
+    const int team = tid / MAXD, el = tid % MAXD;
+    float* base = scratch + (int64_t)head * p.chunks * (d + 2);
+    float part[kMine];
+#pragma unroll
+    for (int j = 0; j < kMine; ++j) part[j] = read_published(base + min(team + j * kTeams, used - 1) * (d + 2) + min(el, d - 1));
+    if (tid < kWave) {
+        const int c = min(tid, used - 1);
+        const float m_c = read_published(base + c * (d + 2) + d), l_c = read_published(base + c * (d + 2) + d + 1);
+        float m = m_c;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+        const float f = tid < used ? expf(m_c - m) : 0.0f;
+        if (tid < N) s_f[tid] = f;
+        const float l = wave_sum_f(f * l_c);
+        if (tid == 0) s_red[0] = l;
+    }
+    __syncthreads();
+    float o = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kMine; ++j)   // beyond the last deposit: the factor is zero, the value finite or that deposit's own
+        o = team + j * kTeams < used ? __builtin_fmaf(s_f[team + j * kTeams], part[j], o) : o;
+    if constexpr (kTeams > 1) {
+        s_o[tid] = o;
+        __syncthreads();
+        if (tid < MAXD) {
+#pragma unroll
+            for (int t = 1; t < kTeams; ++t) o += s_o[t * MAXD + tid];
+        }
+    }
+    if (tid < d) out[head * d + tid] = o / s_red[0];
+}
+
+// Any number of them.
 __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, float* out, int head, int used, float* s_f,
                                            float* s_red) {
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -496,10 +539,12 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 
 // A chunk is 64 cache rows.  Its keys and values (64 x head_dim bf16 each) are requested as W values per thread and
 // request, MAXD / W consecutive lanes on one row; while they travel the query is rotated (and, in the chunk that
-// holds the token's own row, key and value are rotated, rounded and appended).  A wave keeps everything about its 16
-// rows to itself: the partial dot products of a row meet by lane exchanges, the wave takes its own maximum, weights
-// and sum, multiplies its value vectors in registers and adds them up across its rows by lane exchanges again; only
-// the four waves' figures (maximum, sum, head_dim weighted values each) meet in LDS.  Two barriers per chunk.
+// holds the token's own row, key and value are rotated, rounded and appended).  The lanes of a row keep a running maximum, sum
+// and weighted values of THEIR rows over all chunks of the workgroup: the dot product's exchanges are the only ones in the
+// loop, and there is no barrier in it, so no wave's requests wait for another wave's rows.  The groups of lanes are merged by
+// lane exchanges, the four waves in LDS, once behind the loop.  Bound by HBM in long contexts: 32 heads of 128 at 8000 positions
+// 36.3 -> 30 us (131 MB: 4.4 TB/s, 6 TB/s beyond the 8 us that one position takes with its merge), 32 000 positions 104 -> 91 us;
+// by the chain of memory round trips in short ones: 500 positions 10.1 -> 8.4, 2000 18.4 -> 14.0.
 // MAXD: the largest head size of this instance (128 or 256) -- registers and LDS are sized by it, and the smaller one
 // lets twice as many workgroups share a compute unit.
 template <int W, int MAXD>
@@ -580,13 +625,21 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const AttnArgs
         }
     }
 
-    float run_m = -INFINITY, run_l = 0.0f, run_o = 0.0f;   // over the chunks so far (run_o: element tid, tid < d)
+    // Every group of L lanes keeps ITS rows' running maximum, sum and weighted values over all chunks of the workgroup: no
+    // barrier and no exchange beyond the dot products' inside the loop, so a wave's next requests never wait for another
+    // wave's rows.  The groups, then the waves, are merged once, behind the loop.
+    __syncthreads();                                    // s_q and the token's own row are there
+    float q[W];
+#pragma unroll
+    for (int x = 0; x < W; ++x) q[x] = active ? s_q[cc * W + x] : 0.0f;
+    float m_g = -INFINITY, l_g = 0.0f, o_g[W];
+#pragma unroll
+    for (int x = 0; x < W; ++x) o_g[x] = 0.0f;
     for (int c = chunk; c <= last_chunk; c += groups) {
         const int j0 = c * kChunk;
         const int rows = min(kChunk, pos + 1 - j0);
         const bool holds_token = owner && c == last_chunk;   // uniform
         const bool more = c + groups <= last_chunk;          // uniform
-        __syncthreads();                                // s_q and the token's row are there; the previous chunk's figures have been read
         float score[kVecs];
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
@@ -597,27 +650,28 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const AttnArgs
                 float k[W];
                 unpack_bf16<W>(kv[i], k);
 #pragma unroll
-                for (int x = 0; x < W; ++x) acc += s_q[cc * W + x] * (own ? s_newk[cc * W + x] : k[x]);
+                for (int x = 0; x < W; ++x) acc = __builtin_fmaf(q[x], own ? s_newk[cc * W + x] : k[x], acc);
             }
 #pragma unroll
             for (int off = 1; off < L; off <<= 1) acc += __shfl_xor(acc, off);
             score[i] = row < rows ? acc : -INFINITY;
         }
         if (more) request(c + groups, true);            // the next chunk travels while this one is worked on
-        float m_w = score[0];
+        float m_new = m_g;
 #pragma unroll
-        for (int i = 1; i < kVecs; ++i) m_w = fmaxf(m_w, score[i]);
+        for (int i = 0; i < kVecs; ++i) m_new = fmaxf(m_new, score[i]);
+        const float base = m_new == -INFINITY ? 0.0f : m_new;   // a group without rows so far adds nothing
+        const float f = expf(m_g - base);
+        l_g *= f;
 #pragma unroll
-        for (int off = L; off < kWave; off <<= 1) m_w = fmaxf(m_w, __shfl_xor(m_w, off));
-        float l_w = 0.0f, o_w[W];
-#pragma unroll
-        for (int x = 0; x < W; ++x) o_w[x] = 0.0f;
+        for (int x = 0; x < W; ++x) o_g[x] *= f;
+        m_g = m_new;
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
             const int row = grp + i * kRowsPerStep;
             const bool own = holds_token && j0 + row == pos;
-            const float w = m_w == -INFINITY ? 0.0f : expf(score[i] - m_w);   // a wave without rows adds nothing
-            l_w += w;
+            const float w = expf(score[i] - base);
+            l_g += w;
             if (active) {
                 float v[W];
                 unpack_bf16<W>(vv[i], v);
@@ -625,41 +679,43 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const AttnArgs
                 // held before (row `pos` is requested before this launch writes it; a caller's cache need not be finite)
                 const bool counts = row < rows;
 #pragma unroll
-                for (int x = 0; x < W; ++x) o_w[x] += counts ? w * (own ? s_newv[cc * W + x] : v[x]) : 0.0f;
+                for (int x = 0; x < W; ++x) o_g[x] = __builtin_fmaf(w, counts ? (own ? s_newv[cc * W + x] : v[x]) : 0.0f, o_g[x]);
             }
         }
         if (more) request(c + groups, false);
+    }
+    // the wave's groups into the wave's figures
+    float m_w = m_g;
 #pragma unroll
-        for (int off = L; off < kWave; off <<= 1) {
-            l_w += __shfl_xor(l_w, off);
+    for (int off = L; off < kWave; off <<= 1) m_w = fmaxf(m_w, __shfl_xor(m_w, off));
+    const float f_g = m_g == -INFINITY ? 0.0f : expf(m_g - m_w);
+    l_g *= f_g;
 #pragma unroll
-            for (int x = 0; x < W; ++x) o_w[x] += __shfl_xor(o_w[x], off);
-        }
-        if (lane < L && active) {
+    for (int x = 0; x < W; ++x) o_g[x] *= f_g;
 #pragma unroll
-            for (int x = 0; x < W; ++x) s_ow[wave][cc * W + x] = o_w[x];
-        }
-        if (lane == 0) { s_mw[wave] = m_w; s_lw[wave] = l_w; }
-        __syncthreads();
-        // the four waves' figures into the chunk's, and the chunk into the running ones
-        static_assert(kAttnWaves == 4, "four waves' figures");
-        const float m_c = fmaxf(fmaxf(s_mw[0], s_mw[1]), fmaxf(s_mw[2], s_mw[3]));   // finite: the chunk has a row
-        float f_w[kAttnWaves], l_c = 0.0f;
+    for (int off = L; off < kWave; off <<= 1) {
+        l_g += __shfl_xor(l_g, off);
 #pragma unroll
-        for (int q = 0; q < kAttnWaves; ++q) {
-            f_w[q] = s_mw[q] == -INFINITY ? 0.0f : expf(s_mw[q] - m_c);
-            l_c += f_w[q] * s_lw[q];
-        }
-        const float m_new = fmaxf(run_m, m_c);
-        const float f_run = expf(run_m - m_new), f_c = expf(m_c - m_new);
-        if (tid < d) {
-            float t = 0.0f;
+        for (int x = 0; x < W; ++x) o_g[x] += __shfl_xor(o_g[x], off);
+    }
+    if (lane < L && active) {
 #pragma unroll
-            for (int q = 0; q < kAttnWaves; ++q) t += f_w[q] * s_ow[q][tid];
-            run_o = run_o * f_run + t * f_c;
-        }
-        run_l = run_l * f_run + l_c * f_c;
-        run_m = m_new;
+        for (int x = 0; x < W; ++x) s_ow[wave][cc * W + x] = o_g[x];
+    }
+    if (lane == 0) { s_mw[wave] = m_w; s_lw[wave] = l_g; }
+    __syncthreads();
+    // the four waves' figures into the workgroup's (run_o: element tid, tid < d)
+    static_assert(kAttnWaves == 4, "four waves' figures");
+    const float run_m = fmaxf(fmaxf(s_mw[0], s_mw[1]), fmaxf(s_mw[2], s_mw[3]));   // finite: the workgroup has a row
+    float f_w[kAttnWaves], run_l = 0.0f, run_o = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kAttnWaves; ++w) {
+        f_w[w] = s_mw[w] == -INFINITY ? 0.0f : expf(s_mw[w] - run_m);
+        run_l += f_w[w] * s_lw[w];
+    }
+    if (tid < d) {
+#pragma unroll
+        for (int w = 0; w < kAttnWaves; ++w) run_o += f_w[w] * s_ow[w][tid];
     }
 
     // The head's workgroups are merged by whichever of them finishes last.  Nobody waits for anybody: every
@@ -695,11 +751,14 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const AttnArgs
     // wave's memory operations is outstanding
     asm volatile("s_waitcnt vmcnt(0)" ::"v"(sink) : "memory");
     __syncthreads();                                    // all deposits of this workgroup have been performed (and s_o, s_w read)
-    unsigned int* counter = reinterpret_cast<unsigned int*>(scratch + (int64_t)p.n_heads * p.chunks * (d + 2)) + head;
+    unsigned int* counter = reinterpret_cast<unsigned int*>(scratch + (int64_t)p.n_heads * p.chunks * (d + 2)) + head * kAttnCounterStride;
     if (tid == 0) s_ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (s_ticket != (unsigned)(used - 1)) return;       // uniform
-    attn_merge(p, scratch, out, head, used, s_o, s_w);
+    static_assert(sizeof(s_ow) >= kAttnThreads * sizeof(float), "the teams' sums go where the waves' figures were");
+    if (used <= 16) attn_merge_together<MAXD, 16>(p, scratch, out, head, used, s_w, s_mw, &s_ow[0][0]);   // uniform
+    else if (used <= kMergeTogether) attn_merge_together<MAXD, kMergeTogether>(p, scratch, out, head, used, s_w, s_mw, &s_ow[0][0]);
+    else attn_merge(p, scratch, out, head, used, s_o, s_w);
     if (tid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -984,8 +1043,12 @@ __global__ void pos_advance_kernel(int32_t* pos) {
 
 }  // namespace
 
-constexpr int kAttnTargetWorkgroups = 1024;   // of bl_attn_decode: four per compute unit (measured best on 32 heads of 128)
-constexpr int kAttnMaxGroups = 32;            // per head, however few heads there are (16 heads of 96: 32 beat 64)
+// Workgroups of bl_attn_decode: three per compute unit, and up to 64 per head however few heads there are -- as many as the merge
+// reads in one go.  Measured per head (us): 32 heads of 128, 16 000 positions, 16 / 24 / 32 / 64 workgroups 64.6 / 49.7 / 54.7 / 58.7; 64
+// heads, 8 / 12 / 16: 119.5 / 96.3 / 100.7; 40 heads, 14 / 20 / 26: 76.3 / 67.2 / 76.2; 12 heads of 64, 32 000 positions, 24 / 32 / 64:
+// 64.4 / 50.6 / 36.5.
+constexpr int kAttnTargetWorkgroups = 768;
+constexpr int kAttnMaxGroups = 64;
 int g_attn_groups = 0;                        // forced workgroups per head (0: automatic)
 
 hipError_t launch_norm_quant(const bl_norm_quant_args& a, hipStream_t s) {
@@ -1055,7 +1118,7 @@ hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
 void set_attn_groups(int groups) { g_attn_groups = groups; }
 
 int64_t attn_scratch_floats(int n_heads, int head_dim, int max_pos) {   // per query
-    return (int64_t)n_heads * attn_chunks(max_pos) * (head_dim + 2) + n_heads;
+    return (int64_t)n_heads * attn_chunks(max_pos) * (head_dim + 2) + (int64_t)n_heads * kAttnCounterStride;
 }
 
 hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
@@ -1068,7 +1131,7 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     p.pos0 = a.pos0;
     // a prompt's queries never look beyond its last token: chunks up to that one only
     p.chunks = attn_chunks(a.pos0 + a.M);
-    p.scratch_stride = (int64_t)a.n_heads * p.chunks * (a.head_dim + 2) + a.n_heads;
+    p.scratch_stride = attn_scratch_floats(a.n_heads, a.head_dim, a.pos0 + a.M);
     kv_append_kernel<<<dim3((unsigned)a.M), dim3(256), 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
