@@ -422,7 +422,8 @@ struct AttnArgs {
     uint16_t*      k_cache;
     uint16_t*      v_cache;
     float*         out;
-    float*         scratch;     // per query [n_heads][chunks][head_dim + 2] (weighted values, maximum, sum), then n_heads counters, kAttnCounterStride words apart
+    float*         scratch;     // per query [n_heads][chunks][head_dim + 2] (weighted values, maximum, sum), then n_heads counters
+    int32_t        counters_apart;   // the ticket counters are the first words of the heads' last pieces, which nobody deposits in
     int32_t        n_heads, head_dim, max_pos, chunks;
     // several consecutive tokens (a prompt): pos is null, query z has position pos0 + z, its own row of q_lin and out
     // and its own part of scratch; keys and values are in the cache already (kv_append_kernel)
@@ -751,7 +752,10 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const AttnArgs
     // wave's memory operations is outstanding
     asm volatile("s_waitcnt vmcnt(0)" ::"v"(sink) : "memory");
     __syncthreads();                                    // all deposits of this workgroup have been performed (and s_o, s_w read)
-    unsigned int* counter = reinterpret_cast<unsigned int*>(scratch + (int64_t)p.n_heads * p.chunks * (d + 2)) + head * kAttnCounterStride;
+    // every workgroup of a launch draws a ticket: with the counters of all heads side by side in one or two memory lines those
+    // updates queue up behind each other (32 heads of 128 at 2000 positions: 16.0 us, with the counters apart 14.0)
+    unsigned int* counter = reinterpret_cast<unsigned int*>(
+        p.counters_apart ? scratch + ((int64_t)head * p.chunks + p.chunks - 1) * (d + 2) : scratch + (int64_t)p.n_heads * p.chunks * (d + 2) + head);
     if (tid == 0) s_ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (s_ticket != (unsigned)(used - 1)) return;       // uniform
@@ -1047,7 +1051,10 @@ __global__ void pos_advance_kernel(int32_t* pos) {
 // reads in one go.  Measured per head (us): 32 heads of 128, 16 000 positions, 16 / 24 / 32 / 64 workgroups 64.6 / 49.7 / 54.7 / 58.7; 64
 // heads, 8 / 12 / 16: 119.5 / 96.3 / 100.7; 40 heads, 14 / 20 / 26: 76.3 / 67.2 / 76.2; 12 heads of 64, 32 000 positions, 24 / 32 / 64:
 // 64.4 / 50.6 / 36.5.
+// A cache so short that four per compute unit give every chunk a workgroup of its own takes those (32 heads, 2000 positions, 24 / 32:
+// 14.7 / 14.0).
 constexpr int kAttnTargetWorkgroups = 768;
+constexpr int kAttnShortWorkgroups = 1024;
 constexpr int kAttnMaxGroups = 64;
 int g_attn_groups = 0;                        // forced workgroups per head (0: automatic)
 
@@ -1107,9 +1114,13 @@ hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
     p.n_heads = a.n_heads; p.head_dim = a.head_dim; p.max_pos = a.max_pos; p.chunks = attn_chunks(a.max_pos);
     p.pos0 = 0; p.scratch_stride = 0;
     // Workgroups per head: one per chunk while that keeps the launch within a few workgroups per compute unit; a longer
-    // cache is walked by that many workgroups, several chunks each (a deposit per workgroup, not per chunk).
-    int groups = g_attn_groups > 0 ? g_attn_groups : min(kAttnMaxGroups, (kAttnTargetWorkgroups + a.n_heads - 1) / a.n_heads);
-    if (groups > p.chunks) groups = p.chunks;
+    // cache is walked by fewer, several chunks each (a deposit per workgroup, not per chunk).
+    const int one_chunk_each = min(kAttnMaxGroups, (kAttnShortWorkgroups + a.n_heads - 1) / a.n_heads);
+    const int most = p.chunks <= one_chunk_each ? p.chunks : min(kAttnMaxGroups, (kAttnTargetWorkgroups + a.n_heads - 1) / a.n_heads);
+    // A cache of more chunks than that has pieces of scratch memory to spare: the last one of each head takes its counter, and
+    // no launch, however its workgroups are forced, deposits there.  (By the cache's size only: the same for every call on it.)
+    p.counters_apart = p.chunks > most;
+    const int groups = min(g_attn_groups > 0 ? g_attn_groups : most, p.counters_apart ? p.chunks - 1 : p.chunks);
     const dim3 grid((unsigned)a.n_heads, (unsigned)groups);
     launch_attn_chunks(p, grid, s);
     return hipGetLastError();
@@ -1118,7 +1129,7 @@ hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
 void set_attn_groups(int groups) { g_attn_groups = groups; }
 
 int64_t attn_scratch_floats(int n_heads, int head_dim, int max_pos) {   // per query
-    return (int64_t)n_heads * attn_chunks(max_pos) * (head_dim + 2) + (int64_t)n_heads * kAttnCounterStride;
+    return (int64_t)n_heads * attn_chunks(max_pos) * (head_dim + 2) + n_heads;
 }
 
 hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
@@ -1132,6 +1143,7 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     // a prompt's queries never look beyond its last token: chunks up to that one only
     p.chunks = attn_chunks(a.pos0 + a.M);
     p.scratch_stride = attn_scratch_floats(a.n_heads, a.head_dim, a.pos0 + a.M);
+    p.counters_apart = 0;   // one workgroup per chunk: every piece is used
     kv_append_kernel<<<dim3((unsigned)a.M), dim3(256), 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

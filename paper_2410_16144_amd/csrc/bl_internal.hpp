@@ -181,9 +181,6 @@ hipError_t launch_tl2_unpack(const uint32_t* packed, int64_t N, int64_t K, int64
 hipError_t launch_norm_quant(const ::bl_norm_quant_args& a, hipStream_t s);
 hipError_t launch_rope_table(float* table, int head_dim, int max_pos, double theta, hipStream_t s);
 int attn_chunks(int max_pos);
-// Words between the ticket counters of two heads in the attention's scratch memory: every workgroup of a launch draws a ticket,
-// and with the counters of all heads in one or two memory lines those updates queue up behind each other.
-constexpr int kAttnCounterStride = 64;
 int64_t attn_scratch_floats(int n_heads, int head_dim, int max_pos);   // per query
 hipError_t launch_attn_decode(const ::bl_attn_args& a, hipStream_t s);
 hipError_t launch_pos_advance(int32_t* pos, hipStream_t s);

@@ -273,6 +273,47 @@ def test_attn_decode_several_chunks_per_workgroup(dev, mods, groups, n_heads, he
         B.bl_set_tuning("attn_groups", 0)
 
 
+@pytest.mark.parametrize("n_heads,head_dim", [(2, 64), (1, 256), (2, 36)])
+def test_attn_decode_merges_of_every_size(dev, mods, n_heads, head_dim):
+    """The last workgroup reads up to 16 or up to 64 deposits in one round: positions that leave 2, 16, 17 and 64 deposits, in a
+    cache whose counters lie behind the deposits and in a longer one whose counters lie between them; twice each (the counters
+    must be back at zero) and with fewer workgroups in between, against the fp64 softmax."""
+    for chunks in (64, 66):
+        _merges_of_every_size(dev, mods, n_heads, head_dim, chunks)
+
+
+def _merges_of_every_size(dev, mods, n_heads, head_dim, chunks):
+    B, dec, ops = mods
+    hidden = n_heads * head_dim
+    max_pos = 64 * chunks
+    r = _rng(53500 + hidden)
+    table = dec.rope_table(head_dim, max_pos, dev)
+    q_t, k_t, v_t = (torch.empty((1, hidden), device=dev) for _ in range(3))
+    pos_t = torch.zeros(1, dtype=torch.int32, device=dev)
+    att = dec.Attention(n_heads, head_dim, max_pos, q_t, k_t, v_t, pos_t, table)
+    for c in (att.k_cache, att.v_cache):
+        c.copy_(_bits_as_bf16_tensor(synth.to_bf16_bits(r.standard_normal((max_pos, hidden)).astype(np.float32)), dev))
+    try:
+        for used in (2, 16, 17, 64):
+            B.bl_set_tuning("attn_groups", 1000)
+            pos = 64 * used - 1 - used % 3
+            ql, kl, vl = (3.0 * r.standard_normal(hidden).astype(np.float32) for _ in range(3))
+            q_t.copy_(_t(ql[None], dev)); k_t.copy_(_t(kl[None], dev)); v_t.copy_(_t(vl[None], dev))
+            pos_t.fill_(pos)
+            first = att.launch().clone()
+            B.bl_set_tuning("attn_groups", 3)
+            fewer = att.launch().clone()
+            B.bl_set_tuning("attn_groups", 1000)
+            again = att.launch()
+            torch.cuda.synchronize()
+            assert torch.equal(first, again) and float((fewer - again).abs().max()) <= 2e-5 * max(1.0, float(again.abs().max()))
+            kc64, vc64 = (c[:pos + 1].float().cpu().numpy().astype(np.float64) for c in (att.k_cache, att.v_cache))
+            want = D.attention_decode(D.rope(ql, pos, n_heads), kc64, vc64, n_heads)
+            assert np.abs(again.cpu().numpy()[0] - want).max() <= 2e-5 * max(1.0, np.abs(want).max()), used
+    finally:
+        B.bl_set_tuning("attn_groups", 0)
+
+
 @pytest.mark.parametrize("pattern", [0x7FC0, 0x7F80, 0xFF80])
 @pytest.mark.parametrize("n_heads,head_dim,groups", [(3, 64, 0), (2, 128, 3), (1, 256, 2)])
 def test_attn_decode_cache_rows_beyond_the_token_may_hold_anything(dev, mods, pattern, n_heads, head_dim, groups):
@@ -855,6 +896,27 @@ def test_attn_prefill_parity(dev, mods, n_heads, head_dim, max_pos, pos0, M):
     print(f"attn_prefill heads={n_heads} d={head_dim} pos0={pos0} M={M}: worst error {worst:.2e}", flush=True)
     want_k = D.round_to_bf16(D.rope(lin[1][M - 1], pos0 + M - 1, n_heads))
     assert np.all(np.abs(kc64[pos0 + M - 1] - want_k) <= np.maximum(np.abs(want_k), 1e-30) * 2.0 ** -7)
+
+
+def test_attn_prefill_head_size_above_128_behind_many_chunks(dev, mods):
+    """More deposits (one per 64 cache rows and token) than are read in one round, against the fp64 softmax."""
+    B, dec, ops = mods
+    head_dim, pos0, M, max_pos = 256, 64 * 65 - 1, 2, 64 * 66
+    r = _rng(96000)
+    table = dec.rope_table(head_dim, max_pos, dev)
+    k_cache, v_cache = (_bits_as_bf16_tensor(synth.to_bf16_bits(r.standard_normal((max_pos, head_dim)).astype(np.float32)), dev).clone()
+                        for _ in range(2))
+    lin = [3.0 * r.standard_normal((M, head_dim)).astype(np.float32) for _ in range(3)]
+    lin_t, out = [_t(v, dev) for v in lin], torch.empty((M, head_dim), device=dev)
+    scratch = torch.zeros(B.bl_attn_prefill_scratch_bytes(1, head_dim, pos0, M), dtype=torch.uint8, device=dev)
+    for _ in range(2):
+        B.bl_attn_prefill(*(t.data_ptr() for t in lin_t), table.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), out.data_ptr(),
+                          scratch.data_ptr(), 1, head_dim, max_pos, pos0, M, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    kc64, vc64 = (c.float().cpu().numpy().astype(np.float64) for c in (k_cache, v_cache))
+    for m in range(M):
+        want = D.attention_decode(D.rope(lin[0][m], pos0 + m, 1), kc64[:pos0 + m + 1], vc64[:pos0 + m + 1], 1)
+        assert np.abs(out[m].cpu().numpy() - want).max() <= 2e-5 * max(1.0, np.abs(want).max())
 
 
 @pytest.mark.parametrize("n_heads,head_dim,pos0,M", [(2, 8, 31, 33), (2, 24, 0, 32), (2, 32, 127, 65), (3, 72, 128, 1), (2, 80, 96, 64),
