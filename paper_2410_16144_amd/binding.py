@@ -188,6 +188,36 @@ def lib():
     return l
 
 
+_calls = None
+CALLS_PATH = os.path.join(HERE, "_calls.so")
+# bl_calls.cpp: the `which` of calls().launch
+LAUNCH_GEMV_BATCH, LAUNCH_DECODE_BATCH, LAUNCH_QUANT_BATCH, LAUNCH_DECODE_NORM_BATCH, LAUNCH_TL2_BATCH, LAUNCH_ATTN_DECODE = range(6)
+
+
+def calls():
+    """The eager calls in native code (csrc/bl_calls.cpp): allocation, current stream and library call in one.  They answer
+    with None whatever they do not take as it is; the caller then goes through its own checks and this binding."""
+    global _calls
+    if _calls is None:
+        lib()   # torch and the library first
+        if not os.path.exists(CALLS_PATH):
+            raise RuntimeError("_calls.so is not built (%s). Run `python paper_2410_16144_amd/build.py`." % CALLS_PATH)
+        import importlib.machinery
+        import importlib.util
+        loader = importlib.machinery.ExtensionFileLoader("paper_2410_16144_amd._calls", CALLS_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader(loader.name, loader))
+        loader.exec_module(module)
+        _calls = module
+    return _calls
+
+
+def launch(which: int, items, count: int, M: int, workspace_dev: int, where: str):
+    """One prepared launch on the current stream; raises BitLinearError like the calls below."""
+    status = calls().launch(which, items, count, M, workspace_dev)
+    if status:
+        raise BitLinearError(status, where)
+
+
 def _check(status, where):
     if status != BL_OK:
         raise BitLinearError(status, where)

@@ -32,12 +32,17 @@ PER_FILE_FLAGS = {
 }
 
 
+# The eager calls in native code (csrc/bl_calls.cpp): a Python extension on torch's C++ interface, host code only.
+CALLS_SRC = os.path.join(CSRC, "bl_calls.cpp")
+CALLS_LIB = os.path.join(HERE, "_calls.so")
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
 def _newest_input():
-    files = sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(INCLUDE, "*.h"))
+    files = sources() + [CALLS_SRC] + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(INCLUDE, "*.h"))
     return max(os.path.getmtime(f) for f in files)
 
 
@@ -58,7 +63,7 @@ def _hip_runtime_dir() -> str:
 
 def build(force: bool = True, extra_flags=(), verbose: bool = False) -> str:
     """Compile every translation unit and link the shared library.  Returns its path."""
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= _newest_input():
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _newest_input() for f in (LIB, CALLS_LIB)):
         return LIB
     os.makedirs(OBJ_DIR, exist_ok=True)
 
@@ -83,7 +88,26 @@ def build(force: bool = True, extra_flags=(), verbose: bool = False) -> str:
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp,
                            "-no-hip-rt", "-L", _hip_runtime_dir(), "-lamdhip64"])
     os.replace(tmp, LIB)
+    build_calls()
     return LIB
+
+
+def build_calls() -> str:
+    """Compile the extension module against the PyTorch that is installed and the library next to it."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = CALLS_LIB + ".tmp.%d" % os.getpid()
+    inc = os.path.join(root, "include")
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", INCLUDE, "-isystem", inc,
+                           "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+                           "-isystem", sysconfig.get_paths()["include"], CALLS_SRC, "-o", tmp, "-L", HERE, "-lbitlinear",
+                           "-L", os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+                           "-Wl,-rpath,$ORIGIN"])
+    os.replace(tmp, CALLS_LIB)
+    return CALLS_LIB
 
 
 ABI_CHECK_SRC = os.path.join(os.path.dirname(HERE), "tests", "c_abi", "abi_check.c")

@@ -32,7 +32,7 @@ ROPE_THETA = 10000.0
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return B.calls().stream()
 
 
 def norm_quant(mode: int, gamma: Optional[torch.Tensor], eps: float = EPS, a: Optional[torch.Tensor] = None,
@@ -41,6 +41,13 @@ def norm_quant(mode: int, gamma: Optional[torch.Tensor], eps: float = EPS, a: Op
                pieces: int = 0):
     """bl_norm_quant on [M,K] fp32 tensors.  Returns the QuantAct (None if quantize is False).  scratch: a uint8
     tensor of M * BL_NORM_SCRATCH_BYTES bytes lets long rows spread over several workgroups."""
+    if mode != B.BL_NORM_PREMULTIPLIED:
+        given = (out.q, out.a_scale, out.q_sum) if quantize and out is not None else (None, None, None)
+        r = B.calls().norm_quant(mode, gamma, eps, a, b, h, *given, y, quantize, scratch)
+        if r is not None:
+            if not quantize:
+                return None
+            return out if out is not None else ops.QuantAct(r[0], r[1], r[2], int(gamma.shape[0]))
     ref = h if mode == B.BL_NORM_RESIDUAL else a
     M, K = ref.shape
     for t in (a, b, h, y):
@@ -90,7 +97,7 @@ class Attention:
                                      self.scratch.data_ptr(), n_heads, head_dim, max_pos)
 
     def launch(self):
-        B.bl_attn_decode(self.args, _stream())
+        B.launch(B.LAUNCH_ATTN_DECODE, self.args, 1, 1, 0, "bl_attn_decode")
         return self.out
 
 
@@ -144,7 +151,7 @@ class NormDecodeGroup:
         self.items = B.make_decode_norm_items(items)
 
     def launch(self):
-        B.bl_decode_norm_batch(self.items, self.workspace_ptr, _stream())
+        B.launch(B.LAUNCH_DECODE_NORM_BATCH, self.items, len(self.items), 1, self.workspace_ptr, "bl_decode_norm_batch")
         return self.outs
 
 

@@ -9,7 +9,7 @@ from . import binding as B
 
 
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    return B.calls().stream()
 
 
 @dataclass
@@ -106,6 +106,9 @@ def alloc_quant(M: int, K: int, device) -> QuantAct:
 
 def quant_act(x: torch.Tensor, out: Optional[QuantAct] = None) -> QuantAct:
     """x: [M,K] fp32 or bf16 device tensor (last dim contiguous) -> QuantAct (bl_quant_act)."""
+    r = B.calls().quant_act(x, None, None, None) if out is None else B.calls().quant_act(x, out.q, out.a_scale, out.q_sum)
+    if r is not None:
+        return out if out is not None else QuantAct(r[0], r[1], r[2], int(x.shape[1]))
     assert x.is_cuda and x.dim() == 2 and x.stride(1) == 1
     if x.dtype == torch.float32:
         dt = B.BL_F32
@@ -136,13 +139,16 @@ class QuantGroup:
              o.a_scale.data_ptr(), o.q_sum.data_ptr()) for x, o in zip(self.xs, self.outs))
 
     def launch(self):
-        B.bl_quant_act_batch(self.items, _stream())
+        B.launch(B.LAUNCH_QUANT_BATCH, self.items, len(self.items), 0, 0, "bl_quant_act_batch")
         return self.outs
 
 
 def _product(fn, pw: PackedWeight, qa: QuantAct, out, want_acc):
-    M = qa.M
     assert qa.K == pw.K
+    r = B.calls().product(fn is B.bl_gemm, pw.blob, pw.desc, qa.q, qa.a_scale, qa.q_sum, out, want_acc)
+    if r is not None:
+        return r if want_acc else r[0]
+    M = qa.M
     if out is None:
         out = torch.empty((M, pw.N), dtype=torch.float32, device=pw.blob.device)
     acc = torch.empty((M, pw.N), dtype=torch.int32, device=pw.blob.device) if want_acc else None
@@ -166,6 +172,9 @@ def gemm_batch(pws, qa: QuantAct):
     outputs [M, N_i], each identical to gemm(pw_i, qa)."""
     M, dev = qa.M, qa.q.device
     assert 1 <= len(pws) <= B.BL_MAX_GEMM_BATCH and all(pw.K == qa.K for pw in pws)
+    outs = B.calls().gemm_batch([t for pw in pws for t in (pw.blob, pw.desc)], qa.q, qa.a_scale, qa.q_sum)
+    if outs is not None:
+        return outs
     outs = [torch.empty((M, pw.N), dtype=torch.float32, device=dev) for pw in pws]
     B.bl_gemm_batch([(pw.blob.data_ptr(), pw.desc, qa.q.data_ptr(), qa.a_scale.data_ptr(), qa.q_sum.data_ptr(), o.data_ptr(), 0)
                      for pw, o in zip(pws, outs)], M, _stream())
@@ -214,7 +223,7 @@ class GemvGroup:
             for i, (w, a, o) in enumerate(zip(self.weights, self.acts, self.outs)))
 
     def launch(self):
-        B.bl_gemv_batch(self.items, self.M, self.workspace_ptr, _stream())
+        B.launch(B.LAUNCH_GEMV_BATCH, self.items, len(self.items), self.M, self.workspace_ptr, "bl_gemv_batch")
         return self.outs
 
 
@@ -238,7 +247,7 @@ class Tl2GemvGroup:
             for i, (w, a, o) in enumerate(zip(self.weights, self.acts, self.outs)))
 
     def launch(self):
-        B.bl_tl2_gemv_batch(self.items, self.workspace_ptr, _stream())
+        B.launch(B.LAUNCH_TL2_BATCH, self.items, len(self.items), 1, self.workspace_ptr, "bl_tl2_gemv_batch")
         return self.outs
 
 
@@ -287,5 +296,5 @@ class DecodeGroup:
             for i, (w, x, o) in enumerate(zip(self.weights, self.xs, self.outs)))
 
     def launch(self):
-        B.bl_decode_batch(self.items, self.M, self.workspace_ptr, _stream())
+        B.launch(B.LAUNCH_DECODE_BATCH, self.items, len(self.items), self.M, self.workspace_ptr, "bl_decode_batch")
         return self.outs
