@@ -58,7 +58,7 @@ constexpr int gemm_lds_bytes() {
 template <int MB, int H, int WK, int WN>
 __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const int M, const int tile_x, const int tile_y) {
     static_assert(WK == 1 || (MB * H) % WK == 0, "the K groups share out the wave's MFMA tiles for the final sum");
-    static_assert(H >= 2 && H <= 4, "32-row blocks per wave");
+    static_assert(H >= 1 && H <= 4, "32-row blocks per wave");
     using Ring = GemmRing<MB, H, WK, WN>;   // ring depths and wait counts: bl_gemm_ring.hpp, checked by a host-side model
     constexpr int NT = Ring::kNT;         // packed 64-row tiles a wave loads per step
     constexpr int kWaves = WN * WK;
@@ -344,10 +344,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const int M, con
 // Workgroup index -> tile, so that the die (index % 8) depends on the N position only: every die keeps ITS slice of
 // the packed weights in its L2 for the whole launch, and consecutive workgroups (all dies) walk through the same
 // token rows at the same time.  The grid is padded to a multiple of 8 along N; false for a padding workgroup.
-__device__ __forceinline__ bool tile_of_workgroup(int gx, int& tile_x, int& tile_y) {
+__device__ __forceinline__ bool tile_of_workgroup(int wg, int gx, int& tile_x, int& tile_y) {
     const int gxh = (gx + kXcds - 1) / kXcds;
-    const int rest = blockIdx.x / kXcds;
-    tile_x = (rest % gxh) * kXcds + blockIdx.x % kXcds;
+    const int rest = wg / kXcds;
+    tile_x = (rest % gxh) * kXcds + wg % kXcds;
     tile_y = rest / gxh;
     return tile_x < gx;
 }
@@ -355,7 +355,7 @@ __device__ __forceinline__ bool tile_of_workgroup(int gx, int& tile_x, int& tile
 template <int MB, int H, int WK, int WN>
 __global__ __launch_bounds__(64 * WN * WK, WN * WK == 4 ? 2 : 1) void gemm_kernel(const GemmProblem p, const int M, const int gx) {
     int tile_x, tile_y;
-    if (!tile_of_workgroup(gx, tile_x, tile_y)) return;   // uniform
+    if (!tile_of_workgroup(blockIdx.x, gx, tile_x, tile_y)) return;   // uniform
     gemm_tile<MB, H, WK, WN>(p, M, tile_x, tile_y);
 }
 
@@ -369,7 +369,7 @@ struct GemmBatch {
 template <int MB, int H, int WK, int WN>
 __global__ __launch_bounds__(64 * WN * WK, WN * WK == 4 ? 2 : 1) void gemm_batch_kernel(const GemmBatch b, const int M, const int gx) {
     int tile_x, tile_y;
-    if (!tile_of_workgroup(gx, tile_x, tile_y)) return;   // uniform
+    if (!tile_of_workgroup(blockIdx.x, gx, tile_x, tile_y)) return;   // uniform
     int item = 0, first = 0;
 #pragma unroll
     for (int i = 0; i + 1 < kMaxGemmBatch; ++i)
@@ -377,7 +377,39 @@ __global__ __launch_bounds__(64 * WN * WK, WN * WK == 4 ? 2 : 1) void gemm_batch
     gemm_tile<MB, H, WK, WN>(b.p[item], M, tile_x - first, tile_y);
 }
 
+// Two tile widths in one launch, for launches of between one and one and a half 64 x 256 tiles per compute unit: there some
+// units got two tiles and the others one, and the launch took as long as two.  Here every unit gets ONE 64 x 256 tile, and the
+// rest of the rows are cut into 64 x 128 tiles (the same loop, 32 rows per wave), at most one per unit.
+struct GemmMixed {
+    GemmProblem p[kMaxGemmBatch];
+    int32_t     end[kMaxGemmBatch];          // first 256-row position behind product i (INT32_MAX behind the last one in use)
+    int32_t     small_end[kMaxGemmBatch];    // first 128-row position behind product i
+    int32_t     small_first[kMaxGemmBatch];  // product i's first 128-row position in its own rows
+    int32_t     gx, wgs, small_gx;           // 256-row positions and their workgroups; 128-row positions
+};
+
+__global__ __launch_bounds__(256, 2) void gemm_mixed_kernel(const GemmMixed b, const int M) {
+    int tile_x, tile_y, item = 0, first = 0;
+    if ((int)blockIdx.x < b.wgs) {   // uniform
+        if (!tile_of_workgroup(blockIdx.x, b.gx, tile_x, tile_y)) return;
+#pragma unroll
+        for (int i = 0; i + 1 < kMaxGemmBatch; ++i)
+            if (tile_x >= b.end[i]) { item = i + 1; first = b.end[i]; }
+        gemm_tile<2, 2, 1, 4>(b.p[item], M, tile_x - first, tile_y);
+    } else {
+        if (!tile_of_workgroup(blockIdx.x - b.wgs, b.small_gx, tile_x, tile_y)) return;
+#pragma unroll
+        for (int i = 0; i + 1 < kMaxGemmBatch; ++i)
+            if (tile_x >= b.small_end[i]) { item = i + 1; first = b.small_end[i]; }
+        // (the narrow tile's pipeline is the wide one's: the same requests, loads and waits per step)
+        static_assert(GemmRing<2, 1, 1, 4>::kNT == GemmRing<2, 2, 1, 4>::kNT && GemmRing<2, 1, 1, 4>::kRQ == GemmRing<2, 2, 1, 4>::kRQ &&
+                          GemmRing<2, 1, 1, 4>::kYounger == GemmRing<2, 2, 1, 4>::kYounger, "the checked wait counts");
+        gemm_tile<2, 1, 1, 4>(b.p[item], M, tile_x - first + b.small_first[item], tile_y);
+    }
+}
+
 int g_force_mb = 0;
+constexpr int kCodeMixed = 25;   // bl_set_tuning "gemm_mb": the two-width kernel wherever it applies
 
 // One tile form: wave tile (32*MB) tokens x (32*H) weight rows, WN waves along N and WK along K.
 struct TileForm { int mb, h, wk, wn; };
@@ -398,7 +430,7 @@ TileForm form_of_code(int code) {
 // every compute unit two workgroups; 64 x 64 otherwise; and 32 x 64 or the K-split form when even that grid would
 // leave compute units without work.  `rows`: padded weight rows of the launch.
 TileForm choose_tile(int64_t M, int64_t rows) {
-    if (g_force_mb) return form_of_code(g_force_mb);
+    if (g_force_mb && g_force_mb != kCodeMixed && g_force_mb < 1000) return form_of_code(g_force_mb);
     const int64_t tiles_m = (M + 63) / 64;
     const auto wgs = [&](int wn, int hh) { return tiles_m * ((rows + wn * hh * 32 - 1) / (wn * hh * 32)); };
     TileForm f = {2, 2, 1, 4};
@@ -412,14 +444,75 @@ TileForm choose_tile(int64_t M, int64_t rows) {
     return f;
 }
 
-// The kernel of bl_gemm_narrow.hip (waves along K, no barriers) where its estimated time is below this file's: its code, or 0.
-// The estimates are straight lines through measured times (us) with the workgroups per compute unit x; this file's forms,
-// weights cold: 32 x 256 tiles (and, below 128 tokens, the K split) 3.4 + 0.20 KC up to x = 1 (1536^2: 8.2 us, 4096^2: 14.2,
-// 11008 -> 4096: 37.7), 19.1 for KC = 64 at x = 1.34; 64 x 256 tiles 26 us for KC = 64 and 69 for KC = 172 up to x = 2;
-// 64 x 512 tiles 0.40 x per tile of K (KC = 64, x = 3: 80 us).
-int choose_narrow(const GemmProblem* ps, int count, int64_t M) {
-    if (g_force_mb) return g_force_mb >= 1000 && gemm_narrow_takes(ps, count, M) ? g_force_mb : 0;
-    if (!gemm_narrow_takes(ps, count, M)) return 0;
+// Whether a launch takes the two-width kernel, and its shape.
+bool plan_mixed(const GemmProblem* ps, int count, int64_t M, GemmMixed& b) {
+    const int cus = compute_unit_count();
+    const int64_t tiles_m = (M + 63) / 64;
+    if (cus <= 0 || tiles_m > cus / kXcds) return false;
+    int64_t positions = 0;                                    // of 256 rows, product by product
+    for (int i = 0; i < count; ++i) positions += ((int64_t)ps[i].row_blocks + 3) / 4;
+    // positions that take 256-row tiles: a multiple of 8, so that every die gets as many tiles as it has units
+    const int64_t whole = cus / tiles_m / kXcds * kXcds;
+    if (positions * tiles_m <= cus) return false;
+    int64_t at = 0, small = 0;
+    for (int i = 0; i < kMaxGemmBatch; ++i) {
+        const GemmProblem& p = ps[i < count ? i : count - 1];
+        b.p[i] = p;
+        if (i < count) {
+            const int64_t mine = ((int64_t)p.row_blocks + 3) / 4, wide = at + mine <= whole ? mine : (whole > at ? whole - at : 0);
+            b.small_first[i] = (int32_t)(2 * wide);
+            const int64_t rest = (int64_t)p.row_blocks - 4 * wide;   // row blocks left over, two per 128-row position
+            small += rest > 0 ? (rest + 1) / 2 : 0;
+            at += wide;
+        } else {
+            b.small_first[i] = 0;
+        }
+        b.end[i] = i + 1 < count ? (int32_t)at : INT32_MAX;
+        b.small_end[i] = i + 1 < count ? (int32_t)small : INT32_MAX;
+    }
+    b.gx = (int32_t)at;
+    b.wgs = (int32_t)((at + kXcds - 1) / kXcds * kXcds * tiles_m);
+    b.small_gx = (int32_t)small;
+    return small * tiles_m <= cus;
+}
+
+// What a launch takes: one of this file's one-width forms (choose_tile), the two-width kernel or a form of bl_gemm_narrow.hip,
+// by estimated time.  The estimates are straight lines through the measured times (us, weights cold) of 108 launches -- nine
+// shapes from 2560 x 6912 to 4096 x 24064 and 8192^2, 128 to 1024 tokens -- over KC, the tiles along K, and x, the workgroups per
+// compute unit:
+//     32 x 256 (and the K split)   4.4 + KC * (0.18 up to x = 1;  0.21 + 0.056 (x - 1) up to 2;  0.14 x beyond)     0.81 .. 1.17 of the time
+//     64 x 256                     6.6 + KC * (0.20;  0.28 + 0.12 (x - 1);  0.23 x)                                  0.77 .. 1.07
+//     64 x 512                     8.4 + KC * (0.36;  0.57 + 0.17 (x - 1);  0.46 x)                                  0.70 .. 1.13
+//     two widths                   7.0 + KC * (0.245 + 0.055 * share of the units with a narrow tile)                0.89 .. 1.08
+// Small biases (the two-width kernel 5 % ahead, the waves-along-K forms 8 % behind) were set so that no launch of the 108 is
+// more than 1.5 % slower than its one-width form; on average they are 16 % faster (4096 -> 11008 at 384 tokens: 26.7 -> 22.4 us,
+// at 512 26.9 -> 25.0; 3200 -> 8640 at 512 22.1 -> 20.1; 8192^2 at 576 45.2 -> 39.3; 5120^2 at 1024 32.9 -> 29.9) and within 2.5 % of
+// the best choice.
+struct GemmChoice { int narrow = 0; bool mixed = false; };
+
+float tile_estimate(const TileForm& f, int64_t M, int64_t rows, int KC, int cus) {
+    const int64_t gx = (rows + f.wn * f.h * 32 - 1) / (f.wn * f.h * 32), gy = (M + 32 * f.mb - 1) / (32 * f.mb);
+    const float x = (float)(gx * gy) / (float)cus;
+    const auto line = [&](float t0, float one, float step, float slope, float per) {
+        return t0 + (float)KC * (x <= 1.0f ? one : x <= 2.0f ? step + slope * (x - 1.0f) : per * x);
+    };
+    if (f.h == 4) return line(8.4f, 0.356f, 0.565f, 0.174f, 0.463f);
+    if (f.mb == 1 || f.wk > 1) return line(4.4f, 0.182f, 0.211f, 0.056f, 0.141f);
+    return line(6.6f, 0.201f, 0.280f, 0.124f, 0.231f);
+}
+
+GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed& mixed) {
+    GemmChoice c;
+    const bool narrow_ok = gemm_narrow_takes(ps, count, M);
+    if (g_force_mb && g_force_mb != kCodeMixed) {
+        if (g_force_mb >= 1000 && narrow_ok) c.narrow = g_force_mb;
+        return c;
+    }
+    const bool mixed_ok = plan_mixed(ps, count, M, mixed);
+    if (g_force_mb == kCodeMixed && mixed_ok) {
+        c.mixed = true;
+        return c;
+    }
     const int found = compute_unit_count(), cus = found > 0 ? found : 256;
     int64_t rows = 0;
     int KC = 0;
@@ -427,16 +520,18 @@ int choose_narrow(const GemmProblem* ps, int count, int64_t M) {
         rows += (int64_t)ps[i].row_blocks * kTileN;
         KC = ps[i].KC > KC ? ps[i].KC : KC;
     }
-    const TileForm f = choose_tile(M, rows);
-    const int64_t gx = (rows + f.wn * f.h * 32 - 1) / (f.wn * f.h * 32), gy = (M + 32 * f.mb - 1) / (32 * f.mb);
-    const float x = (float)(gx * gy) / (float)cus;
-    float per_tile;
-    if (f.h == 4) per_tile = 0.40f * x;
-    else if (f.mb == 1 || f.wk > 1) per_tile = x <= 1.0f ? 0.20f : 0.20f + 0.13f * (x - 1.0f);
-    else per_tile = x <= 2.0f ? 0.36f : 0.18f * x;
-    float narrow_us = 0.0f;
-    const int code = gemm_narrow_best(ps, count, M, cus, narrow_us);
-    return narrow_us < 3.4f + (float)KC * per_tile ? code : 0;
+    float best = tile_estimate(choose_tile(M, rows), M, rows, KC, cus);
+    if (mixed_ok) {
+        const float share = (float)(mixed.small_gx * ((M + 63) / 64)) / (float)cus;
+        const float us = 0.95f * (7.0f + (float)KC * (0.245f + 0.055f * share));
+        if (us < best) { best = us; c.mixed = true; }
+    }
+    if (narrow_ok) {
+        float us = 0.0f;
+        const int code = gemm_narrow_best(ps, count, M, cus, us);
+        if (1.08f * us < best) { c.mixed = false; c.narrow = code; }
+    }
+    return c;
 }
 
 // One LdsCeiling per kernel: the larger forms need more than the 64 KiB a kernel gets without asking.
@@ -460,6 +555,7 @@ hipError_t launch_form(Kernel kernel, size_t lds_bytes, int threads, unsigned gr
 void set_gemm_mb(int mb) { g_force_mb = mb; }
 
 bool gemm_form_exists(int code) {
+    if (code == kCodeMixed) return true;
     if (code >= 1000) return gemm_narrow_form_exists(code);
     const TileForm f = form_of_code(code);
 #define X(MB, H, WK, WN) if (f.mb == MB && f.h == H && f.wk == WK && f.wn == WN) return true;
@@ -468,8 +564,23 @@ bool gemm_form_exists(int code) {
     return false;
 }
 
+hipError_t launch_mixed(const GemmMixed& b, int64_t M, hipStream_t s) {
+    static LdsCeiling ceiling;
+    const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(&gemm_mixed_kernel));
+    if (e != hipSuccess) return e;
+    constexpr int kLds = gemm_lds_bytes<2, 2, 1, 4>();
+    static_assert(kLds == gemm_lds_bytes<2, 1, 1, 4>(), "both widths stage the same activation tiles");
+    const unsigned grid = (unsigned)(b.wgs + (b.small_gx + kXcds - 1) / kXcds * kXcds * ((M + 63) / 64));
+    note_kernel("gemm_mixed_kernel", (int)grid);
+    gemm_mixed_kernel<<<dim3(grid), dim3(256), kLds, s>>>(b, (int)M);
+    return hipGetLastError();
+}
+
 hipError_t launch_gemm(const GemmProblem& p, int64_t M, hipStream_t s) {
-    if (const int narrow = choose_narrow(&p, 1, M)) return launch_gemm_narrow(&p, 1, M, narrow, s);
+    GemmMixed mixed;
+    const GemmChoice choice = choose_kernel(&p, 1, M, mixed);
+    if (choice.mixed) return launch_mixed(mixed, M, s);
+    if (choice.narrow) return launch_gemm_narrow(&p, 1, M, choice.narrow, s);
     const int64_t rows = (int64_t)p.row_blocks * kTileN;
     const TileForm f = choose_tile(M, rows);
     const int64_t gx = (rows + f.wn * f.h * 32 - 1) / (f.wn * f.h * 32);
@@ -489,7 +600,10 @@ hipError_t launch_gemm(const GemmProblem& p, int64_t M, hipStream_t s) {
 hipError_t launch_gemm_batch(const GemmProblem* ps, int count, int64_t M, hipStream_t s) {
     if (count == 1) return launch_gemm(ps[0], M, s);
     if (count < 1 || count > kMaxGemmBatch) return hipErrorInvalidValue;
-    if (const int narrow = choose_narrow(ps, count, M)) return launch_gemm_narrow(ps, count, M, narrow, s);
+    GemmMixed mixed;
+    const GemmChoice choice = choose_kernel(ps, count, M, mixed);
+    if (choice.mixed) return launch_mixed(mixed, M, s);
+    if (choice.narrow) return launch_gemm_narrow(ps, count, M, choice.narrow, s);
     int64_t rows = 0;
     for (int i = 0; i < count; ++i) rows += (int64_t)ps[i].row_blocks * kTileN;
     const TileForm f = choose_tile(M, rows);

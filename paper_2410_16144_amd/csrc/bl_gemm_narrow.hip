@@ -267,9 +267,9 @@ hipError_t launch_narrow_form(const NarrowBatch& b, int M, int gx, hipStream_t s
 }
 
 // The forms that are built, X(T, RH, W, D, t0, a, s), with the line that their measured times follow (us; least squares over
-// 53 shapes: 9 to 512 tokens on 1536^2, 3200^2, 4096^2, 4096 -> 11008 and 11008 -> 4096, weights cold; every point within 24 %):
+// 55 to 154 launches of 9 to 768 tokens on shapes from 1536^2 to 8192^2 and 4096 x 24064, weights cold; every point within 25 %):
 //     t = t0 + KC * (a + s * (X - 1)),   x = workgroups / compute units,  X = max(1, (x + ceil x) / 2)
-// (KC = packed tiles along K).  Taking the form with the smallest figure is on average 0.5 % off the best form, 7 % at worst.
+// (KC = packed tiles along K).  Among themselves, taking the form with the smallest figure was on average 0.5 % off the best form, 7 % at worst.
 // Measured, tile kernel before -> this one: 3200^2 14.3 -> 4.7 us at 37 tokens, 12.0 -> 5.4 at 128, 12.2 -> 7.6 at 256;
 // 4096 -> 11008 16.6 -> 6.4 at 16, 18.9 -> 9.5 at 64, 17.0 -> 13.9 at 128; 11008 -> 4096 32.7 -> 8.1 at 16, 35 -> 10.4 at 64,
 // 37.7 -> 15.8 at 256, 38.4 -> 25.1 at 512.  Also tried: four or sixteen waves along K, 48-token blocks, three or four steps in
@@ -278,9 +278,9 @@ hipError_t launch_narrow_form(const NarrowBatch& b, int M, int gx, hipStream_t s
     X(16, 1, 8, 2, 2.74f, 0.0317f, 0.0236f)   \
     X(16, 2, 8, 2, 2.93f, 0.0407f, 0.0386f)   \
     X(32, 1, 8, 2, 2.76f, 0.0389f, 0.0345f)   \
-    X(32, 2, 8, 1, 2.79f, 0.0499f, 0.0478f)   \
-    X(32, 4, 8, 1, 4.16f, 0.0639f, 0.0875f)   \
-    X(64, 4, 8, 1, 6.12f, 0.0938f, 0.2331f)
+    X(32, 2, 8, 1, 3.00f, 0.0481f, 0.0501f)   \
+    X(32, 4, 8, 1, 4.53f, 0.0615f, 0.0857f)   \
+    X(64, 4, 8, 1, 6.67f, 0.0936f, 0.2225f)
 
 // Strips of one product: 32*RH rows of W each.
 int64_t strips_of(const GemmProblem& p, int rh) {

@@ -725,6 +725,30 @@ def test_gemm_parity_every_few_token_form(dev, ops, form):
         binding.bl_set_tuning("gemm_mb", 0)
 
 
+@pytest.mark.parametrize("M,ns", [(512, (11008,)), (500, (8640,)), (512, (4096, 4090, 4096)), (449, (10000, 70, 33))])
+def test_gemm_parity_two_tile_widths(dev, ops, M, ns):
+    """Launches of between one and one and a half wide tiles per compute unit: 64 x 256 and 64 x 128 tiles side by side, the
+    switch inside a product and between products, ragged rows and tokens, a product that is all narrow tiles."""
+    from paper_2410_16144_amd import binding
+    K = 64 * 11
+    x = _problem(5500 + M, M, K, 64)[2]
+    qa = ops.quant_act(_to_dev_bf16(x, dev) if x.dtype == np.uint16 else torch.from_numpy(x).to(dev))
+    q_ref, a_ref, _ = oracle.quant_act(x)
+    ws = [_problem(5600 + n, 1, K, n, p_zero=0.4)[:2] for n in ns]
+    pws = [ops.pack_ternary(torch.from_numpy(w).to(dev), float(s)) for w, s in ws]
+    binding.bl_set_tuning("gemm_mb", 25)
+    try:
+        outs = ops.gemm_batch(pws, qa)
+        assert "gemm_mixed_kernel" in binding.bl_last_kernel()
+        acc = ops.gemm(pws[0], qa, want_acc=True)[1]
+        torch.cuda.synchronize()
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)
+    assert np.array_equal(acc.cpu().numpy(), oracle.matmul_i32(q_ref, ws[0][0]))
+    for (w, s), o in zip(ws, outs):
+        _check_out(o, oracle.matmul_i32(q_ref, w), s, a_ref)
+
+
 def test_gemm_long_k(dev, ops):
     M, N, K = 70, 130, 65536 + 64     # 1025 K steps (odd: the K-split form pads one group), ragged M and N
     w, s, x = _problem(3200, M, K, N, p_zero=0.4, outl=0.01)
