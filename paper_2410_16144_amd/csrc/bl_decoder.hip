@@ -10,11 +10,14 @@
 //                       workgroup per token row, the row held in registers from its only read to the int8
 //                       store (the quantizer is the one of bl_quant_act, bit for bit);
 //   rope_table_kernel   cos / sin of every (position, frequency), fp64 arithmetic, rounded to fp32;
-//   attn_chunk_kernel   one (head, chunk of 64 cache rows) per workgroup: rotate query and key, append key and
-//                       value to the bf16 cache, scores, softmax within the chunk, weighted values;
-//                       the head's workgroup that finishes last merges its chunks (running-maximum rescaling);
+//   attn_chunk_kernel   one (head, every G-th chunk of 64 cache rows) per workgroup: rotate query and key, append key
+//                       and value to the bf16 cache, running maximum, sum and weighted values over its chunks;
+//                       the head's workgroup that finishes last merges the others' figures;
+//   kv_append_kernel    a prompt's keys and values into the cache;
+//   attn_block_kernel   a prompt's attention on the matrix cores, head sizes that are 4 modulo 8 (the others:
+//                       bl_attn_prompt.hip);
 //   pos_advance_kernel  the token position lives in device memory, so a captured graph replays unchanged.
-// All of it is bandwidth- and latency-bound glue next to the weight streams; nothing here is a dense contraction.
+// All of it but attn_block_kernel is bandwidth- and latency-bound glue next to the weight streams.
 #include "bl_quant_device.hpp"
 #include "bitlinear_decoder.h"
 
