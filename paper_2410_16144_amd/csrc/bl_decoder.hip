@@ -71,10 +71,15 @@ __device__ __forceinline__ void store4(float* row, int k, int K, const float (&v
 }
 
 // Thread t holds elements 4 (t + THREADS i) .. + 3, i = 0 .. NV-1.
+// The sum of squares is added up in ONE order whatever THREADS is, that of 1024 threads: a thread of a smaller workgroup
+// stands for kParts of those, its vectors i, i + kParts, ... being one of them, and keeps their sums apart until the waves'
+// figures meet.  So a row's result is the same bits in every batch, however its launch is shaped.
 template <int MODE, int NV, bool VEC, int THREADS>
 __global__ __launch_bounds__(THREADS) void norm_quant_kernel(const NormArgs p) {
     constexpr int kNormWaves = THREADS / kWave;
-    __shared__ float s_ss[kNormWaves];
+    constexpr int kParts = kNormThreads / THREADS;
+    constexpr int kSums = NV < kParts ? NV : kParts;   // (the rest of them hold no elements: zeros)
+    __shared__ float s_ss[kSums * kNormWaves];
     __shared__ float s_max[kNormWaves];
     __shared__ int s_sum[kNormWaves];
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -86,7 +91,9 @@ __global__ __launch_bounds__(THREADS) void norm_quant_kernel(const NormArgs p) {
     constexpr int kEarlyVectors = THREADS <= 512 ? 6 : 4;   // (512 threads have twice the registers)
     constexpr bool kGammaEarly = NV <= kEarlyVectors;
     float gam[kGammaEarly ? NV : 1][4];
-    float ss = 0.0f;
+    float ss[kSums];
+#pragma unroll
+    for (int v = 0; v < kSums; ++v) ss[v] = 0.0f;
     // the gated form's inputs, all requested together (its arithmetic has branches that loads do not cross)
     constexpr bool kGatedEarly = MODE == BL_NORM_GATED && NV <= kEarlyVectors;
     float gate[kGatedEarly ? NV : 1][4], up[kGatedEarly ? NV : 1][4];
@@ -131,14 +138,17 @@ __global__ __launch_bounds__(THREADS) void norm_quant_kernel(const NormArgs p) {
             for (int j = 0; j < 4; ++j) x[i][j] *= u[j];
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) ss += x[i][j] * x[i][j];
+        for (int j = 0; j < 4; ++j) ss[i % kParts] += x[i][j] * x[i][j];
     }
-    ss = wave_sum_f(ss);
-    if (lane == 0) s_ss[wave] = ss;
+#pragma unroll
+    for (int v = 0; v < kSums; ++v) {
+        ss[v] = wave_sum_f(ss[v]);
+        if (lane == 0) s_ss[v * kNormWaves + wave] = ss[v];
+    }
     __syncthreads();
     float total = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kNormWaves; ++w) total += s_ss[w];
+    for (int w = 0; w < kSums * kNormWaves; ++w) total += s_ss[w];
     const float r = 1.0f / sqrtf(total / (float)K + p.eps);
 
     float amax = 0.0f;

@@ -101,6 +101,56 @@ def test_norm_quant_at_the_edges_of_the_thread_counts(dev, mods, mode, M, K):
     test_norm_quant_parity(dev, mods, mode, M, K, False)
 
 
+def _norm_of_1024_threads(x, gamma, eps):
+    """The plain norm in fp32, its sum of squares added up in the kernels' one order: element 4 (t + 1024 i) + j belongs to
+    thread t of 1024, which adds its own up in turn; the 64 of a wave by the tree of wave_sum_f; the waves one after another."""
+    M, K = x.shape
+    padded = np.zeros((M, -(-K // 4096) * 4096), np.float32)
+    padded[:, :K] = x
+    sq = (padded * padded).reshape(M, -1, 1024, 4)
+    ss = np.zeros((M, 1024), np.float32)
+    for i in range(sq.shape[1]):
+        for j in range(4):
+            ss = ss + sq[:, i, :, j]
+    lanes = np.arange(64)
+    w = ss.reshape(M, 16, 64)
+    for partner in (lanes ^ 1, lanes ^ 2, lanes ^ 7, lanes ^ 15):
+        w = w + w[:, :, partner]
+    w = (w[:, :, 0] + w[:, :, 16]) + (w[:, :, 32] + w[:, :, 48])
+    total = np.zeros(M, np.float32)
+    for i in range(16):
+        total = total + w[:, i]
+    r = np.float32(1.0) / np.sqrt(total / np.float32(K) + np.float32(eps))
+    return (x * gamma) * r[:, None]
+
+
+@pytest.mark.parametrize("K", [5, 768, 1030, 2048, 2052, 4096, 6000, 8192, 8200, 12032, 20000])
+def test_norm_quant_adds_up_in_one_order(dev, mods, K):
+    """Rows that 256, 512 and 1024 threads take, all the bits of the norm as 1024 threads add them up."""
+    B, dec, ops = mods
+    r = _rng(7100 + K)
+    x, gamma = r.standard_normal((37, K)).astype(np.float32), r.uniform(0.5, 1.5, K).astype(np.float32)
+    y = torch.empty(x.shape, device=dev)
+    dec.norm_quant(B.BL_NORM_PLAIN, _t(gamma, dev), 1e-5, a=_t(x, dev), y=y)
+    np.testing.assert_array_equal(y.cpu().numpy(), _norm_of_1024_threads(x, gamma, 1e-5))
+
+
+@pytest.mark.parametrize("K", [8200, 12032, 12288])
+def test_norm_quant_rows_do_not_depend_on_their_batch(dev, mods, K):
+    """The gated form changes its thread count with the number of rows: the same row, the same bits."""
+    B, dec, ops = mods
+    M = 2048
+    a, b = (torch.randn((M, K), device=dev, generator=torch.Generator(dev).manual_seed(K + i)) for i in range(2))
+    gamma = torch.rand(K, device=dev) + 0.5
+    y = torch.empty_like(a)
+    whole = dec.norm_quant(B.BL_NORM_GATED, gamma, 1e-5, a=a, b=b, y=y)
+    for M1 in (1, 100, 511):
+        y1 = torch.empty((M1, K), device=dev)
+        part = dec.norm_quant(B.BL_NORM_GATED, gamma, 1e-5, a=a[:M1], b=b[:M1], y=y1)
+        assert torch.equal(y1, y[:M1]) and torch.equal(part.q, whole.q[:M1])
+        assert torch.equal(part.a_scale, whole.a_scale[:M1]) and torch.equal(part.q_sum, whole.q_sum[:M1])
+
+
 @pytest.mark.parametrize("K", [512, 45056])
 def test_norm_quant_gate_of_any_size(dev, mods, K):
     """The gate's two ways of computing silu meet at a size of 80: waves below it, waves with one element at or above it, and
