@@ -88,14 +88,13 @@ __global__ __launch_bounds__(THREADS) void norm_quant_kernel(const NormArgs p) {
     float x[NV][4];
     // short rows: the norm weights are requested with the row, before the first barrier (one memory round trip
     // instead of two); long rows have no registers to spare for that
-    constexpr int kEarlyVectors = THREADS <= 512 ? 6 : 4;   // (512 threads have twice the registers)
-    constexpr bool kGammaEarly = NV <= kEarlyVectors;
+    constexpr bool kGammaEarly = NV <= 4;
     float gam[kGammaEarly ? NV : 1][4];
     float ss[kSums];
 #pragma unroll
     for (int v = 0; v < kSums; ++v) ss[v] = 0.0f;
     // the gated form's inputs, all requested together (its arithmetic has branches that loads do not cross)
-    constexpr bool kGatedEarly = MODE == BL_NORM_GATED && NV <= kEarlyVectors;
+    constexpr bool kGatedEarly = MODE == BL_NORM_GATED && NV <= 4;
     float gate[kGatedEarly ? NV : 1][4], up[kGatedEarly ? NV : 1][4];
     if constexpr (kGatedEarly) {
 #pragma unroll
@@ -207,38 +206,35 @@ hipError_t launch_norm_nv(const NormArgs& p, int M, bool vec, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The smallest instance up to MAX_NV vectors per thread that holds the row.
-template <int MODE, int THREADS, int MAX_NV>
+// The smallest instance of MIN_NV up to MAX_NV vectors per thread that holds the row.
+template <int MODE, int THREADS, int MIN_NV, int MAX_NV>
 hipError_t launch_norm_threads(const NormArgs& p, int M, bool vec, hipStream_t s) {
     const int per_thread = (p.K + THREADS * 4 - 1) / (THREADS * 4);
-    if (per_thread <= 1) return launch_norm_nv<MODE, THREADS, 1>(p, M, vec, s);
-    if (per_thread <= 2) return launch_norm_nv<MODE, THREADS, 2>(p, M, vec, s);
-    if constexpr (MAX_NV >= 4) {
-        if (per_thread <= 3) return launch_norm_nv<MODE, THREADS, 3>(p, M, vec, s);
-        if (per_thread <= 4) return launch_norm_nv<MODE, THREADS, 4>(p, M, vec, s);
-    }
-    if constexpr (MAX_NV >= 6)
-        if (per_thread <= 6) return launch_norm_nv<MODE, THREADS, 6>(p, M, vec, s);
-    if constexpr (MAX_NV >= 12) {
-        if (per_thread <= 8) return launch_norm_nv<MODE, THREADS, 8>(p, M, vec, s);
-        if (per_thread <= 12) return launch_norm_nv<MODE, THREADS, 12>(p, M, vec, s);
-    }
+#define BL_NORM_NV(NV)                       \
+    if constexpr (MIN_NV <= NV && NV <= MAX_NV) \
+        if (per_thread <= NV) return launch_norm_nv<MODE, THREADS, NV>(p, M, vec, s);
+    BL_NORM_NV(1)
+    BL_NORM_NV(2)
+    BL_NORM_NV(3)
+    BL_NORM_NV(4)
+    BL_NORM_NV(6)
+    BL_NORM_NV(8)
+    BL_NORM_NV(12)
+#undef BL_NORM_NV
     return hipErrorInvalidValue;
 }
 
 // Threads per row: as few as leave a thread two (rows up to 2048) or four (up to 8192) vectors -- a row's three reductions and
 // barriers cost by the wave -- and 1024 for longer rows, where one row's loads and arithmetic have to be spread out.  Measured
-// with 1024 / 512 / 256 threads (us): 2048 rows of 768, plain 9.9 / 5.7 / 4.0; 1 row of 4096 3.0 / 2.6 / 2.8; 512 rows of 4096,
-// gated 5.5 / 4.8 / 4.8; 2048 of 4096, plain 12.8 / 8.8 / 7.4, residual 19.1 / 17.8 / 17.7, gated 16.2 / 13.8 / 14.7; 512 of 8192, residual
-// 8.3 / 8.0 / 9.3; 256 of 12032, residual 7.1 / 7.5 / 9.3; 512 of 12032, residual 13.5 / 14.7 / 15.6.  The gated form, with twice
-// the arithmetic per byte, gains from 512 threads also there once every compute unit has two rows: 15.7 / 13.7 / 14.0.
+// with 1024 / 512 / 256 threads, inputs from memory (us): 2048 rows of 768, plain 10.3 / 6.2 / 4.7; 2048 of 2048, plain 11.4 / 7.4 /
+// 6.2, gated 13.7 / 9.2 / 9.2; 1 row of 4096, plain 3.0 / 2.7 / 2.9; 2048 of 4096, residual 19.4 / 18.0 / 18.4, gated 18.1 / 15.8 / 15.9; 512
+// of 8192, plain 6.4 / 6.1 / 7.3, gated 9.2 / 9.5 / 11.1; 512 of 8704, residual 9.9 / 10.4 / 12.2, gated 10.8 / 11.2 / 15.2; 512 of 12032,
+// gated 12.6 / 13.2 / 17.3, and so from 64 rows (5.8 / 6.0) to 2048 (41.2 / 41.8).
 template <int MODE>
 hipError_t launch_norm_mode(const NormArgs& p, int M, bool vec, hipStream_t s) {
-    if (p.K <= 2048) return launch_norm_threads<MODE, 256, 2>(p, M, vec, s);
-    if (p.K <= 8192) return launch_norm_threads<MODE, 512, 4>(p, M, vec, s);
-    if constexpr (MODE == BL_NORM_GATED)
-        if (p.K <= 12288 && M >= 512) return launch_norm_threads<MODE, 512, 6>(p, M, vec, s);
-    return launch_norm_threads<MODE, kNormThreads, 12>(p, M, vec, s);
+    if (p.K <= 2048) return launch_norm_threads<MODE, 256, 1, 2>(p, M, vec, s);
+    if (p.K <= 8192) return launch_norm_threads<MODE, 512, 2, 4>(p, M, vec, s);
+    return launch_norm_threads<MODE, kNormThreads, 3, 12>(p, M, vec, s);
 }
 static_assert(BL_NORM_MAX_K == 12 * kNormThreads * 4, "the longest row fills 12 vectors per thread");
 
