@@ -3,9 +3,10 @@
 // kernels they launch (a 1536 x 1536 product of one token with its quantizer: 20.9 us a pass for 6.7 us of kernels).
 //
 // Nothing is decided or checked here that the Python side does not check as well: whatever these functions do not take as it is
-// (an operand that is not a plain device tensor, a shape, a dtype, a status other than BL_OK) they answer with None, and the
-// Python function goes through its own checks and the ctypes binding, which raise what they always raised.  Nothing is kept
-// between calls.
+// (an operand that is not a plain device tensor, a shape, a dtype) they answer with None BEFORE the library is called, and the
+// Python function goes through its own checks and the ctypes binding, which raise what they always raised.  Once the library has
+// been called, a status other than BL_OK is the answer, an int that the Python function raises: a second call could do twice
+// what the first did in part (the residual form of bl_norm_quant adds into its input).  Nothing is kept between calls.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -111,7 +112,7 @@ PyObject* quant_act(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
         status = bl_quant_act(x->data_ptr(), dt, M, K, x->stride(0), static_cast<int8_t*>(out.q.data_ptr()),
                               static_cast<float*>(out.a_scale.data_ptr()), static_cast<int32_t*>(out.q_sum.data_ptr()), stream);
     }
-    if (status != BL_OK) Py_RETURN_NONE;
+    if (status != BL_OK) return PyLong_FromLong(status);
     return out.wrap();
     END_HANDLE_TH_ERRORS
 }
@@ -144,7 +145,7 @@ PyObject* product(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
                                             static_cast<const int32_t*>(s->data_ptr()), M, static_cast<float*>(out.data_ptr()),
                                             want_acc ? static_cast<int32_t*>(acc.data_ptr()) : nullptr, stream);
     }
-    if (status != BL_OK) Py_RETURN_NONE;
+    if (status != BL_OK) return PyLong_FromLong(status);
     PyObject* r = PyTuple_New(2);
     if (!r) return nullptr;
     PyTuple_SET_ITEM(r, 0, THPVariable_Wrap(out));
@@ -182,7 +183,7 @@ PyObject* gemm_batch(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
         WithoutGil release;
         status = bl_gemm_batch(items, (int32_t)count, M, stream);
     }
-    if (status != BL_OK) Py_RETURN_NONE;
+    if (status != BL_OK) return PyLong_FromLong(status);
     PyObject* r = PyList_New(count);
     if (!r) return nullptr;
     for (Py_ssize_t i = 0; i < count; ++i) PyList_SET_ITEM(r, i, THPVariable_Wrap(outs[i]));
@@ -242,7 +243,7 @@ PyObject* norm_quant(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
         WithoutGil release;
         status = bl_norm_quant(&p, stream);
     }
-    if (status != BL_OK) Py_RETURN_NONE;
+    if (status != BL_OK) return PyLong_FromLong(status);
     if (!quantize) Py_RETURN_TRUE;
     return out.wrap();
     END_HANDLE_TH_ERRORS

@@ -45,6 +45,8 @@ def norm_quant(mode: int, gamma: Optional[torch.Tensor], eps: float = EPS, a: Op
         given = (out.q, out.a_scale, out.q_sum) if quantize and out is not None else (None, None, None)
         r = B.calls().norm_quant(mode, gamma, eps, a, b, h, *given, y, quantize, scratch)
         if r is not None:
+            if type(r) is int:   # (True: nothing to quantize)
+                raise B.BitLinearError(r, "bl_norm_quant")
             if not quantize:
                 return None
             return out if out is not None else ops.QuantAct(r[0], r[1], r[2], int(gamma.shape[0]))

@@ -108,6 +108,8 @@ def quant_act(x: torch.Tensor, out: Optional[QuantAct] = None) -> QuantAct:
     """x: [M,K] fp32 or bf16 device tensor (last dim contiguous) -> QuantAct (bl_quant_act)."""
     r = B.calls().quant_act(x, None, None, None) if out is None else B.calls().quant_act(x, out.q, out.a_scale, out.q_sum)
     if r is not None:
+        if type(r) is int:
+            raise B.BitLinearError(r, "bl_quant_act")
         return out if out is not None else QuantAct(r[0], r[1], r[2], int(x.shape[1]))
     assert x.is_cuda and x.dim() == 2 and x.stride(1) == 1
     if x.dtype == torch.float32:
@@ -147,6 +149,8 @@ def _product(fn, pw: PackedWeight, qa: QuantAct, out, want_acc):
     assert qa.K == pw.K
     r = B.calls().product(fn is B.bl_gemm, pw.blob, pw.desc, qa.q, qa.a_scale, qa.q_sum, out, want_acc)
     if r is not None:
+        if type(r) is int:
+            raise B.BitLinearError(r, "bl_gemm" if fn is B.bl_gemm else "bl_gemv")
         return r if want_acc else r[0]
     M = qa.M
     if out is None:
@@ -174,6 +178,8 @@ def gemm_batch(pws, qa: QuantAct):
     assert 1 <= len(pws) <= B.BL_MAX_GEMM_BATCH and all(pw.K == qa.K for pw in pws)
     outs = B.calls().gemm_batch([t for pw in pws for t in (pw.blob, pw.desc)], qa.q, qa.a_scale, qa.q_sum)
     if outs is not None:
+        if type(outs) is int:
+            raise B.BitLinearError(outs, "bl_gemm_batch")
         return outs
     outs = [torch.empty((M, pw.N), dtype=torch.float32, device=dev) for pw in pws]
     B.bl_gemm_batch([(pw.blob.data_ptr(), pw.desc, qa.q.data_ptr(), qa.a_scale.data_ptr(), qa.q_sum.data_ptr(), o.data_ptr(), 0)

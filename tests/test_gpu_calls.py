@@ -1,0 +1,58 @@
+"""The eager calls in native code (csrc/bl_calls.cpp) beside the Python path that they stand in for."""
+import copy
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2410_16144_amd import binding as B      # noqa: E402
+from paper_2410_16144_amd import decoder, ops      # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def _weight(dev, N, K, seed=5):
+    w = torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev, generator=torch.Generator(dev).manual_seed(seed))
+    return ops.pack_ternary(w, 0.02)
+
+
+def _with_desc(pw, **fields):
+    desc = copy.copy(pw.desc)
+    for k, v in fields.items():
+        setattr(desc, k, v)
+    return ops.PackedWeight(pw.blob, desc)
+
+
+def test_a_status_is_raised_and_the_call_is_not_repeated(dev, monkeypatch):
+    """The library refuses the call: its status is raised from the native call's own answer, and the ctypes binding, which
+    would make the call a second time, is not reached."""
+    pw = _weight(dev, 128, 256)
+    x = torch.randn(4, 256, device=dev)
+    qa = ops.quant_act(x)
+    nine = ops.quant_act(torch.randn(9, 256, device=dev))
+    long_h = torch.zeros((1, B.BL_NORM_MAX_K + 4), device=dev)
+    torch.cuda.synchronize()
+
+    def again(name):
+        def called(*a, **k):
+            raise AssertionError(name + " called a second time")
+        return called
+    for name in ("bl_quant_act", "bl_gemv", "bl_gemm", "bl_gemm_batch", "bl_norm_quant"):
+        monkeypatch.setattr(B, name, again(name))
+    for what, status, call in (
+            ("bl_quant_act", B.BL_ERR_SHAPE, lambda: ops.quant_act(x[:1].expand(3, 256))),              # rows closer than K
+            ("bl_gemv", B.BL_ERR_M_RANGE, lambda: ops.gemv(pw, nine)),
+            ("bl_gemv", B.BL_ERR_BUF_SMALL, lambda: ops.gemv(_with_desc(pw, bytes=64), qa)),
+            ("bl_gemm", B.BL_ERR_LAYOUT, lambda: ops.gemm(_with_desc(pw, version=7), qa)),
+            ("bl_gemm_batch", B.BL_ERR_LAYOUT, lambda: ops.gemm_batch([pw, _with_desc(pw, version=7)], qa)),
+            ("bl_norm_quant", B.BL_ERR_SHAPE, lambda: decoder.norm_quant(B.BL_NORM_RESIDUAL, long_h[0].clone(), h=long_h))):
+        with pytest.raises(B.BitLinearError) as e:
+            call()
+        assert e.value.status == status and what + " failed" in str(e.value)
