@@ -211,11 +211,20 @@ def calls():
     return _calls
 
 
-def launch(which: int, items, count: int, M: int, workspace_dev: int, where: str):
-    """One prepared launch on the current stream; raises BitLinearError like the calls below."""
-    status = calls().launch(which, items, count, M, workspace_dev)
-    if status:
-        raise BitLinearError(status, where)
+def launch(which: int, items, M: int, workspace_dev: int = 0):
+    """One prepared launch on the current stream: items is the ctypes array of make_*_items (for LAUNCH_ATTN_DECODE the AttnArgs).
+    Anything else goes to the ctypes binding, which takes or refuses it as it always did.  Raises BitLinearError like the
+    calls below."""
+    of, call, where = _LAUNCHES[which]
+    if isinstance(items, ctypes.Array) and items._type_ is of or type(items) is AttnArgs is of:
+        status = calls().launch(which, items, M, workspace_dev or 0)
+        if status is not None:
+            return _check(status, where)
+    call(items, M, workspace_dev)
+
+
+def _current_stream() -> int:
+    return calls().stream()
 
 
 def _check(status, where):
@@ -448,3 +457,14 @@ def bl_last_kernel() -> str:
 
 def bl_get_stat(key: str) -> int:
     return int(lib().bl_get_stat(key.encode()))
+
+
+# what launch() calls through ctypes, in the order of its `which`: the items' type, the call, its name
+_LAUNCHES = (
+    (GemvItem, lambda items, M, ws: bl_gemv_batch(items, M, ws, _current_stream()), "bl_gemv_batch"),
+    (DecodeItem, lambda items, M, ws: bl_decode_batch(items, M, ws, _current_stream()), "bl_decode_batch"),
+    (QuantItem, lambda items, M, ws: bl_quant_act_batch(items, _current_stream()), "bl_quant_act_batch"),
+    (DecodeNormItem, lambda items, M, ws: bl_decode_norm_batch(items, ws, _current_stream()), "bl_decode_norm_batch"),
+    (GemvItem, lambda items, M, ws: bl_tl2_gemv_batch(items, ws, _current_stream()), "bl_tl2_gemv_batch"),
+    (AttnArgs, lambda items, M, ws: bl_attn_decode(items, _current_stream()), "bl_attn_decode"),
+)

@@ -249,20 +249,23 @@ PyObject* norm_quant(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     END_HANDLE_TH_ERRORS
 }
 
-// The prepared launches: launch(which, items, count, M, workspace) -> bl_status, on the current stream.  items: the ctypes array
-// or argument struct.
-enum { kGemvBatch, kDecodeBatch, kQuantBatch, kDecodeNormBatch, kTl2Batch, kAttnDecode };
+// The prepared launches: launch(which, items, M, workspace) -> bl_status, on the current stream; None if `items`, a ctypes array (for
+// the last one the argument struct), does not hold whole ones of that launch's.
+enum { kGemvBatch, kDecodeBatch, kQuantBatch, kDecodeNormBatch, kTl2Batch, kAttnDecode, kLaunches };
 
 PyObject* launch(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
-    BL_NEEDS(5)
-    const long which = PyLong_AsLong(args[0]), count = PyLong_AsLong(args[2]), M = PyLong_AsLong(args[3]);
-    void* workspace = PyLong_AsVoidPtr(args[4]);
+    BL_NEEDS(4)
+    const long which = PyLong_AsLong(args[0]), M = PyLong_AsLong(args[2]);
+    void* workspace = PyLong_AsVoidPtr(args[3]);
     if (PyErr_Occurred()) return nullptr;
-    Memory items(args[1]);
-    if (!items.ok) Py_RETURN_NONE;
+    constexpr size_t kSizes[kLaunches] = {sizeof(bl_gemv_item), sizeof(bl_decode_item), sizeof(bl_quant_item),
+                                          sizeof(bl_decode_norm_item), sizeof(bl_gemv_item), sizeof(bl_attn_args)};
+    if (which < 0 || which >= kLaunches) Py_RETURN_NONE;
+    Memory items(args[1], kSizes[which]);
+    if (!items.ok || items.view.len % kSizes[which] != 0 || items.view.len / kSizes[which] > INT32_MAX) Py_RETURN_NONE;
+    const int32_t n = (int32_t)(items.view.len / kSizes[which]);
     void* stream = current_stream();
-    const int32_t n = (int32_t)count;
     bl_status status = BL_ERR_SHAPE;
     {
         WithoutGil release;

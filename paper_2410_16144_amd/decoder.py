@@ -99,7 +99,7 @@ class Attention:
                                      self.scratch.data_ptr(), n_heads, head_dim, max_pos)
 
     def launch(self):
-        B.launch(B.LAUNCH_ATTN_DECODE, self.args, 1, 1, 0, "bl_attn_decode")
+        B.launch(B.LAUNCH_ATTN_DECODE, self.args, 1)
         return self.out
 
 
@@ -153,7 +153,7 @@ class NormDecodeGroup:
         self.items = B.make_decode_norm_items(items)
 
     def launch(self):
-        B.launch(B.LAUNCH_DECODE_NORM_BATCH, self.items, len(self.items), 1, self.workspace_ptr, "bl_decode_norm_batch")
+        B.launch(B.LAUNCH_DECODE_NORM_BATCH, self.items, 1, self.workspace_ptr)
         return self.outs
 
 

@@ -141,7 +141,7 @@ class QuantGroup:
              o.a_scale.data_ptr(), o.q_sum.data_ptr()) for x, o in zip(self.xs, self.outs))
 
     def launch(self):
-        B.launch(B.LAUNCH_QUANT_BATCH, self.items, len(self.items), 0, 0, "bl_quant_act_batch")
+        B.launch(B.LAUNCH_QUANT_BATCH, self.items, 0)
         return self.outs
 
 
@@ -229,7 +229,7 @@ class GemvGroup:
             for i, (w, a, o) in enumerate(zip(self.weights, self.acts, self.outs)))
 
     def launch(self):
-        B.launch(B.LAUNCH_GEMV_BATCH, self.items, len(self.items), self.M, self.workspace_ptr, "bl_gemv_batch")
+        B.launch(B.LAUNCH_GEMV_BATCH, self.items, self.M, self.workspace_ptr)
         return self.outs
 
 
@@ -253,7 +253,7 @@ class Tl2GemvGroup:
             for i, (w, a, o) in enumerate(zip(self.weights, self.acts, self.outs)))
 
     def launch(self):
-        B.launch(B.LAUNCH_TL2_BATCH, self.items, len(self.items), 1, self.workspace_ptr, "bl_tl2_gemv_batch")
+        B.launch(B.LAUNCH_TL2_BATCH, self.items, 1, self.workspace_ptr)
         return self.outs
 
 
@@ -302,5 +302,5 @@ class DecodeGroup:
             for i, (w, x, o) in enumerate(zip(self.weights, self.xs, self.outs)))
 
     def launch(self):
-        B.launch(B.LAUNCH_DECODE_BATCH, self.items, len(self.items), self.M, self.workspace_ptr, "bl_decode_batch")
+        B.launch(B.LAUNCH_DECODE_BATCH, self.items, self.M, self.workspace_ptr)
         return self.outs

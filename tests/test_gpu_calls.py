@@ -56,3 +56,29 @@ def test_a_status_is_raised_and_the_call_is_not_repeated(dev, monkeypatch):
         with pytest.raises(B.BitLinearError) as e:
             call()
         assert e.value.status == status and what + " failed" in str(e.value)
+
+
+def test_prepared_launches_refuse_and_take_what_the_binding_does(dev):
+    """Items that are not the launch's ctypes array: none at all and another launch's raise, an iterable of tuples is launched."""
+    pw = _weight(dev, 128, 256)
+    qa = ops.quant_act(torch.randn(1, 256, device=dev))
+    group = ops.GemvGroup([pw], [qa])
+    want = group.launch()[0].clone()
+    row = (pw.blob.data_ptr(), pw.desc, qa.q.data_ptr(), qa.a_scale.data_ptr(), qa.q_sum.data_ptr(), group.outs[0].data_ptr(), 0)
+    for items in ([row], iter([row]), B.make_gemv_items([row])):
+        group.outs[0].fill_(-1.0)
+        group.items = items
+        assert torch.equal(group.launch()[0], want)
+    group.workspace_ptr = None      # as 0: no workspace
+    group.outs[0].fill_(-1.0)
+    group.items = B.make_gemv_items([row])
+    assert torch.equal(group.launch()[0], want)
+    import ctypes
+    for items in ([], B.make_gemv_items([])):
+        group.items = items
+        with pytest.raises(B.BitLinearError) as e:
+            group.launch()
+        assert e.value.status == B.BL_ERR_COUNT
+    group.items = B.make_quant_items([])
+    with pytest.raises(ctypes.ArgumentError):
+        group.launch()
