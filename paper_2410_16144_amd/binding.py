@@ -189,26 +189,36 @@ def lib():
 
 
 _calls = None
-CALLS_PATH = os.path.join(HERE, "_calls.so")
 # bl_calls.cpp: the `which` of calls().launch
 LAUNCH_GEMV_BATCH, LAUNCH_DECODE_BATCH, LAUNCH_QUANT_BATCH, LAUNCH_DECODE_NORM_BATCH, LAUNCH_TL2_BATCH, LAUNCH_ATTN_DECODE = range(6)
 
 
 def calls():
-    """The eager calls in native code (csrc/bl_calls.cpp): allocation, current stream and library call in one.  They answer
-    with None whatever they do not take as it is; the caller then goes through its own checks and this binding."""
+    """The eager calls in native code (csrc/bl_calls.cpp): allocation, current stream and library call in one, or False if the
+    module is not built for the torch of this process; everything then goes through this binding (8 to 10 us more per call).
+    They answer with None whatever they do not take as it is; the caller then goes through its own checks and this binding."""
     global _calls
     if _calls is None:
         lib()   # torch and the library first
-        if not os.path.exists(CALLS_PATH):
-            raise RuntimeError("_calls.so is not built (%s). Run `python paper_2410_16144_amd/build.py`." % CALLS_PATH)
-        import importlib.machinery
-        import importlib.util
-        loader = importlib.machinery.ExtensionFileLoader("paper_2410_16144_amd._calls", CALLS_PATH)
-        module = importlib.util.module_from_spec(importlib.util.spec_from_loader(loader.name, loader))
-        loader.exec_module(module)
+        from .build import calls_path
+        path, module = calls_path(), False
+        if os.path.exists(path):
+            import importlib.machinery
+            import importlib.util
+            loader = importlib.machinery.ExtensionFileLoader("paper_2410_16144_amd._calls", path)
+            module = importlib.util.module_from_spec(importlib.util.spec_from_loader(loader.name, loader))
+            loader.exec_module(module)
         _calls = module
     return _calls
+
+
+def current_stream() -> int:
+    """torch's current stream of the current device."""
+    c = calls()
+    if c:
+        return c.stream()
+    import torch
+    return int(torch.cuda.current_stream().cuda_stream)
 
 
 def launch(which: int, items, M: int, workspace_dev: int = 0):
@@ -216,15 +226,12 @@ def launch(which: int, items, M: int, workspace_dev: int = 0):
     Anything else goes to the ctypes binding, which takes or refuses it as it always did.  Raises BitLinearError like the
     calls below."""
     of, call, where = _LAUNCHES[which]
-    if isinstance(items, ctypes.Array) and items._type_ is of or type(items) is AttnArgs is of:
-        status = calls().launch(which, items, M, workspace_dev or 0)
+    c = calls()
+    if c and (isinstance(items, ctypes.Array) and items._type_ is of or type(items) is AttnArgs is of):
+        status = c.launch(which, items, M, workspace_dev or 0)
         if status is not None:
             return _check(status, where)
     call(items, M, workspace_dev)
-
-
-def _current_stream() -> int:
-    return calls().stream()
 
 
 def _check(status, where):
@@ -461,10 +468,10 @@ def bl_get_stat(key: str) -> int:
 
 # what launch() calls through ctypes, in the order of its `which`: the items' type, the call, its name
 _LAUNCHES = (
-    (GemvItem, lambda items, M, ws: bl_gemv_batch(items, M, ws, _current_stream()), "bl_gemv_batch"),
-    (DecodeItem, lambda items, M, ws: bl_decode_batch(items, M, ws, _current_stream()), "bl_decode_batch"),
-    (QuantItem, lambda items, M, ws: bl_quant_act_batch(items, _current_stream()), "bl_quant_act_batch"),
-    (DecodeNormItem, lambda items, M, ws: bl_decode_norm_batch(items, ws, _current_stream()), "bl_decode_norm_batch"),
-    (GemvItem, lambda items, M, ws: bl_tl2_gemv_batch(items, ws, _current_stream()), "bl_tl2_gemv_batch"),
-    (AttnArgs, lambda items, M, ws: bl_attn_decode(items, _current_stream()), "bl_attn_decode"),
+    (GemvItem, lambda items, M, ws: bl_gemv_batch(items, M, ws, current_stream()), "bl_gemv_batch"),
+    (DecodeItem, lambda items, M, ws: bl_decode_batch(items, M, ws, current_stream()), "bl_decode_batch"),
+    (QuantItem, lambda items, M, ws: bl_quant_act_batch(items, current_stream()), "bl_quant_act_batch"),
+    (DecodeNormItem, lambda items, M, ws: bl_decode_norm_batch(items, ws, current_stream()), "bl_decode_norm_batch"),
+    (GemvItem, lambda items, M, ws: bl_tl2_gemv_batch(items, ws, current_stream()), "bl_tl2_gemv_batch"),
+    (AttnArgs, lambda items, M, ws: bl_attn_decode(items, current_stream()), "bl_attn_decode"),
 )

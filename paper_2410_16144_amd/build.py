@@ -6,6 +6,7 @@ next to this file so that it travels with the source tree.
 import glob
 import os
 import subprocess
+import sys
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -34,7 +35,16 @@ PER_FILE_FLAGS = {
 
 # The eager calls in native code (csrc/bl_calls.cpp): a Python extension on torch's C++ interface, host code only.
 CALLS_SRC = os.path.join(CSRC, "bl_calls.cpp")
-CALLS_LIB = os.path.join(HERE, "_calls.so")
+
+
+def calls_path() -> str:
+    """Where the extension module for the Python and PyTorch of this process lies, built or not.  It reads torch's tensors
+    through inline accessors, so it is good for the very torch it was compiled against and no other: name and build of
+    both are in the file's name, and another torch finds no module rather than a stale one."""
+    import torch
+    return os.path.join(HERE, "_calls.%s-torch%s-%s%s.so" % (
+        sys.implementation.cache_tag, torch.__version__, str(torch.version.git_version)[:12],
+        "" if torch._C._GLIBCXX_USE_CXX11_ABI else "-oldabi"))
 
 
 def sources():
@@ -63,7 +73,7 @@ def _hip_runtime_dir() -> str:
 
 def build(force: bool = True, extra_flags=(), verbose: bool = False) -> str:
     """Compile every translation unit and link the shared library.  Returns its path."""
-    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _newest_input() for f in (LIB, CALLS_LIB)):
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _newest_input() for f in (LIB, calls_path())):
         return LIB
     os.makedirs(OBJ_DIR, exist_ok=True)
 
@@ -93,12 +103,14 @@ def build(force: bool = True, extra_flags=(), verbose: bool = False) -> str:
 
 
 def build_calls() -> str:
-    """Compile the extension module against the PyTorch that is installed and the library next to it."""
+    """Compile the extension module against the PyTorch that is installed and the library next to it.  Without it every call
+    goes through ctypes."""
     import sysconfig
 
     import torch
     root = os.path.dirname(torch.__file__)
-    tmp = CALLS_LIB + ".tmp.%d" % os.getpid()
+    out = calls_path()
+    tmp = out + ".tmp.%d" % os.getpid()
     inc = os.path.join(root, "include")
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
                            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", INCLUDE, "-isystem", inc,
@@ -106,8 +118,8 @@ def build_calls() -> str:
                            "-isystem", sysconfig.get_paths()["include"], CALLS_SRC, "-o", tmp, "-L", HERE, "-lbitlinear",
                            "-L", os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
                            "-Wl,-rpath,$ORIGIN"])
-    os.replace(tmp, CALLS_LIB)
-    return CALLS_LIB
+    os.replace(tmp, out)
+    return out
 
 
 ABI_CHECK_SRC = os.path.join(os.path.dirname(HERE), "tests", "c_abi", "abi_check.c")

@@ -32,7 +32,7 @@ ROPE_THETA = 10000.0
 
 
 def _stream() -> int:
-    return B.calls().stream()
+    return B.current_stream()
 
 
 def norm_quant(mode: int, gamma: Optional[torch.Tensor], eps: float = EPS, a: Optional[torch.Tensor] = None,
@@ -41,10 +41,11 @@ def norm_quant(mode: int, gamma: Optional[torch.Tensor], eps: float = EPS, a: Op
                pieces: int = 0):
     """bl_norm_quant on [M,K] fp32 tensors.  Returns the QuantAct (None if quantize is False).  scratch: a uint8
     tensor of M * BL_NORM_SCRATCH_BYTES bytes lets long rows spread over several workgroups."""
-    if mode != B.BL_NORM_PREMULTIPLIED:
+    c = B.calls()
+    if c and mode != B.BL_NORM_PREMULTIPLIED:
         given = (out.q, out.a_scale, out.q_sum) if quantize and out is not None else (None, None, None)
-        r = B.calls().norm_quant(mode, gamma, eps, a, b, h, *given, y, quantize, scratch)
-        if r is not None:
+        r = c.norm_quant(mode, gamma, eps, a, b, h, *given, y, quantize, scratch)
+        if r:
             if type(r) is int:   # (True: nothing to quantize)
                 raise B.BitLinearError(r, "bl_norm_quant")
             if not quantize:

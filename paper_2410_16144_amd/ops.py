@@ -9,7 +9,7 @@ from . import binding as B
 
 
 def _stream() -> int:
-    return B.calls().stream()
+    return B.current_stream()
 
 
 @dataclass
@@ -106,8 +106,9 @@ def alloc_quant(M: int, K: int, device) -> QuantAct:
 
 def quant_act(x: torch.Tensor, out: Optional[QuantAct] = None) -> QuantAct:
     """x: [M,K] fp32 or bf16 device tensor (last dim contiguous) -> QuantAct (bl_quant_act)."""
-    r = B.calls().quant_act(x, None, None, None) if out is None else B.calls().quant_act(x, out.q, out.a_scale, out.q_sum)
-    if r is not None:
+    c = B.calls()
+    r = c and (c.quant_act(x, None, None, None) if out is None else c.quant_act(x, out.q, out.a_scale, out.q_sum))
+    if r:
         if type(r) is int:
             raise B.BitLinearError(r, "bl_quant_act")
         return out if out is not None else QuantAct(r[0], r[1], r[2], int(x.shape[1]))
@@ -147,8 +148,9 @@ class QuantGroup:
 
 def _product(fn, pw: PackedWeight, qa: QuantAct, out, want_acc):
     assert qa.K == pw.K
-    r = B.calls().product(fn is B.bl_gemm, pw.blob, pw.desc, qa.q, qa.a_scale, qa.q_sum, out, want_acc)
-    if r is not None:
+    c = B.calls()
+    r = c and c.product(fn is B.bl_gemm, pw.blob, pw.desc, qa.q, qa.a_scale, qa.q_sum, out, want_acc)
+    if r:
         if type(r) is int:
             raise B.BitLinearError(r, "bl_gemm" if fn is B.bl_gemm else "bl_gemv")
         return r if want_acc else r[0]
@@ -176,8 +178,9 @@ def gemm_batch(pws, qa: QuantAct):
     outputs [M, N_i], each identical to gemm(pw_i, qa)."""
     M, dev = qa.M, qa.q.device
     assert 1 <= len(pws) <= B.BL_MAX_GEMM_BATCH and all(pw.K == qa.K for pw in pws)
-    outs = B.calls().gemm_batch([t for pw in pws for t in (pw.blob, pw.desc)], qa.q, qa.a_scale, qa.q_sum)
-    if outs is not None:
+    c = B.calls()
+    outs = c and c.gemm_batch([t for pw in pws for t in (pw.blob, pw.desc)], qa.q, qa.a_scale, qa.q_sum)
+    if outs:
         if type(outs) is int:
             raise B.BitLinearError(outs, "bl_gemm_batch")
         return outs

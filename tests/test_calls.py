@@ -1,6 +1,9 @@
 """The choice between the native calls (csrc/bl_calls.cpp) and the ctypes binding, without a GPU: the library and the native
 module are stand-ins that record what reaches them."""
 import ctypes
+import os
+import subprocess
+import sys
 import types
 
 import pytest
@@ -78,3 +81,40 @@ def test_a_status_of_the_native_launch_is_raised(monkeypatch, status):
         B.launch(B.LAUNCH_QUANT_BATCH, B.make_quant_items(LAUNCHES[2][1]), 0)
     assert e.value.status == status and "bl_quant_act_batch failed" in str(e.value)
     assert len(native.seen) == 1
+
+
+def test_without_the_native_module_everything_goes_through_ctypes(monkeypatch):
+    """An installation with the library alone: launches reach it, and the stream comes from torch."""
+    torch = pytest.importorskip("torch")
+    from paper_2410_16144_amd import build
+    library = Recorder(B.BL_OK)
+    monkeypatch.setattr(B, "_lib", library)
+    monkeypatch.setattr(B, "_calls", None)
+    monkeypatch.setattr(build, "calls_path", lambda: os.path.join(build.HERE, "_calls.no-such-torch.so"))
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=STREAM))
+    assert B.calls() is False and B.current_stream() == STREAM
+    items = B.make_quant_items(LAUNCHES[2][1])
+    B.launch(B.LAUNCH_QUANT_BATCH, items, 0)
+    (name, args), = library.seen
+    assert name == "bl_quant_act_batch" and args[0] is items and args[-1] == STREAM
+
+
+def test_the_native_module_is_of_the_torch_that_loads_it(monkeypatch):
+    """Another torch finds no module instead of a stale one, and the build is not up to date for it."""
+    torch = pytest.importorskip("torch")
+    from paper_2410_16144_amd import build
+    here = build.calls_path()
+    assert os.path.dirname(here) == build.HERE and torch.__version__ in here and sys.implementation.cache_tag in here
+    monkeypatch.setattr(torch, "__version__", "9.9.9")
+    assert build.calls_path() != here and not os.path.exists(build.calls_path())
+
+    class Begins(Exception):
+        pass
+
+    def begins(*a, **k):
+        raise Begins
+    monkeypatch.setattr(build, "_newest_input", lambda: 0)
+    monkeypatch.setattr(build, "sources", lambda: [])
+    monkeypatch.setattr(subprocess, "check_call", begins)
+    with pytest.raises(Begins):
+        build.build(force=False)

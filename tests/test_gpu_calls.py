@@ -82,3 +82,33 @@ def test_prepared_launches_refuse_and_take_what_the_binding_does(dev):
     group.items = B.make_quant_items([])
     with pytest.raises(ctypes.ArgumentError):
         group.launch()
+
+
+def test_the_native_module_is_the_one_that_runs(dev):
+    assert B.calls() and B.calls().__file__ == __import__("paper_2410_16144_amd.build", fromlist=["build"]).calls_path()
+
+
+def test_every_function_gives_the_same_without_the_native_module(dev, monkeypatch):
+    """Both paths over the same inputs: same bits, same types."""
+    pw, pw2 = _weight(dev, 200, 260), _weight(dev, 70, 260, 6)
+    x = torch.randn(11, 260, device=dev)
+    a, b, h = (torch.randn(11, 260, device=dev) for _ in range(3))
+    gamma = torch.rand(260, device=dev) + 0.5
+
+    def everything():
+        qa = ops.quant_act(x)
+        qb = ops.quant_act(x.bfloat16(), ops.alloc_quant(11, 260, dev))
+        few = ops.quant_act(x[:3])
+        y = torch.empty_like(a)
+        assert decoder.norm_quant(B.BL_NORM_PLAIN, gamma, a=a, y=y, quantize=False) is None
+        hh = h.clone()
+        n = [decoder.norm_quant(B.BL_NORM_GATED, gamma, a=a, b=b), decoder.norm_quant(B.BL_NORM_RESIDUAL, gamma, a=a, h=hh)]
+        acc = ops.gemm(pw, qa, want_acc=True)
+        group = ops.GemvGroup([pw, pw2], [few, few])
+        outs = [ops.gemm(pw, qa), ops.gemv(pw2, few), *acc, *ops.gemm_batch([pw, pw2], qa), *group.launch(), y, hh]
+        return outs + [t for q in (qa, qb, few, *n) for t in (q.q, q.a_scale, q.q_sum)] + [torch.tensor([q.K for q in (qa, qb, *n)])]
+
+    native = everything()
+    monkeypatch.setattr(B, "_calls", False)
+    for one, other in zip(native, everything()):
+        assert one.dtype == other.dtype and torch.equal(one, other)
