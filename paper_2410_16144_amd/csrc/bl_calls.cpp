@@ -10,6 +10,8 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -21,9 +23,10 @@ namespace {
 
 void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-// A plain device tensor (no subclass with a dispatcher of its own, no functorch wrapper), or nullptr.
+// A plain device tensor (torch's own class or its Parameter, no subclass, which may have a word in every torch function, nor any
+// while a mode has one; no functorch wrapper), or nullptr.
 const at::Tensor* plain(PyObject* o) {
-    if (!THPVariable_Check(o)) return nullptr;
+    if (!THPVariable_CheckExact(o) || at::impl::torch_function_mode_enabled() || c10::impl::dispatch_mode_enabled()) return nullptr;
     const at::Tensor& t = THPVariable_Unpack(o);
     const c10::DispatchKeySet keys = t.unsafeGetTensorImpl()->key_set();
     if (!t.is_cuda() || t.layout() != at::kStrided || keys.has(c10::DispatchKey::Python) || keys.has(c10::DispatchKey::FuncTorchBatched) ||

@@ -112,3 +112,80 @@ def test_every_function_gives_the_same_without_the_native_module(dev, monkeypatc
     monkeypatch.setattr(B, "_calls", False)
     for one, other in zip(native, everything()):
         assert one.dtype == other.dtype and torch.equal(one, other)
+
+
+class Plain(torch.Tensor):
+    """A subclass without a say of its own."""
+
+
+class Loud(torch.Tensor):
+    """A subclass that sees every torch function."""
+    seen = []
+
+    @classmethod
+    def __torch_function__(cls, func, types, args=(), kwargs=None):
+        Loud.seen.append(getattr(func, "__name__", str(func)))
+        return super().__torch_function__(func, types, args, kwargs or {})
+
+
+class Watch(torch.overrides.TorchFunctionMode):
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        Loud.seen.append(getattr(func, "__name__", str(func)))
+        return func(*args, **(kwargs or {}))
+
+
+def _watched(call):
+    with Watch():
+        return call()
+
+
+def _outcome(call):
+    """What a call gives or raises, comparable."""
+    try:
+        r = call()
+    except Exception as e:      # noqa: BLE001 -- the kind and the words are what is compared
+        return type(e).__name__, str(e)
+    torch.cuda.synchronize()
+    r = r if isinstance(r, (list, tuple)) else [r]
+    flat = [t for q in r for t in ((q.q, q.a_scale, q.q_sum) if isinstance(q, ops.QuantAct) else (q,))]
+    return [None if t is None else (t.dtype, t.shape, t.cpu().contiguous().view(torch.uint8).numpy().tobytes()) for t in flat]
+
+
+def test_what_the_native_calls_refuse_ends_as_without_them(dev, monkeypatch):
+    """Operands that are not plain device tensors of the expected kind: the same result, or the same error, as by ctypes."""
+    g = torch.Generator(dev).manual_seed(3)
+    pw = _weight(dev, 96, 128)
+    x, a, b = (torch.randn((5, 128), device=dev, generator=g) for _ in range(3))
+    h, gamma = torch.randn((5, 128), device=dev, generator=g), torch.rand(128, device=dev, generator=g) + 0.5
+    qa = ops.quant_act(x)
+    norm = lambda **k: decoder.norm_quant(k.pop("mode", B.BL_NORM_GATED), k.pop("gamma", gamma), **{"a": a, "b": b, **k})
+    calls = {
+        "half": lambda: ops.quant_act(x.half()), "double": lambda: ops.quant_act(x.double()), "cpu": lambda: ops.quant_act(x.cpu()),
+        "one dimension": lambda: ops.quant_act(x[0]), "transposed": lambda: ops.quant_act(x.t()), "strided rows": lambda: ops.quant_act(x[:, :100]),
+        "no rows": lambda: ops.quant_act(x[:0]), "subclass": lambda: ops.quant_act(x.as_subclass(Plain)),
+        "loud subclass": lambda: ops.quant_act(x.as_subclass(Loud)), "parameter": lambda: ops.quant_act(torch.nn.Parameter(x)),
+        "a mode": lambda: _watched(lambda: ops.quant_act(x)), "a mode over a product": lambda: _watched(lambda: ops.gemm(pw, qa)),
+        "vmap": lambda: torch.func.vmap(lambda r: ops.quant_act(r).a_scale)(x.view(5, 1, 128)),
+        "grad": lambda: torch.func.grad(lambda r: ops.quant_act(r).a_scale.sum())(x),
+        "sparse": lambda: ops.quant_act(x.to_sparse()),
+        "too many rows": lambda: ops.gemv(pw, ops.quant_act(x.repeat(3, 1))), "no token": lambda: ops.gemm(pw, ops.QuantAct(qa.q[:0], qa.a_scale, qa.q_sum, 128)),
+        "another layout": lambda: ops.gemm(_with_desc(pw, version=9), qa),
+        "another K": lambda: ops.gemm(_with_desc(pw, K=64), qa),
+        "batch of another layout": lambda: ops.gemm_batch([pw, _with_desc(pw, version=2)], qa),
+        "norm of half": lambda: norm(a=a.half()), "norm of a slice": lambda: norm(a=a[:, :64], b=b[:, :64], gamma=gamma[:64].clone()),
+        "norm of strided rows": lambda: norm(a=torch.cat([a, a], 1)[:, :128]), "norm of other rows": lambda: norm(b=b[:4]),
+        "norm without a gate": lambda: norm(b=None), "norm weight of another length": lambda: norm(gamma=gamma[:64].clone()),
+        "norm weight of two dimensions": lambda: norm(gamma=gamma[None]), "norm weight of half": lambda: norm(gamma=gamma.half()),
+        "little scratch": lambda: norm(scratch=torch.empty(16, dtype=torch.uint8, device=dev)),
+        "norm of a subclass": lambda: norm(a=a.as_subclass(Plain)), "no such mode": lambda: norm(mode=9),
+        "residual without a delta": lambda: [norm(mode=B.BL_NORM_RESIDUAL, a=None, b=None, h=h.clone())],
+        "norm with integer eps": lambda: norm(eps=1), "norm with an eps of text": lambda: norm(eps="x"),
+    }
+    native = {}
+    for name, call in calls.items():
+        Loud.seen.clear()
+        native[name] = _outcome(call), list(Loud.seen)
+    monkeypatch.setattr(B, "_calls", False)
+    for name, call in calls.items():
+        Loud.seen.clear()
+        assert native[name] == (_outcome(call), list(Loud.seen)), name
