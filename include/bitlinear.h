@@ -18,6 +18,8 @@
  *     and owns no stream: all work is enqueued on `stream` (a hipStream_t
  *     passed as void*; NULL = the default stream) and the call returns at
  *     once.  Results are valid once the stream reaches that point.
+ *   - Every launch may be captured into a HIP graph, a kernel's first one too;
+ *     only bl_gemv_batch_static wants its first call outside the capture.
  *   - Every call returns a bl_status.  Arguments are validated on the host
  *     BEFORE any HIP call, so a bad call has no effect on the device.
  *     A failed launch is reported as BL_ERR_HIP.

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kThreads) void attn_prompt_kernel(const PromptArgs 
 template <int KS>
 hipError_t launch_prompt(const PromptArgs& p, hipStream_t s) {
     static LdsCeiling ceiling;   // per instantiation, i.e. per kernel
-    const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(&attn_prompt_kernel<KS>));
+    const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(&attn_prompt_kernel<KS>), PromptLds<KS>::kBytes);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)p.n_heads, (unsigned)((p.M + kBlockQ - 1) / kBlockQ));
     attn_prompt_kernel<KS><<<grid, dim3(kThreads), PromptLds<KS>::kBytes, s>>>(p);

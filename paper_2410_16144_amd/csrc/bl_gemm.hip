@@ -538,7 +538,7 @@ GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed&
 template <typename Kernel, typename Arg>
 hipError_t launch_form(Kernel kernel, size_t lds_bytes, int threads, unsigned grid, const Arg& arg, int M, int gx, hipStream_t s) {
     static LdsCeiling ceiling;   // per instantiation of this template, i.e. per kernel
-    const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(kernel));
+    const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(kernel), (int)lds_bytes);
     if (e != hipSuccess) return e;
     kernel<<<dim3(grid), dim3((unsigned)threads), lds_bytes, s>>>(arg, M, gx);
     return hipGetLastError();
@@ -565,11 +565,9 @@ bool gemm_form_exists(int code) {
 }
 
 hipError_t launch_mixed(const GemmMixed& b, int64_t M, hipStream_t s) {
-    static LdsCeiling ceiling;
-    const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(&gemm_mixed_kernel));
-    if (e != hipSuccess) return e;
     constexpr int kLds = gemm_lds_bytes<2, 2, 1, 4>();
     static_assert(kLds == gemm_lds_bytes<2, 1, 1, 4>(), "both widths stage the same activation tiles");
+    static_assert(kLds <= kDefaultLds, "no ceiling to raise");
     const unsigned grid = (unsigned)(b.wgs + (b.small_gx + kXcds - 1) / kXcds * kXcds * ((M + 63) / 64));
     note_kernel("gemm_mixed_kernel", (int)grid);
     gemm_mixed_kernel<<<dim3(grid), dim3(256), kLds, s>>>(b, (int)M);

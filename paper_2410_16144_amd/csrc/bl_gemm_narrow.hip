@@ -257,7 +257,7 @@ template <int T, int RH, int W, int D>
 hipError_t launch_narrow_form(const NarrowBatch& b, int M, int gx, hipStream_t s) {
     using F = NarrowForm<T, RH, W, D>;
     static LdsCeiling ceiling;   // per instantiation, i.e. per kernel
-    const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(&gemm_narrow_kernel<T, RH, W, D>));
+    const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(&gemm_narrow_kernel<T, RH, W, D>), F::kLds);
     if (e != hipSuccess) return e;
     const int64_t wgs = (int64_t)(gx + kXcds - 1) / kXcds * kXcds * ((M + T - 1) / T);
     if (wgs > INT32_MAX) return hipErrorInvalidValue;

@@ -136,12 +136,16 @@ struct QuantBatch {
 
 constexpr int kMaxDecodeLds = 128 * 1024;   // dynamic LDS ceiling of the decode kernels
 
+constexpr int kDefaultLds = 64 * 1024;      // what a kernel gets without asking
+
 // Raises one kernel's dynamic-LDS ceiling to kMaxDecodeLds, once per device (the setting belongs to the device the
-// call is made on): a host-side attribute, no allocation.  One object per kernel; a repeated call from another
-// thread is harmless.
+// call is made on): a host-side attribute, no allocation, allowed while a stream is captured.  One object per kernel; a
+// repeated call from another thread is harmless.
 struct LdsCeiling {
     uint64_t done = 0;   // one bit per device ordinal below 64; other devices set the attribute on every launch
-    hipError_t ensure(const void* kernel) {
+    // lds_bytes: the largest size that the kernel is launched with
+    hipError_t ensure(const void* kernel, int lds_bytes = kMaxDecodeLds) {
+        if (lds_bytes <= kDefaultLds) return hipSuccess;
         int dev = -1;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
         if (dev >= 0 && ((done >> dev) & 1)) return hipSuccess;

@@ -307,9 +307,9 @@ class DecoderStack:
 
     def capture(self):
         """Capture launch() into a HIP graph (no memset nodes: every launch here is a kernel).  One token is run
-        eagerly first -- kernels set their launch attributes on first use, which a capture does not allow -- and
-        the residual stream and the position are put back afterwards (the cache row it wrote is rewritten by the
-        first real token at that position)."""
+        eagerly first, so that every kernel has run outside the capture (the library does not need that: a first use
+        under capture works), and the residual stream and the position are put back afterwards (the cache row it wrote
+        is rewritten by the first real token at that position)."""
         h0, pos0 = self.h.clone(), self.pos.clone()
         self.launch()
         torch.cuda.synchronize()
