@@ -19,7 +19,8 @@
 // Waits.  Every vector memory operation of the loop is one of the requests below, written as assembly (the compiler
 // answers loads into LDS that it can see with a wait for everything), kPerStep of them per step, and they complete in
 // issue order: when step i is consumed, the steps behind it that have been requested are i+1 .. i+D-1, so at most
-// (D-1)*kPerStep operations may be outstanding, none at all once the last steps are reached.
+// (D-1)*kPerStep operations may be outstanding, none at all once the last steps are reached (NarrowRing).
+#include "bl_gemm_ring.hpp"
 #include "bl_internal.hpp"
 
 namespace bl {
@@ -42,7 +43,8 @@ struct NarrowForm {
     static_assert(T % 16 == 0 && T <= 64 && (RH == 1 || RH == 2 || RH == 4), "tokens in sixteens, half or whole row blocks");
     static constexpr int kMB = (T + 31) / 32;            // 32-token matrix tiles (the last one half empty if T % 32 == 16)
     static constexpr int kStage = RH * 1024 + T * 128;   // bytes of one step: weights, then activations
-    static constexpr int kPerStep = RH + T / 8;          // requests per step (1 KiB each)
+    using Ring = NarrowRing<T, RH, D>;                   // requests and wait counts: bl_gemm_ring.hpp, checked by a host-side model
+    static_assert(kStage == Ring::kPerStep * 1024, "a step's requests fill its stage");
     static constexpr int kQuads = RH * T / 8;            // accumulator register quadruples that hold tokens < T
     static constexpr int kRing = W * D * kStage;
     // the final exchange goes in as many phases as keep it within half of a compute unit's LDS (two workgroups per unit)
@@ -52,7 +54,6 @@ struct NarrowForm {
     static constexpr int kSets = (kPhaseQuads + W - 1) / W;    // quadruples a wave finishes per phase
     static_assert(kQuads % kPhases == 0, "equal phases");
     static constexpr int kLds = kRing > kExchange ? kRing : kExchange;
-    static_assert((D - 1) * kPerStep < 64, "fits the wait counter");
     static_assert(kLds <= kMaxDecodeLds, "fits the LDS ceiling");
 };
 
@@ -177,7 +178,7 @@ __global__ __launch_bounds__(64 * W) void gemm_narrow_kernel(const NarrowBatch b
     for (int i = 0; i < D; ++i)
         if (i < steps) request(i);
     for (int i = 0; i < steps; ++i) {
-        if (D > 1 && steps - i >= D) wait_vm<(D - 1) * F::kPerStep>();
+        if (F::Ring::steady(steps, i)) wait_vm<F::Ring::kYounger>();
         else wait_vm<0>();
         const uint8_t* stage = lds + wave * D * F::kStage + (D == 1 ? 0 : i % D) * F::kStage;
         uint4 w[RH];

@@ -1,6 +1,6 @@
-// Ring depths and wait counts of the prefill kernel's operand pipeline (bl_gemm.hip), as compile-time constants in a
-// header of their own: the kernel takes them from here, and so does the host-side model that replays the kernel's
-// issue order and checks every wait (tests/ring_model).  Plain C++, no device code.
+// Ring depths and wait counts of the prefill kernels' operand pipelines (bl_gemm.hip, bl_gemm_narrow.hip), as compile-time
+// constants in a header of their own: the kernels take them from here, and so does the host-side model that replays the
+// kernels' issue order and checks every wait (tests/ring_model).  Plain C++, no device code.  First the one of bl_gemm.hip.
 //
 // The pipeline, per thread and K step i (one packed tile per K group):
 //   - activations: the tile of step i + kLead is requested (global -> LDS, kRQ loads per thread of a loader wave, written
@@ -41,6 +41,18 @@ struct GemmRing {
     static_assert(kStages >= kLead + 1, "a stage is rewritten only after the barrier that ended its last read");
     static_assert(kYounger < 16 && kYoungerTail < 16 && kPrologueWait < 16, "fits the low vmcnt field");
     static_assert(kUnroll % kWR == 0, "register ring slots are compile-time phases of the unrolled loop");
+};
+
+// The kernel for few tokens (bl_gemm_narrow.hip): every wave has stages of its own in LDS and waits for nobody.  Step i's
+// requests (kPerStep of them per thread, all assembly) go into stage i % D, D steps ahead; when step i is consumed, the steps
+// behind it that have been requested are i + 1 .. i + D - 1, all of them as long as that many are left, so kYounger operations may
+// be outstanding; towards the end nothing may.  Whatever else a thread has outstanding was issued before its first request.
+template <int T, int RH, int D>
+struct NarrowRing {
+    static constexpr int kPerStep = RH + T / 8;        // 1 KiB each: the weights of 32 RH rows, the activations of T tokens
+    static constexpr int kYounger = (D - 1) * kPerStep;
+    static constexpr bool steady(int steps, int i) { return D > 1 && steps - i >= D; }   // kYounger may be outstanding at step i, else 0
+    static_assert(kYounger < 64, "fits the wait counter");
 };
 
 // The matrix-core decode kernel's one-off copy of the quantized activations into LDS (bl_gemv.hip, QMODE 1): the copy's

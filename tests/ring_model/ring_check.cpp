@@ -1,5 +1,5 @@
-// Host-side model of the vector-memory wait counts in the prefill kernel (csrc/bl_gemm.hip) and in the matrix-core
-// decode kernel's activation copy (csrc/bl_gemv.hip).  No GPU, no HIP: the constants come from the header the kernels
+// Host-side model of the vector-memory wait counts in the prefill kernels (csrc/bl_gemm.hip, csrc/bl_gemm_narrow.hip) and in
+// the matrix-core decode kernel's activation copy (csrc/bl_gemv.hip).  No GPU, no HIP: the constants come from the header the kernels
 // use (csrc/bl_gemm_ring.hpp); the issue order is restated here from the kernels' text.
 //
 // Machine model (the ISA's): every vector memory operation a thread issues -- ordinary loads and global -> LDS loads
@@ -12,6 +12,11 @@
 //   1. whenever a step reads an activation tile from LDS, a barrier lies between that tile's completion and the read;
 //   2. whenever a request overwrites an LDS stage, a barrier lies between the last read of the stage's old tile and it;
 //   3. both hold when the compiler keeps the tail's weight loads and when it removes them (their values are dead).
+// The kernel for few tokens has no barrier in its loop: a wave's stages are its own, so a step's requests must have completed
+// when ITS thread reads the stage, a stage may be requested anew only after its step has been read, and nothing may be
+// outstanding behind the loop, where the partial sums take the stages' place.  For every <T, RH, D> that is built and every
+// step count, with and without the scale loads that some forms issue first.  "--slack" lets each of its waits leave one
+// operation more outstanding: the model must then FAIL.
 // With "--old-tail" the tail uses the main loop's count, the form the kernel had before: the model must then FAIL for
 // some step count (the planted mistake the test suite looks for).
 #include <cstdio>
@@ -118,15 +123,58 @@ int copy_check() {
     return bad;
 }
 
+template <int T, int RH, int D>
+int narrow_check(int slack, bool verbose) {
+    using R = bl::NarrowRing<T, RH, D>;
+    int bad = 0;
+    for (int steps = 0; steps <= kMaxSteps; ++steps)
+        for (int scales = 0; scales <= 16; scales += 8) {
+            Thread t;
+            t.done.assign(steps, false);
+            t.landed_at.assign(steps, -1);
+            std::vector<int> missing(steps, R::kPerStep);
+            std::vector<bool> read(steps, false);
+            bool ok = true;
+            auto fail = [&](const char* what, int step) {
+                ok = false;
+                if (verbose) std::printf("  narrow <%d,%d,%d> steps=%d scales=%d: %s at step %d\n", T, RH, D, steps, scales, what, step);
+            };
+            auto request = [&](int step) {
+                if (step >= D && !read[step - D]) fail("stage requested anew before it was read", step);
+                for (int r = 0; r < R::kPerStep; ++r) t.issue(step);
+            };
+            auto wait = [&](int allowed) {
+                const int must = (int)t.issued.size() - (allowed + slack);
+                for (; t.completed < must; ++t.completed)
+                    if (t.issued[t.completed] >= 0) --missing[t.issued[t.completed]];
+            };
+            for (int l = 0; l < scales; ++l) t.issue(-1);
+            for (int i = 0; i < D; ++i)
+                if (i < steps) request(i);
+            for (int i = 0; i < steps; ++i) {
+                wait(R::steady(steps, i) ? R::kYounger : 0);
+                if (missing[i] != 0) fail("stage read before it had landed", i);
+                read[i] = true;
+                if (i + D < steps) request(i + D);
+            }
+            for (int i = 0; i < steps; ++i)
+                if (missing[i] != 0) fail("request outstanding behind the loop", i);
+            if (!ok) ++bad;
+        }
+    return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const bool old_tail = argc > 1 && std::strcmp(argv[1], "--old-tail") == 0;
-    const bool verbose = argc > 2 || (argc > 1 && !old_tail);
+    const int slack = argc > 1 && std::strcmp(argv[1], "--slack") == 0 ? 1 : 0;
+    const bool verbose = argc > 2 || (argc > 1 && !old_tail && !slack);
     int bad = 0;
     // every form launch_gemm / launch_gemm_batch can choose
     bad += sweep<1, 2, 1, 4>(old_tail, verbose);
     bad += sweep<1, 4, 1, 4>(old_tail, verbose);
+    bad += sweep<2, 1, 1, 4>(old_tail, verbose);   // the narrow tiles of the two-width kernel
     bad += sweep<2, 2, 1, 4>(old_tail, verbose);
     bad += sweep<2, 3, 1, 4>(old_tail, verbose);
     bad += sweep<2, 4, 1, 4>(old_tail, verbose);
@@ -136,6 +184,8 @@ int main(int argc, char** argv) {
     bad += sweep<2, 2, 2, 4>(old_tail, verbose);
     bad += sweep<2, 2, 4, 2>(old_tail, verbose);
     bad += copy_check<4>() + copy_check<6>();
+    bad += narrow_check<16, 1, 2>(slack, verbose) + narrow_check<16, 2, 2>(slack, verbose) + narrow_check<32, 1, 2>(slack, verbose);
+    bad += narrow_check<32, 2, 1>(slack, verbose) + narrow_check<32, 4, 1>(slack, verbose) + narrow_check<64, 4, 1>(slack, verbose);
     std::printf("%s: %d failing cases\n", old_tail ? "old tail count" : "current counts", bad);
     return bad == 0 ? 0 : 1;
 }

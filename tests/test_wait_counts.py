@@ -1,4 +1,4 @@
-"""The hand-counted vector-memory waits of the prefill kernel's operand pipeline and of the decode kernel's activation
+"""The hand-counted vector-memory waits of the prefill kernels' operand pipelines and of the decode kernel's activation
 copy, checked without a GPU.
 
 1. A host-side model (tests/ring_model/ring_check.cpp, plain C++) replays the kernels' per-thread issue order for every
@@ -7,7 +7,8 @@ copy, checked without a GPU.
    outstanding": every LDS read of an activation tile must lie behind a barrier that followed the tile's completion,
    every overwrite of a stage behind a barrier that followed its last read -- whether the compiler keeps the dead weight
    loads of the loop's tail or removes them.  With the tail's count set to the main loop's (the kernel's earlier form)
-   the model must fail: that is the mistake it is there to catch.
+   the model must fail: that is the mistake it is there to catch.  The kernel for few tokens, whose waves have stages of
+   their own and no barrier, is replayed in the same way, and must fail with one operation more left outstanding.
 2. The model's premise -- which loads each step issues -- is checked against the compiler's output: the kernels are
    compiled to assembly for gfx950 and every barrier of the K loop must be preceded by the expected wait and by the
    expected number of global -> LDS requests and weight loads since the barrier before it.
@@ -42,6 +43,11 @@ def test_model_rejects_the_main_loop_count_in_the_tail(model):
     assert r.returncode == 1
     n = int(re.search(r"(\d+) failing cases", r.stdout).group(1))
     assert n > 0
+
+
+def test_model_rejects_a_wait_that_leaves_one_more_outstanding(model):
+    r = subprocess.run([model, "--slack"], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 1 and int(re.search(r"(\d+) failing cases", r.stdout).group(1)) > 0
 
 
 def _functions(asm_path):
@@ -86,31 +92,74 @@ def _compile_to_asm(tmp, name, extra=()):
     return out
 
 
+def _check_tiles(name, seq, mb, h, wk, wn, tiles=1):
+    """The barriers of a kernel with the code of `tiles` tiles of the same wait counts: each a prologue and the main loop's
+    eight steps in a row, and the tails' steps, wherever the compiler laid them."""
+    nt, lead = (h + 1) // 2, 4
+    wr = 8 if nt == 1 else 4
+    rq = -(-(wk * 2 * mb) // (wn * wk))          # requests per loader thread and step
+    younger, younger_tail, prologue = (lead - 2) * (rq + nt), (lead - 2) * rq, (lead - 3) * rq
+    starts = [0] if tiles == 1 else [i for i, b in enumerate(seq) if b[1] == lead * rq and b[2] == (wr - 1) * nt]
+    assert len(starts) == tiles and starts[0] == 0, (name, seq)
+    for i in starts:
+        # prologue: the weight ring's first tiles and the first kLead requests, a wait that leaves kPrologueWait outstanding
+        assert seq[i][1] == lead * rq and seq[i][2] == (wr - 1) * nt and seq[i][0] is not None and seq[i][0] <= prologue, (name, seq[i])
+        if tiles > 1:
+            assert all(b[0] == younger for b in seq[i + 1:i + 9]), (name, seq)
+    rest = [b for i, b in enumerate(seq) if i not in starts]
+    main = [b for b in rest if b[0] == younger]
+    tail = [b for b in rest if b[0] == younger_tail]
+    assert len(main) == 8 * tiles and len(tail) == 7 * tiles, (name, seq)
+    for wait, lds, w in main:          # a step of the main loop: kRQ requests, at least the kNT weight loads
+        assert lds == rq and w >= nt, (name, seq)
+    for wait, lds, w in tail:          # a step of the tail: kRQ requests; its weight loads may be gone
+        assert lds == rq, (name, seq)
+
+
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 def test_compiled_prefill_kernels_issue_what_the_model_assumes(tmp_path):
     fns = _functions(_compile_to_asm(tmp_path, "bl_gemm.hip"))
     seen = 0
     for name, lines in fns.items():
         m = re.search(r"gemm_(?:batch_)?kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)E", name)
+        if m:
+            seen += 1
+            _check_tiles(name, _barriers(lines), *(int(x) for x in m.groups()))
+        elif "gemm_mixed_kernel" in name:      # <2, 2, 1, 4> and <2, 1, 1, 4>, whose constants are the same (static_assert)
+            seen += 1
+            _check_tiles(name, _barriers(lines), 2, 2, 1, 4, tiles=2)
+    assert seen == 15                      # seven forms, single and batched, and the one with two widths
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_compiled_few_token_kernels_issue_what_the_model_assumes(tmp_path):
+    """No barrier in the loop: the requests between the function's start and the first barrier are D steps ahead of it and one
+    step's inside it, the loop waits for 0 or kYounger of them and has no other vector memory operation."""
+    fns = _functions(_compile_to_asm(tmp_path, "bl_gemm_narrow.hip"))
+    forms = {(16, 1): 2, (16, 2): 2, (32, 1): 2, (32, 2): 1, (32, 4): 1, (64, 4): 1}      # (T, RH): D
+    seen = 0
+    for name, lines in fns.items():
+        m = re.search(r"gemm_narrow_kernelILi(\d+)ELi(\d)ELi8ELi(\d)E", name)
         if not m:
             continue
         seen += 1
-        mb, h, wk, wn = (int(x) for x in m.groups())
-        nt, lead = (h + 1) // 2, 4
-        wr = 8 if nt == 1 else 4
-        rq = -(-(wk * 2 * mb) // (wn * wk))          # requests per loader thread and step
-        younger, younger_tail, prologue = (lead - 2) * (rq + nt), (lead - 2) * rq, (lead - 3) * rq
-        seq = _barriers(lines)
-        # prologue: the weight ring's first tiles and the first kLead requests, a wait that leaves kPrologueWait outstanding
-        assert seq[0][1] == lead * rq and seq[0][2] == (wr - 1) * nt and seq[0][0] is not None and seq[0][0] <= prologue, (name, seq[0])
-        main = [b for b in seq[1:] if b[0] == younger]
-        tail = [b for b in seq[1:] if b[0] == younger_tail]
-        assert len(main) == 8 and len(tail) == 7, (name, seq)
-        for wait, lds, w in main:          # a step of the main loop: kRQ requests, at least the kNT weight loads
-            assert lds == rq and w >= nt, (name, seq)
-        for wait, lds, w in tail:          # a step of the tail: kRQ requests; its weight loads may be gone
-            assert lds == rq, (name, seq)
-    assert seen == 14                      # seven forms, single and batched
+        t, rh, d = (int(x) for x in m.groups())
+        assert forms[t, rh] == d
+        per_step = rh + t // 8
+        end = next(i for i, l in enumerate(lines) if l.startswith("s_barrier"))
+        loop = lines[:end]
+        requests = [i for i, l in enumerate(loop) if l.startswith("global_load_lds_dwordx4")]
+        assert len(requests) == (d + 1) * per_step, name
+        for l in loop[requests[0]:]:
+            assert not re.match(r"(scratch_|buffer_|flat_|global_store|global_atomic)", l), (name, l)
+        # ordinary loads: the scales, before the first request or behind the loop, whose products end it or lie before it
+        last = max(i for i, l in enumerate(loop) if l.startswith("v_mfma") or i in set(requests))
+        for i, l in enumerate(loop):
+            if re.match(r"global_load_dword\b", l):
+                assert i < requests[0] or i > last, (name, l)
+        waits = {int(w) for l in loop[requests[0]:last] for w in re.findall(r"vmcnt\((\d+)\)", l)}
+        assert waits == ({0, (d - 1) * per_step} if d > 1 else {0}), (name, waits)
+    assert seen == 6
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
