@@ -6,7 +6,7 @@
 // B = weight codes (w+1) as int8; sum_k q is subtracted in the epilogue.
 //
 // Tiling.  Workgroup = WN x WK waves (4 or 8): WN side by side along N, WK along K; its tile is (32*MB) tokens x
-// (32*H*WN) weight rows; each wave owns (32*MB) x (32*H), i.e. MB x H MFMA tiles, H = 2, 3 or 4.  (With H = 3 a wave's 96 rows are one
+// (32*H*WN) weight rows; each wave owns (32*MB) x (32*H), i.e. MB x H MFMA tiles, H = 1 (the two-width kernel's narrow tiles only), 2, 3 or 4.  (With H = 3 a wave's 96 rows are one
 // packed 64-row tile and half of another, which it shares with its neighbour: both load it, each expands
 // its own half.  The form was built for its workgroup count -- where 128-row wave tiles leave the last round of
 // workgroups mostly empty, 96-row tiles fill it -- and measured no faster: the kernel runs at the chip's power
@@ -473,32 +473,38 @@ bool plan_mixed(const GemmProblem* ps, int count, int64_t M, GemmMixed& b) {
     b.gx = (int32_t)at;
     b.wgs = (int32_t)((at + kXcds - 1) / kXcds * kXcds * tiles_m);
     b.small_gx = (int32_t)small;
-    return small * tiles_m <= cus;
+    // at most one narrow tile per unit, on the die with the most positions of them too (1535 x 3392 -> 3200 has 9 positions of 24
+    // tiles, two of them on one die, 48 tiles for its 32 units: 26.4 us, with 64 x 256 tiles alone 24.0)
+    return (small + kXcds - 1) / kXcds * kXcds * tiles_m <= cus;
 }
 
-// What a launch takes: one of this file's one-width forms (choose_tile), the two-width kernel or a form of bl_gemm_narrow.hip,
-// by estimated time.  The estimates are straight lines through the measured times (us, weights cold) of 108 launches -- nine
-// shapes from 2560 x 6912 to 4096 x 24064 and 8192^2, 128 to 1024 tokens -- over KC, the tiles along K, and x, the workgroups per
-// compute unit:
-//     32 x 256 (and the K split)   4.4 + KC * (0.18 up to x = 1;  0.21 + 0.056 (x - 1) up to 2;  0.14 x beyond)     0.81 .. 1.17 of the time
-//     64 x 256                     6.6 + KC * (0.20;  0.28 + 0.12 (x - 1);  0.23 x)                                  0.77 .. 1.07
-//     64 x 512                     8.4 + KC * (0.36;  0.57 + 0.17 (x - 1);  0.46 x)                                  0.70 .. 1.13
-//     two widths                   7.0 + KC * (0.245 + 0.055 * share of the units with a narrow tile)                0.89 .. 1.08
-// Small biases (the two-width kernel 5 % ahead, the waves-along-K forms 8 % behind) were set so that no launch of the 108 is
-// more than 1.5 % slower than its one-width form; on average they are 16 % faster (4096 -> 11008 at 384 tokens: 26.7 -> 22.4 us,
-// at 512 26.9 -> 25.0; 3200 -> 8640 at 512 22.1 -> 20.1; 8192^2 at 576 45.2 -> 39.3; 5120^2 at 1024 32.9 -> 29.9) and within 2.5 % of
-// the best choice.
+// What a launch takes: the one-width form of choose_tile, the two-width kernel or a form of bl_gemm_narrow.hip, by estimated
+// time.  (choose_tile goes by workgroup counts; the other one-width forms are not weighed against it here.)  The estimates
+// are lines through measured times (us, weights cold) of 9176 launches -- 9 to 6000 tokens, K 64 to 13000, N 64 to 60000, a
+// fifth of them no multiples of 64, sizes spread over their logarithms, every form on each -- over KC, the tiles along K, and x, the
+// workgroups per compute unit, counted with the padding of the N positions to a multiple of 8 (the dies' shares are whole
+// positions).  Eight in ten estimates lie within these limits of the measured time:
+//     32 x 256        4.5 + 0.141 KC up to x = 1;  + 0.211 KC + 2.04 (x - 1) up to 2;  + 0.111 KC x + 1.19 (x - 1) beyond   0.89 .. 1.11
+//     the K split     6.6 + 0.145 KC;  0.222 KC + 2.70 (x - 1);  0.114 KC x + 2.19 (x - 1)                                  0.84 .. 1.16
+//     64 x 256        5.6 + 0.185 KC;  0.304 KC + 4.13 (x - 1);  0.187 KC x + 2.58 (x - 1)                                  0.81 .. 1.18
+//     64 x 512        7.3 + 0.309 KC;  0.586 KC + 6.99 (x - 1);  0.361 KC x + 6.30 (x - 1)                                  0.74 .. 1.21
+//     two widths      8.3 + KC * (0.212 + 0.045 * share of the units with a narrow tile)                                     0.92 .. 1.06
+// The two-width kernel is taken if it is 4 % ahead, the waves-along-K forms if they are 6 % ahead.  Of the 9176 launches 28 are
+// then slower than their one-width form by more than 1.5 %, 15 by more than 5 %, the worst by 18 %; on average (geometric) they take 1/1.63 of
+// its time and are within 3.1 % of the best form.  (4096 -> 11008 at 384 tokens 26.7 -> 22.4 us, at 512 26.9 -> 25.0; 3200 -> 8640 at 512 22.1 -> 20.1; 8192^2 at
+// 576 45.2 -> 39.3; 5120^2 at 1024 32.9 -> 29.9.)
 struct GemmChoice { int narrow = 0; bool mixed = false; };
 
 float tile_estimate(const TileForm& f, int64_t M, int64_t rows, int KC, int cus) {
     const int64_t gx = (rows + f.wn * f.h * 32 - 1) / (f.wn * f.h * 32), gy = (M + 32 * f.mb - 1) / (32 * f.mb);
-    const float x = (float)(gx * gy) / (float)cus;
-    const auto line = [&](float t0, float one, float step, float slope, float per) {
-        return t0 + (float)KC * (x <= 1.0f ? one : x <= 2.0f ? step + slope * (x - 1.0f) : per * x);
+    const float x = (float)((gx + kXcds - 1) / kXcds * kXcds * gy) / (float)cus, k = (float)KC;
+    const auto line = [&](float t0, float one, float two, float each2, float per, float each) {
+        return t0 + (x <= 1.0f ? one * k : x <= 2.0f ? two * k + each2 * (x - 1.0f) : per * k * x + each * (x - 1.0f));
     };
-    if (f.h == 4) return line(8.4f, 0.356f, 0.565f, 0.174f, 0.463f);
-    if (f.mb == 1 || f.wk > 1) return line(4.4f, 0.182f, 0.211f, 0.056f, 0.141f);
-    return line(6.6f, 0.201f, 0.280f, 0.124f, 0.231f);
+    if (f.h == 4) return line(7.25f, 0.309f, 0.586f, 6.99f, 0.361f, 6.30f);
+    if (f.wk > 1) return line(6.61f, 0.145f, 0.222f, 2.70f, 0.114f, 2.19f);
+    if (f.mb == 1) return line(4.52f, 0.141f, 0.211f, 2.04f, 0.111f, 1.19f);
+    return line(5.56f, 0.185f, 0.304f, 4.13f, 0.187f, 2.58f);
 }
 
 GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed& mixed) {
@@ -522,14 +528,14 @@ GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed&
     }
     float best = tile_estimate(choose_tile(M, rows), M, rows, KC, cus);
     if (mixed_ok) {
-        const float share = (float)(mixed.small_gx * ((M + 63) / 64)) / (float)cus;
-        const float us = 0.95f * (7.0f + (float)KC * (0.245f + 0.055f * share));
+        const float share = (float)((mixed.small_gx + kXcds - 1) / kXcds * kXcds * ((M + 63) / 64)) / (float)cus;
+        const float us = 1.04f * (8.31f + (float)KC * (0.212f + 0.045f * share));
         if (us < best) { best = us; c.mixed = true; }
     }
     if (narrow_ok) {
         float us = 0.0f;
         const int code = gemm_narrow_best(ps, count, M, cus, us);
-        if (1.08f * us < best) { c.mixed = false; c.narrow = code; }
+        if (1.06f * us < best) { c.mixed = false; c.narrow = code; }
     }
     return c;
 }

@@ -267,21 +267,23 @@ hipError_t launch_narrow_form(const NarrowBatch& b, int M, int gx, hipStream_t s
     return hipGetLastError();
 }
 
-// The forms that are built, X(T, RH, W, D, t0, a, s), with the line that their measured times follow (us; least squares over
-// 55 to 154 launches of 9 to 768 tokens on shapes from 1536^2 to 8192^2 and 4096 x 24064, weights cold; every point within 25 %):
-//     t = t0 + KC * (a + s * (X - 1)),   x = workgroups / compute units,  X = max(1, (x + ceil x) / 2)
-// (KC = packed tiles along K).  Among themselves, taking the form with the smallest figure was on average 0.5 % off the best form, 7 % at worst.
+// The forms that are built, X(T, RH, W, D, t0, a, e, s), with the line that their measured times follow (us; relative least
+// squares over the 9176 launches described at choose_kernel in bl_gemm.hip, weights cold; eight in ten points within 11 %):
+//     t = t0 + a KC + (X - 1) (e + s KC),   X = max(1, (x + ceil x) / 2),   x = workgroups / compute units
+// (KC = packed tiles along K; e: what a workgroup costs however short K is -- with it left out, 718 x 64 -> 6976 took 22.9 us here
+// where the tile kernel takes 8.5).  The workgroups are counted with the padding of the strips to a multiple of 8: a die
+// gets whole strips, and the die with the most is the one that ends last.
 // Measured, tile kernel before -> this one: 3200^2 14.3 -> 4.7 us at 37 tokens, 12.0 -> 5.4 at 128, 12.2 -> 7.6 at 256;
 // 4096 -> 11008 16.6 -> 6.4 at 16, 18.9 -> 9.5 at 64, 17.0 -> 13.9 at 128; 11008 -> 4096 32.7 -> 8.1 at 16, 35 -> 10.4 at 64,
 // 37.7 -> 15.8 at 256, 38.4 -> 25.1 at 512.  Also tried: four or sixteen waves along K, 48-token blocks, three or four steps in
 // flight, and weights straight into registers -- none ahead of the best of these six by more than 5 % anywhere.
-#define BL_NARROW_FORMS(X)                    \
-    X(16, 1, 8, 2, 2.74f, 0.0317f, 0.0236f)   \
-    X(16, 2, 8, 2, 2.93f, 0.0407f, 0.0386f)   \
-    X(32, 1, 8, 2, 2.76f, 0.0389f, 0.0345f)   \
-    X(32, 2, 8, 1, 3.00f, 0.0481f, 0.0501f)   \
-    X(32, 4, 8, 1, 4.53f, 0.0615f, 0.0857f)   \
-    X(64, 4, 8, 1, 6.67f, 0.0936f, 0.2225f)
+#define BL_NARROW_FORMS(X)                           \
+    X(16, 1, 8, 2, 3.22f, 0.0199f, 0.514f, 0.0182f)  \
+    X(16, 2, 8, 2, 3.43f, 0.0298f, 0.897f, 0.0277f)  \
+    X(32, 1, 8, 2, 3.39f, 0.0244f, 0.879f, 0.0255f)  \
+    X(32, 2, 8, 1, 3.71f, 0.0287f, 1.103f, 0.0359f)  \
+    X(32, 4, 8, 1, 4.76f, 0.0485f, 1.915f, 0.0570f)  \
+    X(64, 4, 8, 1, 6.83f, 0.0780f, 6.112f, 0.1156f)
 
 // Strips of one product: 32*RH rows of W each.
 int64_t strips_of(const GemmProblem& p, int rh) {
@@ -293,7 +295,7 @@ constexpr int narrow_code(int t, int rh) { return 1000 * rh + t; }
 }  // namespace
 
 bool gemm_narrow_form_exists(int code) {
-#define X(T, RH, W, D, T0, A, S) if (code == narrow_code(T, RH)) return true;
+#define X(T, RH, W, D, T0, A, E, S) if (code == narrow_code(T, RH)) return true;
     BL_NARROW_FORMS(X)
 #undef X
     return false;
@@ -308,15 +310,15 @@ bool gemm_narrow_takes(const GemmProblem* ps, int count, int64_t M) {
 int gemm_narrow_best(const GemmProblem* ps, int count, int64_t M, int cus, float& us) {
     int best = 0, KC = 0;
     for (int i = 0; i < count; ++i) KC = ps[i].KC > KC ? ps[i].KC : KC;
-    const auto consider = [&](int t, int rh, float t0, float a, float slope) {
+    const auto consider = [&](int t, int rh, float t0, float a, float each, float slope) {
         int64_t strips = 0;
         for (int i = 0; i < count; ++i) strips += strips_of(ps[i], rh);
-        const int64_t wgs = strips * ((M + t - 1) / t);
+        const int64_t wgs = (strips + kXcds - 1) / kXcds * kXcds * ((M + t - 1) / t);
         const float x = (float)wgs / (float)cus, turns = 0.5f * (x + (float)((wgs + cus - 1) / cus));
-        const float est = t0 + (float)KC * (a + slope * (turns > 1.0f ? turns - 1.0f : 0.0f));
+        const float est = t0 + a * (float)KC + (turns > 1.0f ? turns - 1.0f : 0.0f) * (each + slope * (float)KC);
         if (!best || est < us) { best = narrow_code(t, rh); us = est; }
     };
-#define X(T, RH, W, D, T0, A, S) consider(T, RH, T0, A, S);
+#define X(T, RH, W, D, T0, A, E, S) consider(T, RH, T0, A, E, S);
     BL_NARROW_FORMS(X)
 #undef X
     return best;
@@ -331,7 +333,7 @@ hipError_t launch_gemm_narrow(const GemmProblem* ps, int count, int64_t M, int c
         b.end[i] = i + 1 < count ? (int32_t)gx : INT32_MAX;
     }
     if (gx > INT32_MAX - kXcds) return hipErrorInvalidValue;
-#define X(T, RH, W, D, T0, A, S) if (code == narrow_code(T, RH)) return launch_narrow_form<T, RH, W, D>(b, (int)M, (int)gx, s);
+#define X(T, RH, W, D, T0, A, E, S) if (code == narrow_code(T, RH)) return launch_narrow_form<T, RH, W, D>(b, (int)M, (int)gx, s);
     BL_NARROW_FORMS(X)
 #undef X
     return hipErrorInvalidValue;

@@ -749,6 +749,40 @@ def test_gemm_parity_two_tile_widths(dev, ops, M, ns):
         _check_out(o, oracle.matmul_i32(q_ref, w), s, a_ref)
 
 
+@pytest.mark.parametrize("M,K,N", [(22, 64, 96640), (117, 64, 50304), (377, 64, 20032), (718, 64, 6976), (1771, 64, 12032), (805, 512, 6848),
+                                   (4718, 384, 1600), (16, 79, 344384)])
+def test_gemm_short_k_takes_tiles(dev, ops, M, K, N):
+    """Many workgroups and little K: the waves-along-K forms, whose workgroups cost the same however short K is, took up to 2.7
+    times the tile kernel's time there.  And the result, against the other kernel."""
+    from paper_2410_16144_amd import binding
+    g = torch.Generator(dev).manual_seed(M)
+    pw = ops.pack_ternary(torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev, generator=g), 0.02)
+    qa = ops.quant_act(torch.randn((M, K), device=dev, generator=g))
+    out = ops.gemm(pw, qa)
+    assert "gemm_kernel" in binding.bl_last_kernel(), binding.bl_last_kernel()
+    binding.bl_set_tuning("gemm_mb", 2032)
+    try:
+        assert torch.equal(out, ops.gemm(pw, qa))
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)
+
+
+@pytest.mark.parametrize("M,K,N", [(807, 5760, 6272), (1535, 3392, 3200), (1626, 5952, 3200)])
+def test_gemm_two_tile_widths_only_with_one_narrow_tile_per_unit(dev, ops, M, K, N):
+    """Narrow positions that are no multiple of 8 give one die more tiles than it has units: not the two-width kernel, also when
+    asked for."""
+    from paper_2410_16144_amd import binding
+    pw = ops.pack_ternary(torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev), 0.02)
+    qa = ops.quant_act(torch.randn((M, K), device=dev))
+    try:
+        for code in (0, 25):
+            binding.bl_set_tuning("gemm_mb", code)
+            ops.gemm(pw, qa)
+            assert "gemm_mixed_kernel" not in binding.bl_last_kernel()
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)
+
+
 def test_gemm_long_k(dev, ops):
     M, N, K = 70, 130, 65536 + 64     # 1025 K steps (odd: the K-split form pads one group), ragged M and N
     w, s, x = _problem(3200, M, K, N, p_zero=0.4, outl=0.01)
