@@ -22,9 +22,11 @@
 // 16-byte pieces of a row in permuted order: K for reads of one piece of many rows, V for reads of 64 bytes of four rows.
 //
 // Measured, append launch included, 32 heads of 128, kernel before -> this one (us): 512 tokens from position 0 43.0 -> 24.1,
-// behind 512 cached ones 62.1 -> 33.2, behind 1536 101 -> 51; 2048 tokens from 0 181 -> 115, behind 2048 363 -> 260; 64 tokens
-// behind 1984 97 -> 41.  A step (four chunks, 128 rows) takes 1.9 us = 4200 cycles, 2560 of them products (two waves per
-// SIMD, 40 products of 32 cycles each); the rest is the softmax's vector work that does not hide.
+// behind 512 cached ones 62.1 -> 33.2 (inputs from memory; 60.2 -> 29.7 where a pass finds them in the caches), behind 1536
+// 101 -> 51; 2048 tokens from 0 181 -> 115, behind 2048 363 -> 260; 64 tokens behind 1984 97 -> 41.  Of that the append is 6 to
+// 7.  By the slope over longer prompts a step (four chunks, 128 rows) takes 1.9 us, about 4200 cycles, for 2560 cycles of
+// products (two waves per SIMD, 40 products of 32 cycles each); the rest is the softmax's vector work that does not hide.  Counters
+// over the whole launch, 512 tokens behind 512: the matrix cores are busy in 35 % of the cycles of compute units with waves.
 #include "bl_internal.hpp"
 
 namespace bl {
@@ -59,10 +61,13 @@ __device__ __forceinline__ f32x16 mfma(const s16x8& a, const s16x8& b, const f32
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Place of a row's 16-byte piece c (of 2 * KS) in the LDS image; both are their own inverse.
+// Place of a row's 16-byte piece c (of 2 * KS) in the LDS image; both are their own inverse.  Keys: rows of a power of two of
+// bytes are permuted, rows of an odd number of 32 bytes (KS = 3, 5, 7) spread over the banks by themselves.  KS = 6 (head
+// size 96) is neither: rows of 192 bytes, the fourth next in the same bank; 47 % of the kernel's LDS cycles there are
+// conflicts (8 % with KS = 8).
 template <int KS>
 __device__ __forceinline__ int k_place(int row, int c) {
-    return (KS & (KS - 1)) == 0 ? c ^ (row & (2 * KS - 1)) : c;   // (rows of an odd number of 32 bytes spread by themselves)
+    return (KS & (KS - 1)) == 0 ? c ^ (row & (2 * KS - 1)) : c;
 }
 template <int KS>
 __device__ __forceinline__ int v_place(int row, int c) {

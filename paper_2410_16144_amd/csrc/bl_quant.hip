@@ -88,7 +88,7 @@ __device__ __forceinline__ void quant_row(const void* row, int K, int Kp, int8_t
     }
 }
 
-// The instance by the row's length.
+// The instance by the row's length: a branch inside the one kernel, all of whose rows run with the registers of the longest.
 template <bool BF16, bool VEC>
 __device__ __forceinline__ void quant_row(const void* row, int K, int Kp, int8_t* qrow, float* a_scale, int32_t* q_sum,
                                           float* s_max, int* s_sum) {

@@ -47,9 +47,11 @@ __device__ __forceinline__ float wave_sum_f(float v) {   // a fixed tree: the sa
 __device__ __forceinline__ float silu(float t) { return t / (1.0f + expf(-t)); }
 
 // silu of four values.  Where all of the wave's are below 80 in size nothing overflows or leaves the normal range, and the
-// exponential and the quotient need no special cases: exp(-t) = 2^n 2^((h - n) + l) with h + l = -t log2(e) to twice the
-// precision and n = h rounded, the quotient by the reciprocal and one correction step (errors against 64 bits as with expf and
-// the IEEE division, 14 instructions instead of about 26).  Any other wave takes silu().
+// exponential and the quotient need no special cases: exp(-t) = 2^n 2^((h - n) + l) by Cody and Waite's reduction in two
+// terms (h + l = -t log2(e) to twice the precision, n = h rounded), the quotient by the reciprocal and one correction step.
+// 14 instructions instead of about 26.  Against silu(): the same bits on 33 million normal values of deviation 0.1 to 15, 3 of
+// 8.4 million uniform ones in +-80 differ; the error against 64 bits is the same in all of these sets
+// (rms 2.9e-8 to 4.3e-8, at most 2.7 last places).  Any other wave takes silu().
 __device__ __forceinline__ void silu4(const float (&t)[4], float (&y)[4]) {
     const float size = fmaxf(fmaxf(fabsf(t[0]), fabsf(t[1])), fmaxf(fabsf(t[2]), fabsf(t[3])));
     if (__any(!(size < 80.0f))) {   // uniform
@@ -66,13 +68,6 @@ __device__ __forceinline__ void silu4(const float (&t)[4], float (&y)[4]) {
             y[j] = __builtin_fmaf(__builtin_fmaf(-d, q, t[j]), r, q);
         }
     }
-}
-
-// q = clip(round_half_even(v * inv), -128, 127)
-__device__ __forceinline__ int quant_one(float v, float inv) {
-    float r = rintf(v * inv);
-    r = fminf(fmaxf(r, -128.0f), 127.0f);
-    return (int)r;
 }
 
 // inv = 127/amax and scale = amax/127 (one IEEE division each); a row whose inv is not finite
@@ -188,10 +183,10 @@ __device__ __forceinline__ float absmax8(const float (&v)[8]) {
     return m;
 }
 
-// Four codes as the bytes of a word, quant_one(v[0]) lowest; their sum is added to `sum`.  The same codes as quant_one: the
-// product is clipped before it is rounded (the limits are whole numbers, so the order does not matter), and adding 1.5 * 2^23
-// rounds to nearest, ties to even, leaving the integer in the low bits.  4 vector instructions per code instead of 9 -- the
-// quantizer's second pass is bound by the vector ALU.
+// Four codes q = clip(round_half_even(v * inv), -128, 127) as the bytes of a word, v0's lowest; their sum is added to `sum`.
+// The product is clipped before it is rounded (the limits are whole numbers, so the order does not matter), and adding
+// 1.5 * 2^23 rounds to nearest, ties to even, leaving the integer in the low bits.  4 vector instructions per code instead of
+// the 9 of rounding, clipping and packing one by one -- the quantizer's second pass is bound by the vector ALU.
 __device__ __forceinline__ uint32_t quantize4(float v0, float v1, float v2, float v3, float inv, int& sum) {
     const auto code = [&](float v) { return __float_as_uint(__builtin_amdgcn_fmed3f(v * inv, -128.0f, 127.0f) + 12582912.0f); };
     const uint32_t low = __builtin_amdgcn_perm(code(v1), code(v0), 0x0c0c0400u);    // bytes 0 and 1
