@@ -26,7 +26,7 @@
 // 101 -> 51; 2048 tokens from 0 181 -> 115, behind 2048 363 -> 260; 64 tokens behind 1984 97 -> 41.  Of that the append is 6 to
 // 7.  By the slope over longer prompts a step (four chunks, 128 rows) takes 1.9 us, about 4200 cycles, for 2560 cycles of
 // products (two waves per SIMD, 40 products of 32 cycles each); the rest is the softmax's vector work that does not hide.  Counters
-// over the whole launch, 512 tokens behind 512: the matrix cores are busy in 35 % of the cycles of compute units with waves.
+// over the whole launch, 512 tokens behind 512: the matrix cores are busy in 34 % of the cycles of compute units with waves.
 #include "bl_internal.hpp"
 
 namespace bl {
