@@ -217,7 +217,7 @@ __device__ __forceinline__ void quantize_rows_to_lds(const DecodeProblem& p, int
         }
     } else {
 #pragma unroll
-        for (int m = 0; m < M; ++m) amax[m] = thread_absmax<BF16, false>(x + m * row_bytes, K, tid, kThreads);
+        for (int m = 0; m < M; ++m) amax[m] = element_absmax<BF16>(x + m * row_bytes, K, tid, kThreads);
     }
 #pragma unroll
     for (int m = 0; m < M; ++m) amax[m] = wave_max(amax[m]);
@@ -263,7 +263,7 @@ __device__ __forceinline__ void quantize_rows_to_lds(const DecodeProblem& p, int
     } else {
 #pragma unroll
         for (int m = 0; m < M; ++m)
-            sum[m] = thread_quantize<BF16, false>(x + m * row_bytes, K, Kp, inv[m], lds_q + m * Kp, tid, kThreads);
+            sum[m] = element_quantize<BF16>(x + m * row_bytes, K, Kp, inv[m], lds_q + m * Kp, tid, kThreads);
     }
 #pragma unroll
     for (int m = 0; m < M; ++m) sum[m] = wave_sum(sum[m]);

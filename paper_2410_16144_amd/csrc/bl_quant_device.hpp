@@ -187,10 +187,12 @@ __device__ __forceinline__ float absmax8(const float (&v)[8]) {
 // The product is clipped before it is rounded (the limits are whole numbers, so the order does not matter), and adding
 // 1.5 * 2^23 rounds to nearest, ties to even, leaving the integer in the low bits.  4 vector instructions per code instead of
 // the 9 of rounding, clipping and packing one by one -- the quantizer's second pass is bound by the vector ALU.
+__device__ __forceinline__ uint32_t code_bits(float v, float inv) {   // the code is the lowest byte
+    return __float_as_uint(__builtin_amdgcn_fmed3f(v * inv, -128.0f, 127.0f) + 12582912.0f);
+}
 __device__ __forceinline__ uint32_t quantize4(float v0, float v1, float v2, float v3, float inv, int& sum) {
-    const auto code = [&](float v) { return __float_as_uint(__builtin_amdgcn_fmed3f(v * inv, -128.0f, 127.0f) + 12582912.0f); };
-    const uint32_t low = __builtin_amdgcn_perm(code(v1), code(v0), 0x0c0c0400u);    // bytes 0 and 1
-    const uint32_t high = __builtin_amdgcn_perm(code(v3), code(v2), 0x04000c0cu);   // bytes 2 and 3
+    const uint32_t low = __builtin_amdgcn_perm(code_bits(v1, inv), code_bits(v0, inv), 0x0c0c0400u);    // bytes 0 and 1
+    const uint32_t high = __builtin_amdgcn_perm(code_bits(v3, inv), code_bits(v2, inv), 0x04000c0cu);   // bytes 2 and 3
     const uint32_t word = low | high;
     sum = __builtin_amdgcn_sdot4((int)word, 0x01010101, sum, false);
     return word;
@@ -245,6 +247,32 @@ __device__ __forceinline__ int thread_quantize(const void* row, int K, int Kp, f
     int sum = 0;
     for_thread_vectors<BF16, VEC>(row, K, tid, nthreads, [&](int k, const float (&v)[8]) { sum += quantize8(v, inv, qrow + k); });
     for (int k = (K + 7) / 8 * 8 + tid * 8; k < Kp; k += nthreads * 8) *reinterpret_cast<uint2*>(qrow + k) = make_uint2(0, 0);  // layout padding
+    return sum;
+}
+
+// The same two, element by element: short rows of bl_quant_act, and rows of the fused decode kernels that are no whole aligned
+// vectors -- there the vector form's code alone, executed or not, cost every such launch a tenth (1 token, K = 28: 3.6 -> 4.0 us;
+// 8 tokens, K = 2147: 12.0 -> 14.8).
+template <bool BF16>
+__device__ __forceinline__ float load1(const void* row, int k) {
+    if constexpr (BF16) return bf16_to_f32(static_cast<const uint16_t*>(row)[k]);
+    else return static_cast<const float*>(row)[k];
+}
+template <bool BF16>
+__device__ __forceinline__ float element_absmax(const void* row, int K, int tid, int nthreads) {
+    float amax = 0.0f;
+    for (int k = tid; k < K; k += nthreads) amax = fmaxf(amax, fabsf(load1<BF16>(row, k)));
+    return amax;
+}
+template <bool BF16>
+__device__ __forceinline__ int element_quantize(const void* row, int K, int Kp, float inv, int8_t* qrow, int tid, int nthreads) {
+    int sum = 0;
+    for (int k = tid; k < K; k += nthreads) {
+        const int8_t code = (int8_t)code_bits(load1<BF16>(row, k), inv);
+        sum += code;
+        qrow[k] = code;
+    }
+    for (int k = K + tid; k < Kp; k += nthreads) qrow[k] = 0;   // layout padding
     return sum;
 }
 

@@ -680,6 +680,27 @@ def test_quant_rows_at_any_address(dev, ops, K, bf16):
     assert np.array_equal(qa.a_scale.cpu().numpy(), a_scale) and np.array_equal(qa.q_sum.cpu().numpy(), q_sum)
 
 
+@pytest.mark.parametrize("K", [1, 255, 257, 511, 512, 513])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_quant_short_rows_by_element_and_beside_others(dev, ops, K, bf16):
+    """Rows that are no whole aligned vectors, on either side of what a launch takes element by element, alone and in one launch
+    with rows that do not go that way.  Bit for bit the oracle's, padding included."""
+    rows = {}
+    for name, (M, k, off) in {"short": (5, K, 3), "aligned": (3, 512, 0), "long": (2, 2050, 1)}.items():
+        x = synth.activations(synth.rng_for(6300 + K + k), M, k + off, outlier_frac=0.01)
+        bits = synth.to_bf16_bits(x)
+        t = _to_dev_bf16(bits, dev) if bf16 else torch.from_numpy(x).to(dev)
+        rows[name] = t[:, :k], oracle.quant_act(np.ascontiguousarray((bits if bf16 else x)[:, :k]))
+    for group in (["short"], ["short", "short"], ["aligned", "short"], ["short", "long"], ["short", "aligned", "long"]):
+        g = ops.QuantGroup([rows[n][0] for n in group])
+        for o in g.outs:
+            o.q.fill_(77)
+        for n, qa in zip(group, g.launch()):
+            q, a_scale, q_sum = rows[n][1]
+            assert np.array_equal(qa.q.cpu().numpy()[:, :qa.K], q) and not qa.q[:, qa.K:].any()
+            assert np.array_equal(qa.a_scale.cpu().numpy(), a_scale) and np.array_equal(qa.q_sum.cpu().numpy(), q_sum)
+
+
 # ------------------------------------------------------------------ prefill product
 
 @pytest.mark.parametrize("M,N,K", [(1, 64, 64), (7, 70, 100), (33, 200, 1000), (128, 256, 512), (130, 320, 1536),
