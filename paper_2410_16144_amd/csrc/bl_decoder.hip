@@ -557,8 +557,10 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 // by the chain of memory round trips in short ones: 500 positions 10.1 -> 8.4, 2000 18.4 -> 14.0.
 // MAXD: the largest head size of this instance (128 or 256) -- registers and LDS are sized by it, and the smaller one
 // lets twice as many workgroups share a compute unit.
+// Waves per SIMD: 5 (head sizes up to 128), 4 or, with 8-byte vectors, 3 (beyond), held for the compiler -- with 133 instead of 128
+// registers <8, 256> ran three and took 21.9 instead of 18.3 us for 39 heads of 160 at 1270 positions.
 template <int W, int MAXD>
-__global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const AttnArgs p) {
+__global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) void attn_chunk_kernel(const AttnArgs p) {
     typedef typename CacheVec<W>::type vec_t;
     constexpr int kMaxLanesPerRow = MAXD / W;
     constexpr int kVecs = kChunk * kMaxLanesPerRow / kAttnThreads;            // requests per thread at most
@@ -645,6 +647,8 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const AttnArgs
     float m_g = -INFINITY, l_g = 0.0f, o_g[W];
 #pragma unroll
     for (int x = 0; x < W; ++x) o_g[x] = 0.0f;
+    const int wave_row = __builtin_amdgcn_readfirstlane(wave) * (kWave / L);   // the wave's first row of a step
+    static_assert(L <= kWave, "a row's lanes are one wave's");
     for (int c = chunk; c <= last_chunk; c += groups) {
         const int j0 = c * kChunk;
         const int rows = min(kChunk, pos + 1 - j0);
@@ -678,6 +682,9 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const AttnArgs
         m_g = m_new;
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
+            // the first tokens of a context: the wave has no row in this step (uniform; 8 heads of 128 at 7 positions 5.5 -> 5.2 us, for
+            // 0.3 us at 32 heads and 8000 positions, 29.1 -> 29.4)
+            if (i > 0 && wave_row + i * kRowsPerStep >= rows) continue;
             const int row = grp + i * kRowsPerStep;
             const bool own = holds_token && j0 + row == pos;
             const float w = expf(score[i] - base);

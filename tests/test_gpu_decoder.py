@@ -364,6 +364,28 @@ def _merges_of_every_size(dev, mods, n_heads, head_dim, chunks):
         B.bl_set_tuning("attn_groups", 0)
 
 
+@pytest.mark.parametrize("n_heads,head_dim", [(2, 64), (1, 200), (2, 36), (3, 4)])
+def test_attn_decode_every_position_of_a_short_cache(dev, mods, n_heads, head_dim):
+    """One chunk per workgroup, waves and steps without a row, then the first two-chunk positions; token after token, against the
+    fp64 softmax."""
+    B, dec, ops = mods
+    hidden, max_pos = n_heads * head_dim, 140
+    r = _rng(53900 + hidden)
+    table = dec.rope_table(head_dim, max_pos, dev)
+    lin = [torch.empty((1, hidden), device=dev) for _ in range(3)]
+    pos_t = torch.zeros(1, dtype=torch.int32, device=dev)
+    att = dec.Attention(n_heads, head_dim, max_pos, *lin, pos_t, table)
+    for pos in range(max_pos):
+        vals = [(3.0 * r.standard_normal(hidden)).astype(np.float32) for _ in range(3)]
+        for t, v in zip(lin, vals):
+            t.copy_(_t(v[None], dev))
+        pos_t.fill_(pos)
+        out = att.launch().cpu().numpy()[0]
+        kc64, vc64 = (c[:pos + 1].float().cpu().numpy().astype(np.float64) for c in (att.k_cache, att.v_cache))
+        want = D.attention_decode(D.rope(vals[0], pos, n_heads), kc64, vc64, n_heads)
+        assert np.abs(out - want).max() <= 2e-5 * max(1.0, np.abs(want).max()), pos
+
+
 @pytest.mark.parametrize("pattern", [0x7FC0, 0x7F80, 0xFF80])
 @pytest.mark.parametrize("n_heads,head_dim,groups", [(3, 64, 0), (2, 128, 3), (1, 256, 2)])
 def test_attn_decode_cache_rows_beyond_the_token_may_hold_anything(dev, mods, pattern, n_heads, head_dim, groups):
