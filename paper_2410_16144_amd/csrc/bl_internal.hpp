@@ -25,6 +25,13 @@ __device__ __forceinline__ v4i expand_codes(uint32_t word) {
     return r;
 }
 
+// A wave-uniform address that the compiler can tell for one: requests written as assembly take it in scalar registers.
+__device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* p) {
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const uint8_t*>((uint64_t)hi << 32 | lo);
+}
+
 // One prefill product as the kernel sees it (all device pointers).
 struct GemmProblem {
     const uint4*   packed;

@@ -1038,3 +1038,33 @@ def test_prompt_then_tokens(dev, mods):
         want = D.rmsnorm(h, g_final, 1e-5)
         got = ya[t].cpu().numpy().astype(np.float64)
         assert np.linalg.norm(got - want) <= 5e-2 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("n_heads,head_dim,pos0,M", [(3, 64, 351, 33), (3, 64, 352, 33), (2, 128, 990, 33), (1, 72, 500, 1), (2, 96, 0, 400),
+                                                     (40, 16, 0, 225), (40, 24, 0, 257), (60, 16, 10, 300), (33, 128, 31, 250)])
+def test_attn_prefill_waves_and_block_order(dev, mods, n_heads, head_dim, pos0, M):
+    """The matrix-core attention around its rules: four and eight waves per workgroup (384 positions and one more; few and many
+    workgroups), blocks of 32 tokens in falling order and in pairs (even and odd numbers of blocks), last blocks of one token.
+    Every token against the fp64 softmax over the cache as stored."""
+    B, dec, ops = mods
+    hidden, max_pos = n_heads * head_dim, pos0 + M
+    r = _rng(96000 + hidden + M)
+    table = dec.rope_table(head_dim, max_pos, dev)
+    g = torch.Generator(device=dev).manual_seed(96000 + hidden)
+    k_cache, v_cache = (torch.randn((max_pos, hidden), device=dev, generator=g).to(torch.bfloat16) for _ in range(2))
+    lin = [3.0 * r.standard_normal((M, hidden)).astype(np.float32) for _ in range(3)]
+    lin_t = [_t(v, dev) for v in lin]
+    out = torch.full((M, hidden), float("nan"), device=dev)
+    scratch = torch.zeros(B.bl_attn_prefill_scratch_bytes(n_heads, head_dim, pos0, M), dtype=torch.uint8, device=dev)
+    B.bl_attn_prefill(lin_t[0].data_ptr(), lin_t[1].data_ptr(), lin_t[2].data_ptr(), table.data_ptr(), k_cache.data_ptr(),
+                      v_cache.data_ptr(), out.data_ptr(), scratch.data_ptr(), n_heads, head_dim, max_pos, pos0, M,
+                      torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    q = torch.from_numpy(np.stack([D.rope(lin[0][m], pos0 + m, n_heads) for m in range(M)])).view(M, n_heads, head_dim)
+    k, v = (c.cpu().double().view(max_pos, n_heads, head_dim) for c in (k_cache, v_cache))
+    seen = torch.arange(max_pos)[None] <= torch.arange(pos0, max_pos)[:, None]
+    for h in range(n_heads):
+        s = (q[:, h].double() @ k[:, h].t()) / head_dim ** 0.5
+        want = torch.softmax(s.masked_fill(~seen, -float("inf")), 1) @ v[:, h]
+        got = out[:, h * head_dim:(h + 1) * head_dim].cpu().double()
+        assert (got - want).abs().max() <= PREFILL_BLOCK_TOL * max(1.0, float(want.abs().max())), h
