@@ -11,8 +11,9 @@
 // matrix operands need no lane exchange: in v_mfma_i32_32x32x32_i8 lanes 0-31 carry 16 contraction indices and lanes
 // 32-63 the other 16, and here lanes 0-31 read word j of their row's 16 bytes in tile 2i, lanes 32-63 word j of tile 2i+1.
 //   weights:     LDS image as loaded (lane-linear); operand read = 16 bytes per lane, two contiguous 512-byte runs;
-//   activations: a token's 128 bytes as eight 16-byte chunks, chunk c at position c ^ (row % 8): eight consecutive
-//                lanes read eight different 16-byte columns, free of bank conflicts.
+//   activations: a token's 128 bytes as eight 16-byte chunks, chunk c at position c ^ (row % 8) ^ (row / 8 % 2): a read of
+//                one chunk of many rows takes sixteen lanes per cycle (256 bytes), which meet sixteen different columns.
+//                (With c ^ (row % 8) alone rows r and r + 8 met in one column: every read took twice its cycles.)
 // The operands of a step are all read into registers before its products start, so the step's piece of LDS is free for
 // the next request while they run.
 //
@@ -102,39 +103,38 @@ __global__ __launch_bounds__(64 * W) void gemm_narrow_kernel(const NarrowBatch b
     const int second = lane >> 5;
     const uint32_t w_off = RH >= 2 ? (uint32_t)lane * 16 : (uint32_t)(second * kTileBytes + (half0 * 32 + (lane & 31)) * 16);
     uint32_t a_off[T / 8];
+    constexpr int kBias = 4096;
     const int arow = lane >> 3, chunk = (lane & 7) ^ arow;  // 8 rows per request, position lane % 8 of its row
 #pragma unroll
-    for (int s = 0; s < T / 8; ++s) a_off[s] = (uint32_t)min(m0 + 8 * s + arow, M - 1) * qs + chunk * 16;
+    for (int s = 0; s < T / 8; ++s)   // (the last two terms: a piece's place behind one M0, kept positive)
+        a_off[s] = (uint32_t)min(m0 + 8 * s + arow, M - 1) * qs + (chunk ^ (s & 1)) * 16 + kBias - (RH + s) % 4 * 1024;
     const uint32_t a_back = chunk >= 4 ? kTileK : 0;
 
     auto request = [&](int i) {
         const int pair = wave + i * W;
         const bool last = odd && pair == pairs - 1;         // uniform
-        uint32_t dst = ring0 + (uint32_t)((D == 1 ? 0 : i % D) * F::kStage);
         const uint8_t* wsrc = wbase + (int64_t)pair * (2 * kTileBytes);
-        const uint8_t* qsrc = qbase + (int64_t)pair * (2 * kTileK);
-        const auto put = [&](uint32_t off, const uint8_t* src) {
-            // M0 carries the LDS address of this instruction and of nothing else in this kernel
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(src)
-                         : "memory", "m0");
-#pragma clang diagnostic pop
-            dst += 1024;
-        };
-        if constexpr (RH >= 2) {
-#pragma unroll
-            for (int blk = 0; blk < RH / 2; ++blk) {
-                const uint8_t* src = blk ? wsrc + block2 : wsrc;
-                put(w_off, src);
-                put(w_off, last ? src : src + kTileBytes);  // a tile that is not there: any valid one, its codes are dropped
-            }
-        } else {
-            put(last && second ? w_off - kTileBytes : w_off, wsrc);
-        }
+        const uint8_t* qsrc = qbase + (int64_t)pair * (2 * kTileK) - kBias;
         const uint32_t back = last ? a_back : 0;
+        uint32_t off[F::Ring::kPerStep];
+        const uint8_t* src[F::Ring::kPerStep];
 #pragma unroll
-        for (int s = 0; s < T / 8; ++s) put(a_off[s] - back, qsrc);
+        for (int r = 0; r < RH; ++r) {
+            if constexpr (RH >= 2) {   // even pieces: the pair's first tile; odd ones: its second
+                off[r] = w_off;
+                src[r] = (r >= 2 ? wsrc + block2 : wsrc) - r / 2 * 2048;
+                if (r & 1) src[r] = last ? src[r] - kTileBytes : src[r];   // a tile that is not there: any valid one, its codes are dropped
+            } else {
+                off[r] = last && second ? w_off - kTileBytes : w_off;
+                src[r] = wsrc;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < T / 8; ++s) {
+            off[RH + s] = a_off[s] - back;
+            src[RH + s] = qsrc;
+        }
+        load_to_lds(ring0 + (uint32_t)((D == 1 ? 0 : i % D) * F::kStage), off, src);
     };
 
     v16i c[MB][RH];
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(64 * W) void gemm_narrow_kernel(const NarrowBatch b
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                a[mb][j] = *reinterpret_cast<const v4i*>(stage + RH * 1024 + row_of(mb) * 128 + ((4 * second + j) ^ (l32 & 7)) * 16);
+                a[mb][j] = *reinterpret_cast<const v4i*>(stage + RH * 1024 + row_of(mb) * 128 + ((4 * second + j) ^ (l32 & 7) ^ (l32 >> 3 & 1)) * 16);
         // every operand has left the stage before it is requested anew
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (i + D < steps) request(i + D);
@@ -268,7 +268,7 @@ hipError_t launch_narrow_form(const NarrowBatch& b, int M, int gx, hipStream_t s
 }
 
 // The forms that are built, X(T, RH, W, D, t0, a, e, s), with the line that their measured times follow (us; relative least
-// squares over the 9176 launches described at choose_kernel in bl_gemm.hip, weights cold; eight in ten points within 11 %):
+// squares over the 11065 launches described at choose_kernel in bl_gemm.hip, weights cold; eight in ten points within 9 %):
 //     t = t0 + a KC + (X - 1) (e + s KC),   X = max(1, (x + ceil x) / 2),   x = workgroups / compute units
 // (KC = packed tiles along K; e: what a workgroup costs however short K is -- with it left out, 718 x 64 -> 6976 took 22.9 us here
 // where the tile kernel takes 8.5).  The workgroups are counted with the padding of the strips to a multiple of 8: a die
@@ -278,12 +278,12 @@ hipError_t launch_narrow_form(const NarrowBatch& b, int M, int gx, hipStream_t s
 // 37.7 -> 15.8 at 256, 38.4 -> 25.1 at 512.  Also tried: four or sixteen waves along K, 48-token blocks, three or four steps in
 // flight, and weights straight into registers -- none ahead of the best of these six by more than 5 % anywhere.
 #define BL_NARROW_FORMS(X)                           \
-    X(16, 1, 8, 2, 3.22f, 0.0199f, 0.514f, 0.0182f)  \
-    X(16, 2, 8, 2, 3.43f, 0.0298f, 0.897f, 0.0277f)  \
-    X(32, 1, 8, 2, 3.39f, 0.0244f, 0.879f, 0.0255f)  \
-    X(32, 2, 8, 1, 3.71f, 0.0287f, 1.103f, 0.0359f)  \
-    X(32, 4, 8, 1, 4.76f, 0.0485f, 1.915f, 0.0570f)  \
-    X(64, 4, 8, 1, 6.83f, 0.0780f, 6.112f, 0.1156f)
+    X(16, 1, 8, 2, 3.09f, 0.0203f, 0.506f, 0.0171f)  \
+    X(16, 2, 8, 2, 3.30f, 0.0306f, 0.900f, 0.0281f)  \
+    X(32, 1, 8, 2, 3.27f, 0.0244f, 0.868f, 0.0238f)  \
+    X(32, 2, 8, 1, 3.57f, 0.0296f, 1.128f, 0.0336f)  \
+    X(32, 4, 8, 1, 4.69f, 0.0474f, 1.925f, 0.0576f)  \
+    X(64, 4, 8, 1, 6.84f, 0.0753f, 5.966f, 0.1181f)
 
 // Strips of one product: 32*RH rows of W each.
 int64_t strips_of(const GemmProblem& p, int rh) {

@@ -32,6 +32,36 @@ __device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* p) {
     return reinterpret_cast<const uint8_t*>((uint64_t)hi << 32 | lo);
 }
 
+// N pieces of 1 KiB from global memory straight into LDS (global_load_lds_dwordx4: lane l's 16 bytes at the piece's base + 16 l), one
+// behind the other from LDS address dst on.  Piece r is read at src[r] + off[r] + 1024 * (r % 4): one M0 (the LDS address)
+// serves four pieces, and the instruction's immediate offset counts on both sides.  Assembly on purpose: a load into LDS that the
+// compiler can see is answered with a wait for everything outstanding; unseen, the pieces count in vmcnt, in order.  M0 is
+// used by these instructions and by nothing else in the kernels.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <int N>
+__device__ __forceinline__ void load_to_lds(uint32_t dst, const uint32_t (&off)[N], const uint8_t* const (&src)[N]) {
+#pragma unroll
+    for (int r = 0; r < N; r += 4, dst += 4096) {
+        if (N - r >= 4)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %6 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %3, %7 offset:2048\n\tglobal_load_lds_dwordx4 %4, %8 offset:3072"
+                         ::"s"(dst), "v"(off[r]), "v"(off[(r + 1) % N]), "v"(off[(r + 2) % N]), "v"(off[(r + 3) % N]), "s"(src[r]),
+                         "s"(src[(r + 1) % N]), "s"(src[(r + 2) % N]), "s"(src[(r + 3) % N]) : "memory", "m0");
+        else if (N - r == 3)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %4\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %3, %6 offset:2048"
+                         ::"s"(dst), "v"(off[r]), "v"(off[(r + 1) % N]), "v"(off[(r + 2) % N]), "s"(src[r]), "s"(src[(r + 1) % N]),
+                         "s"(src[(r + 2) % N]) : "memory", "m0");
+        else if (N - r == 2)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %4 offset:1024"
+                         ::"s"(dst), "v"(off[r]), "v"(off[(r + 1) % N]), "s"(src[r]), "s"(src[(r + 1) % N]) : "memory", "m0");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off[r]), "s"(src[r]) : "memory", "m0");
+    }
+}
+#pragma clang diagnostic pop
+
 // One prefill product as the kernel sees it (all device pointers).
 struct GemmProblem {
     const uint4*   packed;
