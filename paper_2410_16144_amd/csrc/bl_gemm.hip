@@ -380,14 +380,6 @@ __global__ __launch_bounds__(64 * WN * WK, WN * WK == 4 ? 2 : 1) void gemm_batch
 // Two tile widths in one launch, for launches of between one and one and a half 64 x 256 tiles per compute unit: there some
 // units got two tiles and the others one, and the launch took as long as two.  Here every unit gets ONE 64 x 256 tile, and the
 // rest of the rows are cut into 64 x 128 tiles (the same loop, 32 rows per wave), at most one per unit.
-struct GemmMixed {
-    GemmProblem p[kMaxGemmBatch];
-    int32_t     end[kMaxGemmBatch];          // first 256-row position behind product i (INT32_MAX behind the last one in use)
-    int32_t     small_end[kMaxGemmBatch];    // first 128-row position behind product i
-    int32_t     small_first[kMaxGemmBatch];  // product i's first 128-row position in its own rows
-    int32_t     gx, wgs, small_gx;           // 256-row positions and their workgroups; 128-row positions
-};
-
 __global__ __launch_bounds__(256, 2) void gemm_mixed_kernel(const GemmMixed b, const int M) {
     int tile_x, tile_y, item = 0, first = 0;
     if ((int)blockIdx.x < b.wgs) {   // uniform
@@ -409,7 +401,8 @@ __global__ __launch_bounds__(256, 2) void gemm_mixed_kernel(const GemmMixed b, c
 }
 
 int g_force_mb = 0;
-constexpr int kCodeMixed = 25;   // bl_set_tuning "gemm_mb": the two-width kernel wherever it applies
+constexpr int kCodeMixed = 25;          // bl_set_tuning "gemm_mb": the two-width kernel wherever it applies
+constexpr int kCodePairMixed = 40025;   // ... and that of bl_gemm_pair.hip
 
 // One tile form: wave tile (32*MB) tokens x (32*H) weight rows, WN waves along N and WK along K.
 struct TileForm { int mb, h, wk, wn; };
@@ -478,64 +471,40 @@ bool plan_mixed(const GemmProblem* ps, int count, int64_t M, GemmMixed& b) {
     return (small + kXcds - 1) / kXcds * kXcds * tiles_m <= cus;
 }
 
-// What a launch takes: the one-width form of choose_tile, the two-width kernel or a form of bl_gemm_narrow.hip, by estimated
-// time.  (choose_tile goes by workgroup counts; the other one-width forms are not weighed against it here.)  The estimates
-// are lines through measured times (us, weights cold) of 9176 launches -- 9 to 6000 tokens, K 64 to 13000, N 64 to 60000, a
-// fifth of them no multiples of 64, sizes spread over their logarithms, every form on each -- over KC, the tiles along K, and x, the
-// workgroups per compute unit, counted with the padding of the N positions to a multiple of 8 (the dies' shares are whole
-// positions).  Eight in ten estimates lie within these limits of the measured time:
-//     32 x 256        4.5 + 0.141 KC up to x = 1;  + 0.211 KC + 2.04 (x - 1) up to 2;  + 0.111 KC x + 1.19 (x - 1) beyond   0.89 .. 1.11
-//     the K split     6.6 + 0.145 KC;  0.222 KC + 2.70 (x - 1);  0.114 KC x + 2.19 (x - 1)                                  0.84 .. 1.16
-//     64 x 256        5.6 + 0.185 KC;  0.304 KC + 4.13 (x - 1);  0.187 KC x + 2.58 (x - 1)                                  0.81 .. 1.18
-//     64 x 512        7.3 + 0.309 KC;  0.586 KC + 6.99 (x - 1);  0.361 KC x + 6.30 (x - 1)                                  0.74 .. 1.21
-//     two widths      8.3 + KC * (0.212 + 0.045 * share of the units with a narrow tile)                                     0.92 .. 1.06
-// The two-width kernel is taken if it is 4 % ahead, the waves-along-K forms if they are 6 % ahead.  Of the 9176 launches 28 are
-// then slower than their one-width form by more than 1.5 %, 15 by more than 5 %, the worst by 18 %; on average (geometric) they take 1/1.63 of
-// its time and are within 3.1 % of the best form.  (4096 -> 11008 at 384 tokens 26.7 -> 22.4 us, at 512 26.9 -> 25.0; 3200 -> 8640 at 512 22.1 -> 20.1; 8192^2 at
-// 576 45.2 -> 39.3; 5120^2 at 1024 32.9 -> 29.9.)
-struct GemmChoice { int narrow = 0; bool mixed = false; };
-
-float tile_estimate(const TileForm& f, int64_t M, int64_t rows, int KC, int cus) {
-    const int64_t gx = (rows + f.wn * f.h * 32 - 1) / (f.wn * f.h * 32), gy = (M + 32 * f.mb - 1) / (32 * f.mb);
-    const float x = (float)((gx + kXcds - 1) / kXcds * kXcds * gy) / (float)cus, k = (float)KC;
-    const auto line = [&](float t0, float one, float two, float each2, float per, float each) {
-        return t0 + (x <= 1.0f ? one * k : x <= 2.0f ? two * k + each2 * (x - 1.0f) : per * k * x + each * (x - 1.0f));
-    };
-    if (f.h == 4) return line(7.25f, 0.309f, 0.586f, 6.99f, 0.361f, 6.30f);
-    if (f.wk > 1) return line(6.61f, 0.145f, 0.222f, 2.70f, 0.114f, 2.19f);
-    if (f.mb == 1) return line(4.52f, 0.141f, 0.211f, 2.04f, 0.111f, 1.19f);
-    return line(5.56f, 0.185f, 0.304f, 4.13f, 0.187f, 2.58f);
-}
+// What a launch takes: a form of bl_gemm_pair.hip (its two-width launch among them) or of bl_gemm_narrow.hip, by estimated
+// time (gemm_pair_best, gemm_narrow_best: lines through measured times).  The tile kernels of this file take what those do not
+// (gemm_pair_takes: more than 2^23 weight rows or 2^25 columns) and the launches that bl_set_tuning sends to them: of 11065 launches measured on
+// every form -- 9 to 6000 tokens, K 64 to 13000, N 64 to 60000, sizes spread over their logarithms -- they are ahead of the best other
+// form by more than 2 % on 40, nearly all of them with 64 or 128 weight rows.
+struct GemmChoice { int narrow = 0, pair = 0; bool mixed = false, pair_mixed = false; };
 
 GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed& mixed) {
     GemmChoice c;
-    const bool narrow_ok = gemm_narrow_takes(ps, count, M);
-    if (g_force_mb && g_force_mb != kCodeMixed) {
-        if (g_force_mb >= 1000 && narrow_ok) c.narrow = g_force_mb;
+    const bool narrow_ok = gemm_narrow_takes(ps, count, M), pair_ok = gemm_pair_takes(ps, count);
+    if (g_force_mb && g_force_mb != kCodeMixed && g_force_mb != kCodePairMixed) {
+        if (gemm_pair_form_exists(g_force_mb)) c.pair = pair_ok ? g_force_mb : 0;
+        else if (gemm_narrow_form_exists(g_force_mb)) c.narrow = narrow_ok ? g_force_mb : 0;
         return c;
     }
     const bool mixed_ok = plan_mixed(ps, count, M, mixed);
-    if (g_force_mb == kCodeMixed && mixed_ok) {
-        c.mixed = true;
-        return c;
-    }
+    c.mixed = g_force_mb == kCodeMixed && mixed_ok;
+    c.pair_mixed = g_force_mb == kCodePairMixed && mixed_ok && pair_ok;
+    if (c.mixed || c.pair_mixed || !pair_ok) return c;
     const int found = compute_unit_count(), cus = found > 0 ? found : 256;
-    int64_t rows = 0;
-    int KC = 0;
-    for (int i = 0; i < count; ++i) {
-        rows += (int64_t)ps[i].row_blocks * kTileN;
-        KC = ps[i].KC > KC ? ps[i].KC : KC;
-    }
-    float best = tile_estimate(choose_tile(M, rows), M, rows, KC, cus);
+    float best = 0.0f;
+    c.pair = gemm_pair_best(ps, count, M, cus, best);
     if (mixed_ok) {
         const float share = (float)((mixed.small_gx + kXcds - 1) / kXcds * kXcds * ((M + 63) / 64)) / (float)cus;
-        const float us = 1.04f * (8.31f + (float)KC * (0.212f + 0.045f * share));
-        if (us < best) { best = us; c.mixed = true; }
+        int KC = 0;
+        for (int i = 0; i < count; ++i) KC = ps[i].KC > KC ? ps[i].KC : KC;
+        // the two-width launch: share = units with a narrow tile beside their wide one
+        const float us = 4.85f + 0.2226f * (float)KC + share * (0.93f + 0.0283f * (float)KC);
+        if (us < best) { best = us; c.pair_mixed = true; }
     }
     if (narrow_ok) {
         float us = 0.0f;
         const int code = gemm_narrow_best(ps, count, M, cus, us);
-        if (1.06f * us < best) { c.mixed = false; c.narrow = code; }
+        if (us < best) { c.pair_mixed = false; c.pair = 0; c.narrow = code; }
     }
     return c;
 }
@@ -562,7 +531,7 @@ void set_gemm_mb(int mb) { g_force_mb = mb; }
 
 bool gemm_form_exists(int code) {
     if (code == kCodeMixed) return true;
-    if (code >= 1000) return gemm_narrow_form_exists(code);
+    if (code >= 1000) return code == kCodePairMixed || gemm_pair_form_exists(code) || gemm_narrow_form_exists(code);
     const TileForm f = form_of_code(code);
 #define X(MB, H, WK, WN) if (f.mb == MB && f.h == H && f.wk == WK && f.wn == WN) return true;
     BL_GEMM_FORMS(X)
@@ -584,6 +553,8 @@ hipError_t launch_gemm(const GemmProblem& p, int64_t M, hipStream_t s) {
     GemmMixed mixed;
     const GemmChoice choice = choose_kernel(&p, 1, M, mixed);
     if (choice.mixed) return launch_mixed(mixed, M, s);
+    if (choice.pair_mixed) return launch_gemm_pair_mixed(mixed, M, s);
+    if (choice.pair) return launch_gemm_pair(&p, 1, M, choice.pair, s);
     if (choice.narrow) return launch_gemm_narrow(&p, 1, M, choice.narrow, s);
     const int64_t rows = (int64_t)p.row_blocks * kTileN;
     const TileForm f = choose_tile(M, rows);
@@ -607,6 +578,8 @@ hipError_t launch_gemm_batch(const GemmProblem* ps, int count, int64_t M, hipStr
     GemmMixed mixed;
     const GemmChoice choice = choose_kernel(ps, count, M, mixed);
     if (choice.mixed) return launch_mixed(mixed, M, s);
+    if (choice.pair_mixed) return launch_gemm_pair_mixed(mixed, M, s);
+    if (choice.pair) return launch_gemm_pair(ps, count, M, choice.pair, s);
     if (choice.narrow) return launch_gemm_narrow(ps, count, M, choice.narrow, s);
     int64_t rows = 0;
     for (int i = 0; i < count; ++i) rows += (int64_t)ps[i].row_blocks * kTileN;

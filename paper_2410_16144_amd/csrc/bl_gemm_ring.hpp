@@ -55,6 +55,23 @@ struct NarrowRing {
     static_assert(kYounger < 64, "fits the wait counter");
 };
 
+// The tile kernel with paired packed tiles (bl_gemm_pair.hip): weights and activations both global -> LDS, kPer requests per
+// thread and step, all assembly.  Step i requests pair i + kLead into stage (i + kLead) % S; the barrier that ends it publishes
+// pair i + 2, behind which the pairs i + 3 .. i + kLead have been requested.
+template <int MB, int H, int WN, int S>
+struct PairRing {
+    static constexpr int kA = 4 * MB / WN;             // 1 KiB each: a wave's share of 32 MB tokens x 128 k
+    static constexpr int kPer = H + kA;                // ... and its weights, 32 H rows x 128 k
+    static constexpr int kLead = S - 1;                // a stage is requested anew in the step behind the one that read it last
+    static constexpr int kYounger = (kLead - 2) * kPer;
+    static_assert(kA >= 1 && kA <= 4 && kLead >= 2 && kYounger < 64, "every wave brings tokens; fits the wait counter");
+};
+
+// The forms that are built, X(MB, H, WN, WK, S): wave tile of 32 MB tokens x 32 H weight rows, WN waves along N, WK along K, S
+// stages.
+#define BL_PAIR_FORMS(X) \
+    X(2, 2, 4, 1, 4) X(2, 1, 4, 1, 4) X(2, 1, 4, 1, 6) X(2, 1, 4, 2, 4) X(1, 2, 4, 1, 4) X(2, 4, 4, 1, 3) X(2, 3, 4, 1, 3)
+
 // The matrix-core decode kernel's one-off copy of the quantized activations into LDS (bl_gemv.hip, QMODE 1): the copy's
 // global -> LDS loads are issued first, then one batch of U weight tiles; the wait that precedes the barrier allows
 // exactly those U loads to be outstanding.

@@ -186,7 +186,8 @@ struct LdsCeiling {
         int dev = -1;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
         if (dev >= 0 && ((done >> dev) & 1)) return hipSuccess;
-        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDecodeLds);
+        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 lds_bytes > kMaxDecodeLds ? lds_bytes : kMaxDecodeLds);
         if (e == hipSuccess && dev >= 0) done |= 1ull << dev;
         return e;
     }
@@ -212,6 +213,20 @@ bool gemm_narrow_form_exists(int code);
 bool gemm_narrow_takes(const GemmProblem* ps, int count, int64_t M);
 int gemm_narrow_best(const GemmProblem* ps, int count, int64_t M, int cus, float& us);   // the form with the smallest estimate
 hipError_t launch_gemm_narrow(const GemmProblem* ps, int count, int64_t M, int code, hipStream_t s);
+// Two tile widths in one launch (planned by plan_mixed of bl_gemm.hip).
+struct GemmMixed {
+    GemmProblem p[kMaxGemmBatch];
+    int32_t     end[kMaxGemmBatch];          // first 256-row position behind product i (INT32_MAX behind the last one in use)
+    int32_t     small_end[kMaxGemmBatch];    // first 128-row position behind product i
+    int32_t     small_first[kMaxGemmBatch];  // product i's first 128-row position in its own rows
+    int32_t     gx, wgs, small_gx;           // 256-row positions and their workgroups; 128-row positions
+};
+// bl_gemm with paired packed tiles (bl_gemm_pair.hip); a form's code is 10000 * stages + 100 * (waves along K - 1) + 10 * MB + H
+bool gemm_pair_form_exists(int code);
+bool gemm_pair_takes(const GemmProblem* ps, int count);
+int gemm_pair_best(const GemmProblem* ps, int count, int64_t M, int cus, float& us);   // the form with the smallest estimate
+hipError_t launch_gemm_pair(const GemmProblem* ps, int count, int64_t M, int code, hipStream_t s);
+hipError_t launch_gemm_pair_mixed(const GemmMixed& b, int64_t M, hipStream_t s);
 hipError_t launch_tl2_pack(const int8_t* w, int64_t N, int64_t K, int64_t Np, int64_t Kp, uint32_t* packed,
                            int32_t* bad_count, hipStream_t s);
 hipError_t launch_tl2_unpack(const uint32_t* packed, int64_t N, int64_t K, int64_t Np, int64_t Kp, int8_t* w,

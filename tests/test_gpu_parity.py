@@ -900,3 +900,40 @@ def test_gemm_first_steps_under_load(dev, ops, tile, K):
     finally:
         binding.bl_set_tuning("gemm_mb", 0)
 
+
+@pytest.mark.parametrize("form", [40022, 40021, 60021, 40121, 40012, 30024, 30023, 40025])
+def test_gemm_parity_every_paired_form(dev, ops, form):
+    """The tile kernel on pairs of packed tiles (40025: its two widths in one launch) at the edges of its tiles and of its pipeline:
+    one tile of K (half a pair), odd tile counts, fewer pairs than stages, as many, and several trips of the main loop; tokens and
+    rows on either side of a workgroup's; several products of different N in one launch.  Integer sums exact, nothing written
+    behind the output."""
+    from paper_2410_16144_amd import binding
+    mixed = form == 40025
+    shapes = (((512, 11008, 64), (500, 8640, 64 * 9)) if mixed else
+              ((1, 1, 64), (31, 33, 100), (32, 64, 128), (64, 128, 64 * 3), (65, 129, 64 * 7), (33, 257, 64 * 8), (63, 385, 64 * 9),
+               (64, 513, 64 * 14), (130, 96, 64 * 22), (70, 600, 64 * 31), (129, 300, 1000)))
+    for M, N, K in shapes:
+        w, s, x = _problem(M * 11 + N + K + form, M, K, N, p_zero=0.4, outl=0.01)
+        binding.bl_set_tuning("gemm_mb", form)
+        try:
+            _assert_product(ops, dev, "gemm", w, s, x)
+            assert "pair_gemm_kernel" in binding.bl_last_kernel()
+            pw = ops.pack_ternary(torch.from_numpy(w).to(dev), float(s))
+            qa = ops.quant_act(_to_dev_bf16(x, dev) if x.dtype == np.uint16 else torch.from_numpy(x).to(dev))
+            behind = torch.full((M + 3, N), -7.0, device=dev)
+            ops.gemm(pw, qa, out=behind[:M])
+            assert bool((behind[M:] == -7.0).all())
+        finally:
+            binding.bl_set_tuning("gemm_mb", 0)
+    M, K, ns = (449, 64 * 11, (10000, 70, 33)) if mixed else (50, 64 * 21, (70, 33, 256, 200))
+    x = _problem(5300 + form, M, K, 64)[2]
+    qa = ops.quant_act(_to_dev_bf16(x, dev) if x.dtype == np.uint16 else torch.from_numpy(x).to(dev))
+    pws = [ops.pack_ternary(torch.from_numpy(_problem(5400 + n, 1, K, n)[0]).to(dev), 0.01 * (i + 1)) for i, n in enumerate(ns)]
+    try:
+        binding.bl_set_tuning("gemm_mb", form)
+        together = ops.gemm_batch(pws, qa)
+        assert "pair_gemm_kernel" in binding.bl_last_kernel()
+        binding.bl_set_tuning("gemm_mb", 22)
+        assert all(torch.equal(o, ops.gemm(pw, qa)) for o, pw in zip(together, pws))
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)

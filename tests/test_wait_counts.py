@@ -176,3 +176,38 @@ def test_compiled_decode_copy_waits_for_the_copy_only(tmp_path):
         # the copy's requests, then exactly the 6 weight tiles of the first batch, and a wait that lets those 6 fly
         assert first[1] >= 1 and first[2] == 6 and first[0] == 6, (name, first)
     assert seen == 16
+
+
+def test_paired_kernels_waits_hold_and_one_operation_less_does_not(tmp_path):
+    """csrc/bl_gemm_pair.hip: the issue order of every form replayed with the constants of the kernel's header (see
+    tests/ring_model/pair_check.cpp), and with every wait one operation too generous, which must fail."""
+    exe = str(tmp_path / "pair_check")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC,
+                           os.path.join(ROOT, "tests", "ring_model", "pair_check.cpp"), "-o", exe])
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "0 failing cases" in r.stdout, r.stdout[-2000:]
+    assert subprocess.run([exe, "--slack"], capture_output=True, timeout=120).returncode == 1
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_compiled_paired_kernels_issue_what_the_model_assumes(tmp_path):
+    """Between two barriers of the main loop: one step's requests, the wait that the header names, no other vector memory
+    operation."""
+    fns = _functions(_compile_to_asm(tmp_path, "bl_gemm_pair.hip"))
+    seen = 0
+    for name, lines in fns.items():
+        m = re.search(r"pair_gemm_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d+)E", name)
+        if not m:
+            continue
+        seen += 1
+        mb, h, wn, wk, s = (int(x) for x in m.groups())
+        per = h + 4 * mb // wn
+        younger = (s - 3) * per
+        # a main loop's steps: one wait of the header's count (two barriers of a tail's step are apart by a second wait, for 0)
+        steps = [b for b in _barriers(lines) if b[1] == per and b[0] == younger and b[2] == 0]
+        assert len(steps) >= s, (name, _barriers(lines))
+        # what the compiler sees is loaded before the first request (the scales) and nothing after it
+        first = next(i for i, l in enumerate(lines) if l.startswith("global_load_lds_dwordx4"))
+        for l in lines[first:]:
+            assert not re.match(r"(scratch_|flat_|global_store|global_atomic|buffer_load|global_load_dword(x2|x4)?\b)", l), (name, l)
+    assert seen == 7
