@@ -460,6 +460,38 @@ __device__ __forceinline__ void unpack_bf16(const typename CacheVec<W>::type& u,
     }
 }
 
+// Sum or maximum over groups of L neighbouring lanes (16, 32 or 64), on the vector ALU's lane moves instead of a trip through LDS per
+// step (ds_bpermute): lane ^ 1 and ^ 2 by quad permutation, the other half of eight and of sixteen lanes by their mirror images -- whose
+// lanes all hold their quad's or half's result by then -- and the 16- and 32-lane blocks by the swaps of two registers.  Every step
+// adds the two halves' figures (in either order the same bits), so every lane gets the same result.
+#define BL_LANES(v, ctrl) __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), (ctrl), 0xf, 0xf, false))
+template <int OFF, typename Op>
+__device__ __forceinline__ float over_blocks(float v, Op op) {   // lane and lane ^ OFF
+    static_assert(OFF == 16 || OFF == 32, "the two swaps");
+    const uint32_t u = __float_as_uint(v);
+    if constexpr (OFF == 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    } else {
+        const auto s = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    }
+}
+template <int L, typename Op>
+__device__ __forceinline__ float over_lanes(float v, Op op) {
+    static_assert(L == 16 || L == 32 || L == 64, "whole rows of sixteen lanes");
+    v = op(v, BL_LANES(v, 0xb1));    // quad_perm [1, 0, 3, 2]
+    v = op(v, BL_LANES(v, 0x4e));    // quad_perm [2, 3, 0, 1]
+    v = op(v, BL_LANES(v, 0x141));   // row_half_mirror
+    v = op(v, BL_LANES(v, 0x140));   // row_mirror
+    if constexpr (L >= 32) v = over_blocks<16>(v, op);
+    if constexpr (L >= 64) v = over_blocks<32>(v, op);
+    return v;
+}
+#undef BL_LANES
+struct AddOp { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct MaxOp { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+
 // One head's chunks merged by one workgroup: out = sum_c f_c o_c / sum_c f_c l_c with f_c = exp(m_c - max m) over the
 // chunks that hold rows 0 .. pos.  The chunks' maxima and sums are read one per thread; the factors go through LDS.
 // A value another workgroup of this launch has published (see publish below): read where it was deposited, by a
@@ -486,9 +518,7 @@ __device__ __forceinline__ void attn_merge_together(const AttnArgs& p, float* sc
     if (tid < kWave) {
         const int c = min(tid, used - 1);
         const float m_c = read_published(base + c * (d + 2) + d), l_c = read_published(base + c * (d + 2) + d + 1);
-        float m = m_c;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+        const float m = over_lanes<kWave>(m_c, MaxOp());
         const float f = tid < used ? expf(m_c - m) : 0.0f;
         if (tid < N) s_f[tid] = f;
         const float l = wave_sum_f(f * l_c);
@@ -519,7 +549,7 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
     const auto src = [&](int i) { return read_published(base + i); };
     float m = -INFINITY;
     for (int c = tid; c < used; c += kAttnThreads) m = fmaxf(m, src(c * (d + 2) + d));
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    m = over_lanes<kWave>(m, MaxOp());
     if (lane == 0) s_red[wave] = m;
     __syncthreads();
     m = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
@@ -553,8 +583,9 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 // and weighted values of THEIR rows over all chunks of the workgroup: the dot product's exchanges are the only ones in the
 // loop, and there is no barrier in it, so no wave's requests wait for another wave's rows.  The groups of lanes are merged by
 // lane exchanges, the four waves in LDS, once behind the loop.  Bound by HBM in long contexts: 32 heads of 128 at 8000 positions
-// 36.3 -> 30 us (131 MB: 4.4 TB/s, 6 TB/s beyond the 8 us that one position takes with its merge), 32 000 positions 104 -> 91 us;
-// by the chain of memory round trips in short ones: 500 positions 10.1 -> 8.4, 2000 18.4 -> 14.0.
+// 36.3 -> 30 -> 26.7 us (131 MB: 4.9 TB/s), 30 000 positions 83.5 (5.9 TB/s);
+// by the chain of memory round trips in short ones: one position 5.1 -> 3.9, 500 positions 10.1 -> 8.5 -> 6.4, 2000 18.4 -> 14.4 -> 10.2 (the last
+// step of each: lane sums on the vector ALU, the next chunk's requests without a condition, fewer workgroups per head).
 // MAXD: the largest head size of this instance (128 or 256) -- registers and LDS are sized by it, and the smaller one
 // lets twice as many workgroups share a compute unit.
 // Waves per SIMD: 5 (head sizes up to 128), 4 or, with 8-byte vectors, 3 (beyond), held for the compiler -- with 133 instead of 128
@@ -565,8 +596,8 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) voi
     constexpr int kMaxLanesPerRow = MAXD / W;
     constexpr int kVecs = kChunk * kMaxLanesPerRow / kAttnThreads;            // requests per thread at most
     __shared__ __attribute__((aligned(16))) float s_q[MAXD];                  // rotated query / sqrt(head_dim)
-    __shared__ __attribute__((aligned(16))) float s_newk[MAXD];               // the token's own key and value as cached
-    __shared__ __attribute__((aligned(16))) float s_newv[MAXD];
+    __shared__ __attribute__((aligned(16))) uint16_t s_newk[MAXD];            // the token's own key and value as cached
+    __shared__ __attribute__((aligned(16))) uint16_t s_newv[MAXD];
     __shared__ float s_ow[kAttnWaves][MAXD];            // per wave: weighted values of its rows
     __shared__ float s_mw[kAttnWaves], s_lw[kAttnWaves];   // per wave: maximum and sum
     __shared__ float s_w[kChunk];                       // the merge's partial results
@@ -610,11 +641,10 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) voi
     const auto request = [&](int c, bool keys) {
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
-            if (active) {
-                const int64_t at = (int64_t)min(c * kChunk + grp + i * kRowsPerStep, pos) * hidden + head * d + cc * W;
-                if (keys) kv[i] = *reinterpret_cast<const vec_t*>(p.k_cache + at);
-                else vv[i] = *reinterpret_cast<const vec_t*>(p.v_cache + at);
-            }
+            // (idle lanes read their row's first piece: a branch around the requests would hide from the compiler how many there are)
+            const int64_t at = (int64_t)min(c * kChunk + grp + i * kRowsPerStep, pos) * hidden + head * d + (active ? cc * W : 0);
+            if (keys) kv[i] = *reinterpret_cast<const vec_t*>(p.k_cache + at);
+            else vv[i] = *reinterpret_cast<const vec_t*>(p.v_cache + at);
         }
     };
     request(chunk, true);
@@ -632,8 +662,8 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) voi
             uint16_t* vrow = p.v_cache + (int64_t)pos * hidden + head * d;
             krow[tid] = k0; krow[tid + half] = k1;
             vrow[tid] = v0; vrow[tid + half] = v1;
-            s_newk[tid] = bf16_to_f32(k0); s_newk[tid + half] = bf16_to_f32(k1);
-            s_newv[tid] = bf16_to_f32(v0); s_newv[tid + half] = bf16_to_f32(v1);
+            s_newk[tid] = k0; s_newk[tid + half] = k1;
+            s_newv[tid] = v0; s_newv[tid + half] = v1;
         }
     }
 
@@ -649,71 +679,83 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) voi
     for (int x = 0; x < W; ++x) o_g[x] = 0.0f;
     const int wave_row = __builtin_amdgcn_readfirstlane(wave) * (kWave / L);   // the wave's first row of a step
     static_assert(L <= kWave, "a row's lanes are one wave's");
-    for (int c = chunk; c <= last_chunk; c += groups) {
+    // One chunk.  While more follow, its successor's keys are requested when the dot products are done and its values when the
+    // weighted ones are, without a condition: with one the compiler has to count on the requests not being there, and waited for the
+    // next keys before it used this chunk's values.  Only the last chunk can hold the token's own row or rows beyond it.
+    const auto pass = [&](int c, auto last) {
+        constexpr bool kLast = decltype(last)::value;
         const int j0 = c * kChunk;
-        const int rows = min(kChunk, pos + 1 - j0);
-        const bool holds_token = owner && c == last_chunk;   // uniform
-        const bool more = c + groups <= last_chunk;          // uniform
+        const int rows = kLast ? min(kChunk, pos + 1 - j0) : kChunk;
+        const bool holds_token = kLast && owner && c == last_chunk;   // uniform
         float score[kVecs];
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
-            const int row = grp + i * kRowsPerStep;
-            const bool own = holds_token && j0 + row == pos;   // this launch appends that row: its values are in LDS
-            float acc = 0.0f;
-            if (active) {
-                float k[W];
-                unpack_bf16<W>(kv[i], k);
+            float k[W], acc = 0.0f;
+            vec_t x16 = kv[i];
+            if (holds_token && j0 + grp + i * kRowsPerStep == pos)   // this launch appends that row: its values are in LDS
+                x16 = *reinterpret_cast<const vec_t*>(&s_newk[active ? cc * W : 0]);
+            unpack_bf16<W>(x16, k);
 #pragma unroll
-                for (int x = 0; x < W; ++x) acc = __builtin_fmaf(q[x], own ? s_newk[cc * W + x] : k[x], acc);
-            }
-#pragma unroll
-            for (int off = 1; off < L; off <<= 1) acc += __shfl_xor(acc, off);
-            score[i] = row < rows ? acc : -INFINITY;
+            for (int x = 0; x < W; ++x) acc = __builtin_fmaf(q[x], k[x], acc);
+            score[i] = active ? acc : 0.0f;
         }
-        if (more) request(c + groups, true);            // the next chunk travels while this one is worked on
+#pragma unroll
+        for (int i = 0; i < kVecs; ++i) {
+            const float acc = over_lanes<L>(score[i], AddOp());
+            score[i] = grp + i * kRowsPerStep < rows ? acc : -INFINITY;
+        }
+        if constexpr (!kLast) request(c + groups, true);   // the next chunk travels while this one is worked on
         float m_new = m_g;
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) m_new = fmaxf(m_new, score[i]);
         const float base = m_new == -INFINITY ? 0.0f : m_new;   // a group without rows so far adds nothing
         const float f = expf(m_g - base);
-        l_g *= f;
-#pragma unroll
-        for (int x = 0; x < W; ++x) o_g[x] *= f;
         m_g = m_new;
+        // the chunk's figures by themselves first: a walk's sums then grow by chunks and not by rows (fewer roundings in a row)
+        float l_c = 0.0f, o_c[W];
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
-            // the first tokens of a context: the wave has no row in this step (uniform; 8 heads of 128 at 2 positions 5.5 -> 4.9 us, for
-            // 0.3 us at 32 heads and 8000 positions, 29.1 -> 29.4)
-            if (i > 0 && wave_row + i * kRowsPerStep >= rows) continue;
-            const int row = grp + i * kRowsPerStep;
-            const bool own = holds_token && j0 + row == pos;
+            // the first tokens of a context: the wave has no row in this step (uniform; 8 heads of 128 at 2 positions 5.5 -> 4.9 us)
+            if (kLast && i > 0 && wave_row + i * kRowsPerStep >= rows) continue;
             const float w = expf(score[i] - base);
-            l_g += w;
-            if (active) {
-                float v[W];
-                unpack_bf16<W>(vv[i], v);
+            l_c += w;
+            float v[W];
+            vec_t x16 = vv[i];
+            if (kLast) {
+                if (holds_token && j0 + grp + i * kRowsPerStep == pos) x16 = *reinterpret_cast<const vec_t*>(&s_newv[active ? cc * W : 0]);
                 // rows beyond the token's are selected out, not multiplied out: their registers hold whatever the cache
                 // held before (row `pos` is requested before this launch writes it; a caller's cache need not be finite)
-                const bool counts = row < rows;
-#pragma unroll
-                for (int x = 0; x < W; ++x) o_g[x] = __builtin_fmaf(w, counts ? (own ? s_newv[cc * W + x] : v[x]) : 0.0f, o_g[x]);
+                if (grp + i * kRowsPerStep >= rows) x16 = vec_t{};
             }
+            unpack_bf16<W>(x16, v);
+#pragma unroll
+            for (int x = 0; x < W; ++x) o_c[x] = i == 0 ? w * v[x] : __builtin_fmaf(w, v[x], o_c[x]);   // (idle lanes': never looked at)
         }
-        if (more) request(c + groups, false);
-    }
+        l_g = __builtin_fmaf(l_g, f, l_c);
+#pragma unroll
+        for (int x = 0; x < W; ++x) o_g[x] = __builtin_fmaf(o_g[x], f, o_c[x]);
+        if constexpr (!kLast) request(c + groups, false);
+    };
+    int c = chunk;
+    for (; c + groups <= last_chunk; c += groups) pass(c, std::false_type{});
+    pass(c, std::true_type{});
     // the wave's groups into the wave's figures
     float m_w = m_g;
-#pragma unroll
-    for (int off = L; off < kWave; off <<= 1) m_w = fmaxf(m_w, __shfl_xor(m_w, off));
+    if constexpr (L <= 16) m_w = over_blocks<16>(m_w, MaxOp());
+    if constexpr (L <= 32) m_w = over_blocks<32>(m_w, MaxOp());
     const float f_g = m_g == -INFINITY ? 0.0f : expf(m_g - m_w);
     l_g *= f_g;
 #pragma unroll
     for (int x = 0; x < W; ++x) o_g[x] *= f_g;
+    if constexpr (L <= 16) {
+        l_g = over_blocks<16>(l_g, AddOp());
 #pragma unroll
-    for (int off = L; off < kWave; off <<= 1) {
-        l_g += __shfl_xor(l_g, off);
+        for (int x = 0; x < W; ++x) o_g[x] = over_blocks<16>(o_g[x], AddOp());
+    }
+    if constexpr (L <= 32) {
+        l_g = over_blocks<32>(l_g, AddOp());
 #pragma unroll
-        for (int x = 0; x < W; ++x) o_g[x] += __shfl_xor(o_g[x], off);
+        for (int x = 0; x < W; ++x) o_g[x] = over_blocks<32>(o_g[x], AddOp());
     }
     if (lane < L && active) {
 #pragma unroll
@@ -1063,14 +1105,14 @@ __global__ void pos_advance_kernel(int32_t* pos) {
 
 }  // namespace
 
-// Workgroups of bl_attn_decode: three per compute unit, and up to 64 per head however few heads there are -- as many as the merge
-// reads in one go.  Measured per head (us): 32 heads of 128, 16 000 positions, 16 / 24 / 32 / 64 workgroups 64.6 / 49.7 / 54.7 / 58.7; 64
-// heads, 8 / 12 / 16: 119.5 / 96.3 / 100.7; 40 heads, 14 / 20 / 26: 76.3 / 67.2 / 76.2; 12 heads of 64, 32 000 positions, 24 / 32 / 64:
-// 64.4 / 50.6 / 36.5.
-// A cache so short that four per compute unit give every chunk a workgroup of its own takes those (32 heads, 2000 positions, 24 / 32:
-// 14.7 / 14.0).
-constexpr int kAttnTargetWorkgroups = 768;
-constexpr int kAttnShortWorkgroups = 1024;
+// Workgroups of bl_attn_decode per head: a launch that fills the 256 compute units once (few heads) or twice, never a few more than
+// that -- a unit with one workgroup more than the others is the launch's duration -- and up to 64 per head, as many as the merge
+// reads in one go.  Measured per head (us; 256, 512, 768 workgroups in the launch): 16 heads of 96, 3000 positions 9.6 / 9.9 / 11.1, 9000
+// 16.2 / 16.9 / 17.5; 20 of 80, 8000 17.5 / 17.6 / 18.0; 24 of 128, 1200 8.1 / 9.1 / 9.1; 32 of 100, 1200 11.4 / 10.3 / 11.2; 32 of 128, 1200 8.9 / 8.9 / 10.0, 8000
+// 23.7 / 23.6 / 24.3; 52 of 128, 9000 43.8 / 45.1 / 45.7, 1200 10.5 / 10.3 / 10.8 (780 workgroups: 50.5 and 11.2); 64 of 128, 8000 48.0 / 48.5 / 49.3.
+// (With 768 and, for caches up to four workgroups per unit, one per chunk, as it was before: 32 of 128 at 1500 positions 10.5, now 9.0.)
+constexpr int kAttnUnits = 256;
+constexpr int kAttnOneRound = 10;   // workgroups per head from which on one per unit is enough
 constexpr int kAttnMaxGroups = 64;
 int g_attn_groups = 0;                        // forced workgroups per head (0: automatic)
 
@@ -1129,10 +1171,8 @@ hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
     p.scratch = static_cast<float*>(a.scratch_dev);
     p.n_heads = a.n_heads; p.head_dim = a.head_dim; p.max_pos = a.max_pos; p.chunks = attn_chunks(a.max_pos);
     p.pos0 = 0; p.scratch_stride = 0;
-    // Workgroups per head: one per chunk while that keeps the launch within a few workgroups per compute unit; a longer
-    // cache is walked by fewer, several chunks each (a deposit per workgroup, not per chunk).
-    const int one_chunk_each = min(kAttnMaxGroups, (kAttnShortWorkgroups + a.n_heads - 1) / a.n_heads);
-    const int most = p.chunks <= one_chunk_each ? p.chunks : min(kAttnMaxGroups, (kAttnTargetWorkgroups + a.n_heads - 1) / a.n_heads);
+    const int one_round = kAttnUnits / a.n_heads;
+    const int most = min(p.chunks, max(1, min(kAttnMaxGroups, one_round >= kAttnOneRound ? one_round : 2 * kAttnUnits / a.n_heads)));
     // A cache of more chunks than that has pieces of scratch memory to spare: the last one of each head takes its counter, and
     // no launch, however its workgroups are forced, deposits there.  (By the cache's size only: the same for every call on it.)
     p.counters_apart = p.chunks > most;
