@@ -851,6 +851,52 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const AttnArgs p) {
     }
 }
 
+// The same for head sizes that are a multiple of 8, sixteen bytes at a time and keys and values in workgroups of their own
+// (blockIdx.y), so that a thread's loads are on their way together.  Bound by memory round trips: with the attention behind it, 32 heads of
+// 128, before -> now (us): 512 tokens behind 512 31.5 -> 31.2, 2048 behind 2048 256 -> 250, 37 from 0 9.3 -> 8.8, 96 behind 100 11.4 -> 10.9.  Rows
+// of fewer than kAppendWide elements do not fill two workgroups (12 heads of 64, 100 tokens behind 150 7.8 -> 8.1).
+constexpr int kAppendWide = 1536;
+__global__ __launch_bounds__(256) void kv_append_wide_kernel(const AttnArgs p) {
+    typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(4)));
+    typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+    const int token = blockIdx.x;
+    const int d = p.head_dim, half = d / 2, hidden = p.n_heads * d;
+    const int pos = p.pos0 + token;
+    if (pos < 0 || pos >= p.max_pos) return;
+    const auto pack = [](float lo, float hi) { return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16); };
+    if (blockIdx.y == 0) {
+        const float* k_lin = p.k_lin + (int64_t)token * hidden;
+        uint16_t* krow = p.k_cache + (int64_t)pos * hidden;
+        const float* cs_row = reinterpret_cast<const float*>(p.rope + (int64_t)pos * half);
+        const int per_head = half / 4;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < p.n_heads * per_head; i += 256) {
+            const int head = i / per_head, t = 4 * (i - head * per_head);
+            const int lo = head * d + t, hi = lo + half;
+            const f32x4_u a = *reinterpret_cast<const f32x4_u*>(k_lin + lo), b = *reinterpret_cast<const f32x4_u*>(k_lin + hi);
+            const f32x4_u c0 = *reinterpret_cast<const f32x4_u*>(cs_row + 2 * t), c1 = *reinterpret_cast<const f32x4_u*>(cs_row + 2 * t + 4);
+            const float cx[4] = {c0[0], c0[2], c1[0], c1[2]}, cy[4] = {c0[1], c0[3], c1[1], c1[3]};
+            float x[4], y[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                x[j] = a[j] * cx[j] - b[j] * cy[j];
+                y[j] = a[j] * cy[j] + b[j] * cx[j];
+            }
+            *reinterpret_cast<u32x2_u*>(krow + lo) = u32x2_u{pack(x[0], x[1]), pack(x[2], x[3])};
+            *reinterpret_cast<u32x2_u*>(krow + hi) = u32x2_u{pack(y[0], y[1]), pack(y[2], y[3])};
+        }
+    } else {
+        const float* v_lin = p.v_lin + (int64_t)token * hidden;
+        uint16_t* vrow = p.v_cache + (int64_t)pos * hidden;
+#pragma unroll 4
+        for (int i = threadIdx.x * 8; i < hidden; i += 256 * 8) {
+            const f32x4_u a = *reinterpret_cast<const f32x4_u*>(v_lin + i), b = *reinterpret_cast<const f32x4_u*>(v_lin + i + 4);
+            *reinterpret_cast<u32x4_u*>(vrow + i) = u32x4_u{pack(a[0], a[1]), pack(a[2], a[3]), pack(b[0], b[1]), pack(b[2], b[3])};
+        }
+    }
+}
+
 // A prompt's attention on the matrix cores for head sizes that are 4 more than a multiple of 8 (the others, up to 128, take
 // the kernel of bl_attn_prompt.hip, whose 16-byte requests they do not fit): one workgroup per (head, block of 64 consecutive prompt tokens), 16 queries
 // per wave.  The block walks the cache's 64-row chunks up to its last token's; per chunk a wave forms its 16 x 64
@@ -1200,7 +1246,8 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     p.chunks = attn_chunks(a.pos0 + a.M);
     p.scratch_stride = attn_scratch_floats(a.n_heads, a.head_dim, a.pos0 + a.M);
     p.counters_apart = 0;   // one workgroup per chunk: every piece is used
-    kv_append_kernel<<<dim3((unsigned)a.M), dim3(256), 0, s>>>(p);
+    if (a.head_dim % 8 == 0 && a.n_heads * a.head_dim >= kAppendWide) kv_append_wide_kernel<<<dim3((unsigned)a.M, 2), dim3(256), 0, s>>>(p);
+    else kv_append_kernel<<<dim3((unsigned)a.M), dim3(256), 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // head sizes up to 128 take a matrix-core kernel (a block of 64 tokens per workgroup): the one of bl_attn_prompt.hip where

@@ -1068,3 +1068,10 @@ def test_attn_prefill_waves_and_block_order(dev, mods, n_heads, head_dim, pos0, 
         want = torch.softmax(s.masked_fill(~seen, -float("inf")), 1) @ v[:, h]
         got = out[:, h * head_dim:(h + 1) * head_dim].cpu().double()
         assert (got - want).abs().max() <= PREFILL_BLOCK_TOL * max(1.0, float(want.abs().max())), h
+
+
+@pytest.mark.parametrize("n_heads,head_dim,max_pos,pos0,M", [(22, 72, 90, 5, 70), (32, 48, 70, 0, 33), (12, 128, 100, 31, 3), (9, 168, 40, 1, 20)])
+def test_attn_prefill_parity_wide_rows(dev, mods, n_heads, head_dim, max_pos, pos0, M):
+    """Rows long enough for the append that takes sixteen bytes at a time: head sizes whose quarters are odd numbers of pieces, and one
+    beyond the matrix-core attention."""
+    test_attn_prefill_parity(dev, mods, n_heads, head_dim, max_pos, pos0, M)
