@@ -227,7 +227,7 @@ bl_status bl_attn_decode(const bl_attn_args *args, void *stream);
  * Attention for M consecutive tokens at positions pos0 .. pos0 + M - 1 (a prompt, or a piece of one): token m attends
  * to cache rows 0 .. pos0 + m.  Two launches: the M keys (rotated) and values go into the cache, rounded to bf16 as
  * bl_attn_decode rounds them (the same bits); then the attention.  Head sizes up to BL_ATTN_BLOCK_MAX_HEAD_DIM take one
- * workgroup per (head, 64 tokens) that forms scores and weighted values on the matrix cores, with the fp32 queries
+ * workgroup per (head, 32 tokens; 64 where the head size is 4 modulo 8) that forms scores and weighted values on the matrix cores, with the fp32 queries
  * entered as the sum of three bf16 numbers (all 24 bits) and the softmax weights, which lie in [0, 1], as the sum of
  * two (relative error below 2^-17), fp32 accumulation: the outputs agree with M bl_attn_decode calls to about 1e-5 of the output's scale, not bit for bit.
  * Larger head sizes take one bl_attn_decode-style workgroup per (head, 64 cache rows, token), and there the results

@@ -1,4 +1,5 @@
-// bl_gemm: the prefill product (any number of tokens) on the int8 matrix cores.
+// bl_gemm: the prefill product (any number of tokens) on the int8 matrix cores: the choice of kernel, the plan of the two-width
+// launch, and the tile kernels that launches took before those of bl_gemm_pair.hip (see choose_kernel for what they are left with).
 //
 // Same mathematics as the decode kernel (Section 2 of arXiv 2410.16144, I2_S: codes back to
 // weights, multiply-add), but M is large, so this is a real dense contraction and runs on

@@ -340,7 +340,9 @@ class DecoderStack:
         H = x.clone()
         new = lambda n: torch.empty((M, n), dtype=torch.float32, device=dev)
         A, Y = new(hidden), new(hidden)
-        scratch = torch.zeros(B.bl_attn_prefill_scratch_bytes(self.n_heads, d, pos0, M), dtype=torch.uint8, device=dev)
+        # (head sizes on the matrix cores do not touch their 16 bytes: no launch to clear them)
+        alloc = torch.empty if d <= B.BL_ATTN_BLOCK_MAX_HEAD_DIM else torch.zeros
+        scratch = alloc(B.bl_attn_prefill_scratch_bytes(self.n_heads, d, pos0, M), dtype=torch.uint8, device=dev)
         delta = None
         for layer in self.layers:
             w = layer.w
