@@ -21,7 +21,7 @@
 //
 // Measured, what was chosen before -> now (us, weights cold): 512 x 4096 -> 11008 23.9 -> 20.9, -> 4096 13.3 -> 10.6, -> 24064 42.8 -> 39.1,
 // 512 x 11008 -> 4096 24.1 -> 21.5, 256 x 4096 -> 11008 18.2 -> 13.5, 128 12.8 -> 9.2, 1024 x 4096 -> 4096 19.3 -> 15.8, 2048 x 4096 -> 11008
-// 78.9 -> 72, 2048 x 11008 -> 4096 68.9 -> 66.  (From 1024 tokens on the chip's power limit sets the clock.)  With its requests left out
+// 78.9 -> 75, 2048 x 11008 -> 4096 68.9 -> 66.  (From 1024 tokens on the chip's power limit sets the clock.)  With its requests left out
 // the loop of 512 x 11008 -> 4096 takes 17.6 of 22.6 us, on cached operands 18.6: the rest waits for the dies' L2s, which all fetch
 // all tokens.  Tried and left: 6, 8 and 12 stages (ahead for 64 x 128 tiles with one or two workgroups per unit only), ordinary
 // instead of streaming stores (0.5 to 1 us slower), eight waves with 64 x 256 tiles and with 32 x 256 (no launch gained 3 %).
