@@ -447,8 +447,8 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {   // nearest, ties to
 
 // W bf16 values as one register vector: 128 bits for W = 8, 64 bits for W = 4.
 template <int W> struct CacheVec;
-template <> struct CacheVec<8> { typedef uint4 type; };
-template <> struct CacheVec<4> { typedef uint2 type; };
+template <> struct CacheVec<8> { typedef uint32_t type __attribute__((ext_vector_type(4))); };
+template <> struct CacheVec<4> { typedef uint32_t type __attribute__((ext_vector_type(2))); };
 
 template <int W>
 __device__ __forceinline__ void unpack_bf16(const typename CacheVec<W>::type& u, float (&f)[W]) {
@@ -583,15 +583,19 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 // and weighted values of THEIR rows over all chunks of the workgroup: the dot product's exchanges are the only ones in the
 // loop, and there is no barrier in it, so no wave's requests wait for another wave's rows.  The groups of lanes are merged by
 // lane exchanges, the four waves in LDS, once behind the loop.  Bound by HBM in long contexts: 32 heads of 128 at 8000 positions
-// 36.3 -> 30 -> 26.7 us (131 MB: 4.9 TB/s), 30 000 positions 83.5 (5.9 TB/s);
-// by the chain of memory round trips in short ones: one position 5.1 -> 3.9, 500 positions 10.1 -> 8.5 -> 6.4, 2000 18.4 -> 14.4 -> 10.2 (the last
-// step of each: lane sums on the vector ALU, the next chunk's requests without a condition, fewer workgroups per head).
+// 36.3 -> 30 -> 26.9 us (131 MB: 4.9 TB/s), 32 000 positions 92 (5.7 TB/s);
+// by the chain of memory round trips in short ones (caches from memory): one position 4.8 -> 3.4, 500 positions 10.2 -> 7.4, 3000 18.0 -> 13.7.
+// Before lane sums on the vector ALU, the next chunk's requests without a condition and fewer workgroups per head -> since; the last
+// change kept the requests where they are written and put the angle's load ahead of them: 16 heads of 100 at 8000 positions
+// 21.2 -> 17.8, 12 of 44 at 16 000 24.2 -> 19.0, 20 of 160 at 500 / 3000 / 8000 8.9 -> 8.0, 16.2 -> 13.3, 31.6 -> 24.4, 30 of 256 10.7 -> 9.4, 25.6 -> 22.4,
+// 55.4 -> 48.1, 32 of 128 at 500 8.1 -> 7.4.
 // MAXD: the largest head size of this instance (128 or 256) -- registers and LDS are sized by it, and the smaller one
 // lets twice as many workgroups share a compute unit.
-// Waves per SIMD: 5 (head sizes up to 128), 4 or, with 8-byte vectors, 3 (beyond), held for the compiler -- with 133 instead of 128
-// registers <8, 256> ran three and took 21.9 instead of 18.3 us for 39 heads of 160 at 1270 positions.
+// Waves per SIMD: 5 (head sizes up to 128) and 4 (beyond), held for the compiler; every instance fits without spilling: 75, 71,
+// 115 and 122 registers.  (Five spilled registers of <8, 256>, reloaded behind the next keys' requests, made every chunk wait for
+// those: 40 heads of 160 at 16 000 positions 92.8 us, without spills 79.7.)
 template <int W, int MAXD>
-__global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) void attn_chunk_kernel(const AttnArgs p) {
+__global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : 4) void attn_chunk_kernel(const AttnArgs p) {
     typedef typename CacheVec<W>::type vec_t;
     constexpr int kMaxLanesPerRow = MAXD / W;
     constexpr int kVecs = kChunk * kMaxLanesPerRow / kAttnThreads;            // requests per thread at most
@@ -620,7 +624,7 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) voi
             va = p.v_lin[head * d + tid]; vb = p.v_lin[head * d + tid + half];
         }
     }
-    const int pos = appended ? p.pos0 + query : *p.pos;
+    const int pos = __builtin_amdgcn_readfirstlane(appended ? p.pos0 + query : *p.pos);
     if (pos < 0 || pos >= p.max_pos) return;            // uniform
     // Workgroup y of a head takes the chunks y, y + G, y + 2G, ... (G = workgroups per head in this launch) that hold
     // rows up to the token's: one chunk each while the context is short, several once it outgrows the launch -- then
@@ -638,21 +642,33 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) voi
     // rows beyond the token's are read as the token's row (always inside the cache) and never used; the token's own
     // row may be read while this workgroup writes it and is replaced by the values kept in LDS
     vec_t kv[kVecs], vv[kVecs];
+    const uint32_t row_bytes = 2u * (uint32_t)hidden;   // a chunk's rows: below 2^32 bytes (heads and head size are bounded)
     const auto request = [&](int c, bool keys) {
+        // scalar base, 32-bit lane offsets, and neither kept from one request to the next (the registers are needed)
+        typedef const __attribute__((address_space(1))) uint8_t* global_t;
+        global_t base = (global_t)(uintptr_t)((keys ? p.k_cache : p.v_cache) + (int64_t)c * kChunk * hidden + head * d);
+        int rest = pos - c * kChunk;
+        asm volatile("" : "+s"(base), "+s"(rest));
+        // Requests stay where they are: the compiler moves loads down to their first use if it finds registers short, behind
+        // the waits that they were to travel under.
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
             // (idle lanes read their row's first piece: a branch around the requests would hide from the compiler how many there are)
-            const int64_t at = (int64_t)min(c * kChunk + grp + i * kRowsPerStep, pos) * hidden + head * d + (active ? cc * W : 0);
-            if (keys) kv[i] = *reinterpret_cast<const vec_t*>(p.k_cache + at);
-            else vv[i] = *reinterpret_cast<const vec_t*>(p.v_cache + at);
+            const uint32_t at = (uint32_t)min(grp + i * kRowsPerStep, rest) * row_bytes + (active ? cc * W * 2u : 0u);
+            typedef const __attribute__((address_space(1))) vec_t* global_vec;
+            if (keys) kv[i] = *(global_vec)(base + at);
+            else vv[i] = *(global_vec)(base + at);
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
+    // (the angle first: what it is needed for goes on under the requests behind it)
+    const float2 cs = p.rope[(int64_t)pos * half + min(tid, half - 1)];
     request(chunk, true);
     request(chunk, false);
 
     const float scale = 1.0f / sqrtf((float)d);
     if (tid < half) {
-        const float2 cs = p.rope[(int64_t)pos * half + tid];
         s_q[tid] = (qa * cs.x - qb * cs.y) * scale;
         s_q[tid + half] = (qa * cs.y + qb * cs.x) * scale;
         if (owner) {
@@ -681,7 +697,8 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) voi
     static_assert(L <= kWave, "a row's lanes are one wave's");
     // One chunk.  While more follow, its successor's keys are requested when the dot products are done and its values when the
     // weighted ones are, without a condition: with one the compiler has to count on the requests not being there, and waited for the
-    // next keys before it used this chunk's values.  Only the last chunk can hold the token's own row or rows beyond it.
+    // next keys before it used this chunk's values.  kVecs requests are on their way at any time (tests/test_wait_counts.py looks at
+    // the compiled loop).  Only the last chunk can hold the token's own row or rows beyond it.
     const auto pass = [&](int c, auto last) {
         constexpr bool kLast = decltype(last)::value;
         const int j0 = c * kChunk;
@@ -699,12 +716,12 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : W == 8 ? 4 : 3) voi
             for (int x = 0; x < W; ++x) acc = __builtin_fmaf(q[x], k[x], acc);
             score[i] = active ? acc : 0.0f;
         }
+        if constexpr (!kLast) request(c + groups, true);   // the next chunk travels while this one is worked on
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
             const float acc = over_lanes<L>(score[i], AddOp());
             score[i] = grp + i * kRowsPerStep < rows ? acc : -INFINITY;
         }
-        if constexpr (!kLast) request(c + groups, true);   // the next chunk travels while this one is worked on
         float m_new = m_g;
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) m_new = fmaxf(m_new, score[i]);

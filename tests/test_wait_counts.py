@@ -211,3 +211,40 @@ def test_compiled_paired_kernels_issue_what_the_model_assumes(tmp_path):
         for l in lines[first:]:
             assert not re.match(r"(scratch_|flat_|global_store|global_atomic|buffer_load|global_load_dword(x2|x4)?\b)", l), (name, l)
     assert seen == 7
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_compiled_token_attention_keeps_a_chunk_half_on_its_way(tmp_path):
+    """bl_decoder.hip's walk over the cache: a loop with one run of requests for the next keys and one for the next values, kVecs
+    each, in which no wait is for fewer than the kVecs requests issued last; and no instance spills a register."""
+    asm = _compile_to_asm(tmp_path, "bl_decoder.hip")
+    fns = _functions(asm)
+    spills = dict(re.findall(r"\.amdhsa_kernel (\S+)\n(?:.*\n)*?\s+\.amdhsa_private_segment_fixed_size (\d+)", open(asm).read()))
+    seen = 0
+    for name, lines in fns.items():
+        m = re.search(r"attn_chunk_kernelILi(\d+)ELi(\d+)E", name)
+        if not m:
+            continue
+        seen += 1
+        w, maxd = (int(x) for x in m.groups())
+        vecs = 64 * (maxd // w) // 256
+        assert spills[name] == "0", (name, spills[name])
+        load = "global_load_dwordx%d" % (w // 2)
+        starts = {l.split(":")[0]: i for i, l in enumerate(lines) if l.startswith(".LBB")}
+        bodies = []
+        for i, l in enumerate(lines):
+            b = re.match(r"s_cbranch_\w+ (\.LBB\w+)", l.replace("\t", " "))
+            if b and starts.get(b.group(1), i) < i and any(x.startswith(load) for x in lines[starts[b.group(1)]:i]):
+                bodies.append(lines[starts[b.group(1)]:i])
+        walk = min(bodies, key=len)
+        runs, waits, since = [], [], vecs
+        for l in walk:
+            if l.startswith(load):
+                runs = runs + [1] if since else runs[:-1] + [runs[-1] + 1]
+                since = 0
+            elif l.startswith("s_waitcnt"):
+                since = 1
+                waits += [int(x) for x in re.findall(r"vmcnt\((\d+)\)", l)]
+            assert not re.match(r"(scratch_|flat_|buffer_|s_barrier)", l), (name, l)
+        assert runs == [vecs, vecs] and min(waits) == vecs, (name, runs, waits)
+    assert seen == 4
