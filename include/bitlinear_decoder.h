@@ -195,7 +195,8 @@ bl_status bl_rope_table(float *table_dev, int32_t head_dim, int32_t max_pos, dou
  *                                     the partial results of the workgroups that share a head and one
  *                                     ticket counter per head, which the call puts back to zero).  Calls
  *                                     that may overlap in time must not share it.
- * One launch: n_heads x G workgroups, G = ceil(max_pos / BL_ATTN_CHUNK) up to min(64, ceil(1024 / n_heads)), else min(64, ceil(768 / n_heads)); a head's
+ * One launch: n_heads x G workgroups, G chosen from n_heads, head_dim and max_pos alone, at most 64 and at most
+ * ceil(max_pos / BL_ATTN_CHUNK), so that the launch fills the compute units a whole number of times; a head's
  * workgroup y walks the chunks y, y + G, ... of BL_ATTN_CHUNK cache rows up to row p (one chunk each while
  * p < 64 G; workgroups with nothing to walk exit at once) and keeps one running maximum, sum and weighted
  * values; the workgroup of a head that finishes last merges the head's partial results -- it is told so by

@@ -18,6 +18,7 @@
 //                       bl_attn_prompt.hip);
 //   pos_advance_kernel  the token position lives in device memory, so a captured graph replays unchanged.
 // All of it but attn_block_kernel is bandwidth- and latency-bound glue next to the weight streams.
+#include "bl_attn_groups.hpp"
 #include "bl_quant_device.hpp"
 #include "bitlinear_decoder.h"
 
@@ -1168,15 +1169,6 @@ __global__ void pos_advance_kernel(int32_t* pos) {
 
 }  // namespace
 
-// Workgroups of bl_attn_decode per head: a launch that fills the 256 compute units once (few heads) or twice, never a few more than
-// that -- a unit with one workgroup more than the others is the launch's duration -- and up to 64 per head, as many as the merge
-// reads in one go.  Measured per head (us; 256, 512, 768 workgroups in the launch): 16 heads of 96, 3000 positions 9.6 / 9.9 / 11.1, 9000
-// 16.2 / 16.9 / 17.5; 20 of 80, 8000 17.5 / 17.6 / 18.0; 24 of 128, 1200 8.1 / 9.1 / 9.1; 32 of 100, 1200 11.4 / 10.3 / 11.2; 32 of 128, 1200 8.9 / 8.9 / 10.0, 8000
-// 23.7 / 23.6 / 24.3; 52 of 128, 9000 43.8 / 45.1 / 45.7, 1200 10.5 / 10.3 / 10.8 (780 workgroups: 50.5 and 11.2); 64 of 128, 8000 48.0 / 48.5 / 49.3.
-// (With 768 and, for caches up to four workgroups per unit, one per chunk, as it was before: 32 of 128 at 1500 positions 10.5, now 9.0.)
-constexpr int kAttnUnits = 256;
-constexpr int kAttnOneRound = 10;   // workgroups per head from which on one per unit is enough
-constexpr int kAttnMaxGroups = 64;
 int g_attn_groups = 0;                        // forced workgroups per head (0: automatic)
 
 hipError_t launch_norm_quant(const bl_norm_quant_args& a, hipStream_t s) {
@@ -1234,8 +1226,7 @@ hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
     p.scratch = static_cast<float*>(a.scratch_dev);
     p.n_heads = a.n_heads; p.head_dim = a.head_dim; p.max_pos = a.max_pos; p.chunks = attn_chunks(a.max_pos);
     p.pos0 = 0; p.scratch_stride = 0;
-    const int one_round = kAttnUnits / a.n_heads;
-    const int most = min(p.chunks, max(1, min(kAttnMaxGroups, one_round >= kAttnOneRound ? one_round : 2 * kAttnUnits / a.n_heads)));
+    const int most = attn_groups_per_head(a.n_heads, a.head_dim, p.chunks);
     // A cache of more chunks than that has pieces of scratch memory to spare: the last one of each head takes its counter, and
     // no launch, however its workgroups are forced, deposits there.  (By the cache's size only: the same for every call on it.)
     p.counters_apart = p.chunks > most;

@@ -5,6 +5,7 @@ machine without a GPU.
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -309,3 +310,28 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_token_attention_fills_whole_rounds(tmp_path):
+    """Workgroups per head of the token attention (csrc/bl_attn_groups.hpp) for every number of heads: within the merge's reach and
+    the cache's chunks, and where neither limits them the launch is no more than 28 % short of whole rounds of the 256 compute units
+    (300 heads once took 300 workgroups: 256 and 44)."""
+    src = tmp_path / "groups.cpp"
+    src.write_text("""
+        #include <cstdio>
+        #include "bl_attn_groups.hpp"
+        int main() {
+            for (int d : {4, 64, 72, 128, 256})
+                for (int chunks : {1, 2, 9, 64, 128, 129, 500, 65535})
+                    for (int h = 1; h <= 1200; ++h) printf("%d %d %d %d\\n", d, chunks, h, bl::attn_groups_per_head(h, d, chunks));
+            printf("%d %d %d %d\\n", 256, 65535, 65535, bl::attn_groups_per_head(65535, 256, 65535));
+        }""")
+    exe = str(tmp_path / "groups")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2410_16144_amd", "csrc"), str(src), "-o", exe])
+    rows = [[int(v) for v in l.split()] for l in subprocess.check_output([exe], text=True).splitlines()]
+    assert len(rows) == 5 * 8 * 1200 + 1
+    for d, chunks, h, g in rows:
+        assert 1 <= g <= min(64, chunks), (d, chunks, h, g)
+        if g < min(64, chunks):
+            rounds = -(-g * h // 256)
+            assert g * h >= 0.72 * 256 * rounds, (d, chunks, h, g)
