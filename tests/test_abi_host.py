@@ -319,6 +319,7 @@ def test_token_attention_fills_whole_rounds(tmp_path):
     src = tmp_path / "groups.cpp"
     src.write_text("""
         #include <cstdio>
+        #include <initializer_list>
         #include "bl_attn_groups.hpp"
         int main() {
             for (int d : {4, 64, 72, 128, 256})
