@@ -231,8 +231,8 @@ bl_status bl_attn_decode(const bl_attn_args *args, void *stream);
  * workgroup per (head, 32 tokens; 64 where the head size is 4 modulo 8) that forms scores and weighted values on the matrix cores, with the fp32 queries
  * entered as the sum of three bf16 numbers (all 24 bits) and the softmax weights, which lie in [0, 1], as the sum of
  * two (relative error below 2^-17), fp32 accumulation: the outputs agree with M bl_attn_decode calls to about 1e-5 of the output's scale, not bit for bit.
- * Larger head sizes take one bl_attn_decode-style workgroup per (head, 64 cache rows, token), and there the results
- * are those of M bl_attn_decode calls in order.
+ * Larger head sizes take, per token, the workgroups of bl_attn_decode on a cache of max_pos rows, and there the results
+ * are those of M bl_attn_decode calls in order, bit for bit.
  *   q_lin_dev, k_lin_dev, v_lin_dev   [M, n_heads * head_dim] fp32, rows contiguous; k_lin_dev and v_lin_dev 8-byte aligned
  *   out_dev                           [M, n_heads * head_dim] fp32
  *   pos0, M                           host values; 0 <= pos0, pos0 + M <= max_pos, 1 <= M <= 65535

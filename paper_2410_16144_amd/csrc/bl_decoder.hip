@@ -1218,6 +1218,15 @@ static void launch_attn_chunks(const AttnArgs& p, const dim3& grid, hipStream_t 
     }
 }
 
+// Workgroups per head of a call on a cache of so many chunks.  A cache of more chunks than that has pieces of scratch memory to
+// spare: the last one of each head takes its counter, and no launch, however its workgroups are forced, deposits there.  (By the
+// cache's size only: the same for every call on it.)
+static int attn_groups(int n_heads, int head_dim, int chunks, int32_t& counters_apart) {
+    const int most = attn_groups_per_head(n_heads, head_dim, chunks);
+    counters_apart = chunks > most;
+    return min(g_attn_groups > 0 ? g_attn_groups : most, counters_apart ? chunks - 1 : chunks);
+}
+
 hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
     AttnArgs p;
     p.q_lin = a.q_lin_dev; p.k_lin = a.k_lin_dev; p.v_lin = a.v_lin_dev; p.pos = a.pos_dev;
@@ -1226,11 +1235,7 @@ hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
     p.scratch = static_cast<float*>(a.scratch_dev);
     p.n_heads = a.n_heads; p.head_dim = a.head_dim; p.max_pos = a.max_pos; p.chunks = attn_chunks(a.max_pos);
     p.pos0 = 0; p.scratch_stride = 0;
-    const int most = attn_groups_per_head(a.n_heads, a.head_dim, p.chunks);
-    // A cache of more chunks than that has pieces of scratch memory to spare: the last one of each head takes its counter, and
-    // no launch, however its workgroups are forced, deposits there.  (By the cache's size only: the same for every call on it.)
-    p.counters_apart = p.chunks > most;
-    const int groups = min(g_attn_groups > 0 ? g_attn_groups : most, p.counters_apart ? p.chunks - 1 : p.chunks);
+    const int groups = attn_groups(a.n_heads, a.head_dim, p.chunks, p.counters_apart);
     const dim3 grid((unsigned)a.n_heads, (unsigned)groups);
     launch_attn_chunks(p, grid, s);
     return hipGetLastError();
@@ -1253,7 +1258,6 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     // a prompt's queries never look beyond its last token: chunks up to that one only
     p.chunks = attn_chunks(a.pos0 + a.M);
     p.scratch_stride = attn_scratch_floats(a.n_heads, a.head_dim, a.pos0 + a.M);
-    p.counters_apart = 0;   // one workgroup per chunk: every piece is used
     if (a.head_dim % 8 == 0 && a.n_heads * a.head_dim >= kAppendWide) kv_append_wide_kernel<<<dim3((unsigned)a.M, 2), dim3(256), 0, s>>>(p);
     else kv_append_kernel<<<dim3((unsigned)a.M), dim3(256), 0, s>>>(p);
     hipError_t e = hipGetLastError();
@@ -1273,7 +1277,11 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
         case 8: return launch_attn_block<8>(p, a.M, s);
         default: break;
     }
-    const dim3 grid((unsigned)a.n_heads, (unsigned)p.chunks, (unsigned)a.M);
+    // the workgroups that bl_attn_decode takes on this cache: the same sums in the same order, token by token.  They may use every
+    // piece of a token's scratch memory (its chunks end at pos0 + M, not at max_pos), so the counters lie behind the pieces.
+    const int groups = min(attn_groups(a.n_heads, a.head_dim, attn_chunks(a.max_pos), p.counters_apart), p.chunks);
+    p.counters_apart = 0;
+    const dim3 grid((unsigned)a.n_heads, (unsigned)groups, (unsigned)a.M);
     launch_attn_chunks(p, grid, s);
     return hipGetLastError();
 }

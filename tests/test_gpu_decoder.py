@@ -971,7 +971,7 @@ def test_attn_prefill_parity(dev, mods, n_heads, head_dim, max_pos, pos0, M):
 
 
 def test_attn_prefill_head_size_above_128_behind_many_chunks(dev, mods):
-    """More deposits (one per 64 cache rows and token) than are read in one round, against the fp64 softmax."""
+    """More deposits (a forced workgroup per 64 cache rows and token) than are read in one round, against the fp64 softmax."""
     B, dec, ops = mods
     head_dim, pos0, M, max_pos = 256, 64 * 65 - 1, 2, 64 * 66
     r = _rng(96000)
@@ -981,9 +981,13 @@ def test_attn_prefill_head_size_above_128_behind_many_chunks(dev, mods):
     lin = [3.0 * r.standard_normal((M, head_dim)).astype(np.float32) for _ in range(3)]
     lin_t, out = [_t(v, dev) for v in lin], torch.empty((M, head_dim), device=dev)
     scratch = torch.zeros(B.bl_attn_prefill_scratch_bytes(1, head_dim, pos0, M), dtype=torch.uint8, device=dev)
-    for _ in range(2):
-        B.bl_attn_prefill(*(t.data_ptr() for t in lin_t), table.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), out.data_ptr(),
-                          scratch.data_ptr(), 1, head_dim, max_pos, pos0, M, torch.cuda.current_stream().cuda_stream)
+    B.bl_set_tuning("attn_groups", 1000)
+    try:
+        for _ in range(2):
+            B.bl_attn_prefill(*(t.data_ptr() for t in lin_t), table.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), out.data_ptr(),
+                              scratch.data_ptr(), 1, head_dim, max_pos, pos0, M, torch.cuda.current_stream().cuda_stream)
+    finally:
+        B.bl_set_tuning("attn_groups", 0)
     torch.cuda.synchronize()
     kc64, vc64 = (c.float().cpu().numpy().astype(np.float64) for c in (k_cache, v_cache))
     for m in range(M):
@@ -1075,3 +1079,31 @@ def test_attn_prefill_parity_wide_rows(dev, mods, n_heads, head_dim, max_pos, po
     """Rows long enough for the append that takes sixteen bytes at a time: head sizes whose quarters are odd numbers of pieces, and one
     beyond the matrix-core attention."""
     test_attn_prefill_parity(dev, mods, n_heads, head_dim, max_pos, pos0, M)
+
+
+@pytest.mark.parametrize("n_heads,head_dim,max_pos,pos0,M", [(40, 160, 1300, 1250, 3), (150, 136, 330, 326, 3), (2, 132, 4400, 4220, 2), (300, 256, 700, 640, 2)])
+def test_attn_prefill_equals_tokens_beyond_one_chunk_per_workgroup(dev, mods, n_heads, head_dim, max_pos, pos0, M):
+    """Head sizes above 128 in caches whose chunks outnumber a head's workgroups (12, 3, 64 and 5): a prompt's tokens add up their
+    chunks in the one-token call's order, bit for bit."""
+    B, dec, ops = mods
+    hidden = n_heads * head_dim
+    table = dec.rope_table(head_dim, max_pos, dev)
+    g = torch.Generator(device=dev).manual_seed(97000 + hidden)
+    kc, vc = (torch.randn((max_pos, hidden), device=dev, generator=g).to(torch.bfloat16) for _ in range(2))
+    lin = [3.0 * torch.randn((M, hidden), device=dev, generator=g) for _ in range(3)]
+    k_cache, v_cache, out = kc.clone(), vc.clone(), torch.empty((M, hidden), device=dev)
+    scratch = torch.zeros(B.bl_attn_prefill_scratch_bytes(n_heads, head_dim, pos0, M), dtype=torch.uint8, device=dev)
+    one, pos_t = [torch.empty((1, hidden), device=dev) for _ in range(3)], torch.zeros(1, dtype=torch.int32, device=dev)
+    att = dec.Attention(n_heads, head_dim, max_pos, *one, pos_t, table)
+    att.k_cache.copy_(kc)
+    att.v_cache.copy_(vc)
+    for _ in range(2):   # twice: the counters in the scratch memory must be back at zero
+        B.bl_attn_prefill(*(t.data_ptr() for t in lin), table.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), out.data_ptr(),
+                          scratch.data_ptr(), n_heads, head_dim, max_pos, pos0, M, torch.cuda.current_stream().cuda_stream)
+        for m in range(M):
+            for t, v in zip(one, lin):
+                t.copy_(v[m:m + 1])
+            pos_t.fill_(pos0 + m)
+            assert torch.equal(att.launch()[0], out[m]), m
+    assert torch.equal(k_cache.view(torch.int16), att.k_cache.view(torch.int16))
+    assert not scratch.view(torch.int32).view(M, -1)[:, -n_heads:].any()
