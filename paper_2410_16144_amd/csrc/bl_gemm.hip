@@ -378,38 +378,15 @@ __global__ __launch_bounds__(64 * WN * WK, WN * WK == 4 ? 2 : 1) void gemm_batch
     gemm_tile<MB, H, WK, WN>(b.p[item], M, tile_x - first, tile_y);
 }
 
-// Two tile widths in one launch, for launches of between one and one and a half 64 x 256 tiles per compute unit: there some
-// units got two tiles and the others one, and the launch took as long as two.  Here every unit gets ONE 64 x 256 tile, and the
-// rest of the rows are cut into 64 x 128 tiles (the same loop, 32 rows per wave), at most one per unit.
-__global__ __launch_bounds__(256, 2) void gemm_mixed_kernel(const GemmMixed b, const int M) {
-    int tile_x, tile_y, item = 0, first = 0;
-    if ((int)blockIdx.x < b.wgs) {   // uniform
-        if (!tile_of_workgroup(blockIdx.x, b.gx, tile_x, tile_y)) return;
-#pragma unroll
-        for (int i = 0; i + 1 < kMaxGemmBatch; ++i)
-            if (tile_x >= b.end[i]) { item = i + 1; first = b.end[i]; }
-        gemm_tile<2, 2, 1, 4>(b.p[item], M, tile_x - first, tile_y);
-    } else {
-        if (!tile_of_workgroup(blockIdx.x - b.wgs, b.small_gx, tile_x, tile_y)) return;
-#pragma unroll
-        for (int i = 0; i + 1 < kMaxGemmBatch; ++i)
-            if (tile_x >= b.small_end[i]) { item = i + 1; first = b.small_end[i]; }
-        // (the narrow tile's pipeline is the wide one's: the same requests, loads and waits per step)
-        static_assert(GemmRing<2, 1, 1, 4>::kNT == GemmRing<2, 2, 1, 4>::kNT && GemmRing<2, 1, 1, 4>::kRQ == GemmRing<2, 2, 1, 4>::kRQ &&
-                          GemmRing<2, 1, 1, 4>::kYounger == GemmRing<2, 2, 1, 4>::kYounger, "the checked wait counts");
-        gemm_tile<2, 1, 1, 4>(b.p[item], M, tile_x - first + b.small_first[item], tile_y);
-    }
-}
-
 int g_force_mb = 0;
-constexpr int kCodeMixed = 25;          // bl_set_tuning "gemm_mb": the two-width kernel wherever it applies
-constexpr int kCodePairMixed = 40025;   // ... and that of bl_gemm_pair.hip
+constexpr int kCodeMixed = 25, kCodePairMixed = 40025;   // bl_set_tuning "gemm_mb": tiles of two widths wherever that launch applies
+bool forced_mixed() { return g_force_mb == kCodeMixed || g_force_mb == kCodePairMixed; }
 
 // One tile form: wave tile (32*MB) tokens x (32*H) weight rows, WN waves along N and WK along K.
 struct TileForm { int mb, h, wk, wn; };
 
 // Forced value (bl_set_tuning "gemm_mb"): 100*(WK-1) + 10*MB + H; four waves per workgroup, WN = 4 / WK.  (From 1000 on: the
-// forms of bl_gemm_narrow.hip.)
+// forms of bl_gemm_narrow.hip and bl_gemm_pair.hip.)
 TileForm form_of_code(int code) {
     TileForm f;
     const int waves = 4;
@@ -420,25 +397,16 @@ TileForm form_of_code(int code) {
     return f;
 }
 
-// Choice by workgroup count: 64 x 128 wave tiles (half the LDS traffic per MFMA) when the grid still gives
-// every compute unit two workgroups; 64 x 64 otherwise; and 32 x 64 or the K-split form when even that grid would
-// leave compute units without work.  `rows`: padded weight rows of the launch.
-TileForm choose_tile(int64_t M, int64_t rows) {
-    if (g_force_mb && g_force_mb != kCodeMixed && g_force_mb < 1000) return form_of_code(g_force_mb);
-    const int64_t tiles_m = (M + 63) / 64;
-    const auto wgs = [&](int wn, int hh) { return tiles_m * ((rows + wn * hh * 32 - 1) / (wn * hh * 32)); };
-    TileForm f = {2, 2, 1, 4};
-    if (wgs(4, 4) >= 512) f.h = 4;
-    else if (wgs(4, 2) < 256) {
-        // too few workgroups either way: 32-token tiles from 128 tokens up (measured 5-8 % ahead of the K split on
-        // shapes from 1536^2 to 8192^2), the K split below
-        if (M >= 128) f.mb = 1;
-        else { f.wk = 2; f.wn = 2; }
-    }
-    return f;
+// The form that is forced, else 64 x 128 wave tiles: launches come here with more than 2^23 weight rows, tens of workgroups per
+// compute unit whatever the form.
+TileForm choose_tile() {
+    if (g_force_mb && !forced_mixed() && g_force_mb < 1000) return form_of_code(g_force_mb);
+    return {2, 4, 1, 4};
 }
 
-// Whether a launch takes the two-width kernel, and its shape.
+// Two tile widths in one launch, for launches of between one and one and a half 64 x 256 tiles per compute unit: there some
+// units would get two tiles and the others one, and the launch take as long as two.  Here every unit gets ONE 64 x 256 tile, and the
+// rest of the rows are cut into 64 x 128 tiles, at most one per unit.  Whether a launch takes it, and its shape.
 bool plan_mixed(const GemmProblem* ps, int count, int64_t M, GemmMixed& b) {
     const int cus = compute_unit_count();
     const int64_t tiles_m = (M + 63) / 64;
@@ -473,24 +441,26 @@ bool plan_mixed(const GemmProblem* ps, int count, int64_t M, GemmMixed& b) {
 }
 
 // What a launch takes: a form of bl_gemm_pair.hip (its two-width launch among them) or of bl_gemm_narrow.hip, by estimated
-// time (gemm_pair_best, gemm_narrow_best: lines through measured times).  The tile kernels of this file take what those do not
-// (gemm_pair_takes: more than 2^23 weight rows or 2^25 columns) and the launches that bl_set_tuning sends to them: of 11065 launches measured on
+// time (gemm_pair_best, gemm_narrow_best: lines through measured times).  The tile kernels of this file take what the paired ones
+// do not (gemm_pair_takes: more than 2^23 weight rows) and the launches that bl_set_tuning sends to them: of 11065 launches measured on
 // every form -- 9 to 6000 tokens, K 64 to 13000, N 64 to 60000, sizes spread over their logarithms -- they are ahead of the best other
-// form by more than 2 % on 40, nearly all of them with 64 or 128 weight rows.
-struct GemmChoice { int narrow = 0, pair = 0; bool mixed = false, pair_mixed = false; };
+// form by more than 2 % on 40, nearly all of them with 64 or 128 weight rows.  Beyond 2^23 rows they are ahead of the forms for few
+// tokens as well, whose workgroups are many and short there (2^23 + 64 rows, K = 1024, us, 64 x 128 wave tiles and the best of those
+// forms: 9 tokens 507 and 679, 16 535 and 717, 32 639 and 828, 64 820 and 1623; K = 64, 16 tokens 151 and 517).
+struct GemmChoice { int narrow = 0, pair = 0; bool mixed = false; };
 
 GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed& mixed) {
     GemmChoice c;
     const bool narrow_ok = gemm_narrow_takes(ps, count, M), pair_ok = gemm_pair_takes(ps, count);
-    if (g_force_mb && g_force_mb != kCodeMixed && g_force_mb != kCodePairMixed) {
+    if (g_force_mb && !forced_mixed()) {
         if (gemm_pair_form_exists(g_force_mb)) c.pair = pair_ok ? g_force_mb : 0;
         else if (gemm_narrow_form_exists(g_force_mb)) c.narrow = narrow_ok ? g_force_mb : 0;
         return c;
     }
+    if (!pair_ok) return c;
     const bool mixed_ok = plan_mixed(ps, count, M, mixed);
-    c.mixed = g_force_mb == kCodeMixed && mixed_ok;
-    c.pair_mixed = g_force_mb == kCodePairMixed && mixed_ok && pair_ok;
-    if (c.mixed || c.pair_mixed || !pair_ok) return c;
+    c.mixed = forced_mixed() && mixed_ok;
+    if (c.mixed) return c;
     const int found = compute_unit_count(), cus = found > 0 ? found : 256;
     float best = 0.0f;
     c.pair = gemm_pair_best(ps, count, M, cus, best);
@@ -500,12 +470,12 @@ GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed&
         for (int i = 0; i < count; ++i) KC = ps[i].KC > KC ? ps[i].KC : KC;
         // the two-width launch: share = units with a narrow tile beside their wide one
         const float us = 4.85f + 0.2226f * (float)KC + share * (0.93f + 0.0283f * (float)KC);
-        if (us < best) { best = us; c.pair_mixed = true; }
+        if (us < best) { best = us; c.mixed = true; }
     }
     if (narrow_ok) {
         float us = 0.0f;
         const int code = gemm_narrow_best(ps, count, M, cus, us);
-        if (us < best) { c.pair_mixed = false; c.pair = 0; c.narrow = code; }
+        if (us < best) { c.mixed = false; c.pair = 0; c.narrow = code; }
     }
     return c;
 }
@@ -531,8 +501,8 @@ hipError_t launch_form(Kernel kernel, size_t lds_bytes, int threads, unsigned gr
 void set_gemm_mb(int mb) { g_force_mb = mb; }
 
 bool gemm_form_exists(int code) {
-    if (code == kCodeMixed) return true;
-    if (code >= 1000) return code == kCodePairMixed || gemm_pair_form_exists(code) || gemm_narrow_form_exists(code);
+    if (code == kCodeMixed || code == kCodePairMixed) return true;
+    if (code >= 1000) return gemm_pair_form_exists(code) || gemm_narrow_form_exists(code);
     const TileForm f = form_of_code(code);
 #define X(MB, H, WK, WN) if (f.mb == MB && f.h == H && f.wk == WK && f.wn == WN) return true;
     BL_GEMM_FORMS(X)
@@ -540,25 +510,14 @@ bool gemm_form_exists(int code) {
     return false;
 }
 
-hipError_t launch_mixed(const GemmMixed& b, int64_t M, hipStream_t s) {
-    constexpr int kLds = gemm_lds_bytes<2, 2, 1, 4>();
-    static_assert(kLds == gemm_lds_bytes<2, 1, 1, 4>(), "both widths stage the same activation tiles");
-    static_assert(kLds <= kDefaultLds, "no ceiling to raise");
-    const unsigned grid = (unsigned)(b.wgs + (b.small_gx + kXcds - 1) / kXcds * kXcds * ((M + 63) / 64));
-    note_kernel("gemm_mixed_kernel", (int)grid);
-    gemm_mixed_kernel<<<dim3(grid), dim3(256), kLds, s>>>(b, (int)M);
-    return hipGetLastError();
-}
-
 hipError_t launch_gemm(const GemmProblem& p, int64_t M, hipStream_t s) {
     GemmMixed mixed;
     const GemmChoice choice = choose_kernel(&p, 1, M, mixed);
-    if (choice.mixed) return launch_mixed(mixed, M, s);
-    if (choice.pair_mixed) return launch_gemm_pair_mixed(mixed, M, s);
+    if (choice.mixed) return launch_gemm_pair_mixed(mixed, M, s);
     if (choice.pair) return launch_gemm_pair(&p, 1, M, choice.pair, s);
     if (choice.narrow) return launch_gemm_narrow(&p, 1, M, choice.narrow, s);
     const int64_t rows = (int64_t)p.row_blocks * kTileN;
-    const TileForm f = choose_tile(M, rows);
+    const TileForm f = choose_tile();
     const int64_t gx = (rows + f.wn * f.h * 32 - 1) / (f.wn * f.h * 32);
     const int64_t gy = (M + 32 * f.mb - 1) / (32 * f.mb);
     const int64_t wgs_total = (gx + kXcds - 1) / kXcds * kXcds * gy;
@@ -578,13 +537,10 @@ hipError_t launch_gemm_batch(const GemmProblem* ps, int count, int64_t M, hipStr
     if (count < 1 || count > kMaxGemmBatch) return hipErrorInvalidValue;
     GemmMixed mixed;
     const GemmChoice choice = choose_kernel(ps, count, M, mixed);
-    if (choice.mixed) return launch_mixed(mixed, M, s);
-    if (choice.pair_mixed) return launch_gemm_pair_mixed(mixed, M, s);
+    if (choice.mixed) return launch_gemm_pair_mixed(mixed, M, s);
     if (choice.pair) return launch_gemm_pair(ps, count, M, choice.pair, s);
     if (choice.narrow) return launch_gemm_narrow(ps, count, M, choice.narrow, s);
-    int64_t rows = 0;
-    for (int i = 0; i < count; ++i) rows += (int64_t)ps[i].row_blocks * kTileN;
-    const TileForm f = choose_tile(M, rows);
+    const TileForm f = choose_tile();
     GemmBatch b;
     int64_t gx = 0;
     for (int i = 0; i < kMaxGemmBatch; ++i) {

@@ -442,10 +442,12 @@ bool gemm_pair_form_exists(int code) {
     return false;
 }
 
-// 32-bit offsets: 64 rows of the output and of the activations, a row block's tiles.
+// 32-bit offsets: 64 rows of the output within 2^31 bytes.  (64 rows of the activations and a row block's tiles are far from it:
+// K is at most 2^20.)
+static_assert(BL_MAX_K <= 1 << 25, "64 activation rows within 2^31 bytes");
 bool gemm_pair_takes(const GemmProblem* ps, int count) {
     for (int i = 0; i < count; ++i)
-        if (ps[i].N > 1 << 23 || ps[i].KC > 1 << 19) return false;
+        if (ps[i].N > 1 << 23) return false;
     return true;
 }
 

@@ -174,7 +174,6 @@ int main(int argc, char** argv) {
     // every form launch_gemm / launch_gemm_batch can choose
     bad += sweep<1, 2, 1, 4>(old_tail, verbose);
     bad += sweep<1, 4, 1, 4>(old_tail, verbose);
-    bad += sweep<2, 1, 1, 4>(old_tail, verbose);   // the narrow tiles of the two-width kernel
     bad += sweep<2, 2, 1, 4>(old_tail, verbose);
     bad += sweep<2, 3, 1, 4>(old_tail, verbose);
     bad += sweep<2, 4, 1, 4>(old_tail, verbose);

@@ -760,7 +760,7 @@ def test_gemm_parity_two_tile_widths(dev, ops, M, ns):
     binding.bl_set_tuning("gemm_mb", 25)
     try:
         outs = ops.gemm_batch(pws, qa)
-        assert "gemm_mixed_kernel" in binding.bl_last_kernel()
+        assert "mixed_pair_gemm_kernel" in binding.bl_last_kernel()
         acc = ops.gemm(pws[0], qa, want_acc=True)[1]
         torch.cuda.synchronize()
     finally:
@@ -796,10 +796,10 @@ def test_gemm_two_tile_widths_only_with_one_narrow_tile_per_unit(dev, ops, M, K,
     pw = ops.pack_ternary(torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev), 0.02)
     qa = ops.quant_act(torch.randn((M, K), device=dev))
     try:
-        for code in (0, 25):
+        for code in (0, 25, 40025):
             binding.bl_set_tuning("gemm_mb", code)
             ops.gemm(pw, qa)
-            assert "gemm_mixed_kernel" not in binding.bl_last_kernel()
+            assert "mixed" not in binding.bl_last_kernel()
     finally:
         binding.bl_set_tuning("gemm_mb", 0)
 

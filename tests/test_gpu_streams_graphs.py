@@ -161,7 +161,7 @@ qa.a_scale.fill_(0.01)
 qa.q_sum.copy_(qa.q.sum(1, dtype=torch.int32))
 out = torch.empty(512, 11008, device=dev)
 captured_first("gemm 25", lambda: ops.gemm(pw, qa, out=out), out)
-assert "gemm_mixed_kernel" in B.bl_last_kernel()
+assert "mixed_pair_gemm_kernel" in B.bl_last_kernel()
 x, y, gamma = torch.randn(3, 5000, device=dev), torch.empty(3, 5000, device=dev), torch.rand(5000, device=dev)
 captured_first("norm", lambda: decoder.norm_quant(B.BL_NORM_PLAIN, gamma, a=x, y=y, quantize=False), y)
 print("all of them")
