@@ -873,15 +873,16 @@ def _launch_gemm(ops, pw, qa, out, acc):
 
 
 @pytest.mark.parametrize("K", [192, 64 * 30])
-@pytest.mark.parametrize("tile", [12, 14, 22, 23, 24, 122, 124])
+@pytest.mark.parametrize("tile", [12, 14, 22, 23, 24, 122, 124, 40022, 40021, 60021, 40121, 40012, 30024, 30023, 40025])
 def test_gemm_first_steps_under_load(dev, ops, tile, K):
     """Short K and enough workgroups to keep every compute unit's load queue busy, launched back to back: every launch
     must give the oracle's bits.  K = 192: the whole product is the kernel's first three steps (the waits of the
     activation ring's first stages, whose margin is the smallest when the memory system is busy).  K = 1920: 30 steps
     (15 with two K groups), i.e. three whole trips of the unrolled loop and a tail of six or seven steps, whose waits
-    count requests only."""
+    count requests only; of the forms on pairs of packed tiles 2 pairs (fewer than are requested ahead) and 15 (whole trips of
+    their loops, and a tail)."""
     from paper_2410_16144_amd import binding
-    M, N = 1024, 2048                  # 128 to 1024 workgroups depending on the tile
+    M, N = (1024, 2048) if tile != 40025 else (512, 11008)   # 128 to 1024 workgroups depending on the tile
     w, s, x = _problem(5000 + tile + K, M, K, N, p_zero=0.4, outl=0.01)
     q_ref, a_ref, s_ref = oracle.quant_act(x)
     acc_ref = torch.from_numpy(oracle.matmul_i32(q_ref, w)).to(dev)
@@ -909,7 +910,8 @@ def test_gemm_parity_every_paired_form(dev, ops, form):
     behind the output."""
     from paper_2410_16144_amd import binding
     mixed = form == 40025
-    shapes = (((512, 11008, 64), (500, 8640, 64 * 9)) if mixed else
+    name = "mixed_pair_gemm_kernel" if mixed else "pair_gemm_kernel<%d, %d, 4, %d, %d>" % (form // 10 % 10, form % 10, form // 100 % 100 + 1, form // 10000)
+    shapes = (((512, 11008, 64), (500, 8640, 64 * 9), (497, 11003, 64 * 31), (512, 8643, 64 * 30)) if mixed else
               ((1, 1, 64), (31, 33, 100), (32, 64, 128), (64, 128, 64 * 3), (65, 129, 64 * 7), (33, 257, 64 * 8), (63, 385, 64 * 9),
                (64, 513, 64 * 14), (130, 96, 64 * 22), (70, 600, 64 * 31), (129, 300, 1000)))
     for M, N, K in shapes:
@@ -917,7 +919,7 @@ def test_gemm_parity_every_paired_form(dev, ops, form):
         binding.bl_set_tuning("gemm_mb", form)
         try:
             _assert_product(ops, dev, "gemm", w, s, x)
-            assert "pair_gemm_kernel" in binding.bl_last_kernel()
+            assert binding.bl_last_kernel().startswith(name), (name, binding.bl_last_kernel())
             pw = ops.pack_ternary(torch.from_numpy(w).to(dev), float(s))
             qa = ops.quant_act(_to_dev_bf16(x, dev) if x.dtype == np.uint16 else torch.from_numpy(x).to(dev))
             behind = torch.full((M + 3, N), -7.0, device=dev)
@@ -932,7 +934,7 @@ def test_gemm_parity_every_paired_form(dev, ops, form):
     try:
         binding.bl_set_tuning("gemm_mb", form)
         together = ops.gemm_batch(pws, qa)
-        assert "pair_gemm_kernel" in binding.bl_last_kernel()
+        assert binding.bl_last_kernel().startswith(name)
         binding.bl_set_tuning("gemm_mb", 22)
         assert all(torch.equal(o, ops.gemm(pw, qa)) for o, pw in zip(together, pws))
     finally:

@@ -145,7 +145,7 @@ for d in (8, 36, 96, 128, 256):
         heads, d, pos0 + M, pos0, M, stream()), out)
 pw = ops.pack_ternary(torch.randint(-1, 2, (300, 1000), dtype=torch.int8, device=dev), 0.02)
 for M, form in ((9, 0), (40, 1016), (40, 1032), (40, 2016), (40, 2032), (40, 4032), (70, 4064), (70, 12), (70, 14), (70, 22), (70, 23),
-                (70, 24), (70, 122), (70, 124)):
+                (70, 24), (70, 122), (70, 124), (70, 40022), (70, 40021), (70, 60021), (70, 40121), (70, 40012), (70, 30024), (70, 30023)):
     qa = ops.alloc_quant(M, 1000, dev)
     qa.q.random_(-127, 128)
     qa.a_scale.fill_(0.01)

@@ -83,6 +83,17 @@ def _barriers(lines):
     return seq
 
 
+def _loops(lines):
+    """The bodies between a label and a branch back to it."""
+    at = {l.split(":")[0]: i for i, l in enumerate(lines) if l.startswith(".LBB")}
+    bodies = []
+    for i, l in enumerate(lines):
+        m = re.match(r"s_c?branch\w*\s+(\.LBB\w+)", l)
+        if m and at.get(m.group(1), i) < i:
+            bodies.append(lines[at[m.group(1)]:i])
+    return bodies
+
+
 def _compile_to_asm(tmp, name, extra=()):
     out = str(tmp / (name + ".s"))
     cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang",
@@ -181,26 +192,35 @@ def test_paired_kernels_waits_hold_and_one_operation_less_does_not(tmp_path):
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 def test_compiled_paired_kernels_issue_what_the_model_assumes(tmp_path):
-    """Between two barriers of the main loop: one step's requests, the wait that the header names, no other vector memory
-    operation."""
+    """The main loop of every form, and both of the two-width kernel, by its back edge: S steps, each with one step's requests, the
+    wait that the header names and a barrier; and no other vector memory operation behind the first request but the output's stores."""
     fns = _functions(_compile_to_asm(tmp_path, "bl_gemm_pair.hip"))
     seen = 0
     for name, lines in fns.items():
         m = re.search(r"pair_gemm_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d+)E", name)
-        if not m:
+        if m:
+            forms = [tuple(int(x) for x in m.groups())]
+        elif "mixed_pair_gemm_kernel" in name:
+            forms = [(2, 2, 4, 1, 4), (2, 1, 4, 1, 4)]
+        else:
             continue
         seen += 1
-        mb, h, wn, wk, s = (int(x) for x in m.groups())
-        per = h + 4 * mb // wn
-        younger = (s - 3) * per
-        # a main loop's steps: one wait of the header's count (two barriers of a tail's step are apart by a second wait, for 0)
-        steps = [b for b in _barriers(lines) if b[1] == per and b[0] == younger and b[2] == 0]
-        assert len(steps) >= s, (name, _barriers(lines))
+        # per form: S steps of H + 4 MB / WN requests and a wait that leaves the S - 3 steps requested last on their way
+        want = [[((s - 3) * (h + 4 * mb // wn), h + 4 * mb // wn, 0)] * s for mb, h, wn, wk, s in forms]
+        # (the main loop is straight code; a tail's steps, laid out in any order with branches between them, are not)
+        got = [_barriers(body) for body in _loops(lines)
+               if any(l.startswith("s_barrier") for l in body) and not any(re.match(r"s_c?branch", l) for l in body)]
+        assert sorted(got) == sorted(want), (name, got)
         # what the compiler sees is loaded before the first request (the scales) and nothing after it
-        first = next(i for i, l in enumerate(lines) if l.startswith("global_load_lds_dwordx4"))
-        for l in lines[first:]:
-            assert not re.match(r"(scratch_|flat_|global_store|global_atomic|buffer_load|global_load_dword(x2|x4)?\b)", l), (name, l)
-    assert seen == 7
+        requests = [i for i, l in enumerate(lines) if l.startswith("global_load_lds_dwordx4")]
+        others = [i for i, l in enumerate(lines) if re.match(r"(scratch_|flat_|global_store|global_atomic|buffer_load|global_load_dword(x2|x4)?\b)", l)]
+        if len(forms) == 1:
+            assert all(i < requests[0] for i in others), (name, [lines[i] for i in others])
+        else:   # two tiles' code, one behind the other: each loads its scales ahead of its own first request
+            assert not any(re.match(r"(scratch_|flat_|global_store|global_atomic|buffer_load)", lines[i]) for i in others), name
+            for body in _loops(lines):
+                assert not any(re.match(r"global_load_dword(x2|x4)?\b", l) for l in body if any(x.startswith("s_barrier") for x in body)), name
+    assert seen == 8
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
@@ -220,12 +240,7 @@ def test_compiled_token_attention_keeps_a_chunk_half_on_its_way(tmp_path):
         vecs = 64 * (maxd // w) // 256
         assert spills[name] == "0", (name, spills[name])
         load = "global_load_dwordx%d" % (w // 2)
-        starts = {l.split(":")[0]: i for i, l in enumerate(lines) if l.startswith(".LBB")}
-        bodies = []
-        for i, l in enumerate(lines):
-            b = re.match(r"s_cbranch_\w+ (\.LBB\w+)", l.replace("\t", " "))
-            if b and starts.get(b.group(1), i) < i and any(x.startswith(load) for x in lines[starts[b.group(1)]:i]):
-                bodies.append(lines[starts[b.group(1)]:i])
+        bodies = [body for body in _loops(lines) if any(l.startswith(load) for l in body)]
         walk = min(bodies, key=len)
         runs, waits, since = [], [], vecs
         for l in walk:
