@@ -272,13 +272,15 @@ hipError_t launch_narrow_form(const NarrowBatch& b, int M, int gx, hipStream_t s
 //     t = t0 + a KC + (X - 1) (e + s KC),   X = max(1, (x + ceil x) / 2),   x = workgroups / compute units
 // (KC = packed tiles along K; e: what a workgroup costs however short K is -- with it left out, 718 x 64 -> 6976 took 22.9 us here
 // where the tile kernel takes 8.5).  The workgroups are counted with the padding of the strips to a multiple of 8: a die
-// gets whole strips, and the die with the most is the one that ends last.
+// gets whole strips, and the die with the most is the one that ends last.  16 x 32: X = max(1, 0.35 x + 0.65 ceil x), from 8211 launches with weights
+// from memory and from the memory-side cache: with the common X and the line of the others' launches it was taken where a few units have
+// two workgroups (12 x 8320 -> 8704 10.2 us, 16 x 64 8.6).
 // Measured, tile kernel before -> this one: 3200^2 14.3 -> 4.7 us at 37 tokens, 12.0 -> 5.4 at 128, 12.2 -> 7.6 at 256;
 // 4096 -> 11008 16.6 -> 6.4 at 16, 18.9 -> 9.5 at 64, 17.0 -> 13.9 at 128; 11008 -> 4096 32.7 -> 8.1 at 16, 35 -> 10.4 at 64,
 // 37.7 -> 15.8 at 256, 38.4 -> 25.1 at 512.  Also tried: four or sixteen waves along K, 48-token blocks, three or four steps in
 // flight, and weights straight into registers -- none ahead of the best of these six by more than 5 % anywhere.
 #define BL_NARROW_FORMS(X)                           \
-    X(16, 1, 8, 2, 3.09f, 0.0203f, 0.506f, 0.0171f)  \
+    X(16, 1, 8, 2, 2.98f, 0.0223f, 0.500f, 0.0166f)  \
     X(16, 2, 8, 2, 3.30f, 0.0306f, 0.900f, 0.0281f)  \
     X(32, 1, 8, 2, 3.27f, 0.0244f, 0.868f, 0.0238f)  \
     X(32, 2, 8, 1, 3.57f, 0.0296f, 1.128f, 0.0336f)  \
@@ -314,7 +316,8 @@ int gemm_narrow_best(const GemmProblem* ps, int count, int64_t M, int cus, float
         int64_t strips = 0;
         for (int i = 0; i < count; ++i) strips += strips_of(ps[i], rh);
         const int64_t wgs = (strips + kXcds - 1) / kXcds * kXcds * ((M + t - 1) / t);
-        const float x = (float)wgs / (float)cus, turns = 0.5f * (x + (float)((wgs + cus - 1) / cus));
+        const float x = (float)wgs / (float)cus, whole = (float)((wgs + cus - 1) / cus);
+        const float turns = x + (t == 16 && rh == 1 ? 0.65f : 0.5f) * (whole - x);
         const float est = t0 + a * (float)KC + (turns > 1.0f ? turns - 1.0f : 0.0f) * (each + slope * (float)KC);
         if (!best || est < us) { best = narrow_code(t, rh); us = est; }
     };

@@ -422,6 +422,9 @@ constexpr int pair_code(int mb, int h, int wk, int s) { return 10000 * s + 100 *
 // with the N positions padded to a multiple of 8 (a die gets whole positions):
 //     x <= 1:  t0 + a KC + e x      x <= 2:  t1 + b KC + (x - 1) (f + c KC)      beyond:  t2 + d KC x + g x + h KC
 // Eight in ten estimates lie within 7 % of the measured time (64 x 384 and 64 x 512 beyond two workgroups per unit: 18 %).
+// 64 x 384 and 64 x 512 are not taken with at most one workgroup per unit and more than two tiles along K: there one wave per SIMD waits
+// for weights that come from memory, the lines fall short by up to a quarter, and of 8211 further launches they were ahead on one, by 3 %
+// (483 x 5888 -> 15168: 64 x 512 47.3 us, estimated 34; 64 x 256 40.7; 1978 x 6080 -> 3392 48.6 and 39.9).
 struct PairLine { int code, bm, bn; float t0, a, e, t1, b, f, c, t2, d, g, h; };
 constexpr PairLine kPairLines[] = {
     {pair_code(2, 2, 1, 4), 64, 256, 4.16f, 0.1469f, 1.55f, 5.27f, 0.2837f, 1.12f, 0.0366f, 3.24f, 0.1351f, 2.36f, 0.1218f},
@@ -459,6 +462,7 @@ int gemm_pair_best(const GemmProblem* ps, int count, int64_t M, int cus, float& 
         int64_t gx = 0;
         for (int i = 0; i < count; ++i) gx += ((int64_t)ps[i].row_blocks * kTileN + l.bn - 1) / l.bn;
         const float x = (float)((gx + kXcds - 1) / kXcds * kXcds * ((M + l.bm - 1) / l.bm)) / (float)cus;
+        if (x <= 1.0f && l.bn > 256 && KC > 2) continue;
         const float est = x <= 1.0f ? l.t0 + l.a * k + l.e * x
                         : x <= 2.0f ? l.t1 + l.b * k + (x - 1.0f) * (l.f + l.c * k)
                                     : l.t2 + l.d * k * x + l.g * x + l.h * k;

@@ -788,6 +788,24 @@ def test_gemm_short_k_takes_tiles(dev, ops, M, K, N):
         binding.bl_set_tuning("gemm_mb", 0)
 
 
+@pytest.mark.parametrize("M,K,N,kernel", [(483, 5888, 15168, "pair_gemm_kernel<2, 2,"), (1978, 6080, 3392, "pair_gemm_kernel<2, 2,"),
+                                          (12, 8320, 8704, "gemm_narrow_kernel<16, 2,")])
+def test_gemm_choice_with_weights_from_memory(dev, ops, M, K, N, kernel):
+    """Shapes where the estimated times once fell short by a quarter: tiles wider than 256 rows with at most one workgroup per
+    unit, and the narrowest form for few tokens where a few units have two workgroups."""
+    from paper_2410_16144_amd import binding
+    g = torch.Generator(dev).manual_seed(M)
+    pw = ops.pack_ternary(torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev, generator=g), 0.02)
+    qa = ops.quant_act(torch.randn((M, K), device=dev, generator=g))
+    out = ops.gemm(pw, qa)
+    assert binding.bl_last_kernel().startswith(kernel), binding.bl_last_kernel()
+    binding.bl_set_tuning("gemm_mb", 22)
+    try:
+        assert torch.equal(out, ops.gemm(pw, qa))
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)
+
+
 @pytest.mark.parametrize("M,K,N", [(807, 5760, 6272), (1535, 3392, 3200), (1626, 5952, 3200)])
 def test_gemm_two_tile_widths_only_with_one_narrow_tile_per_unit(dev, ops, M, K, N):
     """Narrow positions that are no multiple of 8 give one die more tiles than it has units: not the two-width kernel, also when
