@@ -102,11 +102,6 @@ struct PromptLds {
     static_assert(kRows * 64 * KS <= kTile, "a set's V tile holds its share of the queries");
 };
 
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 template <int KS, int SETS>
 __global__ __launch_bounds__(64 * SETS, SETS == 4 ? 2 : 1) void attn_prompt_kernel(const PromptArgs p) {
     using L = PromptLds<KS, SETS>;

@@ -1262,8 +1262,8 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     else kv_append_kernel<<<dim3((unsigned)a.M), dim3(256), 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // head sizes up to 128 take a matrix-core kernel (a block of 64 tokens per workgroup): the one of bl_attn_prompt.hip where
-    // a cache row's head is whole 16-byte pieces, else the one of this file; larger ones go token by token
+    // head sizes up to 128 take a matrix-core kernel: the one of bl_attn_prompt.hip (32 tokens per workgroup) where a cache row's
+    // head is whole 16-byte pieces, else the one of this file (64 tokens); larger ones go token by token
     if (attn_prompt_takes(a.n_heads, a.head_dim)) return launch_attn_prompt(a, s);
     static_assert(BL_ATTN_BLOCK_MAX_HEAD_DIM == 128, "the dispatch below covers head sizes up to 8 sixteens");
     switch ((a.head_dim + 15) / 16) {

@@ -40,8 +40,6 @@ namespace {
 
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kXcds = 8;   // workgroup i runs on accelerator die i % 8, each die with its own L2
-
 // Dynamic LDS of one form: the activation ring (reused for the K groups' final exchange), then the workgroup's per-token
 // scales and sums.
 template <int MB, int H, int WK, int WN>
@@ -340,17 +338,6 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const int M, con
             }
         }
     }
-}
-
-// Workgroup index -> tile, so that the die (index % 8) depends on the N position only: every die keeps ITS slice of
-// the packed weights in its L2 for the whole launch, and consecutive workgroups (all dies) walk through the same
-// token rows at the same time.  The grid is padded to a multiple of 8 along N; false for a padding workgroup.
-__device__ __forceinline__ bool tile_of_workgroup(int wg, int gx, int& tile_x, int& tile_y) {
-    const int gxh = (gx + kXcds - 1) / kXcds;
-    const int rest = wg / kXcds;
-    tile_x = (rest % gxh) * kXcds + wg % kXcds;
-    tile_y = rest / gxh;
-    return tile_x < gx;
 }
 
 template <int MB, int H, int WK, int WN>

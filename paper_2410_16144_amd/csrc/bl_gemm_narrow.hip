@@ -30,8 +30,6 @@ namespace {
 
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kXcds = 8;   // workgroup i runs on accelerator die i % 8, each die with its own L2
-
 // Up to four products over the same tokens: their strips side by side, `end[i]` the first strip behind product i
 // (INT32_MAX behind the last one in use).
 struct NarrowBatch {
@@ -58,18 +56,13 @@ struct NarrowForm {
     static_assert(kLds <= kMaxDecodeLds, "fits the LDS ceiling");
 };
 
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 template <int T, int RH, int W, int D>
 __global__ __launch_bounds__(64 * W) void gemm_narrow_kernel(const NarrowBatch b, const int M, const int gx) {
     using F = NarrowForm<T, RH, W, D>;
     constexpr int MB = F::kMB;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
-    // workgroup -> (strip, token block): the die depends on the strip only, as in bl_gemm.hip
+    // workgroup -> (strip, token block): the die depends on the strip only, as in tile_of_workgroup
     const int gxh = (gx + kXcds - 1) / kXcds;
     const int rest = blockIdx.x / kXcds;
     int strip = (rest % gxh) * kXcds + blockIdx.x % kXcds;

@@ -36,13 +36,6 @@ namespace {
 
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kXcds = 8;   // workgroup i runs on accelerator die i % 8, each die with its own L2
-
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 template <int N, int I = 0, typename Fn>
 __device__ __forceinline__ void unroll(Fn&& f) {
     if constexpr (I < N) {
@@ -351,15 +344,6 @@ __device__ __forceinline__ void pair_tile(const GemmProblem& p, const int M, con
     };
     store(p.out, std::false_type{});
     if (p.acc) store(p.acc, std::true_type{});
-}
-
-// Workgroup index -> tile, as in bl_gemm.hip: the die (index % 8) depends on the N position only.
-__device__ __forceinline__ bool tile_of_workgroup(int wg, int gx, int& tile_x, int& tile_y) {
-    const int gxh = (gx + kXcds - 1) / kXcds;
-    const int rest = wg / kXcds;
-    tile_x = (rest % gxh) * kXcds + wg % kXcds;
-    tile_y = rest / gxh;
-    return tile_x < gx;
 }
 
 struct PairBatch {

@@ -62,6 +62,25 @@ __device__ __forceinline__ void load_to_lds(uint32_t dst, const uint32_t (&off)[
 }
 #pragma clang diagnostic pop
 
+// Until at most N of the wave's vector memory operations are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+constexpr int kXcds = 8;   // workgroup i runs on accelerator die i % 8, each die with its own L2
+
+// Workgroup index -> tile, so that the die (index % 8) depends on the N position only: every die keeps ITS slice of
+// the packed weights in its L2 for the whole launch, and consecutive workgroups (all dies) walk through the same
+// token rows at the same time.  The grid is padded to a multiple of 8 along N; false for a padding workgroup.
+__device__ __forceinline__ bool tile_of_workgroup(int wg, int gx, int& tile_x, int& tile_y) {
+    const int gxh = (gx + kXcds - 1) / kXcds;
+    const int rest = wg / kXcds;
+    tile_x = (rest % gxh) * kXcds + wg % kXcds;
+    tile_y = rest / gxh;
+    return tile_x < gx;
+}
+
 // One prefill product as the kernel sees it (all device pointers).
 struct GemmProblem {
     const uint4*   packed;
