@@ -386,7 +386,7 @@ bl_status bl_tl2_gemv_batch(const bl_gemv_item *items, int32_t count, void *work
  * bl_decode_batch), -1 = never; "decode_wait_limit" = polls before a waiting workgroup of that form gives up (0 = the default, 262144);
  * "decode_stream" = how the decode kernels load weight tiles: 0 automatic (streaming, i.e. nontemporal, loads for launches of
  * 4 MiB of packed weights and more; ordinary loads below, so that a small model may stay in the memory-side cache), 1 always streaming, -1 never;
- * "attn_groups" = workgroups per head of bl_attn_decode (0 = automatic, else 1..65535, capped at the cache's chunks -- less one for caches of more chunks than the automatic count) -- the one
+ * "attn_groups" = workgroups per head of bl_attn_decode, and of bl_attn_prefill for head sizes above 128 (0 = automatic, else 1..65535, capped at the cache's chunks -- less one for caches of more chunks than the automatic count) -- the one
  * key that moves results, within that call's tolerance: it decides which chunks are folded together before the merge.
  * Errors: BL_ERR_NULL, BL_ERR_SHAPE (unknown key/value).
  */
