@@ -60,6 +60,11 @@ __device__ __forceinline__ void load_to_lds(uint32_t dst, const uint32_t (&off)[
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off[r]), "s"(src[r]) : "memory", "m0");
     }
 }
+// One such piece, at src + off + kOffset (also the place behind dst): for requests that stand between products.
+template <int kOffset>
+__device__ __forceinline__ void load_piece_to_lds(uint32_t dst, uint32_t off, const uint8_t* src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(dst), "v"(off), "s"(src), "n"(kOffset) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 // Until at most N of the wave's vector memory operations are outstanding.
