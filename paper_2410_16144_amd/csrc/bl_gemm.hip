@@ -434,13 +434,16 @@ bool plan_mixed(const GemmProblem* ps, int count, int64_t M, GemmMixed& b) {
 // form by more than 2 % on 40, nearly all of them with 64 or 128 weight rows.  Beyond 2^23 rows they are ahead of the forms for few
 // tokens as well, whose workgroups are many and short there (2^23 + 64 rows, K = 1024, us, 64 x 128 wave tiles and the best of those
 // forms: 9 tokens 507 and 679, 16 535 and 717, 32 639 and 828, 64 820 and 1623; K = 64, 16 tokens 151 and 517).
-struct GemmChoice { int narrow = 0, pair = 0; bool mixed = false; };
+struct GemmChoice { int narrow = 0, pair = 0, halves = 0; bool mixed = false; };
 
 GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed& mixed) {
     GemmChoice c;
     const bool narrow_ok = gemm_narrow_takes(ps, count, M), pair_ok = gemm_pair_takes(ps, count);
     if (g_force_mb && !forced_mixed()) {
-        if (gemm_pair_form_exists(g_force_mb)) c.pair = pair_ok ? g_force_mb : 0;
+        if (gemm_pair_form_exists(g_force_mb)) {
+            c.pair = pair_ok ? g_force_mb : 0;
+            c.halves = c.pair ? gemm_pair_halves(ps, count, M, c.pair) : 0;
+        }
         else if (gemm_narrow_form_exists(g_force_mb)) c.narrow = narrow_ok ? g_force_mb : 0;
         return c;
     }
@@ -450,7 +453,7 @@ GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed&
     if (c.mixed) return c;
     const int found = compute_unit_count(), cus = found > 0 ? found : 256;
     float best = 0.0f;
-    c.pair = gemm_pair_best(ps, count, M, cus, best);
+    c.pair = gemm_pair_best(ps, count, M, cus, best, c.halves);
     if (mixed_ok) {
         const float share = (float)((mixed.small_gx + kXcds - 1) / kXcds * kXcds * ((M + 63) / 64)) / (float)cus;
         int KC = 0;
@@ -501,7 +504,7 @@ hipError_t launch_gemm(const GemmProblem& p, int64_t M, hipStream_t s) {
     GemmMixed mixed;
     const GemmChoice choice = choose_kernel(&p, 1, M, mixed);
     if (choice.mixed) return launch_gemm_pair_mixed(mixed, M, s);
-    if (choice.pair) return launch_gemm_pair(&p, 1, M, choice.pair, s);
+    if (choice.pair) return launch_gemm_pair(&p, 1, M, choice.pair, choice.halves, s);
     if (choice.narrow) return launch_gemm_narrow(&p, 1, M, choice.narrow, s);
     const int64_t rows = (int64_t)p.row_blocks * kTileN;
     const TileForm f = choose_tile();
@@ -525,7 +528,7 @@ hipError_t launch_gemm_batch(const GemmProblem* ps, int count, int64_t M, hipStr
     GemmMixed mixed;
     const GemmChoice choice = choose_kernel(ps, count, M, mixed);
     if (choice.mixed) return launch_gemm_pair_mixed(mixed, M, s);
-    if (choice.pair) return launch_gemm_pair(ps, count, M, choice.pair, s);
+    if (choice.pair) return launch_gemm_pair(ps, count, M, choice.pair, choice.halves, s);
     if (choice.narrow) return launch_gemm_narrow(ps, count, M, choice.narrow, s);
     const TileForm f = choose_tile();
     GemmBatch b;

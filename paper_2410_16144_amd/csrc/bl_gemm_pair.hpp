@@ -1,5 +1,6 @@
 // The paired-tile kernel of bl_gemm as a template: a workgroup's tile, the launch of one form.  What it does and what bounds it stand in
-// bl_gemm_pair.hip, which builds the forms and chooses.
+// bl_gemm_pair.hip, which builds the forms for any number of tokens and chooses; bl_gemm_pair_wide.hip builds those of one workgroup
+// per compute unit.
 #pragma once
 #include <type_traits>
 
@@ -316,9 +317,9 @@ struct PairBatch {
 };
 
 template <int MB, int H, int WN, int WK, int S>
-__global__ __launch_bounds__(64 * WN * WK, WN * WK == 4 ? 2 : 1) void pair_gemm_kernel(const PairBatch b, const int M, const int gx) {
+__global__ __launch_bounds__(64 * WN * WK, WN * WK == 4 ? 2 : 1) void pair_gemm_kernel(const PairBatch b, const int M, const int gx, const int halves) {
     int tile_x, tile_y;
-    if (!tile_of_workgroup(blockIdx.x, gx, tile_x, tile_y)) return;   // uniform
+    if (!tile_of_workgroup(blockIdx.x, gx, (M + 32 * MB - 1) / (32 * MB), halves, tile_x, tile_y)) return;   // uniform
     int item = 0, first = 0;
 #pragma unroll
     for (int i = 0; i + 1 < kMaxGemmBatch; ++i)
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(64 * WN * WK, WN * WK == 4 ? 2 : 1) void pair_gemm_
 }
 
 template <int MB, int H, int WN, int WK, int S>
-hipError_t launch_pair_form(const GemmProblem* ps, int count, int64_t M, hipStream_t s) {
+hipError_t launch_pair_form(const GemmProblem* ps, int count, int64_t M, int halves, hipStream_t s) {
     using F = PairForm<MB, H, WN, WK, S>;
     PairBatch b;
     int64_t gx = 0;
@@ -336,13 +337,13 @@ hipError_t launch_pair_form(const GemmProblem* ps, int count, int64_t M, hipStre
         if (i < count) gx += ((int64_t)ps[i].row_blocks * kTileN + WN * H * 32 - 1) / (WN * H * 32);
         b.end[i] = i + 1 < count ? (int32_t)gx : INT32_MAX;
     }
-    const int64_t wgs = (gx + kXcds - 1) / kXcds * kXcds * ((M + 32 * MB - 1) / (32 * MB));
+    const int64_t wgs = gemm_padded_tiles(gx, (M + 32 * MB - 1) / (32 * MB), halves);
     if (wgs > INT32_MAX) return hipErrorInvalidValue;
     static LdsCeiling ceiling;
     const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(&pair_gemm_kernel<MB, H, WN, WK, S>), F::kLds);
     if (e != hipSuccess) return e;
     note_kernel("pair_gemm_kernel<%d, %d, %d, %d, %d>", (int)wgs, MB, H, WN, WK, S);
-    pair_gemm_kernel<MB, H, WN, WK, S><<<dim3((unsigned)wgs), dim3(64 * WN * WK), F::kLds, s>>>(b, (int)M, (int)gx);
+    pair_gemm_kernel<MB, H, WN, WK, S><<<dim3((unsigned)wgs), dim3(64 * WN * WK), F::kLds, s>>>(b, (int)M, (int)gx, halves);
     return hipGetLastError();
 }
 

@@ -72,6 +72,9 @@ struct PairRing {
 #define BL_PAIR_FORMS(X) \
     X(2, 2, 4, 1, 4) X(2, 1, 4, 1, 4) X(2, 1, 4, 1, 6) X(2, 1, 4, 2, 4) X(1, 2, 4, 1, 4) X(2, 4, 4, 1, 3) X(2, 3, 4, 1, 3)
 
+// ... of bl_gemm_pair_wide.hip, one workgroup per compute unit:
+#define BL_PAIR_WIDE_FORMS(X) X(4, 2, 4, 1, 4) X(2, 3, 4, 1, 4)
+
 // The matrix-core decode kernel's one-off copy of the quantized activations into LDS (bl_gemv.hip, QMODE 1): the copy's
 // global -> LDS loads are issued first, then one batch of U weight tiles; the wait that precedes the barrier allows
 // exactly those U loads to be outstanding.

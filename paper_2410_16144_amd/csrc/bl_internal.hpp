@@ -86,6 +86,16 @@ __device__ __forceinline__ bool tile_of_workgroup(int wg, int gx, int& tile_x, i
     return tile_x < gx;
 }
 
+// The same with the dies in two halves (halves = 1): dies 0-3 take the even token tiles, dies 4-7 the odd ones, and the N positions go
+// by die % 4.  A die then fetches half of the tokens and twice the weights.
+__device__ __forceinline__ bool tile_of_workgroup(int wg, int gx, int gy, int halves, int& tile_x, int& tile_y) {
+    const int columns = kXcds >> halves, die = wg % kXcds, gxh = (gx + columns - 1) / columns;
+    const int rest = wg / kXcds;
+    tile_x = (rest % gxh) * columns + die % columns;
+    tile_y = ((rest / gxh) << halves) + die / columns;
+    return tile_x < gx && tile_y < gy;
+}
+
 // One prefill product as the kernel sees it (all device pointers).
 struct GemmProblem {
     const uint4*   packed;
@@ -245,11 +255,19 @@ struct GemmMixed {
     int32_t     small_first[kMaxGemmBatch];  // product i's first 128-row position in its own rows
     int32_t     gx, wgs, small_gx;           // 256-row positions and their workgroups; 128-row positions
 };
+// Workgroups of a launch of gx x gy tiles with the padding of tile_of_workgroup.
+inline int64_t gemm_padded_tiles(int64_t gx, int64_t gy, int halves) {
+    const int64_t columns = kXcds >> halves, rows = 1 << halves;
+    return (gx + columns - 1) / columns * columns * ((gy + rows - 1) / rows * rows);
+}
 // bl_gemm with paired packed tiles (bl_gemm_pair.hip); a form's code is 10000 * stages + 100 * (waves along K - 1) + 10 * MB + H
 bool gemm_pair_form_exists(int code);
 bool gemm_pair_takes(const GemmProblem* ps, int count);
-int gemm_pair_best(const GemmProblem* ps, int count, int64_t M, int cus, float& us);   // the form with the smallest estimate
-hipError_t launch_gemm_pair(const GemmProblem* ps, int count, int64_t M, int code, hipStream_t s);
+// the form with the smallest estimate, and whether its launch splits the dies over the tokens
+int gemm_pair_best(const GemmProblem* ps, int count, int64_t M, int cus, float& us, int& halves);
+int gemm_pair_halves(const GemmProblem* ps, int count, int64_t M, int code);   // the same for a form that is asked for
+hipError_t launch_gemm_pair(const GemmProblem* ps, int count, int64_t M, int code, int halves, hipStream_t s);
+hipError_t launch_gemm_pair_wide(const GemmProblem* ps, int count, int64_t M, int code, int halves, hipStream_t s);   // bl_gemm_pair_wide.hip
 hipError_t launch_gemm_pair_mixed(const GemmMixed& b, int64_t M, hipStream_t s);
 hipError_t launch_tl2_pack(const int8_t* w, int64_t N, int64_t K, int64_t Np, int64_t Kp, uint32_t* packed,
                            int32_t* bad_count, hipStream_t s);

@@ -97,6 +97,7 @@ int main(int argc, char** argv) {
     int bad = 0;
 #define X(MB, H, WN, WK, S) bad += run<MB, H, WN, WK, S>(slack);
     BL_PAIR_FORMS(X)
+    BL_PAIR_WIDE_FORMS(X)
 #undef X
     printf("%d failing cases\n", bad);
     return bad ? 1 : 0;

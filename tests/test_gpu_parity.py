@@ -957,3 +957,52 @@ def test_gemm_parity_every_paired_form(dev, ops, form):
         assert all(torch.equal(o, ops.gemm(pw, qa)) for o, pw in zip(together, pws))
     finally:
         binding.bl_set_tuning("gemm_mb", 0)
+
+
+@pytest.mark.parametrize("form", [40042, 40023])
+def test_gemm_paired_forms_of_one_workgroup_per_unit(dev, ops, form):
+    """128 x 256 and 64 x 384 tiles with four stages: the edges of their tiles and of their pipeline, and their first steps under load."""
+    test_gemm_parity_every_paired_form(dev, ops, form)
+    for K in (192, 64 * 30):
+        test_gemm_first_steps_under_load(dev, ops, form, K)
+
+
+@pytest.mark.parametrize("form,bm,bn", [(40022, 64, 256), (40021, 64, 128), (40012, 32, 256), (40023, 64, 384), (40042, 128, 256)])
+@pytest.mark.parametrize("tiles_m,tiles_n,K,halves", [
+    (1, 8, 128, 0), (2, 8, 128, 0), (1, 4, 128, 0), (2, 4, 128, 1), (3, 4, 128, 1), (5, 3, 192, 1), (4, 9, 128, 1), (2, 13, 128, 0),
+    (3, 1, 64, 1), (16, 1, 64 * 70, 1)])
+def test_gemm_dies_split_over_the_tokens(dev, ops, form, bm, bn, tiles_m, tiles_n, K, halves):
+    """Both mappings of workgroups to tiles: one, odd and even numbers of token tiles, positions that fill the dies, their halves or
+    neither.  The grid says which mapping ran; the sums are those of another kernel."""
+    from paper_2410_16144_amd import binding
+    M, N = bm * tiles_m - 3, bn * tiles_n - 70
+    g = torch.Generator(dev).manual_seed(M + N)
+    pw = ops.pack_ternary(torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev, generator=g), 0.02)
+    qa = ops.quant_act(torch.randn((M, K), device=dev, generator=g))
+    try:
+        binding.bl_set_tuning("gemm_mb", form)
+        out, acc = ops.gemm(pw, qa, want_acc=True)
+        grid = int(binding.bl_last_kernel().split("grid=")[1].split()[0])
+        whole, split = -(-tiles_n // 8) * 8 * tiles_m, -(-tiles_n // 4) * 4 * (-(-tiles_m // 2) * 2)
+        assert split < whole if halves else split >= whole
+        assert grid == (split if halves else whole)
+        binding.bl_set_tuning("gemm_mb", 22)
+        ref, ref_acc = ops.gemm(pw, qa, want_acc=True)
+        assert torch.equal(acc, ref_acc) and torch.equal(out, ref)
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)
+
+
+def test_gemm_dies_split_for_fewer_bytes(dev, ops):
+    """As many tiles either way, and more tokens than a die's cache holds."""
+    from paper_2410_16144_amd import binding
+    M, K, N = 2048, 2048, 2048
+    pw = ops.pack_ternary(torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev), 0.02)
+    qa = ops.quant_act(torch.randn((M, K), device=dev))
+    try:
+        binding.bl_set_tuning("gemm_mb", 40022)
+        out = ops.gemm(pw, qa)
+        binding.bl_set_tuning("gemm_mb", 22)
+        assert torch.equal(out, ops.gemm(pw, qa))
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)

@@ -224,6 +224,28 @@ def test_compiled_paired_kernels_issue_what_the_model_assumes(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_compiled_paired_kernels_of_one_workgroup_per_unit_issue_what_the_model_assumes(tmp_path):
+    """bl_gemm_pair_wide.hip, looked at as the paired kernels above: S steps per trip, each with one step's requests, the header's
+    wait and a barrier, and nothing else behind the first request but the output's stores."""
+    fns = _functions(_compile_to_asm(tmp_path, "bl_gemm_pair_wide.hip"))
+    seen = 0
+    for name, lines in fns.items():
+        m = re.search(r"pair_gemm_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d+)E", name)
+        if not m:
+            continue
+        seen += 1
+        mb, h, wn, wk, s = (int(x) for x in m.groups())
+        want = [((s - 3) * (h + 4 * mb // wn), h + 4 * mb // wn, 0)] * s
+        got = [_barriers(body) for body in _loops(lines)
+               if any(l.startswith("s_barrier") for l in body) and not any(re.match(r"s_c?branch", l) for l in body)]
+        assert got == [want], (name, got)
+        requests = [i for i, l in enumerate(lines) if l.startswith("global_load_lds_dwordx4")]
+        others = [i for i, l in enumerate(lines) if re.match(r"(scratch_|flat_|global_store|global_atomic|buffer_load|global_load_dword(x2|x4)?\b)", l)]
+        assert all(i < requests[0] for i in others), (name, [lines[i] for i in others])
+    assert seen == 2
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 def test_compiled_token_attention_keeps_a_chunk_half_on_its_way(tmp_path):
     """bl_decoder.hip's walk over the cache: a loop with one run of requests for the next keys and one for the next values, kVecs
     each, in which no wait is for fewer than the kVecs requests issued last; and no instance spills a register."""
