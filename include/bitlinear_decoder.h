@@ -263,6 +263,30 @@ uint64_t bl_attn_prefill_scratch_bytes(int32_t n_heads, int32_t head_dim, int32_
 
 bl_status bl_attn_prefill(const bl_attn_prefill_args *args, void *stream);
 
+/*
+ * A model's last norm, y = rmsnorm(h + delta, gamma) without a quantizer (bl_norm_quant's arithmetic in mode
+ * BL_NORM_RESIDUAL, the same bits), and the step of the token position in the same launch.
+ *   h_dev, y_dev   [M, K] fp32; delta_dev optional
+ *   h_out_dev      optional [M, K]: receives h + delta if there is a delta.  May be h_dev.
+ *   pos_dev        optional: *pos_dev becomes pos_set or, if that is negative, one more
+ * 1 <= K <= BL_NORM_MAX_K, M >= 1.
+ * Errors: BL_ERR_NULL (h, gamma or y), BL_ERR_SHAPE, BL_ERR_ALIGN (4 bytes), BL_ERR_HIP.
+ */
+typedef struct bl_final_norm_args {
+    const float *h_dev;
+    const float *delta_dev;
+    float       *h_out_dev;
+    const float *gamma_dev;
+    float       *y_dev;
+    int64_t      K;
+    int32_t      M;
+    float        eps;
+    int32_t     *pos_dev;
+    int32_t      pos_set;
+} bl_final_norm_args;
+
+bl_status bl_final_norm(const bl_final_norm_args *args, void *stream);
+
 /* *pos_dev += 1 on the device (one thread), so that the token loop's position lives in the
  * graph's own memory.  Errors: BL_ERR_NULL, BL_ERR_ALIGN, BL_ERR_HIP. */
 bl_status bl_pos_advance(int32_t *pos_dev, void *stream);

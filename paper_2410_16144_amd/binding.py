@@ -35,7 +35,7 @@ DECLARED_SYMBOLS = (
     "bl_padded_k", "bl_padded_n", "bl_packed_desc_init", "bl_pack_ternary", "bl_unpack_ternary",
     "bl_quant_act", "bl_quant_act_batch", "bl_gemv", "bl_gemv_batch", "bl_gemv_batch_static", "bl_decode_batch", "bl_gemm", "bl_gemm_batch", "bl_set_tuning", "bl_get_stat", "bl_status_str", "bl_last_hip_error", "bl_last_kernel", "bl_version",
     "bl_tl2_padded_k", "bl_tl2_desc_init", "bl_tl2_pack", "bl_tl2_unpack", "bl_tl2_gemv", "bl_tl2_gemv_batch",
-    "bl_norm_quant", "bl_rope_table", "bl_attn_scratch_bytes", "bl_attn_decode", "bl_pos_advance", "bl_decode_norm_batch", "bl_pack_gate_up", "bl_attn_prefill", "bl_attn_prefill_scratch_bytes",
+    "bl_norm_quant", "bl_final_norm", "bl_rope_table", "bl_attn_scratch_bytes", "bl_attn_decode", "bl_pos_advance", "bl_decode_norm_batch", "bl_pack_gate_up", "bl_attn_prefill", "bl_attn_prefill_scratch_bytes",
 )
 
 BL_NORM_MAX_K = 49152
@@ -92,6 +92,13 @@ class NormQuantArgs(ctypes.Structure):
                 ("gamma_dev", ctypes.c_void_p), ("eps", ctypes.c_float), ("q_dev", ctypes.c_void_p),
                 ("a_scale_dev", ctypes.c_void_p), ("q_sum_dev", ctypes.c_void_p), ("y_dev", ctypes.c_void_p),
                 ("scratch_dev", ctypes.c_void_p), ("pieces", ctypes.c_int32)]
+
+
+class FinalNormArgs(ctypes.Structure):
+    """Mirror of bl_final_norm_args."""
+    _fields_ = [("h_dev", ctypes.c_void_p), ("delta_dev", ctypes.c_void_p), ("h_out_dev", ctypes.c_void_p),
+                ("gamma_dev", ctypes.c_void_p), ("y_dev", ctypes.c_void_p), ("K", ctypes.c_int64), ("M", ctypes.c_int32),
+                ("eps", ctypes.c_float), ("pos_dev", ctypes.c_void_p), ("pos_set", ctypes.c_int32)]
 
 
 class AttnArgs(ctypes.Structure):
@@ -162,6 +169,7 @@ def lib():
     l.bl_tl2_gemv.argtypes = [vp, dp, vp, vp, vp, vp, vp]
     l.bl_tl2_gemv_batch.argtypes = [ctypes.POINTER(GemvItem), i32, vp, vp]
     l.bl_norm_quant.argtypes = [ctypes.POINTER(NormQuantArgs), vp]
+    l.bl_final_norm.argtypes = [ctypes.POINTER(FinalNormArgs), vp]
     l.bl_rope_table.argtypes = [vp, i32, i32, ctypes.c_double, vp]
     l.bl_attn_scratch_bytes.argtypes = [i32, i32, i32]
     l.bl_attn_scratch_bytes.restype = ctypes.c_uint64
@@ -181,7 +189,7 @@ def lib():
     l.bl_last_kernel.restype = ctypes.c_char_p
     for name in ("bl_packed_desc_init", "bl_pack_ternary", "bl_unpack_ternary", "bl_quant_act", "bl_quant_act_batch", "bl_gemv",
                  "bl_gemv_batch", "bl_decode_batch", "bl_gemm", "bl_set_tuning", "bl_tl2_desc_init", "bl_tl2_pack",
-                 "bl_tl2_unpack", "bl_tl2_gemv", "bl_tl2_gemv_batch", "bl_norm_quant", "bl_rope_table", "bl_attn_decode",
+                 "bl_tl2_unpack", "bl_tl2_gemv", "bl_tl2_gemv_batch", "bl_norm_quant", "bl_final_norm", "bl_rope_table", "bl_attn_decode",
                  "bl_pos_advance", "bl_decode_norm_batch", "bl_attn_prefill", "bl_gemm_batch", "bl_gemv_batch_static", "bl_pack_gate_up"):
         getattr(l, name).restype = ctypes.c_int
     _lib = l
@@ -399,6 +407,10 @@ def make_norm_quant_args(mode: int, M: int, K: int, gamma_dev: int, eps: float, 
 
 def bl_norm_quant(args: NormQuantArgs, stream: int = 0):
     _check(lib().bl_norm_quant(ctypes.byref(args), stream), "bl_norm_quant")
+
+
+def bl_final_norm(args: FinalNormArgs, stream: int = 0):
+    _check(lib().bl_final_norm(ctypes.byref(args), stream), "bl_final_norm")
 
 
 def bl_rope_table(table_dev: int, head_dim: int, max_pos: int, theta: float, stream: int = 0):

@@ -449,6 +449,16 @@ bl_status bl_norm_quant(const bl_norm_quant_args* a, void* stream) {
     return hip_status(bl::launch_norm_quant(*a, static_cast<hipStream_t>(stream)));
 }
 
+bl_status bl_final_norm(const bl_final_norm_args* a, void* stream) {
+    if (!a || !a->h_dev || !a->gamma_dev || !a->y_dev) return BL_ERR_NULL;
+    if (a->M < 1 || a->K < 1 || a->K > BL_NORM_MAX_K) return BL_ERR_SHAPE;
+    if (!aligned(a->h_dev, 4) || !aligned(a->delta_dev, 4) || !aligned(a->h_out_dev, 4) || !aligned(a->gamma_dev, 4) ||
+        !aligned(a->y_dev, 4) || !aligned(a->pos_dev, 4))
+        return BL_ERR_ALIGN;
+    drop_stale_hip_error();
+    return hip_status(bl::launch_final_norm(*a, static_cast<hipStream_t>(stream)));
+}
+
 bl_status bl_decode_norm_batch(const bl_decode_norm_item* items, int32_t count, void* workspace_dev, void* stream) {
     if (!items) return BL_ERR_NULL;
     if (count < 1 || count > BL_MAX_BATCH) return BL_ERR_COUNT;

@@ -252,6 +252,39 @@ PyObject* norm_quant(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     END_HANDLE_TH_ERRORS
 }
 
+// final_norm(h, delta or None, h_out or None, gamma, eps, y, pos, pos_set) -> True
+PyObject* final_norm(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+    HANDLE_TH_ERRORS
+    BL_NEEDS(8)
+    const double eps = PyFloat_AsDouble(args[4]);
+    const long pos_set = PyLong_AsLong(args[7]);
+    if (PyErr_Occurred()) { PyErr_Clear(); Py_RETURN_NONE; }
+    const at::Tensor *h = plain(args[0], at::kFloat), *gamma = plain(args[3], at::kFloat), *pos = plain(args[6], at::kInt);
+    if (!h || !gamma || !pos || h->dim() != 2 || pos->numel() != 1 || pos_set > INT32_MAX) Py_RETURN_NONE;
+    const int64_t M = h->size(0), K = h->size(1);
+    if (M < 1 || M > INT32_MAX || gamma->dim() != 1 || gamma->size(0) != K) Py_RETURN_NONE;
+    void* rows[3] = {nullptr, nullptr, nullptr};
+    const int at_arg[3] = {1, 2, 5};   // delta, h_out, y
+    for (int i = 0; i < 3; ++i) {
+        if (args[at_arg[i]] == Py_None) continue;
+        const at::Tensor* t = plain(args[at_arg[i]], at::kFloat);
+        if (!t || t->sizes() != h->sizes()) Py_RETURN_NONE;
+        rows[i] = t->data_ptr();
+    }
+    const bl_final_norm_args p{static_cast<const float*>(h->data_ptr()), static_cast<const float*>(rows[0]), static_cast<float*>(rows[1]),
+                               static_cast<const float*>(gamma->data_ptr()), static_cast<float*>(rows[2]), K, (int32_t)M, (float)eps,
+                               static_cast<int32_t*>(pos->data_ptr()), pos_set < 0 ? -1 : (int32_t)pos_set};
+    bl_status status;
+    void* stream = current_stream();
+    {
+        WithoutGil release;
+        status = bl_final_norm(&p, stream);
+    }
+    if (status != BL_OK) return PyLong_FromLong(status);
+    Py_RETURN_TRUE;
+    END_HANDLE_TH_ERRORS
+}
+
 // The prepared launches: launch(which, items, M, workspace) -> bl_status, on the current stream; None if `items`, a ctypes array (for
 // the last one the argument struct), does not hold whole ones of that launch's.
 enum { kGemvBatch, kDecodeBatch, kQuantBatch, kDecodeNormBatch, kTl2Batch, kAttnDecode, kLaunches };
@@ -292,7 +325,7 @@ PyObject* stream(PyObject*, PyObject*) {
 }
 
 #define BL_FAST(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {BL_FAST(quant_act), BL_FAST(product), BL_FAST(gemm_batch), BL_FAST(norm_quant), BL_FAST(launch),
+PyMethodDef methods[] = {BL_FAST(quant_act), BL_FAST(product), BL_FAST(gemm_batch), BL_FAST(norm_quant), BL_FAST(final_norm), BL_FAST(launch),
                          {"stream", stream, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -277,6 +277,7 @@ hipError_t launch_tl2_unpack(const uint32_t* packed, int64_t N, int64_t K, int64
 
 // The decoder block around the products (bl_decoder.hip); arguments already validated.
 hipError_t launch_norm_quant(const ::bl_norm_quant_args& a, hipStream_t s);
+hipError_t launch_final_norm(const ::bl_final_norm_args& a, hipStream_t s);
 hipError_t launch_rope_table(float* table, int head_dim, int max_pos, double theta, hipStream_t s);
 int attn_chunks(int max_pos);
 int64_t attn_scratch_floats(int n_heads, int head_dim, int max_pos);   // per query

@@ -72,6 +72,28 @@ def norm_quant(mode: int, gamma: Optional[torch.Tensor], eps: float = EPS, a: Op
     return out if quantize else None
 
 
+def final_norm(h: torch.Tensor, delta: Optional[torch.Tensor], gamma: torch.Tensor, eps: float, y: torch.Tensor, pos: torch.Tensor,
+               pos_set: Optional[int] = None, h_out: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """y = rmsnorm(h + delta, gamma) on [M,K] fp32 tensors (h_out receives the sum), and in the same launch the position's step: *pos
+    becomes pos_set, or one more."""
+    at = -1 if pos_set is None else pos_set
+    c = B.calls()
+    r = c.final_norm(h, delta, h_out, gamma, eps, y, pos, at) if c else None
+    if r:
+        if type(r) is int:
+            raise B.BitLinearError(r, "bl_final_norm")
+        return y
+    M, K = h.shape
+    for t in (h, delta, h_out, y):
+        assert t is None or (t.is_cuda and t.dtype == torch.float32 and t.shape == (M, K) and t.is_contiguous())
+    assert gamma.dtype == torch.float32 and gamma.shape == (K,) and gamma.is_contiguous()
+    assert pos.is_cuda and pos.dtype == torch.int32 and pos.numel() == 1
+    ptr = lambda t: t.data_ptr() if t is not None else None
+    B.bl_final_norm(B.FinalNormArgs(h.data_ptr(), ptr(delta), ptr(h_out), gamma.data_ptr(), y.data_ptr(), K, M, eps, pos.data_ptr(), at),
+                    _stream())
+    return y
+
+
 def rope_table(head_dim: int, max_pos: int, device, theta: float = ROPE_THETA) -> torch.Tensor:
     """[max_pos, head_dim/2, 2] fp32 (cos, sin) table (bl_rope_table)."""
     t = torch.empty((max_pos, head_dim // 2, 2), dtype=torch.float32, device=device)
@@ -296,14 +318,11 @@ class DecoderStack:
         self._next_pos = pos
 
     def launch(self):
-        """All launches of one token on the current stream: the layers, the last residual add with the final
-        norm (-> self.y), the position's increment."""
+        """All launches of one token on the current stream: the layers, and the last residual add with the final
+        norm (-> self.y) and the position's increment in one."""
         for layer in self.layers:
             layer.launch()
-        norm_quant(B.BL_NORM_RESIDUAL, self.g_final, self.eps, a=self.layers[-1].delta_out, h=self.h_last, y=self.y,
-                   quantize=False)
-        B.bl_pos_advance(self.pos.data_ptr(), _stream())
-        return self.y
+        return final_norm(self.h_last, self.layers[-1].delta_out, self.g_final, self.eps, self.y, self.pos, h_out=self.h_last)
 
     def capture(self):
         """Capture launch() into a HIP graph (no memset nodes: every launch here is a kernel).  One token is run
@@ -337,30 +356,30 @@ class DecoderStack:
         if pos0 + M > self.max_pos:
             raise RuntimeError("the key/value cache holds %d positions: no room for %d more" % (self.max_pos, M))
         dev, d = x.device, self.hidden // self.n_heads
-        H = x.clone()
         new = lambda n: torch.empty((M, n), dtype=torch.float32, device=dev)
         A, Y = new(hidden), new(hidden)
         # (head sizes on the matrix cores do not touch their 16 bytes: no launch to clear them)
         alloc = torch.empty if d <= B.BL_ATTN_BLOCK_MAX_HEAD_DIM else torch.zeros
         scratch = alloc(B.bl_attn_prefill_scratch_bytes(self.n_heads, d, pos0, M), dtype=torch.uint8, device=dev)
-        delta = None
+        H = delta = None      # the residual stream, from the first layer's attention on; until then it is x
         for layer in self.layers:
             w = layer.w
             assert "gate" in w.proj and "up" in w.proj, "prefill needs gate and up as separate matrices"
             ffn = w.proj["down"].K
             wide = torch.empty(M * B.BL_NORM_SCRATCH_BYTES, dtype=torch.uint8, device=dev)
-            q1 = norm_quant(B.BL_NORM_RESIDUAL, w.g_in, self.eps, a=delta, h=H)
+            q1 = norm_quant(B.BL_NORM_PLAIN, w.g_in, self.eps, a=x) if H is None else norm_quant(B.BL_NORM_RESIDUAL, w.g_in, self.eps, a=delta, h=H)
             ql, kl, vl = ops.gemm_batch([w.proj[n] for n in "qkv"], q1)
             B.bl_attn_prefill(ql.data_ptr(), kl.data_ptr(), vl.data_ptr(), self.table.data_ptr(), layer.attn.k_cache.data_ptr(),
                               layer.attn.v_cache.data_ptr(), A.data_ptr(), scratch.data_ptr(), self.n_heads, d, self.max_pos,
                               pos0, M, _stream())
             o = ops.gemm(w.proj["o"], norm_quant(B.BL_NORM_PLAIN, w.g_attn, self.eps, a=A))
-            q3 = norm_quant(B.BL_NORM_RESIDUAL, w.g_post, self.eps, a=o, h=H)
+            H, more = (o, x) if H is None else (H, o)      # x stays as it is: the first sum goes where o was
+            q3 = norm_quant(B.BL_NORM_RESIDUAL, w.g_post, self.eps, a=more, h=H)
             gate, up = ops.gemm_batch([w.proj["gate"], w.proj["up"]], q3)
             q4 = norm_quant(B.BL_NORM_GATED, w.g_ffn, self.eps, a=gate, b=up, out=ops.alloc_quant(M, ffn, dev), scratch=wide)
             delta = ops.gemm(w.proj["down"], q4)
-        norm_quant(B.BL_NORM_RESIDUAL, self.g_final, self.eps, a=delta, h=H, y=Y, quantize=False)
-        self.set_position(pos0 + M)
+        final_norm(H, delta, self.g_final, self.eps, Y, self.pos, pos_set=pos0 + M)
+        self._next_pos = pos0 + M
         return Y
 
     def step(self):

@@ -252,6 +252,20 @@ def test_decoder_block_validation():
     assert _st(B.bl_pos_advance, 0) == B.BL_ERR_NULL and _st(B.bl_pos_advance, P + 2) == B.BL_ERR_ALIGN
 
 
+def test_final_norm_validation():
+    P = 0x10000
+    good = [P, P, P, P, P, 64, 1, 1e-5, P, -1]
+    def norm(i, v):
+        a = list(good)
+        a[i] = v
+        return _st(B.bl_final_norm, B.FinalNormArgs(*a))
+    for i in (0, 3, 4):
+        assert norm(i, None) == B.BL_ERR_NULL
+    for i in (0, 1, 2, 3, 4, 8):
+        assert norm(i, P + 2) == B.BL_ERR_ALIGN
+    assert norm(5, 0) == B.BL_ERR_SHAPE and norm(5, B.BL_NORM_MAX_K + 1) == B.BL_ERR_SHAPE and norm(6, 0) == B.BL_ERR_SHAPE
+
+
 def test_decode_norm_batch_validation():
     P = 0x10000
     d = B.bl_packed_desc_init(128, 256, 0.5)

@@ -151,6 +151,28 @@ def test_norm_quant_rows_do_not_depend_on_their_batch(dev, mods, K):
         assert torch.equal(part.a_scale, whole.a_scale[:M1]) and torch.equal(part.q_sum, whole.q_sum[:M1])
 
 
+@pytest.mark.parametrize("M,K", [(1, 4096), (1, 100), (3, 2050), (37, 2048), (2, 8196), (5, 12288), (1, 49152)])
+@pytest.mark.parametrize("pos_set", [None, 0, 77])
+def test_final_norm_is_the_residual_norm_with_the_position(dev, mods, M, K, pos_set):
+    """bl_final_norm: the bits of bl_norm_quant's residual form, the sum where it is wanted and nowhere else, the position's step."""
+    B, dec, ops = mods
+    g = torch.Generator(dev).manual_seed(K + M)
+    h, delta = (torch.randn((M, K), device=dev, generator=g) for _ in range(2))
+    gamma = torch.rand(K, device=dev, generator=g) + 0.5
+    for d in (delta, None):
+        ref_h, ref_y = h.clone(), torch.empty_like(h)
+        dec.norm_quant(B.BL_NORM_RESIDUAL, gamma, 1e-5, a=d, h=ref_h, y=ref_y, quantize=False)
+        for where in ("nowhere", "other", "itself"):
+            src, other = h.clone(), torch.full_like(h, 3.0)
+            out = {"nowhere": None, "other": other, "itself": src}[where]
+            y = torch.empty_like(h)
+            pos = torch.full((1,), 41, dtype=torch.int32, device=dev)
+            assert dec.final_norm(src, d, gamma, 1e-5, y, pos, pos_set=pos_set, h_out=out) is y
+            assert torch.equal(y, ref_y) and pos.item() == (42 if pos_set is None else pos_set)
+            assert torch.equal(src, ref_h if where == "itself" else h)
+            assert torch.equal(other, ref_h if where == "other" and d is not None else torch.full_like(h, 3.0))
+
+
 @pytest.mark.parametrize("K", [512, 45056])
 def test_norm_quant_gate_of_any_size(dev, mods, K):
     """The gate's two ways of computing silu meet at a size of 80: waves below it, waves with one element at or above it, and
