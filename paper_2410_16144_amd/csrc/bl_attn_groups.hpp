@@ -6,25 +6,24 @@ namespace bl {
 constexpr int kAttnUnits = 256;       // compute units
 constexpr int kAttnMaxGroups = 64;    // as many deposits as the merge reads in one go
 constexpr int kAttnOneRound = 10;     // workgroups per head from which on one per unit is enough
-constexpr int kAttnLongChunks = 128;  // a cache of more than 8192 positions: one workgroup per unit streams best
-constexpr int kAttnHalfRow = 64;      // head sizes up to this leave half of a cache row's lanes idle
 
 // By heads, head size and the cache's size, not by the position: the same for every call on a cache.  The launch fills the units
 // a whole number of times (rounds), never a little more than that -- units with one workgroup more than the others are the launch's
-// duration.  Measured in us, caches from memory, heads of 128 unless stated:
-//   - one round or two: 16 heads of 96, 3000 positions 9.9 and 10.5, 8000 16.1 and 16.4; 20 heads, 8000 19.1 and 19.7; but 64 heads, 1270
-//     12.6 and 12.1, 40 heads 10.4 and 10.0: one round from 10 workgroups per head on.
-//   - one round in long caches, whatever the heads, 16 000 positions: 32 heads 45.4 and 47.1, 48 heads 66.3 and 73.0, 64 90.8 and 96.2, 80 107.2 and
-//     117.9, 104 137.3 and 156.0, 40 of 80 47.9 and 49.0, 28 of 160 55.1 and 56.8; where it fills 72 % of the units (90 heads, 70 %: 5000 positions
-//     44.2 and 42.2) and more than half of a cache row's lanes have elements: 32 heads of 64 36.0 and 27.7, 52 of 64 63.1 and 39.3.
-//   - one workgroup per head where that fills as much: 200 heads, 500 / 1270 / 5000 positions 12.8 / 24.8 / 84.2, two (400 workgroups, 144
-//     units with two) 15.1 / 28.3 / 96.7; 256 heads 14.7 / 29.3 / 105.1 and 16.2 / 31.8 / 115.9.
-//   - else the fewest rounds that are full: 260 heads, 5000 positions 1 / 4 / 6 workgroups per head 156.9 / 127.3 / 123.1, 300 heads 1 / 4 168.5 / 136.7,
-//     180 heads 2 / 4 94.0 / 83.6.  Two rounds that are 80 % full are taken (140 heads, 1270 positions 3 / 5: 21.3 / 20.8; 104
+// duration.  Measured in us, caches from memory by streaming loads, heads of 128 unless stated; one round and two:
+//   - one round where it fills 72 % of the units and a cache row leaves at most three eighths of its lanes idle (16 lanes for head sizes up
+//     to 128, 32 beyond): half as many deposits, and a unit's one workgroup keeps as many requests under way as two that wait for each
+//     other's.  26 heads 1000 positions 8.20 and 9.04, 4000 13.6 and 14.5; 32 heads 1000 7.88 and 8.30, 7000 22.7 and 23.5, 12 000 34.8 and 36.2; 64 heads
+//     500 8.07 and 8.32, 4000 25.1 and 25.8; 80 heads 7000 46.0 and 48.6; 120 heads 39.7 and 43.0 at 4000; 32 of 96 22.8 and 24.1 at 7000; 28 of 160 13.0 and
+//     14.7 at 2000; 30 of 256 15.7 and 17.1; 200 heads 65.4 and 73.4 at 4000.  With 80 of 128 even (40 heads 18.4 and 18.2 at 4000, 7.90 and 8.34 at 500);
+//     with fewer two: 52 of 72 22.9 and 21.7 at 4000, 32 of 64 12.5 and 11.1, 36 of 132 30.1 and 27.4.  Less full than that two as well: 90 heads (70 %)
+//     37.3 and 33.0 at 4000, 140 (55 %) 60.8 and 52.0.  (With ordinary loads two rounds were ahead below 8192 positions.)
+//   - one round from 10 workgroups per head on, whatever the lanes: 16 heads of 256 at 2000 positions 11.0 and 12.8.
+//   - else the fewest rounds that are full (ordinary loads): 260 heads, 5000 positions 1 / 4 / 6 workgroups per head 156.9 / 127.3 / 123.1, 300 heads
+//     1 / 4 168.5 / 136.7, 180 heads 2 / 4 94.0 / 83.6.  Two rounds that are 80 % full are taken (140 heads, 1270 positions 3 / 5: 21.3 / 20.8; 104
 //     heads 4 / 7: 16.8 / 16.8), more only at 85 %: 260 heads have 81 % in five rounds.
 constexpr int attn_groups_per_head(int n_heads, int head_dim, int chunks) {
-    const int one = kAttnUnits / n_heads;
-    const bool few = head_dim > kAttnHalfRow && one * n_heads * 100 >= kAttnUnits * 72 && (one == 1 || chunks > kAttnLongChunks);
+    const int one = kAttnUnits / n_heads, row = head_dim <= 128 ? 128 : 256;
+    const bool few = head_dim * 8 >= row * 5 && one * n_heads * 100 >= kAttnUnits * 72;
     int groups = one;
     if (one < kAttnOneRound && !few) {
         for (int rounds = 2;; ++rounds) {

@@ -592,19 +592,24 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 // and weighted values of THEIR rows over all chunks of the workgroup: the dot product's exchanges are the only ones in the
 // loop, and there is no barrier in it, so no wave's requests wait for another wave's rows.  The groups of lanes are merged by
 // lane exchanges, the four waves in LDS, once behind the loop.  Bound by HBM in long contexts: 32 heads of 128 at 8000 positions
-// 36.3 -> 30 -> 26.9 us (131 MB: 4.9 TB/s), 32 000 positions 92 (5.7 TB/s);
+// 36.3 -> 30 -> 26.9 -> 23.0 us (131 MB: 5.7 TB/s, behind 5 us of start and merge 7.2), 16 000 positions 47.8 -> 41.7;
 // by the chain of memory round trips in short ones (caches from memory): one position 4.8 -> 3.4, 500 positions 10.2 -> 7.4, 3000 18.0 -> 13.7.
 // Before lane sums on the vector ALU, the next chunk's requests without a condition and fewer workgroups per head -> since; the last
 // change kept the requests where they are written and put the angle's load ahead of them: 16 heads of 100 at 8000 positions
 // 21.2 -> 17.8, 12 of 44 at 16 000 24.2 -> 19.0, 20 of 160 at 500 / 3000 / 8000 8.9 -> 8.0, 16.2 -> 13.3, 31.6 -> 24.4, 30 of 256 10.7 -> 9.4, 25.6 -> 22.4,
 // 55.4 -> 48.1, 32 of 128 at 500 8.1 -> 7.4.
+// A token's cache rows are read once, by streaming loads: caches from memory, ordinary -> streaming, 32 heads of 128 at 500 positions 7.9 -> 7.6,
+// 2000 11.1 -> 10.5, 8000 27.7 -> 25.2, 16 000 47.8 -> 42.0, 64 heads at 4000 28.5 -> 25.9; caches that the memory-side cache holds stay there
+// and are as fast (8000: 24.3 and 24.0), and so do a model's weights: 700M shape 810 -> 740 us per token at 3000 positions, 715 -> 694 at 500.
+// With them one workgroup per unit is enough at any length (bl_attn_groups.hpp: 25.2 -> 23.0 at 8000).
 // MAXD: the largest head size of this instance (128 or 256) -- registers and LDS are sized by it, and the smaller one
 // lets twice as many workgroups share a compute unit.
 // Waves per SIMD: 5 (head sizes up to 128) and 4 (beyond), held for the compiler; every instance fits without spilling: 75, 71,
 // 115 and 122 registers.  (Five spilled registers of <8, 256>, reloaded behind the next keys' requests, made every chunk wait for
 // those: 40 heads of 160 at 16 000 positions 92.8 us, without spills 79.7.)
-template <int W, int MAXD>
-__global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : 4) void attn_chunk_kernel(const AttnArgs p) {
+// PROMPT: several tokens whose keys and values are cached already, one per grid z.
+template <int W, int MAXD, bool PROMPT>
+__device__ __forceinline__ void attn_walk(const AttnArgs& p) {
     typedef typename CacheVec<W>::type vec_t;
     constexpr int kMaxLanesPerRow = MAXD / W;
     constexpr int kVecs = kChunk * kMaxLanesPerRow / kAttnThreads;            // requests per thread at most
@@ -620,7 +625,6 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : 4) void attn_chunk_
     const int d = p.head_dim, half = d / 2;
     const int hidden = p.n_heads * d;
     const int query = blockIdx.z;                       // 0 unless a prompt's tokens are processed together
-    const bool appended = p.pos == nullptr;             // uniform: the prompt form, keys and values already cached
     const float* q_lin = p.q_lin + (int64_t)query * hidden;
     float* out = p.out + (int64_t)query * hidden;
     float* scratch = p.scratch + (int64_t)query * p.scratch_stride;
@@ -628,12 +632,12 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : 4) void attn_chunk_
     float qa = 0.0f, qb = 0.0f, ka = 0.0f, kb = 0.0f, va = 0.0f, vb = 0.0f;
     if (tid < half) {
         qa = q_lin[head * d + tid]; qb = q_lin[head * d + tid + half];
-        if (!appended) {
+        if (!PROMPT) {
             ka = p.k_lin[head * d + tid]; kb = p.k_lin[head * d + tid + half];
             va = p.v_lin[head * d + tid]; vb = p.v_lin[head * d + tid + half];
         }
     }
-    const int pos = __builtin_amdgcn_readfirstlane(appended ? p.pos0 + query : *p.pos);
+    const int pos = __builtin_amdgcn_readfirstlane(PROMPT ? p.pos0 + query : *p.pos);
     if (pos < 0 || pos >= p.max_pos) return;            // uniform
     // Workgroup y of a head takes the chunks y, y + G, y + 2G, ... (G = workgroups per head in this launch) that hold
     // rows up to the token's: one chunk each while the context is short, several once it outgrows the launch -- then
@@ -641,7 +645,7 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : 4) void attn_chunk_
     const int groups = (int)gridDim.y;
     const int last_chunk = pos / kChunk;
     if (chunk > last_chunk) return;                     // uniform: nothing cached this far yet
-    const bool owner = !appended && last_chunk % groups == chunk;   // uniform: one of this workgroup's chunks holds the row this launch appends
+    const bool owner = !PROMPT && last_chunk % groups == chunk;   // uniform: one of this workgroup's chunks holds the row this launch appends
     constexpr int L = kMaxLanesPerRow;                  // lanes per cache row: a power of two; those beyond head_dim / W idle
     constexpr int kRowsPerStep = kAttnThreads / L;      // rows the workgroup takes per request
     const int lane = tid % kWave, wave = tid / kWave;
@@ -666,8 +670,10 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : 4) void attn_chunk_
             // (idle lanes read their row's first piece: a branch around the requests would hide from the compiler how many there are)
             const uint32_t at = (uint32_t)min(grp + i * kRowsPerStep, rest) * row_bytes + (active ? cc * W * 2u : 0u);
             typedef const __attribute__((address_space(1))) vec_t* global_vec;
-            if (keys) kv[i] = *(global_vec)(base + at);
-            else vv[i] = *(global_vec)(base + at);
+            vec_t& to = keys ? kv[i] : vv[i];
+            // streaming (nontemporal) loads; a prompt's queries read the same rows (16 heads of 164, 9 behind 4000: streaming 87 us, 74)
+            if constexpr (!PROMPT) to = __builtin_nontemporal_load((global_vec)(base + at));
+            else to = *(global_vec)(base + at);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -848,6 +854,17 @@ __global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : 4) void attn_chunk_
     else if (used <= kMergeTogether) attn_merge_together<MAXD, kMergeTogether>(p, scratch, out, head, used, s_w, s_mw, &s_ow[0][0]);
     else attn_merge(p, scratch, out, head, used, s_o, s_w);
     if (tid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int W, int MAXD>
+__global__ __launch_bounds__(kAttnThreads, MAXD <= 128 ? 5 : 4) void attn_chunk_kernel(const AttnArgs p) {
+    attn_walk<W, MAXD, false>(p);
+}
+
+// A kernel of its own: both kinds of loads in one, behind a uniform branch, cost a token's first positions 0.15 of 3.5 us.
+template <int W>
+__global__ __launch_bounds__(kAttnThreads, 4) void attn_chunk_prompt_kernel(const AttnArgs p) {
+    attn_walk<W, BL_ATTN_MAX_HEAD_DIM, true>(p);
 }
 
 // A prompt's keys and values into the cache, ahead of its attention: one token per workgroup, the rotation and
@@ -1303,7 +1320,8 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     const int groups = min(attn_groups(a.n_heads, a.head_dim, attn_chunks(a.max_pos), p.counters_apart), p.chunks);
     p.counters_apart = 0;
     const dim3 grid((unsigned)a.n_heads, (unsigned)groups, (unsigned)a.M);
-    launch_attn_chunks(p, grid, s);
+    if (p.head_dim % 8 == 0) attn_chunk_prompt_kernel<8><<<grid, dim3(kAttnThreads), 0, s>>>(p);   // (head sizes above 128)
+    else attn_chunk_prompt_kernel<4><<<grid, dim3(kAttnThreads), 0, s>>>(p);
     return hipGetLastError();
 }
 

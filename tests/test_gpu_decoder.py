@@ -345,6 +345,35 @@ def test_attn_decode_several_chunks_per_workgroup(dev, mods, groups, n_heads, he
         B.bl_set_tuning("attn_groups", 0)
 
 
+@pytest.mark.parametrize("n_heads,head_dim,groups", [(32, 128, 8), (26, 80, 9), (60, 100, 4), (28, 160, 9), (200, 88, 1), (40, 72, 12), (27, 156, 18),
+                                                     (90, 128, 5)])
+def test_attn_decode_one_round_or_two(dev, mods, n_heads, head_dim, groups):
+    """The workgroups that a call takes by itself: one round of the units (cache rows with few idle lanes, 72 % of the units filled)
+    or more, each walking one chunk, several of them, and the last one in part; some heads against the fp64 softmax on the cache as
+    it lies there."""
+    B, dec, ops = mods
+    hidden, max_pos = n_heads * head_dim, 64 * 20 - 7
+    r = _rng(53900 + hidden)
+    table = dec.rope_table(head_dim, max_pos, dev)
+    q_t, k_t, v_t = (torch.empty((1, hidden), device=dev) for _ in range(3))
+    pos_t = torch.zeros(1, dtype=torch.int32, device=dev)
+    att = dec.Attention(n_heads, head_dim, max_pos, q_t, k_t, v_t, pos_t, table)
+    for c in (att.k_cache, att.v_cache):
+        c.copy_(_bits_as_bf16_tensor(synth.to_bf16_bits(r.standard_normal((max_pos, hidden)).astype(np.float32)), dev))
+    heads = sorted({0, n_heads // 2, n_heads - 1})
+    cols = np.concatenate([np.arange(h * head_dim, (h + 1) * head_dim) for h in heads])
+    for pos in sorted({0, 63, 64, 64 * groups - 1, 64 * groups, 64 * groups + 63, 64 * 19 + 5, max_pos - 1}):
+        if pos >= max_pos:
+            continue
+        ql, kl, vl = (3.0 * r.standard_normal(hidden).astype(np.float32) for _ in range(3))
+        q_t.copy_(_t(ql[None], dev)); k_t.copy_(_t(kl[None], dev)); v_t.copy_(_t(vl[None], dev))
+        pos_t.fill_(pos)
+        got = att.launch().cpu().numpy()[0]
+        kc, vc = (c[:pos + 1].float().cpu().numpy().astype(np.float64)[:, cols] for c in (att.k_cache, att.v_cache))
+        want = D.attention_decode(D.rope(ql[cols], pos, len(heads)), kc, vc, len(heads))
+        assert np.abs(got[cols] - want).max() <= 2e-5 * max(1.0, np.abs(want).max()), (pos, float(np.abs(got[cols] - want).max()))
+
+
 @pytest.mark.parametrize("n_heads,head_dim", [(2, 64), (1, 256), (2, 36)])
 def test_attn_decode_merges_of_every_size(dev, mods, n_heads, head_dim):
     """The last workgroup reads up to 16 or up to 64 deposits in one round: positions that leave 2, 16, 17 and 64 deposits, in a
