@@ -10,7 +10,9 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/TracerMode.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -41,8 +43,12 @@ const at::Tensor* plain(PyObject* o, at::ScalarType type) {
     return t && t->scalar_type() == type && t->is_contiguous() ? t : nullptr;
 }
 
+// An output, every byte of which the library writes: straight from the allocator that at::empty asks (plain() has made sure that no mode
+// or wrapper has a word in it; a trace still gets to see it).  At four outputs a pass the dispatcher's 0.25 us each were 8 % of a small product with its
+// quantizer (11.3 -> 10.4 us).
 at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) {
-    return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
+    if (at::tracer::impl::is_dispatch_enabled()) return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
+    return at::Tensor(at::detail::empty_cuda(shape, type, like.device(), std::nullopt));
 }
 
 // Memory of a ctypes object (a descriptor, an argument struct, an array of items) for the time of one call.

@@ -151,6 +151,25 @@ def _outcome(call):
     return [None if t is None else (t.dtype, t.shape, t.cpu().contiguous().view(torch.uint8).numpy().tobytes()) for t in flat]
 
 
+@pytest.mark.parametrize("inference", [False, True])
+def test_fresh_outputs_are_what_torch_allocates(dev, monkeypatch, inference):
+    """Outputs come straight from the allocator: the same kind of tensors as torch.empty's, in inference mode too."""
+    pw = _weight(dev, 100, 256)
+    x = torch.randn(3, 256, device=dev)
+
+    def outputs():
+        with torch.inference_mode(inference):
+            qa = ops.quant_act(x)
+            return [qa.q, qa.a_scale, qa.q_sum, *ops.gemv(pw, qa, want_acc=True), *ops.gemm_batch([pw, pw], qa)]
+    native = outputs()
+    monkeypatch.setattr(B, "calls", lambda: None)
+    for a, b in zip(native, outputs(), strict=True):
+        assert torch.equal(a, b)
+        for what in (lambda t: t.is_inference(), lambda t: t.requires_grad, lambda t: t.dtype, lambda t: t.device, lambda t: t.stride(),
+                     lambda t: t.untyped_storage().nbytes(), lambda t: t.storage_offset(), lambda t: t.layout, lambda t: type(t)):
+            assert what(a) == what(b)
+
+
 def test_what_the_native_calls_refuse_ends_as_without_them(dev, monkeypatch):
     """Operands that are not plain device tensors of the expected kind: the same result, or the same error, as by ctypes."""
     g = torch.Generator(dev).manual_seed(3)
