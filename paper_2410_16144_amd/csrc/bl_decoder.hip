@@ -601,6 +601,9 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 // A token's cache rows are read once, by streaming loads: caches from memory, ordinary -> streaming, 32 heads of 128 at 500 positions 7.9 -> 7.6,
 // 2000 11.1 -> 10.5, 8000 27.7 -> 25.2, 16 000 47.8 -> 42.0, 64 heads at 4000 28.5 -> 25.9; caches that the memory-side cache holds stay there
 // and are as fast (8000: 24.3 and 24.0), and so do a model's weights: 700M shape 810 -> 740 us per token at 3000 positions, 715 -> 694 at 500.
+// Rows shorter than a line are the exception: two heads share every line, and the launch alone is slower (32 heads of 48, 4700 positions 15.8 -> 16.3,
+// 16 000 41.9 -> 42.5).  A whole token of that shape (1.5B) still gains up to there, by its weights: 968 -> 914 us at 1500, 1140 -> 1091 at 4500; at 14 000
+// it is 1 % behind (1682 -> 1700).  So one kind of load for all head sizes.
 // With them one workgroup per unit is enough at any length (bl_attn_groups.hpp: 25.2 -> 23.0 at 8000).
 // MAXD: the largest head size of this instance (128 or 256) -- registers and LDS are sized by it, and the smaller one
 // lets twice as many workgroups share a compute unit.
