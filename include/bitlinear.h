@@ -381,7 +381,8 @@ bl_status bl_tl2_gemv_batch(const bl_gemv_item *items, int32_t count, void *work
  * along N.  Forms: 12, 14, 22, 23, 24, 122, 124; 25 or 40025 = tiles of two widths wherever that launch applies; or of the kernel for few
  * tokens as 1000*R + T: T tokens x (32*R) weight rows per workgroup, its waves along K.  Forms: 1016, 1032, 2016, 2032, 4032, 4064; or of
  * the kernel on pairs of packed tiles as 10000*S + 100*(WK-1) + 10*MB + H with S stages.  Forms: 40022, 40021, 60021, 40121, 40012,
- * 30024, 30023 (0 = automatic);
+ * 30024, 30023, 40042, 40023 (0 = automatic; a form that does not take a launch, those of pairs one of more than 2^23 weight rows -- 40042
+ * 2^22 --, leaves it to 24);
  * "decode_publish" = fused launches of 2..8 tokens: 0 = quantize every distinct input once and publish it when the call allows it (see
  * bl_decode_batch), -1 = never; "decode_wait_limit" = polls before a waiting workgroup of that form gives up (0 = the default, 262144);
  * "decode_stream" = how the decode kernels load weight tiles: 0 automatic (streaming, i.e. nontemporal, loads for launches of

@@ -441,7 +441,7 @@ GemmChoice choose_kernel(const GemmProblem* ps, int count, int64_t M, GemmMixed&
     const bool narrow_ok = gemm_narrow_takes(ps, count, M), pair_ok = gemm_pair_takes(ps, count);
     if (g_force_mb && !forced_mixed()) {
         if (gemm_pair_form_exists(g_force_mb)) {
-            c.pair = pair_ok ? g_force_mb : 0;
+            c.pair = gemm_pair_takes(ps, count, g_force_mb / 10 % 10) ? g_force_mb : 0;
             c.halves = c.pair ? gemm_pair_halves(ps, count, M, c.pair) : 0;
         }
         else if (gemm_narrow_form_exists(g_force_mb)) c.narrow = narrow_ok ? g_force_mb : 0;

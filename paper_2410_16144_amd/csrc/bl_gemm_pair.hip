@@ -95,12 +95,12 @@ bool gemm_pair_form_exists(int code) {
     return false;
 }
 
-// 32-bit offsets: 64 rows of the output within 2^31 bytes.  (64 rows of the activations and a row block's tiles are far from it:
-// K is at most 2^20.)
-static_assert(BL_MAX_K <= 1 << 25, "64 activation rows within 2^31 bytes");
-bool gemm_pair_takes(const GemmProblem* ps, int count) {
+// Whether a form of 32 mb tokens takes a launch: its matrices are no wider than pair_max_columns.  (A tile's activation rows and a row
+// block's tiles are far from 32-bit offsets' ends: K is at most 2^20.)
+static_assert((int64_t)BL_MAX_K * 32 * 4 <= (int64_t)1 << 31, "128 activation rows within 2^31 bytes");
+bool gemm_pair_takes(const GemmProblem* ps, int count, int mb) {
     for (int i = 0; i < count; ++i)
-        if (ps[i].N > 1 << 23) return false;
+        if (ps[i].N > pair_max_columns(mb)) return false;
     return true;
 }
 
@@ -132,7 +132,7 @@ int gemm_pair_best(const GemmProblem* ps, int count, int64_t M, int cus, float& 
     }
     const float k = (float)KC;
     for (const PairLine& l : kPairLines) {
-        if (KC < l.least) continue;
+        if (KC < l.least || !gemm_pair_takes(ps, count, l.mb)) continue;
         const int64_t gx = pair_positions(ps, count, l.bn), gy = (M + l.bm - 1) / l.bm;
         float factor;
         const int splits = pair_may_split(gx, gy, M, rows, (int64_t)KC * kTileK, factor) ? 2 : 1;

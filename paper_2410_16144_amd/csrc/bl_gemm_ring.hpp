@@ -67,6 +67,11 @@ struct PairRing {
     static_assert(kA >= 1 && kA <= 4 && kLead >= 2 && kYounger < 64, "every wave brings tokens; fits the wait counter");
 };
 
+// The widest matrix that a form of 32 mb tokens takes: its epilogue reaches a tile's rows of the output by 32-bit byte offsets, of which
+// those from 2^31 on stand for columns that are not there, so the 32 mb rows have to end by then.  (Beyond 2^23 columns no form is
+// taken: the tile kernel of bl_gemm.hip is ahead there.)
+constexpr long long pair_max_columns(int mb) { return (1LL << 31) / (4 * 32 * (mb < 2 ? 2 : mb)); }
+
 // The forms that are built, X(MB, H, WN, WK, S): wave tile of 32 MB tokens x 32 H weight rows, WN waves along N, WK along K, S
 // stages.
 #define BL_PAIR_FORMS(X) \

@@ -262,7 +262,7 @@ inline int64_t gemm_padded_tiles(int64_t gx, int64_t gy, int halves) {
 }
 // bl_gemm with paired packed tiles (bl_gemm_pair.hip); a form's code is 10000 * stages + 100 * (waves along K - 1) + 10 * MB + H
 bool gemm_pair_form_exists(int code);
-bool gemm_pair_takes(const GemmProblem* ps, int count);
+bool gemm_pair_takes(const GemmProblem* ps, int count, int mb = 1);   // a form of 32 mb tokens; by default whether there is one
 // the form with the smallest estimate, and whether its launch splits the dies over the tokens
 int gemm_pair_best(const GemmProblem* ps, int count, int64_t M, int cus, float& us, int& halves);
 int gemm_pair_halves(const GemmProblem* ps, int count, int64_t M, int code);   // the same for a form that is asked for

@@ -1006,3 +1006,23 @@ def test_gemm_dies_split_for_fewer_bytes(dev, ops):
         assert torch.equal(out, ops.gemm(pw, qa))
     finally:
         binding.bl_set_tuning("gemm_mb", 0)
+
+
+@pytest.mark.parametrize("form,limit", [(40042, 1 << 22), (40022, 1 << 23)])
+@pytest.mark.parametrize("beyond", [0, 70])
+def test_gemm_paired_forms_up_to_their_widest_matrix(dev, ops, form, limit, beyond):
+    """The output's rows of one tile end where 32-bit offsets stand for missing columns (2^31 bytes): a form takes the last width at
+    which they do, with a tile that is full, and leaves wider ones to another kernel."""
+    from paper_2410_16144_amd import binding
+    M, K, N = form // 10 % 10 * 32 + 2, 64, limit + beyond
+    g = torch.Generator(dev).manual_seed(N)
+    pw = ops.pack_ternary(torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev, generator=g), 0.02)
+    qa = ops.quant_act(torch.randn((M, K), device=dev, generator=g))
+    try:
+        binding.bl_set_tuning("gemm_mb", form)
+        out = ops.gemm(pw, qa, out=torch.full((M, N), -7.0, device=dev))
+        assert ("pair_gemm_kernel" in binding.bl_last_kernel()) == (beyond == 0), binding.bl_last_kernel()
+        binding.bl_set_tuning("gemm_mb", 22)
+        assert torch.equal(out, ops.gemm(pw, qa))
+    finally:
+        binding.bl_set_tuning("gemm_mb", 0)
