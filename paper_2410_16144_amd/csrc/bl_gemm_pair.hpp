@@ -88,10 +88,10 @@ __device__ __forceinline__ void pair_tile(const GemmProblem& p, const int M, con
         load_to_lds(dst, off, src);
     };
     // any pair, also the last one and those behind it (a valid pair instead: its codes are taken as 0)
-    auto request_any = [&](int i) {
+    auto request_any = [&](int i, int stage) {
         const int pair = min(i * WK + kg, pairs - 1);
         const bool half = odd && pair == pairs - 1;   // uniform: the pair is one tile, its second half brings that one again
-        request(mine + (uint32_t)((i % S) * F::kStage), w_off + (uint32_t)pair * (2 * kTileBytes) - (half ? second * kTileBytes : 0),
+        request(mine + (uint32_t)(stage * F::kStage), w_off + (uint32_t)pair * (2 * kTileBytes) - (half ? second * kTileBytes : 0),
                 abase + (int64_t)pair * (2 * kTileK), half ? a_second : 0);
     };
 
@@ -143,7 +143,7 @@ __device__ __forceinline__ void pair_tile(const GemmProblem& p, const int M, con
         s_qsum[tid] = p.q_sum[m];
     }
 #pragma unroll
-    for (int i = 0; i < kLead; ++i) request_any(i);
+    for (int i = 0; i < kLead; ++i) request_any(i, i);
     wait_vm<Ring::kYounger>();
     __syncthreads();
 
@@ -162,24 +162,17 @@ __device__ __forceinline__ void pair_tile(const GemmProblem& p, const int M, con
 
     // One step: four blocks of MB * H products, and beside each product its share of everything else, held there by a scheduling barrier:
     // a token operand of the block after the next, some of the next block's codes, in block 0 a request of pair i + kLead (right
-    // behind the barrier: spread over three blocks the forms with three stages had too little of the step left for them).
+    // behind the barrier: spread over three blocks the forms with three stages had too little of the step left for them).  The last
+    // steps, which ask for any pair or for none, do so in one place.  (M0 written anew for every request, a branch around each one in the last
+    // steps and a mapping to tiles by two divisions: 307 x 4032 -> 6464 15.2 us, so 14.6; 437 x 3072 -> 4160 11.6 and 11.0; 598 x 768 -> 11008
+    // 10.7 and 9.9; 2048 x 11008 -> 4096 66.9 and 65.9.)
     auto step = [&](auto phase, auto tail, int i) {
         constexpr int st = decltype(phase)::value % S, st1 = (st + 1) % S, stq = (st + kLead) % S;
         constexpr bool T = decltype(tail)::value;
         constexpr int kSlots = MB * H, kCodes = 4 / MB, kPer = Ring::kPer, kSpread = H >= 2 ? 2 : 1;   // products of a block; operand words expanded beside each
         static_assert(4 % MB == 0, "a block's products share out the next block's 4 H operand words");
         WWords wn;
-        uint32_t w_from = w_next, back = 0;
-        const uint8_t* a_from = a_next;
-        bool ask = true;
-        if constexpr (T) {   // any pair, as request_any
-            ask = i + kLead < steps;
-            const int pair = min((i + kLead) * WK + kg, pairs - 1);
-            const bool half = odd && pair == pairs - 1;
-            w_from = w_off + (uint32_t)pair * (2 * kTileBytes) - (half ? second * kTileBytes : 0);
-            a_from = abase + (int64_t)pair * (2 * kTileK);
-            back = half ? a_second : 0;
-        }
+        uint32_t m0 = 0;   // the present request's LDS address register
         unroll<4>([&](auto block) {
             constexpr int j = decltype(block)::value;
             BOps bn;
@@ -197,15 +190,18 @@ __device__ __forceinline__ void pair_tile(const GemmProblem& p, const int M, con
                     asm volatile("" : "+v"(x));   // expanded here, under this product
                     bn.v[eh][q] = x;
                 });
-                if constexpr (j == 0) {
+                if constexpr (j == 0 && !T) {
                     constexpr int r0 = t * kPer / kSlots, r1 = (t + 1) * kPer / kSlots;
-                    if (!T || ask)
-                        unroll<r1 - r0>([&](auto which) {
-                            constexpr int r = r0 + decltype(which)::value;
-                            load_piece_to_lds<r % 4 * 1024>(mine + (uint32_t)(stq * F::kStage + r / 4 * 4096),
-                                                            r < H ? w_from : a_off[r < H ? 0 : r - H] - back, r < H ? wbase[r < H ? r : 0] : a_from);
-                        });
+                    unroll<r1 - r0>([&](auto which) {
+                        constexpr int r = r0 + decltype(which)::value;
+                        const uint32_t off = r < H ? w_next : a_off[r < H ? 0 : r - H];
+                        const uint8_t* src = r < H ? wbase[r < H ? r : 0] : a_next;
+                        if constexpr (r % 4 == 0) m0 = load_first_to_lds(mine + (uint32_t)(stq * F::kStage + r * 1024), off, src);
+                        else load_next_to_lds<r % 4 * 1024>(m0, off, src);
+                    });
                 }
+                if constexpr (j == 0 && T && t == 0)
+                    if (i + kLead < steps) request_any(i + kLead, stq);
                 __builtin_amdgcn_sched_barrier(0);
             });
             if constexpr (T && j == 2) mask_w(wn, i + 1);

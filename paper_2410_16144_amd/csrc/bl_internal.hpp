@@ -60,10 +60,18 @@ __device__ __forceinline__ void load_to_lds(uint32_t dst, const uint32_t (&off)[
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off[r]), "s"(src[r]) : "memory", "m0");
     }
 }
-// One such piece, at src + off + kOffset (also the place behind dst): for requests that stand between products.
+// The same for requests that stand between products, piece by piece: the first one sets M0 and returns it, up to three more take it, at
+// src + off + kOffset (also the place behind dst).  M0 is an operand of theirs, so the compiler knows that it lives from the one to
+// the other; it is written nowhere else in between, and a write of the compiler's own would lack the pause that these loads need behind one
+// (tests/test_wait_counts.py counts the writes).
+__device__ __forceinline__ uint32_t load_first_to_lds(uint32_t dst, uint32_t off, const uint8_t* src) {
+    uint32_t m0;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" : "={m0}"(m0) : "s"(dst), "v"(off), "s"(src) : "memory");
+    return m0;
+}
 template <int kOffset>
-__device__ __forceinline__ void load_piece_to_lds(uint32_t dst, uint32_t off, const uint8_t* src) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(dst), "v"(off), "s"(src), "n"(kOffset) : "memory", "m0");
+__device__ __forceinline__ void load_next_to_lds(uint32_t m0, uint32_t off, const uint8_t* src) {
+    asm volatile("global_load_lds_dwordx4 %1, %2 offset:%3" ::"{m0}"(m0), "v"(off), "s"(src), "n"(kOffset) : "memory");
 }
 #pragma clang diagnostic pop
 
@@ -87,13 +95,15 @@ __device__ __forceinline__ bool tile_of_workgroup(int wg, int gx, int& tile_x, i
 }
 
 // The same with the dies in two halves (halves = 1): dies 0-3 take the even token tiles, dies 4-7 the odd ones, and the N positions go
-// by die % 4.  A die then fetches half of the tokens and twice the weights.
-__device__ __forceinline__ bool tile_of_workgroup(int wg, int gx, int gy, int halves, int& tile_x, int& tile_y) {
-    const int columns = kXcds >> halves, die = wg % kXcds, gxh = (gx + columns - 1) / columns;
-    const int rest = wg / kXcds;
-    tile_x = (rest % gxh) * columns + die % columns;
-    tile_y = ((rest / gxh) << halves) + die / columns;
-    return tile_x < gx && tile_y < gy;
+// by die % 4.  A die then fetches half of the tokens and twice the weights.  (One division, by a count: ahead of a launch's first request
+// every instruction counts, 4 to 5 cycles each.)
+__device__ __forceinline__ bool tile_of_workgroup(uint32_t wg, uint32_t gx, uint32_t gy, int halves, int& tile_x, int& tile_y) {
+    const uint32_t shift = 3 - halves, die = wg % kXcds, rest = wg / kXcds;
+    static_assert(kXcds == 1 << 3, "columns of dies by shift and mask");
+    const uint32_t gxh = (gx + (1u << shift) - 1) >> shift, y = rest / gxh, x = rest - y * gxh;
+    tile_x = (int)(x << shift | (die & ((1u << shift) - 1)));
+    tile_y = (int)(y << halves | die >> shift);
+    return tile_x < (int)gx && tile_y < (int)gy;
 }
 
 // One prefill product as the kernel sees it (all device pointers).

@@ -179,6 +179,19 @@ def test_compiled_decode_copy_waits_for_the_copy_only(tmp_path):
     assert seen == 16
 
 
+def _check_paired_extras(name, lines, loops, forms):
+    """What stands between the products and ahead of them: the LDS address register is written once for up to four requests, always with
+    the pause they need behind it and by nobody else; one division, the mapping to tiles, ahead of the first request."""
+    code = [l for l in lines if l and not l.startswith((";", ".")) and not l.endswith(":")]
+    for i, l in enumerate(code):
+        if re.search(r"\bm0\b", l):
+            assert l.startswith("s_mov_b32 m0,") and code[i + 1] == "s_nop 0" and code[i + 2].startswith("global_load_lds_dwordx4"), (name, code[i:i + 3])
+    writes = sorted(sum(l.startswith("s_mov_b32 m0,") for l in body) for body in loops)
+    assert writes == sorted(s * -(-(h + 4 * mb // wn) // 4) for mb, h, wn, wk, s in forms), (name, writes)
+    first = next(i for i, l in enumerate(code) if l.startswith("global_load_lds_dwordx4"))
+    assert sum("v_rcp" in l for l in code[:first]) == 1, name
+
+
 def test_paired_kernels_waits_hold_and_one_operation_less_does_not(tmp_path):
     """csrc/bl_gemm_pair.hip: the issue order of every form replayed with the constants of the kernel's header (see
     tests/ring_model/pair_check.cpp), and with every wait one operation too generous, which must fail."""
@@ -208,9 +221,11 @@ def test_compiled_paired_kernels_issue_what_the_model_assumes(tmp_path):
         # per form: S steps of H + 4 MB / WN requests and a wait that leaves the S - 3 steps requested last on their way
         want = [[((s - 3) * (h + 4 * mb // wn), h + 4 * mb // wn, 0)] * s for mb, h, wn, wk, s in forms]
         # (the main loop is straight code; a tail's steps, laid out in any order with branches between them, are not)
-        got = [_barriers(body) for body in _loops(lines)
-               if any(l.startswith("s_barrier") for l in body) and not any(re.match(r"s_c?branch", l) for l in body)]
+        loops = [body for body in _loops(lines)
+                 if any(l.startswith("s_barrier") for l in body) and not any(re.match(r"s_c?branch", l) for l in body)]
+        got = [_barriers(body) for body in loops]
         assert sorted(got) == sorted(want), (name, got)
+        _check_paired_extras(name, lines, loops, forms)
         # what the compiler sees is loaded before the first request (the scales) and nothing after it
         requests = [i for i, l in enumerate(lines) if l.startswith("global_load_lds_dwordx4")]
         others = [i for i, l in enumerate(lines) if re.match(r"(scratch_|flat_|global_store|global_atomic|buffer_load|global_load_dword(x2|x4)?\b)", l)]
@@ -236,9 +251,11 @@ def test_compiled_paired_kernels_of_one_workgroup_per_unit_issue_what_the_model_
         seen += 1
         mb, h, wn, wk, s = (int(x) for x in m.groups())
         want = [((s - 3) * (h + 4 * mb // wn), h + 4 * mb // wn, 0)] * s
-        got = [_barriers(body) for body in _loops(lines)
-               if any(l.startswith("s_barrier") for l in body) and not any(re.match(r"s_c?branch", l) for l in body)]
+        loops = [body for body in _loops(lines)
+                 if any(l.startswith("s_barrier") for l in body) and not any(re.match(r"s_c?branch", l) for l in body)]
+        got = [_barriers(body) for body in loops]
         assert got == [want], (name, got)
+        _check_paired_extras(name, lines, loops, [(mb, h, wn, wk, s)])
         requests = [i for i, l in enumerate(lines) if l.startswith("global_load_lds_dwordx4")]
         others = [i for i, l in enumerate(lines) if re.match(r"(scratch_|flat_|global_store|global_atomic|buffer_load|global_load_dword(x2|x4)?\b)", l)]
         assert all(i < requests[0] for i in others), (name, [lines[i] for i in others])
