@@ -21,6 +21,9 @@ constexpr int kAttnOneRound = 10;     // workgroups per head from which on one p
 //   - else the fewest rounds that are full (ordinary loads): 260 heads, 5000 positions 1 / 4 / 6 workgroups per head 156.9 / 127.3 / 123.1, 300 heads
 //     1 / 4 168.5 / 136.7, 180 heads 2 / 4 94.0 / 83.6.  Two rounds that are 80 % full are taken (140 heads, 1270 positions 3 / 5: 21.3 / 20.8; 104
 //     heads 4 / 7: 16.8 / 16.8), more only at 85 %: 260 heads have 81 % in five rounds.
+// A prompt with head sizes above 128 follows (its tokens are bit for bit one-token calls), with ordinary loads and the launch of
+// attn_prompt_units; two rounds per token and one: 28 heads of 160 behind 2000, 4 tokens 31.5 and 29.5, 16 tokens 88 and 74; 40 of 160, 9 behind 4000 168
+// and 160; 30 of 256, 9 behind 2000 93 and 76; 52 of 192, 3 behind 1000 28.8 and 24.6.
 constexpr int attn_groups_per_head(int n_heads, int head_dim, int chunks) {
     const int one = kAttnUnits / n_heads, row = head_dim <= 128 ? 128 : 256;
     const bool few = head_dim * 8 >= row * 5 && one * n_heads * 100 >= kAttnUnits * 72;
@@ -34,5 +37,9 @@ constexpr int attn_groups_per_head(int n_heads, int head_dim, int chunks) {
     if (groups > kAttnMaxGroups) groups = kAttnMaxGroups;
     return groups < chunks ? groups : chunks;
 }
+
+// A prompt's launch: heads times workgroups per head, padded to whole rounds of the dies (workgroup i of a launch runs on die i % 8), so
+// that every query's workgroup on a piece of the cache is on the same die.
+constexpr unsigned attn_prompt_units(int n_heads, int groups) { return ((unsigned)n_heads * (unsigned)groups + 7u) / 8u * 8u; }
 
 }  // namespace bl

@@ -446,6 +446,7 @@ struct AttnArgs {
     // several consecutive tokens (a prompt): pos is null, query z has position pos0 + z, its own row of q_lin and out
     // and its own part of scratch; keys and values are in the cache already (kv_append_kernel)
     int32_t        pos0;
+    int32_t        groups;           // workgroups per head (the one-token launch's are its grid's)
     int64_t        scratch_stride;   // floats per query
 };
 
@@ -610,7 +611,9 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 // Waves per SIMD: 5 (head sizes up to 128) and 4 (beyond), held for the compiler; every instance fits without spilling: 75, 71,
 // 115 and 122 registers.  (Five spilled registers of <8, 256>, reloaded behind the next keys' requests, made every chunk wait for
 // those: 40 heads of 160 at 16 000 positions 92.8 us, without spills 79.7.)
-// PROMPT: several tokens whose keys and values are cached already, one per grid z.
+// PROMPT: several tokens whose keys and values are cached already, one per grid z.  Its grid's x counts heads and workgroups together,
+// padded to whole rounds of the dies, so that one die's L2 serves a piece of the cache to all queries (28 heads of 160, nine workgroups each,
+// behind 2000 positions, unpadded and padded: 4 tokens 35.3 and 29.5 us, 16 tokens 107 and 74; 12 of 160, 9 behind 3000 42.2 and 33.3).
 template <int W, int MAXD, bool PROMPT>
 __device__ __forceinline__ void attn_walk(const AttnArgs& p) {
     typedef typename CacheVec<W>::type vec_t;
@@ -624,7 +627,10 @@ __device__ __forceinline__ void attn_walk(const AttnArgs& p) {
     __shared__ float s_w[kChunk];                       // the merge's partial results
     __shared__ float s_o[kAttnThreads];                 // the merge's factors
     const int tid = threadIdx.x;
-    const int head = blockIdx.x, chunk = blockIdx.y;
+    const int head = PROMPT ? (int)(blockIdx.x % (unsigned)p.n_heads) : (int)blockIdx.x;
+    const int chunk = PROMPT ? (int)(blockIdx.x / (unsigned)p.n_heads) : (int)blockIdx.y;
+    const int groups = PROMPT ? p.groups : (int)gridDim.y;   // workgroups per head
+    if (PROMPT && chunk >= groups) return;              // uniform: the grid's padding
     const int d = p.head_dim, half = d / 2;
     const int hidden = p.n_heads * d;
     const int query = blockIdx.z;                       // 0 unless a prompt's tokens are processed together
@@ -642,10 +648,9 @@ __device__ __forceinline__ void attn_walk(const AttnArgs& p) {
     }
     const int pos = __builtin_amdgcn_readfirstlane(PROMPT ? p.pos0 + query : *p.pos);
     if (pos < 0 || pos >= p.max_pos) return;            // uniform
-    // Workgroup y of a head takes the chunks y, y + G, y + 2G, ... (G = workgroups per head in this launch) that hold
+    // Workgroup y of a head takes the chunks y, y + G, y + 2G, ... (G = `groups`) that hold
     // rows up to the token's: one chunk each while the context is short, several once it outgrows the launch -- then
     // a workgroup folds its chunks into ONE running maximum, sum and weighted values before it deposits anything.
-    const int groups = (int)gridDim.y;
     const int last_chunk = pos / kChunk;
     if (chunk > last_chunk) return;                     // uniform: nothing cached this far yet
     const bool owner = !PROMPT && last_chunk % groups == chunk;   // uniform: one of this workgroup's chunks holds the row this launch appends
@@ -1275,7 +1280,7 @@ hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
     p.k_cache = a.k_cache_dev; p.v_cache = a.v_cache_dev; p.out = a.out_dev;
     p.scratch = static_cast<float*>(a.scratch_dev);
     p.n_heads = a.n_heads; p.head_dim = a.head_dim; p.max_pos = a.max_pos; p.chunks = attn_chunks(a.max_pos);
-    p.pos0 = 0; p.scratch_stride = 0;
+    p.pos0 = 0; p.groups = 0; p.scratch_stride = 0;
     const int groups = attn_groups(a.n_heads, a.head_dim, p.chunks, p.counters_apart);
     const dim3 grid((unsigned)a.n_heads, (unsigned)groups);
     launch_attn_chunks(p, grid, s);
@@ -1295,7 +1300,7 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     p.k_cache = a.k_cache_dev; p.v_cache = a.v_cache_dev; p.out = a.out_dev;
     p.scratch = static_cast<float*>(a.scratch_dev);
     p.n_heads = a.n_heads; p.head_dim = a.head_dim; p.max_pos = a.max_pos;
-    p.pos0 = a.pos0;
+    p.pos0 = a.pos0; p.groups = 0;
     // a prompt's queries never look beyond its last token: chunks up to that one only
     p.chunks = attn_chunks(a.pos0 + a.M);
     p.scratch_stride = attn_scratch_floats(a.n_heads, a.head_dim, a.pos0 + a.M);
@@ -1320,9 +1325,9 @@ hipError_t launch_attn_prefill(const bl_attn_prefill_args& a, hipStream_t s) {
     }
     // the workgroups that bl_attn_decode takes on this cache: the same sums in the same order, token by token.  They may use every
     // piece of a token's scratch memory (its chunks end at pos0 + M, not at max_pos), so the counters lie behind the pieces.
-    const int groups = min(attn_groups(a.n_heads, a.head_dim, attn_chunks(a.max_pos), p.counters_apart), p.chunks);
+    p.groups = min(attn_groups(a.n_heads, a.head_dim, attn_chunks(a.max_pos), p.counters_apart), p.chunks);
     p.counters_apart = 0;
-    const dim3 grid((unsigned)a.n_heads, (unsigned)groups, (unsigned)a.M);
+    const dim3 grid(attn_prompt_units(a.n_heads, p.groups), 1, (unsigned)a.M);
     if (p.head_dim % 8 == 0) attn_chunk_prompt_kernel<8><<<grid, dim3(kAttnThreads), 0, s>>>(p);   // (head sizes above 128)
     else attn_chunk_prompt_kernel<4><<<grid, dim3(kAttnThreads), 0, s>>>(p);
     return hipGetLastError();

@@ -350,3 +350,25 @@ def test_token_attention_fills_whole_rounds(tmp_path):
         if g < min(64, chunks):
             rounds = -(-g * h // 256)
             assert g * h >= 0.72 * 256 * rounds, (d, chunks, h, g)
+
+
+def test_prompt_attention_keeps_a_piece_of_the_cache_on_one_die(tmp_path):
+    """The grid of a prompt's token-by-token attention: every head's workgroups, and the same die (workgroup index % 8) for a piece of the
+    cache whichever query asks for it.  (28 heads with nine workgroups each, 252 in all, once moved four dies on with every query.)"""
+    src = tmp_path / "units.cpp"
+    src.write_text("""
+        #include <initializer_list>
+        #include "bl_attn_groups.hpp"
+        int main() {
+            for (int h = 1; h <= 1200; ++h)
+                for (int g : {1, 2, 3, 9, 12, 64, 1000}) {
+                    const unsigned units = bl::attn_prompt_units(h, g);
+                    if (units < (unsigned)(h * g) || units >= (unsigned)(h * g + 8)) return 1;
+                    for (unsigned query : {1u, 2u, 5u})
+                        if ((units * query) % 8) return 2;
+                }
+            return bl::attn_groups_per_head(28, 160, 32) == 9 && bl::attn_prompt_units(28, 9) == 256 ? 0 : 3;
+        }""")
+    exe = str(tmp_path / "units")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2410_16144_amd", "csrc"), str(src), "-o", exe])
+    assert subprocess.run([exe]).returncode == 0

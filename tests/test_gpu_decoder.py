@@ -1132,9 +1132,11 @@ def test_attn_prefill_parity_wide_rows(dev, mods, n_heads, head_dim, max_pos, po
     test_attn_prefill_parity(dev, mods, n_heads, head_dim, max_pos, pos0, M)
 
 
-@pytest.mark.parametrize("n_heads,head_dim,max_pos,pos0,M", [(40, 160, 1300, 1250, 3), (150, 136, 330, 326, 3), (2, 132, 4400, 4220, 2), (300, 256, 700, 640, 2)])
+@pytest.mark.parametrize("n_heads,head_dim,max_pos,pos0,M", [(40, 160, 1300, 1250, 3), (150, 136, 330, 326, 3), (2, 132, 4400, 4220, 2), (300, 256, 700, 640, 2),
+                                                             (28, 160, 2100, 2000, 4), (13, 164, 3000, 2900, 3), (7, 136, 130, 126, 4)])
 def test_attn_prefill_equals_tokens_beyond_one_chunk_per_workgroup(dev, mods, n_heads, head_dim, max_pos, pos0, M):
-    """Head sizes above 128 in caches whose chunks outnumber a head's workgroups (12, 3, 64 and 5): a prompt's tokens add up their
+    """Head sizes above 128 in caches whose chunks outnumber a head's workgroups (12, 3, 64 and 5; 9 and 19 that do not fill rounds of the dies with their heads, and one
+    cache of as few chunks as workgroups): a prompt's tokens add up their
     chunks in the one-token call's order, bit for bit."""
     B, dec, ops = mods
     hidden = n_heads * head_dim
