@@ -110,11 +110,18 @@ bool gemm_pair_takes(const GemmProblem* ps, int count, int mb) {
 //     700 x 5120 -> 5120, 64 x 256: 26.9 -> 18.5);
 //   - with as many tiles if the bytes are at most three quarters and the tokens more than a die's L2 holds (4 MB): 2048 x 11008 -> 4096,
 //     128 x 256 tiles 66.2 -> 63.8, 64 x 256 71.4 -> 68.0; with the bytes the other way 512 x 4096 -> 24064 went from 41.0 to 41.8.
-static bool pair_may_split(int64_t gx, int64_t gy, int64_t M, int64_t rows, int64_t K, float& factor) {
+// With few tiles of K there are few bytes to save, and the outputs' stores, which the lines know least about, are the launch; measured against the
+// choice without the split on 10 156 launches (weights cold) and 3490 (warm), those that became more than 6 % slower: 60 and 37.  So below 32 tiles the
+// estimate needs 6 % more in its favour, below 16 the forms with three stages keep all dies on all tokens (2153 x 418 -> 10152, 64 x 512: 24.7 -> 31.5),
+// and 32 x 256 always does where it is not asked for (877 x 2624 -> 4736 13.3 -> 15.8, 1599 x 2240 -> 3072 12.7 -> 14.6): 14 and 15 are left, and what
+// the split gives on average stays (0.988 and 0.969 of the time).
+static bool pair_may_split(int stages, int64_t gx, int64_t gy, int64_t M, int64_t rows, int KC, float& factor) {
     const int64_t all = gemm_padded_tiles(gx, gy, 0), halves = gemm_padded_tiles(gx, gy, 1);
     const bool less = 5 * rows <= 32 * M;   // M / 2 + N / 16 <= 3 / 4 (M + N / 32)
     factor = less ? 0.97f : 1.03f;          // geometric mean of the launches at kPairLines, and a margin
-    return halves < all || (halves == all && less && M * K > 4000000);
+    if (KC < 32) factor *= 1.06f;
+    if (stages < 4 && KC < 16) return false;
+    return halves < all || (halves == all && less && M * KC * kTileK > 4000000);
 }
 
 static int64_t pair_positions(const GemmProblem* ps, int count, int bn) {
@@ -135,7 +142,7 @@ int gemm_pair_best(const GemmProblem* ps, int count, int64_t M, int cus, float& 
         if (KC < l.least || !gemm_pair_takes(ps, count, l.mb)) continue;
         const int64_t gx = pair_positions(ps, count, l.bn), gy = (M + l.bm - 1) / l.bm;
         float factor;
-        const int splits = pair_may_split(gx, gy, M, rows, (int64_t)KC * kTileK, factor) ? 2 : 1;
+        const int splits = l.mb > 1 && pair_may_split(l.s, gx, gy, M, rows, KC, factor) ? 2 : 1;
         for (int split = 0; split < splits; ++split) {
             const float x = (float)gemm_padded_tiles(gx, gy, split) / (float)cus;
             if (x <= 1.0f && l.s < 4 && KC > 2) continue;
@@ -153,9 +160,13 @@ int gemm_pair_halves(const GemmProblem* ps, int count, int64_t M, int code) {
     for (const PairLine& l : kPairLines) {
         if (l.code() != code) continue;
         int64_t rows = 0;
-        for (int i = 0; i < count; ++i) rows += (int64_t)ps[i].row_blocks * kTileN;
+        int KC = 0;
+        for (int i = 0; i < count; ++i) {
+            KC = ps[i].KC > KC ? ps[i].KC : KC;
+            rows += (int64_t)ps[i].row_blocks * kTileN;
+        }
         float factor;
-        return pair_may_split(pair_positions(ps, count, l.bn), (M + l.bm - 1) / l.bm, M, rows, (int64_t)ps[0].KC * kTileK, factor);
+        return pair_may_split(l.s, pair_positions(ps, count, l.bn), (M + l.bm - 1) / l.bm, M, rows, KC, factor);
     }
     return 0;
 }

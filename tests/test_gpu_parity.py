@@ -806,6 +806,14 @@ def test_gemm_choice_with_weights_from_memory(dev, ops, M, K, N, kernel):
         binding.bl_set_tuning("gemm_mb", 0)
 
 
+@pytest.mark.parametrize("M,K,N,kernel", [(2153, 418, 10152, "pair_gemm_kernel<1, 2, 4, 1, 4> grid=2720"), (2143, 832, 5761, "pair_gemm_kernel<1, 2, 4, 1, 4> grid=1608"),
+                                          (877, 2624, 4736, "mixed_pair_gemm_kernel"), (1599, 2240, 3072, "mixed_pair_gemm_kernel")])
+def test_gemm_choice_where_a_split_of_the_dies_does_not_pay(dev, ops, M, K, N, kernel):
+    """Launches that took 15 to 28 % longer when the dies' split was estimated too well: short contractions in wide tiles with three
+    stages, and 32 x 256 tiles."""
+    test_gemm_choice_with_weights_from_memory(dev, ops, M, K, N, kernel)
+
+
 @pytest.mark.parametrize("M,K,N", [(807, 5760, 6272), (1535, 3392, 3200), (1626, 5952, 3200)])
 def test_gemm_two_tile_widths_only_with_one_narrow_tile_per_unit(dev, ops, M, K, N):
     """Narrow positions that are no multiple of 8 give one die more tiles than it has units: not the two-width kernel, also when
