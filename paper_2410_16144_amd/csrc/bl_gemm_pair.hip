@@ -62,12 +62,13 @@ __global__ __launch_bounds__(256, 2) void mixed_pair_gemm_kernel(const GemmMixed
 // (483 x 5888 -> 15168: 64 x 512 47.3 us, estimated 34; 64 x 256 40.7; 1978 x 6080 -> 3392 48.6 and 39.9).  The last two have four
 // stages for that case.  Their lines come from 4959 launches (24 to 2600 tokens, K 256 to 13000, N 512 to 30000, every form on each, with
 // both die mappings, weights cold), less 3 %: on those launches the other lines fall 6 % short above 10 us (the clock that power left
-// that day), and with 3 % off the choice was best.  Over them it takes 0.987 of the time (geometric mean; 0.963 of those above 15 us) that
-// it took without the two forms and the split of the dies, is ahead by more than 3 % on 539 and behind by as much on 53; over 2826
-// with weights in the memory-side cache (150 tokens and 6e9 products up) 0.970, ahead on 795, behind on 82.
+// that day), and with 3 % off the choice was best.  With the rules below, over 10 156 launches of those ranges it takes 0.988 of the time
+// (geometric mean; 0.967 of those above 15 us) that it took without the two forms and the split of the dies, is ahead by more than 3 % on 980 and
+// behind by as much on 36; over 3490 with weights in the memory-side cache (150 tokens and 6e9 products up) 0.969, ahead on 952, behind on 63.
 // `least`: 64 x 384 with four stages against 64 x 256 and 64 x 128 in one launch, where both apply, by tiles of K: 24 to 48 warm 1.14 of its time,
-// cold 0.99; 48 to 80 1.06 and 0.93; 80 to 120 0.98 and 0.88; beyond 0.93 and 0.88.  128 x 256 is left out below 96 tiles, where a test
-// holds the choice to the forms before it (1978 x 6080 -> 3392: 36.5 us, 64 x 256 40.4).
+// cold 0.99; 48 to 80 1.06 and 0.93; 80 to 120 0.98 and 0.88; beyond 0.93 and 0.88.  128 x 256 where the lines take it against the other forms
+// there: 32 to 40 warm 1.08, cold 1.04; 40 to 56 1.06 and 0.99; 56 to 80 1.00 and 0.97; 80 to 96 0.99 and 0.91 (1978 x 6080 -> 3392 34.2 us, 64 x 256
+// 37.7; 483 x 5888 -> 15168 36.5 and 37.5); beyond 0.97 and 0.92.
 struct PairLine {
     int mb, h, wk, s, bm, bn, least;   // least: fewest tiles of K
     float t0, a, e, t1, b, f, c, t2, d, g, h1;
@@ -82,7 +83,7 @@ constexpr PairLine kPairLines[] = {
     {2, 4, 1, 3, 64, 512, 0, 4.92f, 0.2967f, 2.21f, 7.68f, 0.5438f, 1.89f, 0.0375f, -0.88f, 0.1313f, 5.83f, 0.4951f},
     {2, 3, 1, 3, 64, 384, 0, 4.13f, 0.2674f, 2.05f, 6.57f, 0.4074f, 1.16f, 0.0778f, 1.52f, 0.1353f, 3.85f, 0.3415f},
     {2, 3, 1, 4, 64, 384, 80, 4.44f, 0.2053f, 2.52f, 10.01f, 0.4065f, 2.08f, 0.0629f, 6.46f, 0.2355f, 3.96f, 0.0986f},
-    {4, 2, 1, 4, 128, 256, 96, 4.68f, 0.2508f, 3.22f, 11.42f, 0.5206f, 2.93f, 0.0887f, 5.18f, 0.2962f, 5.54f, 0.1514f},
+    {4, 2, 1, 4, 128, 256, 80, 4.68f, 0.2508f, 3.22f, 11.42f, 0.5206f, 2.93f, 0.0887f, 5.18f, 0.2962f, 5.54f, 0.1514f},
 };
 
 }  // namespace

@@ -788,11 +788,12 @@ def test_gemm_short_k_takes_tiles(dev, ops, M, K, N):
         binding.bl_set_tuning("gemm_mb", 0)
 
 
-@pytest.mark.parametrize("M,K,N,kernel", [(483, 5888, 15168, "pair_gemm_kernel<2, 2,"), (1978, 6080, 3392, "pair_gemm_kernel<2, 2,"),
-                                          (12, 8320, 8704, "gemm_narrow_kernel<16, 2,")])
+@pytest.mark.parametrize("M,K,N,kernel", [(483, 5888, 15168, "pair_gemm_kernel<4, 2, 4, 1, 4>"), (1978, 6080, 3392, "pair_gemm_kernel<4, 2, 4, 1, 4>"),
+                                          (2046, 5056, 3840, "pair_gemm_kernel<2, 2,"), (12, 8320, 8704, "gemm_narrow_kernel<16, 2,")])
 def test_gemm_choice_with_weights_from_memory(dev, ops, M, K, N, kernel):
-    """Shapes where the estimated times once fell short by a quarter: tiles wider than 256 rows with at most one workgroup per
-    unit, and the narrowest form for few tokens where a few units have two workgroups."""
+    """Shapes where the estimated times once fell short by a quarter: tiles wider than 256 rows with three stages and at most one
+    workgroup per unit (now four stages there: 64 x 256, and 128 x 256 from 80 tiles of K), and the narrowest form for few tokens where
+    a few units have two workgroups."""
     from paper_2410_16144_amd import binding
     g = torch.Generator(dev).manual_seed(M)
     pw = ops.pack_ternary(torch.randint(-1, 2, (N, K), dtype=torch.int8, device=dev, generator=g), 0.02)
