@@ -4,6 +4,7 @@
 #pragma once
 #include <type_traits>
 
+#include "bl_gemm_pair_choice.hpp"
 #include "bl_gemm_ring.hpp"
 #include "bl_internal.hpp"
 
@@ -305,8 +306,6 @@ __device__ __forceinline__ void pair_tile(const GemmProblem& p, const int M, con
     if (p.acc) store(p.acc, std::true_type{});
 }
 
-constexpr int pair_code(int mb, int h, int wk, int s) { return 10000 * s + 100 * (wk - 1) + 10 * mb + h; }
-
 struct PairBatch {
     GemmProblem p[kMaxGemmBatch];
     int32_t     end[kMaxGemmBatch];
@@ -333,7 +332,7 @@ hipError_t launch_pair_form(const GemmProblem* ps, int count, int64_t M, int hal
         if (i < count) gx += ((int64_t)ps[i].row_blocks * kTileN + WN * H * 32 - 1) / (WN * H * 32);
         b.end[i] = i + 1 < count ? (int32_t)gx : INT32_MAX;
     }
-    const int64_t wgs = gemm_padded_tiles(gx, (M + 32 * MB - 1) / (32 * MB), halves);
+    const int64_t wgs = pair_padded_tiles(gx, (M + 32 * MB - 1) / (32 * MB), halves);
     if (wgs > INT32_MAX) return hipErrorInvalidValue;
     static LdsCeiling ceiling;
     const hipError_t e = ceiling.ensure(reinterpret_cast<const void*>(&pair_gemm_kernel<MB, H, WN, WK, S>), F::kLds);

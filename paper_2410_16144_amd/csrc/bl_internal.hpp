@@ -265,11 +265,6 @@ struct GemmMixed {
     int32_t     small_first[kMaxGemmBatch];  // product i's first 128-row position in its own rows
     int32_t     gx, wgs, small_gx;           // 256-row positions and their workgroups; 128-row positions
 };
-// Workgroups of a launch of gx x gy tiles with the padding of tile_of_workgroup.
-inline int64_t gemm_padded_tiles(int64_t gx, int64_t gy, int halves) {
-    const int64_t columns = kXcds >> halves, rows = 1 << halves;
-    return (gx + columns - 1) / columns * columns * ((gy + rows - 1) / rows * rows);
-}
 // bl_gemm with paired packed tiles (bl_gemm_pair.hip); a form's code is 10000 * stages + 100 * (waves along K - 1) + 10 * MB + H
 bool gemm_pair_form_exists(int code);
 bool gemm_pair_takes(const GemmProblem* ps, int count, int mb = 1);   // a form of 32 mb tokens; by default whether there is one

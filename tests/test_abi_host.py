@@ -3,7 +3,9 @@ validation.  No kernel is launched (validation runs before any HIP call), so thi
 machine without a GPU.
 """
 import ctypes
+import math
 import os
+import random
 import re
 import subprocess
 
@@ -372,3 +374,72 @@ def test_prompt_attention_keeps_a_piece_of_the_cache_on_one_die(tmp_path):
     exe = str(tmp_path / "units")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2410_16144_amd", "csrc"), str(src), "-o", exe])
     assert subprocess.run([exe]).returncode == 0
+
+
+@pytest.fixture(scope="module")
+def pair_choice(tmp_path_factory):
+    """The choice among the paired tile kernel's forms (csrc/bl_gemm_pair_choice.hpp) on a machine of 256 units, as a program: lines "M N K"
+    of one product in, "code halves" and the split of forms 40022, 30023 and 40012 if asked for out."""
+    tmp = tmp_path_factory.mktemp("choice")
+    src = tmp / "choice.cpp"
+    src.write_text("""
+        #include <cstdio>
+        #include "bl_gemm_pair_choice.hpp"
+        int main(int argc, char**) {
+            if (argc > 1) for (const bl::PairLine& l : bl::kPairLines) printf("%d\\n", l.code());
+            long long M, N, K;
+            while (argc == 1 && scanf("%lld %lld %lld", &M, &N, &K) == 3) {
+                bl::PairLaunch p;
+                p.M = M; p.widest = N; p.KC = (int)((K + 63) / 64); p.count = 1; p.row_blocks[0] = (int32_t)((N + 63) / 64);
+                const bl::PairChoice c = bl::pair_choice(p, 256);
+                printf("%d %d %d %d %d\\n", c.code, c.halves, bl::pair_forced_halves(p, 40022), bl::pair_forced_halves(p, 30023), bl::pair_forced_halves(p, 40012));
+            }
+        }""")
+    exe = str(tmp / "choice")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2410_16144_amd", "csrc"), str(src), "-o", exe])
+
+    def run(launches):
+        if launches is None:
+            return [int(l) for l in subprocess.check_output([exe, "lines"], text=True).split()]
+        out = subprocess.run([exe], input="".join("%d %d %d\n" % l for l in launches), text=True, capture_output=True, check=True).stdout
+        return [tuple(int(v) for v in l.split()) for l in out.splitlines()]
+    return run
+
+
+def test_every_paired_form_of_the_choice_is_taken_somewhere(pair_choice):
+    """A line that no launch takes is dead weight: sizes spread over the range reach every one of them."""
+    rng = random.Random(3)
+    size = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    taken = {c[0] for c in pair_choice([(size(9, 6000), size(64, 60000), size(64, 13000)) for _ in range(20000)])}
+    assert taken == set(pair_choice(None)), taken
+
+
+def test_paired_forms_are_not_chosen_beyond_their_widest_matrix(pair_choice):
+    """128-token tiles up to 2^22 columns, the others up to 2^23."""
+    rng = random.Random(4)
+    wide = [(rng.randint(64, 6000), (1 << 22) + rng.randint(1, 1 << 22), rng.randint(64, 20000)) for _ in range(4000)]
+    assert all(c[0] and c[0] // 10 % 10 < 4 for c in pair_choice(wide))
+    assert all(c[0] == 0 for c in pair_choice([(M, (1 << 23) + 1, K) for M, _, K in wide]))
+
+
+@pytest.mark.parametrize("M,N,K,forced", [
+    (2048, 2048, 2048, 1),      # as many tiles (8 positions of 256, 32 of 64 tokens), fewer bytes, 4.2e6 of tokens
+    (1024, 2048, 2048, 0),      # ... 2.1e6 of tokens: a die's L2 holds them
+    (1920, 2048, 2048, 0), (1984, 2048, 2048, 0), (2048, 2048, 1984, 1), (2048, 2048, 1920, 0),   # either side of 4e6 (31 of 64 tokens pad to 32)
+    (2048, 12288, 2048, 1),     # 5 N <= 32 M: 61 440 of 65 536
+    (2048, 14336, 2048, 0),     # more weights than that
+    (512, 1024, 128, 1),        # four positions: half as many padded tiles, whatever the bytes
+])
+def test_paired_forms_split_the_dies(pair_choice, M, N, K, forced):
+    """The rule on both sides of each of its conditions, for 64 x 256 tiles that are asked for."""
+    assert pair_choice([(M, N, K)])[0][2] == forced
+
+
+def test_paired_forms_split_the_dies_only_where_it_pays(pair_choice):
+    """Not below 16 tiles of K with three stages (2153 x 418 -> 10152), and 32 x 256 tiles only where they are asked for."""
+    assert pair_choice([(700, 1500, 64 * 15)])[0][3] == 0 and pair_choice([(700, 1500, 64 * 16)])[0][3] == 1
+    assert pair_choice([(500, 1000, 128)])[0][4] == 1
+    rng = random.Random(5)
+    got = pair_choice([(rng.randint(9, 3000), rng.randint(64, 20000), rng.randint(64, 13000)) for _ in range(5000)])
+    assert not any(code == 40012 and halves for code, halves, *_ in got)
+    assert any(code != 40012 and halves for code, halves, *_ in got)
