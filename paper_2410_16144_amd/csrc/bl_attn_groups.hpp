@@ -38,6 +38,15 @@ constexpr int attn_groups_per_head(int n_heads, int head_dim, int chunks) {
     return groups < chunks ? groups : chunks;
 }
 
+// A token's launch: `columns` x workgroups per head x (heads / columns), and workgroup (x, y, z) is head attn_head_at's y-th.  Workgroup i of a
+// launch runs on die i % 8.  Where a head's part of a cache row is no whole number of 128-byte lines, neighbouring heads share lines, so every
+// die takes an eighth of the heads, all workgroups of one behind those of the one before; else, and where the dies cannot have as many
+// heads each, the heads go around the dies one by one.  Caches from memory, us, one by one and so: 32 heads of 48 at 1 / 5000 / 16 000 positions 3.90 and 3.42, 16.6
+// and 11.9, 42.0 and 28.3; 16 of 96 at 5000 11.5 and 10.5; 32 of 120 22.6 and 19.1; 40 of 72 at 3000 14.8 and 12.8; 24 of 160 at 4000 17.7 and 16.9.  Dies with
+// parts of heads, for the other numbers: 52 of 72 at 3000 17.4 and 15.4, but 12 of 100 at 1 position 4.02 and 4.17, for the division.
+constexpr unsigned attn_columns(int n_heads, int head_dim) { return head_dim % 64 && n_heads % 8 == 0 ? 8u : (unsigned)n_heads; }
+constexpr int attn_head_at(unsigned x, unsigned z, unsigned depth) { return (int)(x * depth + z); }
+
 // A prompt's launch: heads times workgroups per head, padded to whole rounds of the dies (workgroup i of a launch runs on die i % 8), so
 // that every query's workgroup on a piece of the cache is on the same die.
 constexpr unsigned attn_prompt_units(int n_heads, int groups) { return ((unsigned)n_heads * (unsigned)groups + 7u) / 8u * 8u; }

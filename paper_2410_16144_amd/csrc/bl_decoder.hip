@@ -602,9 +602,11 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 // A token's cache rows are read once, by streaming loads: caches from memory, ordinary -> streaming, 32 heads of 128 at 500 positions 7.9 -> 7.6,
 // 2000 11.1 -> 10.5, 8000 27.7 -> 25.2, 16 000 47.8 -> 42.0, 64 heads at 4000 28.5 -> 25.9; caches that the memory-side cache holds stay there
 // and are as fast (8000: 24.3 and 24.0), and so do a model's weights: 700M shape 810 -> 740 us per token at 3000 positions, 715 -> 694 at 500.
-// Rows shorter than a line are the exception: two heads share every line, and the launch alone is slower (32 heads of 48, 4700 positions 15.8 -> 16.3,
-// 16 000 41.9 -> 42.5).  A whole token of that shape (1.5B) still gains up to there, by its weights: 968 -> 914 us at 1500, 1140 -> 1091 at 4500; at 14 000
-// it is 1 % behind (1682 -> 1700).  So one kind of load for all head sizes.
+// Heads that share lines of the cache are on one die (attn_columns), so that its L2 hands a line that came for one of them to the other; without
+// that, streaming loads brought it from memory twice (32 heads of 48, 5000 positions, ordinary / streaming / so: 16.0 / 16.6 / 11.9).  Whole
+// tokens of that shape (1.5B) 967 / 905 / 887 us at 1500, 1142 / 1092 / 987 at 4500, 1722 / 1713 / 1315 at 14 000.
+// Below 100 positions a token's rows come from the L2 if the loads are ordinary: there streaming costs a model 0.5 % (7B shape 1075 -> 1081 us at 10,
+// 1147 -> 1150 at 100, then 1190 -> 1164 at 450).  Both kinds in one kernel, by the position, cost more than that (1088, 1158, 1183).
 // With them one workgroup per unit is enough at any length (bl_attn_groups.hpp: 25.2 -> 23.0 at 8000).
 // MAXD: the largest head size of this instance (128 or 256) -- registers and LDS are sized by it, and the smaller one
 // lets twice as many workgroups share a compute unit.
@@ -627,13 +629,13 @@ __device__ __forceinline__ void attn_walk(const AttnArgs& p) {
     __shared__ float s_w[kChunk];                       // the merge's partial results
     __shared__ float s_o[kAttnThreads];                 // the merge's factors
     const int tid = threadIdx.x;
-    const int head = PROMPT ? (int)(blockIdx.x % (unsigned)p.n_heads) : (int)blockIdx.x;
+    const int head = PROMPT ? (int)(blockIdx.x % (unsigned)p.n_heads) : attn_head_at(blockIdx.x, blockIdx.z, gridDim.z);
     const int chunk = PROMPT ? (int)(blockIdx.x / (unsigned)p.n_heads) : (int)blockIdx.y;
     const int groups = PROMPT ? p.groups : (int)gridDim.y;   // workgroups per head
     if (PROMPT && chunk >= groups) return;              // uniform: the grid's padding
     const int d = p.head_dim, half = d / 2;
     const int hidden = p.n_heads * d;
-    const int query = blockIdx.z;                       // 0 unless a prompt's tokens are processed together
+    const int query = PROMPT ? (int)blockIdx.z : 0;     // 0 unless a prompt's tokens are processed together
     const float* q_lin = p.q_lin + (int64_t)query * hidden;
     float* out = p.out + (int64_t)query * hidden;
     float* scratch = p.scratch + (int64_t)query * p.scratch_stride;
@@ -1308,7 +1310,8 @@ hipError_t launch_attn_decode(const bl_attn_args& a, hipStream_t s) {
     p.n_heads = a.n_heads; p.head_dim = a.head_dim; p.max_pos = a.max_pos; p.chunks = attn_chunks(a.max_pos);
     p.pos0 = 0; p.groups = 0; p.scratch_stride = 0;
     const int groups = attn_groups(a.n_heads, a.head_dim, p.chunks, p.counters_apart);
-    const dim3 grid((unsigned)a.n_heads, (unsigned)groups);
+    const unsigned columns = attn_columns(a.n_heads, a.head_dim);
+    const dim3 grid(columns, (unsigned)groups, (unsigned)a.n_heads / columns);
     launch_attn_chunks(p, grid, s);
     return hipGetLastError();
 }

@@ -376,6 +376,41 @@ def test_prompt_attention_keeps_a_piece_of_the_cache_on_one_die(tmp_path):
     assert subprocess.run([exe]).returncode == 0
 
 
+def test_token_attention_keeps_heads_that_share_lines_on_one_die(tmp_path):
+    """The grid of a token's attention: every head once, and where a head's cache row ends inside a 128-byte line, its workgroups and the
+    next head's on the same die (workgroup index % 8), but for the seven pairs at the dies' ends."""
+    src = tmp_path / "columns.cpp"
+    src.write_text("""
+        #include <vector>
+        #include "bl_attn_groups.hpp"
+        int main() {
+            for (int h = 1; h <= 1200; ++h)
+                for (int d = 4; d <= 256; d += 4) {
+                    const unsigned columns = bl::attn_columns(h, d), depth = h / columns;
+                    const int groups = bl::attn_groups_per_head(h, d, 70);
+                    if (columns * depth != (unsigned)h) return 1;
+                    std::vector<std::vector<unsigned>> dies(h);
+                    for (unsigned z = 0; z < depth; ++z)
+                        for (int y = 0; y < groups; ++y)
+                            for (unsigned x = 0; x < columns; ++x) {
+                                const int head = bl::attn_head_at(x, z, depth);
+                                if (head < 0 || head >= h) return 2;
+                                dies[head].push_back((x + columns * (y + groups * z)) % 8);
+                            }
+                    int shared = 0;
+                    for (int i = 0; i < h; ++i) {
+                        if ((int)dies[i].size() != groups) return 3;
+                        if (i + 1 < h) shared += dies[i] == dies[i + 1];
+                    }
+                    if (d * 2 % 128 && h % 8 == 0 && shared < h - 8) return 4;
+                }
+            return 0;
+        }""")
+    exe = str(tmp_path / "columns")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2410_16144_amd", "csrc"), str(src), "-o", exe])
+    assert subprocess.run([exe]).returncode == 0
+
+
 @pytest.fixture(scope="module")
 def pair_choice(tmp_path_factory):
     """The choice among the paired tile kernel's forms (csrc/bl_gemm_pair_choice.hpp) on a machine of 256 units, as a program: lines "M N K"

@@ -346,7 +346,7 @@ def test_attn_decode_several_chunks_per_workgroup(dev, mods, groups, n_heads, he
 
 
 @pytest.mark.parametrize("n_heads,head_dim,groups", [(32, 128, 8), (26, 80, 9), (60, 100, 4), (28, 160, 9), (200, 88, 1), (40, 72, 12), (27, 156, 18),
-                                                     (90, 128, 5)])
+                                                     (90, 128, 5), (32, 48, 16), (16, 96, 16), (8, 36, 32)])
 def test_attn_decode_one_round_or_two(dev, mods, n_heads, head_dim, groups):
     """The workgroups that a call takes by itself: one round of the units (cache rows with few idle lanes, 72 % of the units filled)
     or more, each walking one chunk, several of them, and the last one in part; some heads against the fp64 softmax on the cache as
