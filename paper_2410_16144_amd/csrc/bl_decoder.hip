@@ -593,7 +593,7 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& p, float* scratch, fl
 // and weighted values of THEIR rows over all chunks of the workgroup: the dot product's exchanges are the only ones in the
 // loop, and there is no barrier in it, so no wave's requests wait for another wave's rows.  The groups of lanes are merged by
 // lane exchanges, the four waves in LDS, once behind the loop.  Bound by HBM in long contexts: 32 heads of 128 at 8000 positions
-// 36.3 -> 30 -> 26.9 -> 23.0 us (131 MB: 5.7 TB/s, behind 5 us of start and merge 7.2), 16 000 positions 47.8 -> 41.7;
+// 36.3 -> 30 -> 26.9 -> 23.0 us (131 MB: 5.7 TB/s), 16 000 positions 47.8 -> 41.7 (every 8000 positions more 18.2: 7.2 TB/s);
 // by the chain of memory round trips in short ones (caches from memory): one position 4.8 -> 3.4, 500 positions 10.2 -> 7.4, 3000 18.0 -> 13.7.
 // Before lane sums on the vector ALU, the next chunk's requests without a condition and fewer workgroups per head -> since; the last
 // change kept the requests where they are written and put the angle's load ahead of them: 16 heads of 100 at 8000 positions

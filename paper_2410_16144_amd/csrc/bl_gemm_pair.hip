@@ -4,10 +4,10 @@
 // instruction in 4.3 to 5 cycles whatever it is, and a 32-cycle product hides five of them (measured: max(32, 8 + 4.8 n) cycles for a
 // product and n other instructions of ONE wave; two waves of a SIMD: 8 per product + 4 per vector instruction, summed), and it had
 // eight per product, a barrier per 64 k, operand reads of two cycles for one (below) and 4 us of epilogue.  Here, per wave
-// and step (64 x 64 tile: 16 products, 85 other instructions):
+// and step (64 x 64 tile: 16 products, 87 other instructions):
 //   - a pair of tiles needs no lane exchange: lanes 0-31 carry word j of their row's 16 bytes in the pair's first tile, lanes
 //     32-63 word j of the second, and the tokens' operand is chosen alike;
-//   - weights and tokens both go from global memory straight into LDS (load_to_lds: one M0 for four pieces), several pairs ahead;
+//   - weights and tokens both go from global memory straight into LDS (load_to_lds, load_first_to_lds: one M0 for up to four pieces), several pairs ahead;
 //     scalar and 32-bit lane offsets only.  Weights are read by the wave that brought them, tokens by all waves along N;
 //   - tokens: a row's 128 bytes as eight 16-byte chunks, chunk c at place c ^ (row % 8) ^ (row / 8 % 2), so that the sixteen
 //     lanes of a cycle meet sixteen columns (without the last term every read took two cycles for one: 1.4 of 3.2 million LDS
@@ -21,7 +21,7 @@
 // Waits: every vector memory operation of the loop is one of these requests, kPer per step, and they complete in issue order;
 // PairRing (bl_gemm_ring.hpp) has the counts, tests/ring_model/pair_check.cpp replays them.
 //
-// Measured, what was chosen before -> now (us, weights cold): 512 x 4096 -> 11008 23.9 -> 20.9, -> 4096 13.3 -> 10.6, -> 24064 42.8 -> 39.1,
+// Measured, what was chosen before -> this kernel's first form (us, weights cold): 512 x 4096 -> 11008 23.9 -> 20.9, -> 4096 13.3 -> 10.6, -> 24064 42.8 -> 39.1,
 // 512 x 11008 -> 4096 24.1 -> 21.5, 256 x 4096 -> 11008 18.2 -> 13.5, 128 12.8 -> 9.2, 1024 x 4096 -> 4096 19.3 -> 15.8, 2048 x 4096 -> 11008
 // 78.9 -> 75, 2048 x 11008 -> 4096 68.9 -> 66 (since then 128 x 256 tiles, bl_gemm_pair_wide.hip).  From 1024 tokens on the chip's power limit sets
 // the clock: 2048 x 11008 -> 4096 70 us at 1.72 GHz, with all tokens zero 53 at 2.28; products alone, in registers, make 4.3 POP/s on such
